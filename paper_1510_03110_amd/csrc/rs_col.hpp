@@ -1,0 +1,588 @@
+// Column-owner form of the per-stage Riccati recursion (matrix lines of
+// Alg. 1 and Alg. 4) for n_x <= 64 and n_u <= n_x (in tiles of 16), in FP64
+// or FP32.
+//
+// A workgroup of 2 NXT wavefronts (NXT = n_x / 16 rounded up) owns one
+// subproblem.  Wave j < NXT owns the 16-wide column block j of A, F, H', Y,
+// K and P; wave NXT + j (Alg. 4) owns column block j of V, A'V, B'V, X, L_t
+// and Q_w_hat.  The 16x16x4 matrix instructions leave a result tile in the
+// register layout in which a tile enters the next product as its right-hand
+// operand (element (k, j) in lane j + 16 (k mod 4) for FP64; for FP32 the
+// inner index is only permuted, the same way in both operands), so a column
+// block passes through the whole chain of a stage in its owner's registers:
+//
+//   W(:,j) = P A(:,j)   F(:,j) = Qx + A'W(:,j)   H'(:,j) = Qxw' + B'W(:,j)
+//   Y(:,j) = L^{-1} H'(:,j)   K(:,j) = -L^{-T} Y(:,j)   P(:,j) = F - Y'Y(:,j)
+//   A'V(:,j)  B'V(:,j)  X(:,j) = L^{-1} B'V(:,j)   L_t(:,j) = -L^{-T} X(:,j)
+//   V(:,j) = A'V - Y'X(:,j)   Q_w_hat(:,j) += X'X(:,j)
+//
+// Only left-hand operands (P, A, B, L^{-1}, Y, X) live in LDS; V and Q_w_hat
+// never leave their owner's registers.  G = Qw + B'PB is formed by the waves
+// j < n_u / 16 (column block j of B) and factored by the last wave while the
+// others form W, F and H'.  P, F and Q_w_hat are formed on the lower tiles
+// and mirrored, so they are exactly symmetric.  Four workgroup barriers a
+// stage; the next stage's A and B wait in registers.
+//
+// Sizes that are not multiples of 16 are padded with zeros on load (an
+// identity in the padded block of Q_w), which decouples the padding.
+#pragma once
+#include "rs_mfma.hpp"
+
+namespace rs {
+namespace cw {
+
+using mf::lane;
+using mf::MT;
+using mf::v4_t;
+using mf::wave;
+using mf::wave_fence;
+using mf::zero4;
+typedef mf::d4 d4;
+
+// A lane's place in the operand and result layouts: c = lane % 16, q = lane /
+// 16; element r of a result tile is in row(r).  Taken afresh in every stage
+// through an opaque copy: the addresses formed from it are cheap, and the
+// compiler would otherwise hoist all of them out of the stage loop and spill.
+template <class T>
+struct Ln {
+    int c, q;
+    __device__ __forceinline__ Ln() {
+        int l = lane();
+        asm volatile("" : "+v"(l));
+        c = l & 15;
+        q = l >> 4;
+    }
+    __device__ __forceinline__ int row(int r) const { return sizeof(T) == 8 ? q + 4 * r : 4 * q + r; }
+};
+
+// LDS position of element (k, i) of a matrix with row pitch PT: the column is
+// permuted within its tile by an exclusive-or with the row, so that the 16
+// lanes of an operand read fall on distinct banks whether they run along a
+// row or down a column.
+template <int PT>
+__device__ __forceinline__ int at(int k, int i) {
+    return k * PT + (i ^ (k & 15));
+}
+
+// Left-hand operand tile of a product, one matrix-instruction slice r at a
+// time: the element of row 16 ti + lane % 16 and inner index 16 kt + row(r).
+// N: M[k][i] (the transposed view of a row-major matrix, or a symmetric one);
+// it also reads a right-hand operand column block straight from LDS.
+// R: M[i][k].
+template <int PT, class T>
+__device__ __forceinline__ T ldN(const Ln<T> &L, const T *M, int kt, int ti, int r) {
+    const int row = L.row(r);
+    return M[row * PT + (L.c ^ row) + 16 * kt * PT + 16 * ti];
+}
+template <int PT, class T>
+__device__ __forceinline__ T ldR(const Ln<T> &L, const T *M, int ti, int kt, int r) {
+    return M[L.c * PT + (L.c ^ L.row(r)) + 16 * ti * PT + 16 * kt];
+}
+
+// Keeps the operand reads of one tile product from being moved across the
+// products before it: the compiler would otherwise issue the reads of a whole
+// phase at once and spill.
+__device__ __forceinline__ void tile_fence() { __builtin_amdgcn_sched_barrier(0); }
+
+// acc += sum over inner tiles k0 <= kt < KT of (N view of M)(ti, kt) b[kt].
+// The next inner tile's operands are read while this one's are multiplied.
+template <int PT, int KT, class T>
+__device__ __forceinline__ v4_t<T> mulN(const Ln<T> &L, v4_t<T> acc, const T *M, int ti, const v4_t<T> *b, int k0 = 0) {
+    tile_fence();
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+        if (kt < k0) continue;
+        T a[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[r] = ldN<PT>(L, M, kt, ti, r);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc = MT<T>::mfma(a[r], b[kt][r], acc);
+    }
+    tile_fence();
+    return acc;
+}
+
+// Tile (ti, tj) of C written at LDS (row, column) and, for a lower tile of a
+// symmetric result, also mirrored (the diagonal tile's upper half is the
+// mirror of its lower half).
+template <int PT, class T>
+__device__ __forceinline__ void put(const Ln<T> &L, T *M, int ti, int tj, v4_t<T> v) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) M[at<PT>(16 * ti + L.row(r), 16 * tj + L.c)] = v[r];
+}
+template <int PT, class T>
+__device__ __forceinline__ void put_sym(const Ln<T> &L, T *M, int ti, int tj, v4_t<T> v) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = 16 * ti + L.row(r), j = 16 * tj + L.c;
+        if (ti != tj || i >= j) {
+            M[at<PT>(i, j)] = v[r];
+            M[at<PT>(j, i)] = v[r];
+        }
+    }
+}
+
+// Cholesky factorization and inverse of the NB x NB blocks of G (lower part
+// and full diagonal blocks given), by one wavefront, in place: on return the
+// lower blocks hold L^{-1} (the diagonal ones with a zero upper half), the
+// upper ones the off-diagonal blocks of L'.  Right-looking over 16-wide
+// blocks: L_kk^{-1} by elimination (chol16_step), L_ik' = L_kk^{-1} G_ik',
+// G_ij -= L_ik L_jk'; then block row by block row of the inverse,
+// X_ij = -X_ii sum_k L_ik X_kj.  Returns nonzero if a pivot failed.
+template <class T, int NB>
+__device__ __forceinline__ int chol_inv(const Ln<T> &L, T *G) {
+    constexpr int PU = 16 * NB;
+    int fail = 0;
+#pragma unroll
+    for (int kb = 0; kb < NB; ++kb) {
+        {
+            int l = lane();
+            asm volatile("" : "+v"(l));          // see mf::chol_inv16
+            const int i = l & 15, h = l >> 4;
+            T a[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const T g = G[at<PU>(16 * kb + i, 16 * kb + ((8 * h + c) & 15))];
+                a[c] = h < 2 ? g : (8 * (h - 2) + c == i ? T(1) : T(0));
+            }
+            T sdi = T(0);
+            mf::chol16_step<0>(a, i, sdi, fail);
+            if (h >= 2) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) G[at<PU>(16 * kb + i, 16 * kb + 8 * (h - 2) + c)] = a[c] * sdi;
+            }
+        }
+        wave_fence();
+        // L_ik' into the upper block (k, i)
+        v4_t<T> u[NB];
+#pragma unroll
+        for (int ib = kb + 1; ib < NB; ++ib) {
+            v4_t<T> acc = zero4<T>();
+#pragma unroll
+            for (int r = 0; r < 4; ++r)          // G_ik' (k, i) = G[i][k]
+                acc = MT<T>::mfma(ldR<PU>(L, G, kb, kb, r), ldR<PU>(L, G, ib, kb, r), acc);
+            u[ib] = acc;
+            put<PU>(L, G, kb, ib, acc);
+        }
+        wave_fence();
+#pragma unroll
+        for (int jb = kb + 1; jb < NB; ++jb)
+#pragma unroll
+            for (int ib = jb; ib < NB; ++ib) {
+                v4_t<T> acc = zero4<T>();
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc = MT<T>::mfma(ldN<PU>(L, G, kb, ib, r), u[jb][r], acc);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int e = at<PU>(16 * ib + L.row(r), 16 * jb + L.c);
+                    G[e] -= acc[r];
+                }
+            }
+        wave_fence();
+    }
+#pragma unroll
+    for (int ib = 1; ib < NB; ++ib) {
+#pragma unroll
+        for (int jb = 0; jb < ib; ++jb) {
+            v4_t<T> s = zero4<T>();
+#pragma unroll
+            for (int kb = jb; kb < ib; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s = MT<T>::mfma(ldN<PU>(L, G, kb, ib, r), ldN<PU>(L, G, kb, jb, r), s);
+            v4_t<T> x = zero4<T>();
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x = MT<T>::mfma(ldR<PU>(L, G, ib, ib, r), s[r], x);
+            put<PU>(L, G, ib, jb, v4_t<T>{-x[0], -x[1], -x[2], -x[3]});
+        }
+        wave_fence();
+    }
+    return fail;
+}
+
+// LDS of one workgroup.  Y and X lie over A and B (dead once W, F, H', A'V
+// and B'V are formed) where they do not fit beside them; the next stage's A
+// and B are then written after one more barrier.
+template <class T, int NXT, int NUT>
+struct Smem {
+    static constexpr int RX = 16 * NXT, RU = 16 * NUT, NTH = 128 * NXT;
+    static constexpr size_t apart = sizeof(T) * (2 * RX * RX + RX * RU + RU * RU + 2 * RU * RX);
+    static constexpr bool OVER = apart > 159 * 1024;
+    T P[RX * RX], A[RX * RX], B[RX * RU], G[RU * RU];
+    T YX[OVER ? 1 : 2 * RU * RX];
+    int bad;
+    __device__ T *Y() { return OVER ? A : YX; }
+    __device__ T *X() { return OVER ? B : YX + (OVER ? 0 : RU * RX); }
+};
+
+// Column blocks that outlive a stage (Alg. 4): V(:, j) and the lower tiles
+// of Q_w_hat(:, j) of wave NXT + j.
+template <class T, int NXT>
+struct Cols {
+    v4_t<T> V[NXT], Q[NXT];
+};
+
+// Where the factors of a stage go (row-major; nullptr: not kept).
+template <class T>
+struct Rec {
+    T *P, *K, *V, *Lt, *L, *LT;
+};
+
+// 16x16 tile of problem data in the result layout; zeros outside n1 x n2
+// (identity where ONE).  TR reads the transposed element.
+template <bool EX, bool TR, bool ONE, class T>
+__device__ __forceinline__ d4 load_tile(const Ln<T> &L, const double *M, int ld, int ti, int tj, int n1, int n2) {
+    d4 v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = 16 * ti + L.row(r), j = 16 * tj + L.c;
+        const bool ok = EX || (i < n1 && j < n2);
+        const double pad = (ONE && i == j) ? 1.0 : 0.0;
+        v[r] = ok ? gload(M + (uint32_t)(TR ? j * ld + i : i * ld + j)) : pad;
+    }
+    return v;
+}
+template <class T>
+__device__ __forceinline__ v4_t<T> as_t(d4 v) {
+    return v4_t<T>{(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
+}
+
+// Result tile (ti, tj) to global memory (rows of length ld).
+template <bool EX, class T>
+__device__ __forceinline__ void store_tile(const Ln<T> &L, T *M, int ld, int ti, int tj, int n1, int n2, v4_t<T> v) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = 16 * ti + L.row(r), j = 16 * tj + L.c;
+        if (EX || (i < n1 && j < n2)) M[(uint32_t)(i * ld + j)] = v[r];
+    }
+}
+
+// P (n x n) from LDS to global memory, row by row, by the threads
+// t0 <= threadIdx.x < t1.
+template <class T, int NXT, int NUT, class U>
+__device__ __forceinline__ void copy_P(const Smem<T, NXT, NUT> &S, U *dst, int n, int t0 = 0,
+                                       int t1 = Smem<T, NXT, NUT>::NTH) {
+    using SM = Smem<T, NXT, NUT>;
+    int t = (int)threadIdx.x - t0;
+    const int nt = t1 - t0;
+    if (t < 0 || t >= nt) return;
+    asm volatile("" : "+v"(t));
+#pragma unroll 4
+    for (int e = t; e < SM::RX * SM::RX; e += nt) {
+        const int i = e / SM::RX, j = e % SM::RX;
+        if (i < n && j < n) dst[(uint32_t)(i * n + j)] = (U)S.P[at<SM::RX>(i, j)];
+    }
+}
+
+// Start of a pass: P from an element function (rows and columns < n).
+template <class T, int NXT, int NUT, class F>
+__device__ __forceinline__ void set_P(Smem<T, NXT, NUT> &S, int n, F f) {
+    using SM = Smem<T, NXT, NUT>;
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+#pragma unroll 4
+    for (int e = t; e < SM::RX * SM::RX; e += SM::NTH) {
+        const int i = e / SM::RX, j = e % SM::RX;
+        S.P[at<SM::RX>(i, j)] = (i < n && j < n) ? (T)f(i * n + j) : T(0);
+    }
+}
+
+// L^{-1} and L^{-T} (m x m, dense) from LDS to their records, by the threads
+// t0 <= threadIdx.x < t1.
+template <class T, int NXT, int NUT>
+__device__ __forceinline__ void copy_L(const Smem<T, NXT, NUT> &S, T *L, T *LT, int m, int t0, int t1) {
+    constexpr int RU = Smem<T, NXT, NUT>::RU;
+    int t = (int)threadIdx.x - t0;
+    asm volatile("" : "+v"(t));
+#pragma unroll 2
+    for (int e = t; e < RU * RU; e += t1 - t0) {
+        const int i = e / RU, k = e % RU;
+        if (i < m && k < m) {
+            L[(uint32_t)(i * m + k)] = k <= i ? S.G[at<RU>(i, k)] : T(0);
+            LT[(uint32_t)(i * m + k)] = i <= k ? S.G[at<RU>(k, i)] : T(0);
+        }
+    }
+}
+
+// Y = L^{-1} H' or X = L^{-1} B'V of one column block, in place and to LDS.
+// L^{-1} is lower triangular: row tile ti takes the inner tiles <= ti, so the
+// block is replaced from its last tile up.
+template <int RU, int RX, int NUT, class T>
+__device__ __forceinline__ void apply_Linv(const Ln<T> &L, const T *G, v4_t<T> *R2, T *D, int j) {
+#pragma unroll
+    for (int ti = NUT - 1; ti >= 0; --ti) {
+        v4_t<T> acc = zero4<T>();
+#pragma unroll
+        for (int kt = 0; kt <= ti; ++kt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc = MT<T>::mfma(ldR<RU>(L, G, ti, kt, r), R2[kt][r], acc);
+        R2[ti] = acc;
+        put<RX>(L, D, ti, j, acc);
+    }
+}
+
+// K = -L^{-T} Y or L_t = -L^{-T} X of one column block, to its record.
+template <bool EX, int RU, int NUT, class T>
+__device__ __forceinline__ void store_feedback(const Ln<T> &L, const T *G, const v4_t<T> *R2, T *D, int j, int n, int m) {
+#pragma unroll
+    for (int ti = 0; ti < NUT; ++ti) {
+        const v4_t<T> acc = mulN<RU, NUT>(L, zero4<T>(), G, ti, R2, ti);
+        store_tile<EX>(L, D, n, ti, j, m, n, v4_t<T>{-acc[0], -acc[1], -acc[2], -acc[3]});
+    }
+}
+
+// Stage loop of the waves that own a column block of A (w < NXT).
+template <bool RED, bool EX, class T, int NXT, int NUT, class Get, class RecOf>
+__device__ __forceinline__ void loop_P(Smem<T, NXT, NUT> &S, int n, int m, Get get, int count, int32_t *info, int inst,
+                                       int stage_base, int fail_code, RecOf rec) {
+    using SM = Smem<T, NXT, NUT>;
+    constexpr int RX = SM::RX, RU = SM::RU;
+    const int j = wave();
+    for (int s = count - 1; s >= 0; --s) {
+        const Ln<T> L;
+        const StageSrc src = get(s);
+        // ---- G = Qw + B'PB by the owners of B's columns
+        if (j < NUT) {
+            d4 qg[NUT];
+#pragma unroll
+            for (int ti = 0; ti < NUT; ++ti)
+                if (ti >= j) qg[ti] = load_tile<EX, false, true>(L, src.Qw, m, ti, j, m, m);
+            v4_t<T> b[NXT], wb[NXT];
+#pragma unroll
+            for (int kt = 0; kt < NXT; ++kt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) b[kt][r] = ldN<RU>(L, S.B, kt, j, r);
+#pragma unroll
+            for (int ti = 0; ti < NXT; ++ti) wb[ti] = mulN<RX, NXT>(L, zero4<T>(), S.P, ti, b);
+#pragma unroll
+            for (int ti = 0; ti < NUT; ++ti)
+                if (ti >= j) put_sym<RU>(L, S.G, ti, j, mulN<RU, NXT>(L, as_t<T>(qg[ti]), S.B, ti, wb));
+        }
+        lds_sync();
+        // ---- W, F, H' (the last wave of the workgroup factors G)
+        v4_t<T> R1[NXT], R2[NUT];
+        {
+            d4 q1[NXT], q2[NUT];
+#pragma unroll
+            for (int ti = 0; ti < NUT; ++ti)
+                q2[ti] = src.Qxw ? load_tile<EX, true, false>(L, src.Qxw, m, ti, j, m, n) : d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int ti = 0; ti < NXT; ++ti)
+                if (ti >= j) q1[ti] = load_tile<EX, false, false>(L, src.Qx, n, ti, j, n, n);
+            v4_t<T> a[NXT], wa[NXT];
+#pragma unroll
+            for (int kt = 0; kt < NXT; ++kt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) a[kt][r] = ldN<RX>(L, S.A, kt, j, r);
+#pragma unroll
+            for (int ti = 0; ti < NXT; ++ti) wa[ti] = mulN<RX, NXT>(L, zero4<T>(), S.P, ti, a);
+#pragma unroll
+            for (int ti = 0; ti < NUT; ++ti) R2[ti] = mulN<RU, NXT>(L, as_t<T>(q2[ti]), S.B, ti, wa);
+#pragma unroll
+            for (int ti = 0; ti < NXT; ++ti)
+                if (ti >= j) R1[ti] = mulN<RX, NXT>(L, as_t<T>(q1[ti]), S.A, ti, wa);
+        }
+        lds_sync();
+        if (threadIdx.x == 0 && S.bad) {
+            record_failure(info, inst, fail_code, stage_base < 0 ? -1 : stage_base + s);
+            S.bad = 0;
+        }
+        apply_Linv<RU, RX, NUT>(L, S.G, R2, S.Y(), j);
+        lds_sync();
+        // ---- P = F - Y'Y, K = -L^{-T} Y
+#pragma unroll
+        for (int ti = 0; ti < NXT; ++ti)
+            if (ti >= j) {
+                const v4_t<T> acc = mulN<RX, NUT>(L, zero4<T>(), S.Y(), ti, R2);
+                put_sym<RX>(L, S.P, ti, j,
+                            v4_t<T>{R1[ti][0] - acc[0], R1[ti][1] - acc[1], R1[ti][2] - acc[2], R1[ti][3] - acc[3]});
+            }
+        const Rec<T> out = rec(s);
+        if (out.K) store_feedback<EX, RU, NUT>(L, S.G, R2, out.K, j, n, m);
+        if (RED && out.L) copy_L(S, out.L, out.LT, m, 0, 64 * NXT);
+        lds_sync();
+        if (SM::OVER) lds_sync();
+    }
+}
+
+// Stage loop of the waves NXT + j: A and B of the next stage are loaded into
+// their registers, the last of them factors G, and for Alg. 4 they own the
+// column blocks of V and Q_w_hat.
+template <bool RED, bool EX, class T, int NXT, int NUT, class Get, class Pre, class RecOf>
+__device__ __forceinline__ void loop_V(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, int n, int m, Get get, int count, Pre pre,
+                                       RecOf rec) {
+    using SM = Smem<T, NXT, NUT>;
+    constexpr int RX = SM::RX, RU = SM::RU, NTV = 64 * NXT;
+    constexpr int NA = (RX * RX + NTV - 1) / NTV, NB = (RX * RU + NTV - 1) / NTV;
+    const int j = wave() - NXT;
+    double pa[NA], pb[NB];
+    auto fetch = [&](const StageSrc &src) {
+        int tv = (int)threadIdx.x - NTV;
+        asm volatile("" : "+v"(tv));
+#pragma unroll
+        for (int q = 0; q < NA; ++q) {
+            const int e = tv + q * NTV, i = e / RX, k = e % RX;
+            pa[q] = (EX || (i < n && k < n)) ? gload(src.A + (uint32_t)(i * n + k)) : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            const int e = tv + q * NTV, i = e / RU, k = e % RU;
+            pb[q] = (EX || (i < n && k < m)) ? gload(src.B + (uint32_t)(i * m + k)) : 0.0;
+        }
+    };
+    static_assert(RX * RX % NTV == 0 && RX * RU % NTV == 0, "whole rounds");
+    auto commit = [&]() {
+        int tv = (int)threadIdx.x - NTV;
+        asm volatile("" : "+v"(tv));
+#pragma unroll
+        for (int q = 0; q < NA; ++q) {
+            const int e = tv + q * NTV;
+            S.A[at<RX>(e / RX, e % RX)] = (T)pa[q];
+        }
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            const int e = tv + q * NTV;
+            S.B[at<RU>(e / RU, e % RU)] = (T)pb[q];
+        }
+    };
+    if (RED) {
+        const Ln<T> L;
+#pragma unroll
+        for (int ti = 0; ti < NXT; ++ti) {
+            C.Q[ti] = zero4<T>();
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                C.V[ti][r] = (16 * ti + L.row(r) == 16 * j + L.c) ? T(1) : T(0);
+        }
+    }
+    for (int s = count - 1; s >= 0; --s) {
+        const Ln<T> L;
+        if (s > 0) fetch(get(s - 1));
+        v4_t<T> R1[NXT], R2[NUT];
+        if (RED) {
+#pragma unroll
+            for (int ti = 0; ti < NUT; ++ti) R2[ti] = mulN<RU, NXT>(L, zero4<T>(), S.B, ti, C.V);
+#pragma unroll
+            for (int ti = 0; ti < NXT; ++ti) R1[ti] = mulN<RX, NXT>(L, zero4<T>(), S.A, ti, C.V);
+        }
+        lds_sync();
+        if (j == NXT - 1) {
+            const int f = chol_inv<T, NUT>(L, S.G);
+            if (f && lane() == 0) S.bad = 1;
+        }
+        if (NXT == 1 || j < NXT - 1) {
+            // the record of P_{s+1}, still in LDS
+            constexpr int t1 = NXT == 1 ? 2 * NTV : 2 * NTV - 64;
+            pre(s, NTV, t1);
+            if (s + 1 < count) {
+                T *p = rec(s + 1).P;
+                if (p) copy_P(S, p, n, NTV, t1);
+            }
+        }
+        lds_sync();
+        const Rec<T> out = rec(s);
+        if (RED) apply_Linv<RU, RX, NUT>(L, S.G, R2, S.X(), j);
+        if (!SM::OVER && s > 0) commit();        // A and B are dead
+        lds_sync();
+        if (RED) {
+            // ---- V = A'V - Y'X, Q_w_hat += X'X, L_t = -L^{-T} X
+#pragma unroll
+            for (int ti = 0; ti < NXT; ++ti) {
+                const v4_t<T> acc = mulN<RX, NUT>(L, zero4<T>(), S.Y(), ti, R2);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) C.V[ti][r] = R1[ti][r] - acc[r];
+                if (out.V) store_tile<EX>(L, out.V, n, ti, j, n, n, C.V[ti]);
+            }
+#pragma unroll
+            for (int ti = 0; ti < NXT; ++ti)
+                if (ti >= j) C.Q[ti] = mulN<RX, NUT>(L, C.Q[ti], S.X(), ti, R2);
+            if (out.Lt) store_feedback<EX, RU, NUT>(L, S.G, R2, out.Lt, j, n, m);
+        } else if (out.L) {
+            copy_L(S, out.L, out.LT, m, NTV, 2 * NTV);
+        }
+        lds_sync();
+        if (SM::OVER) {
+            if (s > 0) commit();
+            lds_sync();
+        }
+    }
+}
+
+// Backward pass over `count` stages (local s = count-1 .. 0).  P_{count} in
+// S.P (written by the caller; the pass starts with a barrier); RED: Alg. 4
+// from V = I, Q_w_hat = 0, result in C.  get(s): stage data; pre(s, t0, t1)
+// is called by the threads [t0, t1) before stage s and may read P_{s+1} from
+// S.P; rec(s): where its factors go.  EX: n = 16 NXT and m = 16 NUT exactly.
+// The two kinds of waves run loops of their own (with the same barriers), so
+// that neither carries the other's registers.
+template <bool RED, bool EX, class T, int NXT, int NUT, class Get, class Pre, class RecOf>
+__device__ __forceinline__ void pass(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, int n_, int m_, Get get, int count,
+                                     int32_t *info, int inst, int stage_base, int fail_code, Pre pre, RecOf rec) {
+    using SM = Smem<T, NXT, NUT>;
+    constexpr int RX = SM::RX, RU = SM::RU, NTH = SM::NTH;
+    static_assert(NUT <= NXT, "one column block of B per owner of A");
+    const int n = EX ? RX : n_, m = EX ? RU : m_;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    count = uni(count);
+    if (tid == 0) S.bad = 0;
+    if (count > 0) {
+        const StageSrc src = get(count - 1);
+#pragma unroll 4
+        for (int e = tid; e < RX * RX; e += NTH) {
+            const int i = e / RX, k = e % RX;
+            S.A[at<RX>(i, k)] = (EX || (i < n && k < n)) ? (T)gload(src.A + i * n + k) : T(0);
+        }
+#pragma unroll 4
+        for (int e = tid; e < RX * RU; e += NTH) {
+            const int i = e / RU, k = e % RU;
+            S.B[at<RU>(i, k)] = (EX || (i < n && k < m)) ? (T)gload(src.B + i * m + k) : T(0);
+        }
+    }
+    lds_sync();
+    if (wave() < NXT)
+        loop_P<RED, EX>(S, n, m, get, count, info, inst, stage_base, fail_code, rec);
+    else
+        loop_V<RED, EX>(S, C, n, m, get, count, pre, rec);
+    lds_sync();
+    if (count > 0) {
+        T *p = rec(0).P;
+        if (p) copy_P(S, p, n);
+    }
+}
+
+// V_0' and Q_w_hat (symmetric) from their owners' registers to row-major
+// n x n places.
+template <class T, int NXT, class U>
+__device__ __forceinline__ void store_V_transposed(const Cols<T, NXT> &C, U *dst, int n) {
+    const int j = wave() - NXT;
+    if (j < 0) return;
+    const Ln<T> L;
+#pragma unroll
+    for (int ti = 0; ti < NXT; ++ti)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 16 * ti + L.row(r), k = 16 * j + L.c;
+            if (i < n && k < n) dst[(uint32_t)(k * n + i)] = (U)C.V[ti][r];
+        }
+}
+template <class T, int NXT, class U>
+__device__ __forceinline__ void store_Q(const Cols<T, NXT> &C, U *dst, int n) {
+    const int j = wave() - NXT;
+    if (j < 0) return;
+    const Ln<T> L;
+#pragma unroll
+    for (int ti = 0; ti < NXT; ++ti) {
+        if (ti < j) continue;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 16 * ti + L.row(r), k = 16 * j + L.c;
+            if (i < n && k < n && i >= k) {
+                dst[(uint32_t)(i * n + k)] = (U)C.Q[ti][r];
+                dst[(uint32_t)(k * n + i)] = (U)C.Q[ti][r];
+            }
+        }
+    }
+}
+
+}  // namespace cw
+}  // namespace rs

@@ -1,10 +1,12 @@
 // Large-block kernels of the parallel Riccati solve: any n_x, n_u up to 128
-// without a register- and LDS-resident specialisation (the n_x = 64 and
-// n_x = 128 problems; also the stored factorization of the small shapes
-// whose fused solve has no matrix-core form).  A 64 x 64 FP64 stage already needs
-// about 260 KB of working set, more than a CU's LDS, so here the matrices of a
+// without a register- and LDS-resident specialisation.  Here the matrices of a
 // work unit live in a per-workgroup workspace in global memory (L2-resident
 // while the unit runs) and only vectors use LDS.  Sizes are run-time values.
+// The matrix side serves n_x > 64, shapes with more 16-wide tiles of inputs
+// than of states, and the BF16 products; the others up to n_x = 64 run on the
+// column-owner kernels (rs_mid.hip), which keep a stage in registers and LDS
+// (64 x 32, N = 1024, batch of 64: leaf factorization 26.3 ms here, 6.1 ms
+// there; master levels 4.2 and 0.95 ms).  The vector side serves all of them.
 //
 // The family implements the factor / solve split; the fused FP64 solve of
 // these shapes is the stored factorization followed by the solve on it.
@@ -984,7 +986,6 @@ __device__ void publish(const GroupArgs &g, int idx) {
     __syncthreads();
 }
 
-template <bool BIG>
 __global__ void __launch_bounds__(LB_MT) kl_tree(GroupArgs g) {
     __shared__ int s_item, bad;
     const int n = g.nx, tid = threadIdx.x;
@@ -1007,7 +1008,7 @@ __global__ void __launch_bounds__(LB_MT) kl_tree(GroupArgs g) {
             // excluded instance: only its completion flag is published
         } else if (it.kind == ITEM_UP) {
             init_red(S);
-            mpass<double, true, false, BIG>(S, get, it.count, g.info, it.inst, -1, 3, [](int) {},
+            mpass<double, true, false, true>(S, get, it.count, g.info, it.inst, -1, 3, [](int) {},
                                        SlotOut{slots, it.first, n, true, g.superpose != 0}, &bad);
             double *out = slot(it.out_slot);
             for (int e = tid; e < n * n; e += nthr()) {
@@ -1028,7 +1029,7 @@ __global__ void __launch_bounds__(LB_MT) kl_tree(GroupArgs g) {
             double *term = it.last ? slot(it.term_slot) : nullptr;
             for (int e = tid; e < n * n; e += nthr()) S.P[e] = term ? term[SL.Qx() + e] : msg[SL.P() + e];
             __syncthreads();
-            mpass<double, false, false, BIG>(
+            mpass<double, false, false, true>(
                 S, get, it.count, g.info, it.inst, -1, 3,
                 [&](int s) {      // M2 for child s: P at the end of master stage s
                     if (!upl) {
@@ -1810,6 +1811,7 @@ inline bool big_stage(const GroupArgs &g) { return g.nx > 64; }
 
 template <class T, bool BF = false>
 hipError_t launch_leaf_up(const GroupArgs &g, int, hipStream_t st) {
+    if (!BF && mid_shape(g.nx, g.nu)) return sizeof(T) == 4 ? mid_leaf_f32(g, false, st) : mid_leaf_f64(g, false, st);
     if (big_stage(g))
         hipLaunchKernelGGL((kl_leaf_up<T, BF, true>), dim3(leaf_units(g)), dim3(LB_MT), 0, st, g);
     else
@@ -1817,15 +1819,14 @@ hipError_t launch_leaf_up(const GroupArgs &g, int, hipStream_t st) {
     return hipGetLastError();
 }
 hipError_t launch_tree(const GroupArgs &g, int grid, hipStream_t st) {
-    if (big_stage(g))
-        hipLaunchKernelGGL(kl_tree<true>, dim3(std::min(grid, LB_TREE_UNITS)), dim3(LB_MT), 0, st, g);
-    else
-        hipLaunchKernelGGL(kl_tree<false>, dim3(std::min(grid, LB_TREE_UNITS)), dim3(LB_MT), 0, st, g);
+    if (!big_stage(g)) return mid_tree(g, grid, st);
+    hipLaunchKernelGGL(kl_tree, dim3(std::min(grid, LB_TREE_UNITS)), dim3(LB_MT), 0, st, g);
     return hipGetLastError();
 }
 template <class T, bool BF = false>
 hipError_t launch_leaf_down(const GroupArgs &g, int, hipStream_t st) {
     if (g.ntop == 0) return hipSuccess;
+    if (!BF && mid_shape(g.nx, g.nu)) return sizeof(T) == 4 ? mid_leaf_f32(g, true, st) : mid_leaf_f64(g, true, st);
     if (big_stage(g))
         hipLaunchKernelGGL((kl_leaf_down<T, BF, true>), dim3(leaf_units(g)), dim3(LB_MT), 0, st, g);
     else

@@ -66,6 +66,13 @@ size_t large_unit_bytes(int nx, int nu);
 Launcher large_factor(int which, bool fp32, bool bf16 = false);
 Launcher large_vector(int which, bool fp32);
 Launcher large_refine(int which);
+// Stored factorization on the column-owner engine (rs_mid.hip): n_x <= 64 and
+// no more 16-wide tiles of inputs than of states; the larger shapes, and those
+// with more inputs than states, need the global-memory workspace.
+inline bool mid_shape(int nx, int nu) { return nx <= 64 && (nu + 15) / 16 <= (nx + 15) / 16; }
+hipError_t mid_leaf_f64(const GroupArgs &g, bool down, hipStream_t st);
+hipError_t mid_leaf_f32(const GroupArgs &g, bool down, hipStream_t st);
+hipError_t mid_tree(const GroupArgs &g, int grid, hipStream_t st);      // n_x <= 64
 Launcher mfma_factor_leaf32(int nx, int nu, int which);   // FP32 leaves of n_x = 64 (which 0 up, 2 down)
 
 const ShapeEntry *find_shape(int nx, int nu);

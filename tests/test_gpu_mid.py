@@ -1,0 +1,34 @@
+"""GPU parity of the column-owner stored factorization (n_x <= 64, run-time
+sizes padded to 16-wide tiles) at the edges of its tiles, against the serial
+FP64 oracle: one below, at and one above a multiple of 16, the smallest and
+the largest sizes, a single input, as many inputs as states (where Y and X lie
+over A and B), single-leaf instances and short last leaves.  Tolerance: the
+repository's bar of 1e-10 relative per block."""
+import pytest
+
+from oracle import kkt, riccati
+from paper_1510_03110_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-10
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("nx,nu,N,Ns", [(5, 3, 37, 8), (15, 15, 40, 4), (17, 16, 33, 8), (17, 17, 26, 6), (33, 1, 60, 70),
+                                        (33, 32, 41, 8), (47, 33, 30, 6), (49, 7, 50, 16), (63, 31, 43, 8),
+                                        (64, 33, 29, 7), (64, 48, 20, 5), (64, 64, 21, 4), (50, 25, 12, 16)])
+def test_column_owner_shapes(nx, nu, N, Ns, precision):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1510_03110_amd import rs
+    prob = W.with_costs(W.g2(nx, nu, N, seed=nx * 100 + nu), seed=N)
+    bt = rs.Batch({k: [prob[k]] for k in prob}, precision=precision, Ns=Ns, branch=2, factored=True)
+    bt.factor()
+    bt.solve_factored()
+    torch.cuda.synchronize()
+    assert bt.status()[0].tolist() == [0, -1]
+    sol, ref = bt.result(0), riccati.solve(prob)
+    assert kkt.rel_error(sol, ref) <= TOL
+    assert abs(sol["obj"] - ref["obj"]) <= 1e-9 * max(1.0, abs(ref["obj"]))
+    bt.close()
