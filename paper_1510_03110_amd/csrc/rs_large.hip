@@ -6,7 +6,9 @@
 // than of states, and the BF16 products; the others up to n_x = 64 run on the
 // column-owner kernels (rs_mid.hip), which keep a stage in registers and LDS
 // (64 x 32, N = 1024, batch of 64: leaf factorization 26.3 ms here, 6.1 ms
-// there; master levels 4.2 and 0.95 ms).  The vector side serves all of them.
+// there; master levels 4.2 and 0.95 ms).  The vector side serves n_x or
+// n_u > 64, and the tree of RS_PLAN_REFACTOR_DOWN at any size; the others run
+// on the prefetching sweeps (rs_vsweep.hip).
 //
 // The family implements the factor / solve split; the fused FP64 solve of
 // these shapes is the stored factorization followed by the solve on it.
@@ -1835,15 +1837,18 @@ hipError_t launch_leaf_down(const GroupArgs &g, int, hipStream_t st) {
 }
 template <class TR>
 hipError_t launch_vup(const GroupArgs &g, int, hipStream_t st) {
+    if (sweep_shape(g.nx, g.nu)) return sweep_leaf(g, sizeof(TR) == 4, false, st);
     hipLaunchKernelGGL((kw_leaf_up<TR>), dim3(g.nleaves), dim3(vthreads(g)), 0, st, g);
     return hipGetLastError();
 }
 hipError_t launch_vtree(const GroupArgs &g, int grid, hipStream_t st) {
+    if (g.nx <= 64 && g.superpose) return sweep_tree(g, grid, st);
     hipLaunchKernelGGL(kw_tree, dim3(grid), dim3(vthreads(g)), 0, st, g);
     return hipGetLastError();
 }
 template <class TR>
 hipError_t launch_vdown(const GroupArgs &g, int, hipStream_t st) {
+    if (sweep_shape(g.nx, g.nu)) return sweep_leaf(g, sizeof(TR) == 4, true, st);
     hipLaunchKernelGGL((kw_leaf_down<TR>), dim3(g.nleaves), dim3(vthreads(g)), 0, st, g);
     return hipGetLastError();
 }

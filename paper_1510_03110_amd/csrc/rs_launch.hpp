@@ -73,6 +73,11 @@ inline bool mid_shape(int nx, int nu) { return nx <= 64 && (nu + 15) / 16 <= (nx
 hipError_t mid_leaf_f64(const GroupArgs &g, bool down, hipStream_t st);
 hipError_t mid_leaf_f32(const GroupArgs &g, bool down, hipStream_t st);
 hipError_t mid_tree(const GroupArgs &g, int grid, hipStream_t st);      // n_x <= 64
+// Right-hand-side sweeps with register prefetch (rs_vsweep.hip), n_x, n_u <= 64
+// (the tree: superposition down pass only).
+inline bool sweep_shape(int nx, int nu) { return nx <= 64 && nu <= 64; }
+hipError_t sweep_leaf(const GroupArgs &g, bool fp32, bool down, hipStream_t st);
+hipError_t sweep_tree(const GroupArgs &g, int grid, hipStream_t st);
 Launcher mfma_factor_leaf32(int nx, int nu, int which);   // FP32 leaves of n_x = 64 (which 0 up, 2 down)
 
 const ShapeEntry *find_shape(int nx, int nu);

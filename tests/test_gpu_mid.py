@@ -32,3 +32,31 @@ def test_column_owner_shapes(nx, nu, N, Ns, precision):
     assert kkt.rel_error(sol, ref) <= TOL
     assert abs(sol["obj"] - ref["obj"]) <= 1e-9 * max(1.0, abs(ref["obj"]))
     bt.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("nx,nu,N,Ns,b", [(3, 7, 7, 1, 2), (8, 4, 9, 4, 3), (16, 32, 11, 2, 2), (31, 33, 8, 2, 4), (33, 64, 10, 3, 2),
+                                          (64, 64, 5, 2, 2)])
+def test_prefetched_sweeps_at_short_lengths(nx, nu, N, Ns, b, precision):
+    """The right-hand-side sweeps, whose matrices come through registers one
+    stage ahead, at leaf and master lengths of one to four stages, at the
+    edges of their size classes, with more inputs than states, and without
+    the optional vectors a, lx, lw and c.  Bar as above."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1510_03110_amd import rs
+    prob = W.with_costs(W.g2(nx, nu, N, seed=nx * 100 + nu + 7), seed=N)
+    for drop in ((), ("a", "lx", "lw", "c")):
+        data = {k: [prob[k]] for k in prob if k not in drop}
+        data["N"] = [N]
+        ref = riccati.solve({**prob, **{k: 0.0 * prob[k] for k in drop}})
+        bt = rs.Batch(data, precision=precision, Ns=Ns, branch=b, factored=True)
+        bt.factor()
+        bt.solve_factored()
+        torch.cuda.synchronize()
+        assert bt.status()[0].tolist() == [0, -1]
+        sol = bt.result(0)
+        assert kkt.rel_error(sol, ref) <= TOL
+        assert abs(sol["obj"] - ref["obj"]) <= 1e-9 * max(1.0, abs(ref["obj"]))
+        bt.close()
