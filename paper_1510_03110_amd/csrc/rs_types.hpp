@@ -1,6 +1,7 @@
 // Plain structs shared by the host planner and the device kernels of the
 // parallel Riccati solver.  No arithmetic lives here.
 #pragma once
+#include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace rs {
@@ -119,6 +120,11 @@ struct LeafRec {
     __host__ __device__ int per_stage() const { return up() + down(); }
     __host__ __device__ int vec() const { return nx + nu; }
 };
+
+// Record of one leaf stage of the fused solve (leaf scratch, FP64):
+//   K (m n) | k (m) | P (n n) | Psi (n) | V (n n) | L_t (m n)
+// (the last two for reduced leaves only).
+__host__ __device__ constexpr int leaf_rec_len(int n, int m) { return 2 * n * m + m + 2 * n * n + n; }
 
 // Per-instance entry of the refinement tables: the instance's leaves are
 // global leaf indices first_leaf .. first_leaf + nleaves - 1.

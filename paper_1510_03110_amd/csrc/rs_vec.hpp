@@ -54,6 +54,36 @@ __device__ __forceinline__ double group_sum(double v) {
 
 __device__ __forceinline__ double wave_sum(double v) { return group_sum<64>(v); }
 
+// Global-memory accesses through address space 1: pointers that come out of a
+// descriptor are generic, and a generic access also counts as an LDS access,
+// so that every wait for LDS would wait for the loads in flight.
+template <class U>
+__device__ __forceinline__ U gl(const U *p) {
+    return *(const __attribute__((address_space(1))) U *)p;
+}
+template <class U>
+__device__ __forceinline__ void gs(U *p, U v) {
+    *(__attribute__((address_space(1))) U *)p = v;
+}
+
+// Sum over the lanes that differ in bit log2(B) of their index; every lane
+// receives it.  Rows of 16 are exchanged with the row and half-wave swaps.
+template <int B>
+__device__ __forceinline__ double xor_sum(double v) {
+    if constexpr (B == 32 || B == 16) {
+        const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+        const auto l = B == 32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                               : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        const auto h = B == 32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                               : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    } else if constexpr (B == 8) {
+        return v + dpp_move<0x128>(v);          // row_ror:8
+    } else {
+        return v + __shfl_xor(v, B, 64);
+    }
+}
+
 // Matrix operand of one product y = M x with R outputs and C inputs, held in
 // registers.  The wavefront is split into 64 / Rp parts (Rp = R rounded up to
 // a power of two); part p sums the contiguous input range
