@@ -1,6 +1,7 @@
-// Column-owner form of the per-stage Riccati recursion (matrix lines of
-// Alg. 1 and Alg. 4) for n_x <= 64 and n_u <= n_x (in tiles of 16), in FP64
-// or FP32.
+// Column-owner form of the per-stage Riccati recursion (Alg. 1-2 and Alg. 4)
+// for n_x <= 64 and n_u <= n_x (in tiles of 16), in FP64 or FP32: the matrix
+// lines alone (stored factorization), or with the right-hand-side lines (VEC,
+// fused solve, FP64).
 //
 // A workgroup of 2 NXT wavefronts (NXT = n_x / 16 rounded up) owns one
 // subproblem.  Wave j < NXT owns the 16-wide column block j of A, F, H', Y,
@@ -23,10 +24,17 @@
 // and mirrored, so they are exactly symmetric.  Four workgroup barriers a
 // stage; the next stage's A and B wait in registers.
 //
+// The vector lines ride on the same registers: the owner of a column block
+// also owns those entries of Psi, v and g_x, whose products with a column
+// block are sums over its own lanes (P a, A'pt, V'a, Y'z, X'z), and the owner
+// of column block 0 forms z = L^{-1} g_w and k = L^{-T} z from the operands it
+// reads for Y and K anyway.
+//
 // Sizes that are not multiples of 16 are padded with zeros on load (an
 // identity in the padded block of Q_w), which decouples the padding.
 #pragma once
 #include "rs_mfma.hpp"
+#include "rs_vec.hpp"
 
 namespace rs {
 namespace cw {
@@ -122,36 +130,81 @@ __device__ __forceinline__ void put_sym(const Ln<T> &L, T *M, int ti, int tj, v4
     }
 }
 
+__device__ __forceinline__ double rcp_est(double d) { return __builtin_amdgcn_rcp(d); }
+__device__ __forceinline__ float rcp_est(float d) { return __builtin_amdgcn_rcpf(d); }
+
+// Step K of the in-place elimination below: column K of the block becomes
+// column K of L_u^{-1}.  r = 1 / d_K comes from the hardware estimate and two
+// Newton steps; the square roots are left to the end.
+template <int K, class T>
+__device__ __forceinline__ void elim_step(T (&a)[4], int i, int h, T &piv, int &fail, int steps) {
+    if constexpr (K % 4 == 0 && K > 0) {
+        if (K >= steps) return;                       // padding: unit pivots, nothing to eliminate
+    }
+    constexpr int kh = K >> 2, kc = K & 3;
+    T d = bcast_lane(a[kc], 16 * kh + K);            // pivot d_K (wave-uniform)
+    const T f = __shfl(a[kc], 16 * kh + i, 64);       // entry (i, K) of this lane's row
+    const bool bad = !(d > T(0)) || !__builtin_isfinite(d);
+    fail |= bad ? 1 : 0;
+    d = bad ? T(1) : d;
+    T r = rcp_est(d);
+    r = r + r * (T(1) - d * r);
+    r = r + r * (T(1) - d * r);
+    if (i == K) piv = d;
+    const T m = i > K ? f * r : T(0);                 // rows above the pivot keep their values
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const T t = a[c] - m * mf::row_bcast<K>(a[c]);
+        a[c] = (c == kc && h == kh && i > K) ? -m : t;
+    }
+    if constexpr (K + 1 < 16) elim_step<K + 1>(a, i, h, piv, fail, steps);
+}
+
+// Inverse Cholesky factor of the 16 x 16 diagonal block kb of G, in place
+// (upper half zero), by one wavefront: Gaussian elimination without pivoting
+// in place (lane i + 16 h holds columns 4 h .. 4 h + 3 of row i) turns the
+// block into D L_u' on and above the diagonal and L_u^{-1} below it, with
+// G = L_u D L_u', so that L^{-1} = D^{-1/2} L_u^{-1}: the same factorization
+// and forward substitution as the textbook sweep, in the 256 elements of the
+// block itself.  `steps`: rows that are not padding.  (On [G | I], twice the
+// elements and a square root in every step, a block took 5 to 6 k cycles.)
+template <int PU, class T>
+__device__ __forceinline__ int chol_block(T *G, int kb, int steps) {
+    int l = lane();
+    asm volatile("" : "+v"(l));          // lane constants are not kept across stages
+    const int i = l & 15, h = l >> 4;
+    T a[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) a[c] = G[at<PU>(16 * kb + i, 16 * kb + 4 * h + c)];
+    int fail = 0;
+    T piv = T(1);
+    elim_step<0>(a, i, h, piv, fail, steps);
+    T is = mf::rsq_est(piv);
+    is = is * (T(1.5) - T(0.5) * piv * is * is);
+    is = is * (T(1.5) - T(0.5) * piv * is * is);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int j = 4 * h + c;
+        G[at<PU>(16 * kb + i, 16 * kb + j)] = j < i ? a[c] * is : j == i ? is : T(0);
+    }
+    return fail;
+}
+
 // Cholesky factorization and inverse of the NB x NB blocks of G (lower part
-// and full diagonal blocks given), by one wavefront, in place: on return the
-// lower blocks hold L^{-1} (the diagonal ones with a zero upper half), the
-// upper ones the off-diagonal blocks of L'.  Right-looking over 16-wide
-// blocks: L_kk^{-1} by elimination (chol16_step), L_ik' = L_kk^{-1} G_ik',
+// and full diagonal blocks given; m rows, the rest identity), by one
+// wavefront, in place: on return the lower blocks hold L^{-1} (the diagonal
+// ones with a zero upper half), the upper ones the off-diagonal blocks of L'.
+// Right-looking over 16-wide blocks: L_kk^{-1}, L_ik' = L_kk^{-1} G_ik',
 // G_ij -= L_ik L_jk'; then block row by block row of the inverse,
 // X_ij = -X_ii sum_k L_ik X_kj.  Returns nonzero if a pivot failed.
 template <class T, int NB>
-__device__ __forceinline__ int chol_inv(const Ln<T> &L, T *G) {
+__device__ __forceinline__ int chol_inv(const Ln<T> &L, T *G, int m) {
     constexpr int PU = 16 * NB;
     int fail = 0;
 #pragma unroll
     for (int kb = 0; kb < NB; ++kb) {
-        {
-            int l = lane();
-            asm volatile("" : "+v"(l));          // see mf::chol_inv16
-            const int i = l & 15, h = l >> 4;
-            T a[8];
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const T g = G[at<PU>(16 * kb + i, 16 * kb + ((8 * h + c) & 15))];
-                a[c] = h < 2 ? g : (8 * (h - 2) + c == i ? T(1) : T(0));
-            }
-            T sdi = T(0);
-            mf::chol16_step<0>(a, i, sdi, fail);
-            if (h >= 2) {
-#pragma unroll
-                for (int c = 0; c < 8; ++c) G[at<PU>(16 * kb + i, 16 * kb + 8 * (h - 2) + c)] = a[c] * sdi;
-            }
-        }
+        fail |= chol_block<PU>(G, kb, m - 16 * kb);
+        if constexpr (NB == 1) return fail;
         wave_fence();
         // L_ik' into the upper block (k, i)
         v4_t<T> u[NB];
@@ -188,7 +241,8 @@ __device__ __forceinline__ int chol_inv(const Ln<T> &L, T *G) {
 #pragma unroll
             for (int kb = jb; kb < ib; ++kb)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) s = MT<T>::mfma(ldN<PU>(L, G, kb, ib, r), ldN<PU>(L, G, kb, jb, r), s);
+                for (int r = 0; r < 4; ++r)
+                    s = MT<T>::mfma(ldN<PU>(L, G, kb, ib, r), ldN<PU>(L, G, kb, jb, r), s);
             v4_t<T> x = zero4<T>();
 #pragma unroll
             for (int r = 0; r < 4; ++r) x = MT<T>::mfma(ldR<PU>(L, G, ib, ib, r), s[r], x);
@@ -209,6 +263,8 @@ struct Smem {
     static constexpr bool OVER = apart > 159 * 1024;
     T P[RX * RX], A[RX * RX], B[RX * RU], G[RU * RU];
     T YX[OVER ? 1 : 2 * RU * RX];
+    double av[RX], pt[RX], gw[RU], z[RU];      // VEC
+    double red[2 * NXT];
     int bad;
     __device__ T *Y() { return OVER ? A : YX; }
     __device__ T *X() { return OVER ? B : YX + (OVER ? 0 : RU * RX); }
@@ -221,11 +277,28 @@ struct Cols {
     v4_t<T> V[NXT], Q[NXT];
 };
 
-// Where the factors of a stage go (row-major; nullptr: not kept).
+// Where the factors of a stage go (row-major; nullptr: not kept), and Psi_t
+// and k_{t+1} (VEC).
 template <class T>
 struct Rec {
     T *P, *K, *V, *Lt, *L, *LT;
+    double *Psi, *k;
 };
+// What of it a pass keeps: decided per stage by the pointers (KEEP_GIVEN), or
+// at compile time all of it but L^{-1} and L^{-T} (KEEP_ALL, the records of
+// the fused solve; the loop then has no branches around its stores, and a
+// wait for a load need not assume anything about them).
+enum { KEEP_GIVEN = 0, KEEP_ALL = 1 };
+
+// Running right-hand side of a pass (VEC) in its owners' lanes: entry 16 j +
+// lane % 16 of Psi (waves j) and of v (waves NXT + j), and this lane's part of
+// cbar (without the constants c).
+struct Vec {
+    double psi, v, cb;
+};
+
+// Sum over the four lanes that hold one column of a result tile.
+__device__ __forceinline__ double q_sum(double v) { return sv::xor_sum<32>(sv::xor_sum<16>(v)); }
 
 // 16x16 tile of problem data in the result layout; zeros outside n1 x n2
 // (identity where ONE).  TR reads the transposed element.
@@ -305,47 +378,128 @@ __device__ __forceinline__ void copy_L(const Smem<T, NXT, NUT> &S, T *L, T *LT, 
 
 // Y = L^{-1} H' or X = L^{-1} B'V of one column block, in place and to LDS.
 // L^{-1} is lower triangular: row tile ti takes the inner tiles <= ti, so the
-// block is replaced from its last tile up.
-template <int RU, int RX, int NUT, class T>
-__device__ __forceinline__ void apply_Linv(const Ln<T> &L, const T *G, v4_t<T> *R2, T *D, int j) {
+// block is replaced from its last tile up.  Z: also z = L^{-1} gw (to zv).
+template <int RU, int RX, int NUT, bool Z = false, class T>
+__device__ __forceinline__ void apply_Linv(const Ln<T> &L, const T *G, v4_t<T> *R2, T *D, int j,
+                                           const double *gw = nullptr, double *zv = nullptr, double *zz = nullptr) {
 #pragma unroll
     for (int ti = NUT - 1; ti >= 0; --ti) {
+        tile_fence();
         v4_t<T> acc = zero4<T>();
+        double z = 0.0;
 #pragma unroll
         for (int kt = 0; kt <= ti; ++kt)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc = MT<T>::mfma(ldR<RU>(L, G, ti, kt, r), R2[kt][r], acc);
+            for (int r = 0; r < 4; ++r) {
+                const T a = ldR<RU>(L, G, ti, kt, r);
+                acc = MT<T>::mfma(a, R2[kt][r], acc);
+                if constexpr (Z) z += (double)a * gw[16 * kt + L.row(r)];
+            }
         R2[ti] = acc;
         put<RX>(L, D, ti, j, acc);
+        if constexpr (Z) {
+            z = q_sum(z);
+            if (L.q == 0) {
+                zv[16 * ti + L.c] = z;
+                *zz -= 0.5 * z * z;
+            }
+        }
     }
 }
 
-// K = -L^{-T} Y or L_t = -L^{-T} X of one column block, to its record.
-template <bool EX, int RU, int NUT, class T>
-__device__ __forceinline__ void store_feedback(const Ln<T> &L, const T *G, const v4_t<T> *R2, T *D, int j, int n, int m) {
+// K = -L^{-T} Y or L_t = -L^{-T} X of one column block, to its record.  Z:
+// also k = L^{-T} z.
+template <bool EX, int RU, int NUT, bool Z = false, class T>
+__device__ __forceinline__ void store_feedback(const Ln<T> &L, const T *G, const v4_t<T> *R2, T *D, int j, int n, int m,
+                                               const double *zv = nullptr, double *k = nullptr) {
 #pragma unroll
     for (int ti = 0; ti < NUT; ++ti) {
-        const v4_t<T> acc = mulN<RU, NUT>(L, zero4<T>(), G, ti, R2, ti);
+        tile_fence();
+        v4_t<T> acc = zero4<T>();
+        double s = 0.0;
+#pragma unroll
+        for (int kt = ti; kt < NUT; ++kt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const T a = ldN<RU>(L, G, kt, ti, r);
+                acc = MT<T>::mfma(a, R2[kt][r], acc);
+                if constexpr (Z) s += (double)a * zv[16 * kt + L.row(r)];
+            }
         store_tile<EX>(L, D, n, ti, j, m, n, v4_t<T>{-acc[0], -acc[1], -acc[2], -acc[3]});
+        if constexpr (Z) {
+            s = q_sum(s);
+            if (L.q == 0 && (EX || 16 * ti + L.c < m)) sv::gs(k + (uint32_t)(16 * ti + L.c), s);
+        }
     }
 }
 
+// The inputs a wave that owns a column block of A adds to its products,
+// loaded one stage ahead at n_x <= 32 (where a stage is shorter than a memory
+// latency) and at the start of their phase otherwise.
+template <int NXT, int NUT>
+struct QTiles {
+    static constexpr bool AHEAD = NXT <= 2;
+    d4 g[NUT], f[NXT], h[NUT];
+    double lx, lw;
+};
+
 // Stage loop of the waves that own a column block of A (w < NXT).
-template <bool RED, bool EX, class T, int NXT, int NUT, class Get, class RecOf>
+template <bool RED, bool EX, bool VEC, int KEEP, class T, int NXT, int NUT, class Get, class Pre, class RecOf>
 __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT> &S, int n, int m, Get get, int count, int32_t *info, int inst,
-                                       int stage_base, int fail_code, RecOf rec) {
+                                       int stage_base, int fail_code, Pre pre, RecOf rec, Vec &y) {
     using SM = Smem<T, NXT, NUT>;
+    using QT = QTiles<NXT, NUT>;
     constexpr int RX = SM::RX, RU = SM::RU;
     const int j = wave();
-    for (int s = count - 1; s >= 0; --s) {
-        const Ln<T> L;
-        const StageSrc src = get(s);
-        // ---- G = Qw + B'PB by the owners of B's columns
+    QT q;
+    auto load_g = [&](const Ln<T> &L, const StageSrc &src) {
         if (j < NUT) {
-            d4 qg[NUT];
 #pragma unroll
             for (int ti = 0; ti < NUT; ++ti)
-                if (ti >= j) qg[ti] = load_tile<EX, false, true>(L, src.Qw, m, ti, j, m, m);
+                if (ti >= j) q.g[ti] = load_tile<EX, false, true>(L, src.Qw, m, ti, j, m, m);
+            if constexpr (VEC)
+                q.lw = (src.lw && (EX || 16 * j + L.c < m)) ? gload(src.lw + (uint32_t)(16 * j + L.c)) : 0.0;
+        }
+    };
+    auto load_f = [&](const Ln<T> &L, const StageSrc &src) {
+        if (src.Qxw) {
+#pragma unroll
+            for (int ti = 0; ti < NUT; ++ti) q.h[ti] = load_tile<EX, true, false>(L, src.Qxw, m, ti, j, m, n);
+        } else {
+#pragma unroll
+            for (int ti = 0; ti < NUT; ++ti) q.h[ti] = d4{0.0, 0.0, 0.0, 0.0};
+        }
+#pragma unroll
+        for (int ti = 0; ti < NXT; ++ti)
+            if (ti >= j) q.f[ti] = load_tile<EX, false, false>(L, src.Qx, n, ti, j, n, n);
+        if constexpr (VEC)
+            q.lx = (src.lx && (EX || 16 * j + L.c < n)) ? gload(src.lx + (uint32_t)(16 * j + L.c)) : 0.0;
+    };
+    StageSrc src = get(count - 1);
+    if (QT::AHEAD) {
+        const Ln<T> L;
+        load_g(L, src);
+        load_f(L, src);
+    }
+    for (int s = count - 1; s >= 0; --s) {
+        const Ln<T> L;
+        const StageSrc nxt = s > 0 ? get(s - 1) : StageSrc{};
+        if (!QT::AHEAD) load_g(L, src);
+        double pa = 0.0;
+        if constexpr (VEC) {
+            // ---- pt = Psi - P a, cbar += 1/2 a'Pa - Psi'a
+#pragma unroll
+            for (int kt = 0; kt < NXT; ++kt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) pa += ldN<RX>(L, S.P, kt, j, r) * S.av[16 * kt + L.row(r)];
+            pa = q_sum(pa);
+            if (L.q == 0) {
+                S.pt[16 * j + L.c] = y.psi - pa;
+                y.cb += S.av[16 * j + L.c] * (0.5 * pa - y.psi);
+            }
+        }
+        // ---- G = Qw + B'PB by the owners of B's columns
+        if (j < NUT) {
             v4_t<T> b[NXT], wb[NXT];
 #pragma unroll
             for (int kt = 0; kt < NXT; ++kt)
@@ -355,40 +509,66 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT> &S, int n, int m, Get g
             for (int ti = 0; ti < NXT; ++ti) wb[ti] = mulN<RX, NXT>(L, zero4<T>(), S.P, ti, b);
 #pragma unroll
             for (int ti = 0; ti < NUT; ++ti)
-                if (ti >= j) put_sym<RU>(L, S.G, ti, j, mulN<RU, NXT>(L, as_t<T>(qg[ti]), S.B, ti, wb));
+                if (ti >= j) put_sym<RU>(L, S.G, ti, j, mulN<RU, NXT>(L, as_t<T>(q.g[ti]), S.B, ti, wb));
         }
         lds_sync();
-        // ---- W, F, H' (the last wave of the workgroup factors G)
+        // ---- W, F, H', g_x, g_w (the last wave of the workgroup factors G)
         v4_t<T> R1[NXT], R2[NUT];
+        double gx = 0.0;
+        if (!QT::AHEAD) load_f(L, src);
         {
-            d4 q1[NXT], q2[NUT];
-#pragma unroll
-            for (int ti = 0; ti < NUT; ++ti)
-                q2[ti] = src.Qxw ? load_tile<EX, true, false>(L, src.Qxw, m, ti, j, m, n) : d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int ti = 0; ti < NXT; ++ti)
-                if (ti >= j) q1[ti] = load_tile<EX, false, false>(L, src.Qx, n, ti, j, n, n);
             v4_t<T> a[NXT], wa[NXT];
 #pragma unroll
             for (int kt = 0; kt < NXT; ++kt)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) a[kt][r] = ldN<RX>(L, S.A, kt, j, r);
+            if constexpr (VEC) {
+#pragma unroll
+                for (int kt = 0; kt < NXT; ++kt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) gx += a[kt][r] * S.pt[16 * kt + L.row(r)];
+                gx = q_sum(gx) - q.lx;
+                if (j < NUT) {
+                    double g = 0.0;
+#pragma unroll
+                    for (int kt = 0; kt < NXT; ++kt)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) g += ldN<RU>(L, S.B, kt, j, r) * S.pt[16 * kt + L.row(r)];
+                    g = q_sum(g) - q.lw;
+                    if (L.q == 0) S.gw[16 * j + L.c] = g;
+                }
+            }
+            if (QT::AHEAD && s > 0) load_g(L, nxt);
 #pragma unroll
             for (int ti = 0; ti < NXT; ++ti) wa[ti] = mulN<RX, NXT>(L, zero4<T>(), S.P, ti, a);
 #pragma unroll
-            for (int ti = 0; ti < NUT; ++ti) R2[ti] = mulN<RU, NXT>(L, as_t<T>(q2[ti]), S.B, ti, wa);
+            for (int ti = 0; ti < NUT; ++ti) R2[ti] = mulN<RU, NXT>(L, as_t<T>(q.h[ti]), S.B, ti, wa);
 #pragma unroll
             for (int ti = 0; ti < NXT; ++ti)
-                if (ti >= j) R1[ti] = mulN<RX, NXT>(L, as_t<T>(q1[ti]), S.A, ti, wa);
+                if (ti >= j) R1[ti] = mulN<RX, NXT>(L, as_t<T>(q.f[ti]), S.A, ti, wa);
         }
+        if (QT::AHEAD && s > 0) load_f(L, nxt);
+        if (NXT == 1) {
+            // the record of P_{s+1}, still in LDS (the other wave factors G)
+            pre(s, 0, 64);
+            if (s + 1 < count) {
+                T *p = rec(s + 1).P;
+                if (KEEP == KEEP_ALL || p) copy_P(S, p, n, 0, 64);
+            }
+        }
+        src = nxt;
         lds_sync();
         if (threadIdx.x == 0 && S.bad) {
             record_failure(info, inst, fail_code, stage_base < 0 ? -1 : stage_base + s);
             S.bad = 0;
         }
-        apply_Linv<RU, RX, NUT>(L, S.G, R2, S.Y(), j);
+        if (VEC && j == 0)
+            apply_Linv<RU, RX, NUT, VEC>(L, S.G, R2, S.Y(), j, S.gw, S.z, &y.cb);
+        else
+            apply_Linv<RU, RX, NUT>(L, S.G, R2, S.Y(), j);
         lds_sync();
-        // ---- P = F - Y'Y, K = -L^{-T} Y
+        // ---- P = F - Y'Y, K = -L^{-T} Y, Psi = g_x - Y'z, k = L^{-T} z
+        const Rec<T> out = rec(s);
 #pragma unroll
         for (int ti = 0; ti < NXT; ++ti)
             if (ti >= j) {
@@ -396,9 +576,23 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT> &S, int n, int m, Get g
                 put_sym<RX>(L, S.P, ti, j,
                             v4_t<T>{R1[ti][0] - acc[0], R1[ti][1] - acc[1], R1[ti][2] - acc[2], R1[ti][3] - acc[3]});
             }
-        const Rec<T> out = rec(s);
-        if (out.K) store_feedback<EX, RU, NUT>(L, S.G, R2, out.K, j, n, m);
-        if (RED && out.L) copy_L(S, out.L, out.LT, m, 0, 64 * NXT);
+        if constexpr (VEC) {
+            double yz = 0.0;
+#pragma unroll
+            for (int ti = 0; ti < NUT; ++ti)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) yz += R2[ti][r] * S.z[16 * ti + L.row(r)];
+            y.psi = gx - q_sum(yz);
+            if ((KEEP == KEEP_ALL || out.Psi) && L.q == 0 && (EX || 16 * j + L.c < n))
+                sv::gs(out.Psi + (uint32_t)(16 * j + L.c), y.psi);
+        }
+        if (KEEP == KEEP_ALL || out.K) {
+            if (VEC && j == 0)
+                store_feedback<EX, RU, NUT, VEC>(L, S.G, R2, out.K, j, n, m, S.z, out.k);
+            else
+                store_feedback<EX, RU, NUT>(L, S.G, R2, out.K, j, n, m);
+        }
+        if (KEEP == KEEP_GIVEN && RED && out.L) copy_L(S, out.L, out.LT, m, 0, 64 * NXT);
         lds_sync();
         if (SM::OVER) lds_sync();
     }
@@ -407,14 +601,15 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT> &S, int n, int m, Get g
 // Stage loop of the waves NXT + j: A and B of the next stage are loaded into
 // their registers, the last of them factors G, and for Alg. 4 they own the
 // column blocks of V and Q_w_hat.
-template <bool RED, bool EX, class T, int NXT, int NUT, class Get, class Pre, class RecOf>
+template <bool RED, bool EX, bool VEC, int KEEP, class T, int NXT, int NUT, class Get, class Pre, class RecOf>
 __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, int n, int m, Get get, int count, Pre pre,
-                                       RecOf rec) {
+                                       RecOf rec, Vec &y) {
     using SM = Smem<T, NXT, NUT>;
     constexpr int RX = SM::RX, RU = SM::RU, NTV = 64 * NXT;
-    constexpr int NA = (RX * RX + NTV - 1) / NTV, NB = (RX * RU + NTV - 1) / NTV;
+    constexpr int NA = RX * RX / NTV, NB = RX * RU / NTV;
+    static_assert(RX * RX % NTV == 0 && RX * RU % NTV == 0, "whole rounds");
     const int j = wave() - NXT;
-    double pa[NA], pb[NB];
+    double pa[NA], pb[NB], pv = 0.0;
     auto fetch = [&](const StageSrc &src) {
         int tv = (int)threadIdx.x - NTV;
         asm volatile("" : "+v"(tv));
@@ -428,8 +623,8 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, in
             const int e = tv + q * NTV, i = e / RU, k = e % RU;
             pb[q] = (EX || (i < n && k < m)) ? gload(src.B + (uint32_t)(i * m + k)) : 0.0;
         }
+        if constexpr (VEC) pv = (src.a && tv < n) ? gload(src.a + (uint32_t)tv) : 0.0;
     };
-    static_assert(RX * RX % NTV == 0 && RX * RU % NTV == 0, "whole rounds");
     auto commit = [&]() {
         int tv = (int)threadIdx.x - NTV;
         asm volatile("" : "+v"(tv));
@@ -443,6 +638,7 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, in
             const int e = tv + q * NTV;
             S.B[at<RU>(e / RU, e % RU)] = (T)pb[q];
         }
+        if (VEC && tv < RX) S.av[tv] = pv;
     };
     if (RED) {
         const Ln<T> L;
@@ -459,6 +655,14 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, in
         if (s > 0) fetch(get(s - 1));
         v4_t<T> R1[NXT], R2[NUT];
         if (RED) {
+            if constexpr (VEC) {
+                double va = 0.0;
+#pragma unroll
+                for (int ti = 0; ti < NXT; ++ti)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) va += C.V[ti][r] * S.av[16 * ti + L.row(r)];
+                y.v += q_sum(va);
+            }
 #pragma unroll
             for (int ti = 0; ti < NUT; ++ti) R2[ti] = mulN<RU, NXT>(L, zero4<T>(), S.B, ti, C.V);
 #pragma unroll
@@ -466,16 +670,14 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, in
         }
         lds_sync();
         if (j == NXT - 1) {
-            const int f = chol_inv<T, NUT>(L, S.G);
+            const int f = chol_inv<T, NUT>(L, S.G, m);
             if (f && lane() == 0) S.bad = 1;
-        }
-        if (NXT == 1 || j < NXT - 1) {
+        } else {
             // the record of P_{s+1}, still in LDS
-            constexpr int t1 = NXT == 1 ? 2 * NTV : 2 * NTV - 64;
-            pre(s, NTV, t1);
+            pre(s, NTV, 2 * NTV - 64);
             if (s + 1 < count) {
                 T *p = rec(s + 1).P;
-                if (p) copy_P(S, p, n, NTV, t1);
+                if (KEEP == KEEP_ALL || p) copy_P(S, p, n, NTV, 2 * NTV - 64);
             }
         }
         lds_sync();
@@ -484,19 +686,27 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, in
         if (!SM::OVER && s > 0) commit();        // A and B are dead
         lds_sync();
         if (RED) {
-            // ---- V = A'V - Y'X, Q_w_hat += X'X, L_t = -L^{-T} X
+            // ---- V = A'V - Y'X, Q_w_hat += X'X, L_t = -L^{-T} X, v += X'z
 #pragma unroll
             for (int ti = 0; ti < NXT; ++ti) {
                 const v4_t<T> acc = mulN<RX, NUT>(L, zero4<T>(), S.Y(), ti, R2);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) C.V[ti][r] = R1[ti][r] - acc[r];
-                if (out.V) store_tile<EX>(L, out.V, n, ti, j, n, n, C.V[ti]);
+                if (KEEP == KEEP_ALL || out.V) store_tile<EX>(L, out.V, n, ti, j, n, n, C.V[ti]);
             }
 #pragma unroll
             for (int ti = 0; ti < NXT; ++ti)
                 if (ti >= j) C.Q[ti] = mulN<RX, NUT>(L, C.Q[ti], S.X(), ti, R2);
-            if (out.Lt) store_feedback<EX, RU, NUT>(L, S.G, R2, out.Lt, j, n, m);
-        } else if (out.L) {
+            if constexpr (VEC) {
+                double xz = 0.0;
+#pragma unroll
+                for (int ti = 0; ti < NUT; ++ti)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) xz += R2[ti][r] * S.z[16 * ti + L.row(r)];
+                y.v += q_sum(xz);
+            }
+            if (KEEP == KEEP_ALL || out.Lt) store_feedback<EX, RU, NUT>(L, S.G, R2, out.Lt, j, n, m);
+        } else if (KEEP == KEEP_GIVEN && out.L) {
             copy_L(S, out.L, out.LT, m, NTV, 2 * NTV);
         }
         lds_sync();
@@ -507,47 +717,63 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, in
     }
 }
 
-// Backward pass over `count` stages (local s = count-1 .. 0).  P_{count} in
-// S.P (written by the caller; the pass starts with a barrier); RED: Alg. 4
+// Backward pass over `count` >= 1 stages (local s = count-1 .. 0).  P_{count}
+// in S.P (written by the caller; the pass starts with a barrier); RED: Alg. 4
 // from V = I, Q_w_hat = 0, result in C.  get(s): stage data; pre(s, t0, t1)
 // is called by the threads [t0, t1) before stage s and may read P_{s+1} from
 // S.P; rec(s): where its factors go.  EX: n = 16 NXT and m = 16 NUT exactly.
+// VEC: with the right-hand side, y holding Psi_{count} on entry.
 // The two kinds of waves run loops of their own (with the same barriers), so
 // that neither carries the other's registers.
-template <bool RED, bool EX, class T, int NXT, int NUT, class Get, class Pre, class RecOf>
+template <bool RED, bool EX, bool VEC, int KEEP, class T, int NXT, int NUT, class Get, class Pre, class RecOf>
 __device__ __forceinline__ void pass(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, int n_, int m_, Get get, int count,
-                                     int32_t *info, int inst, int stage_base, int fail_code, Pre pre, RecOf rec) {
+                                     int32_t *info, int inst, int stage_base, int fail_code, Pre pre, RecOf rec, Vec &y) {
     using SM = Smem<T, NXT, NUT>;
     constexpr int RX = SM::RX, RU = SM::RU, NTH = SM::NTH;
     static_assert(NUT <= NXT, "one column block of B per owner of A");
+    static_assert(!VEC || !SM::OVER, "the vector lines read Y's place in LDS");
     const int n = EX ? RX : n_, m = EX ? RU : m_;
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     count = uni(count);
     if (tid == 0) S.bad = 0;
-    if (count > 0) {
+    {
         const StageSrc src = get(count - 1);
 #pragma unroll 4
         for (int e = tid; e < RX * RX; e += NTH) {
             const int i = e / RX, k = e % RX;
-            S.A[at<RX>(i, k)] = (EX || (i < n && k < n)) ? (T)gload(src.A + i * n + k) : T(0);
+            S.A[at<RX>(i, k)] = (EX || (i < n && k < n)) ? (T)gload(src.A + (uint32_t)(i * n + k)) : T(0);
         }
 #pragma unroll 4
         for (int e = tid; e < RX * RU; e += NTH) {
             const int i = e / RU, k = e % RU;
-            S.B[at<RU>(i, k)] = (EX || (i < n && k < m)) ? (T)gload(src.B + i * m + k) : T(0);
+            S.B[at<RU>(i, k)] = (EX || (i < n && k < m)) ? (T)gload(src.B + (uint32_t)(i * m + k)) : T(0);
         }
+        if (VEC && tid < RX) S.av[tid] = (src.a && tid < n) ? gload(src.a + (uint32_t)tid) : 0.0;
     }
     lds_sync();
     if (wave() < NXT)
-        loop_P<RED, EX>(S, n, m, get, count, info, inst, stage_base, fail_code, rec);
+        loop_P<RED, EX, VEC, KEEP>(S, n, m, get, count, info, inst, stage_base, fail_code, pre, rec, y);
     else
-        loop_V<RED, EX>(S, C, n, m, get, count, pre, rec);
+        loop_V<RED, EX, VEC, KEEP>(S, C, n, m, get, count, pre, rec, y);
     lds_sync();
-    if (count > 0) {
+    {
         T *p = rec(0).P;
-        if (p) copy_P(S, p, n);
+        if (KEEP == KEEP_ALL || p) copy_P(S, p, n);
     }
+}
+
+// Sum of v over the workgroup, in thread 0's wave (every thread calls).
+template <class T, int NXT, int NUT>
+__device__ __forceinline__ double total(Smem<T, NXT, NUT> &S, double v) {
+    v = sv::wave_sum(v);
+    if (lane() == 0) S.red[wave()] = v;
+    lds_sync();
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < 2 * NXT; ++w) s += S.red[w];
+    lds_sync();
+    return s;
 }
 
 // V_0' and Q_w_hat (symmetric) from their owners' registers to row-major

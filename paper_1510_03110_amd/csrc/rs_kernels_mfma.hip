@@ -888,35 +888,16 @@ hipError_t launch_factor_leaf_down(const GroupArgs &g, int, hipStream_t st) {
 
 }  // namespace mf
 
-// which: 0 leaf up, 1 tree, 2 leaf down; fp32: leaf passes in FP32 (the tree
-// is FP64 in both).
+// Stored factorization on the column-owner engine; which: 0 leaf up, 1 tree,
+// 2 leaf down; fp32: leaf passes in FP32 (the tree is FP64 in both).
 Launcher mfma_factor(int nx, int nu, int which, bool fp32) {
-#define RS_FAC(a, b)                                                                   \
-    if (nx == a && nu == b) {                                                          \
-        if (which == 1) return &mf::launch_factor_tree<a>;                             \
-        if (which == 0)                                                                \
-            return fp32 ? &mf::launch_factor_leaf_up<float, a, b>                     \
-                        : &mf::launch_factor_leaf_up<double, a, b>;                   \
-        return fp32 ? &mf::launch_factor_leaf_down<float, a, b>                       \
-                    : &mf::launch_factor_leaf_down<double, a, b>;                     \
-    }
-    RS_FAC(16, 16)
-    RS_FAC(32, 16)
-    RS_FAC(32, 32)
-#undef RS_FAC
-    return nullptr;
-}
-
-// FP32 leaf factorization of the state dimension 64 (mixed precision): the
-// FP32 working set of a stage fits in LDS while the FP64 one does not, so
-// the leaves run on the matrix-core engine and the master levels and vector
-// passes of these shapes on the large-block kernels (same record layouts).
-Launcher mfma_factor_leaf32(int nx, int nu, int which) {
-    if (nx == 64 && nu == 32)
-        return which == 0 ? &mf::launch_factor_leaf_up<float, 64, 32> : &mf::launch_factor_leaf_down<float, 64, 32>;
-    if (nx == 64 && nu == 16)
-        return which == 0 ? &mf::launch_factor_leaf_up<float, 64, 16> : &mf::launch_factor_leaf_down<float, 64, 16>;
-    return nullptr;
+    if (!((nx == 16 && nu == 16) || (nx == 32 && nu == 16) || (nx == 32 && nu == 32))) return nullptr;
+    if (which == 1) return [](const GroupArgs &g, int grid, hipStream_t st) { return mid_tree(g, grid, st); };
+    if (which == 0)
+        return fp32 ? [](const GroupArgs &g, int, hipStream_t st) { return mid_leaf_f32(g, false, st); }
+                    : [](const GroupArgs &g, int, hipStream_t st) { return mid_leaf_f64(g, false, st); };
+    return fp32 ? [](const GroupArgs &g, int, hipStream_t st) { return g.ntop ? mid_leaf_f32(g, true, st) : hipSuccess; }
+                : [](const GroupArgs &g, int, hipStream_t st) { return g.ntop ? mid_leaf_f64(g, true, st) : hipSuccess; };
 }
 
 // MFMA launchers for the shapes that have them (nullptr: use the generic kernel).

@@ -78,7 +78,6 @@ hipError_t mid_tree(const GroupArgs &g, int grid, hipStream_t st);      // n_x <
 inline bool sweep_shape(int nx, int nu) { return nx <= 64 && nu <= 64; }
 hipError_t sweep_leaf(const GroupArgs &g, bool fp32, bool down, hipStream_t st);
 hipError_t sweep_tree(const GroupArgs &g, int grid, hipStream_t st);
-Launcher mfma_factor_leaf32(int nx, int nu, int which);   // FP32 leaves of n_x = 64 (which 0 up, 2 down)
 
 const ShapeEntry *find_shape(int nx, int nu);
 

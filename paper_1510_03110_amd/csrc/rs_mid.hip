@@ -77,12 +77,13 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_leaf(GroupArgs g, int down) {
     auto get = [&](int s) { return prob_stage(p, it.t0 + s); };
     auto no_pre = [](int, int, int) {};
     Cols<T, NXT> C;
+    Vec y{};
     if (!(it.flags & LEAF_LAST)) {
         set_P(S, n, [](int) { return 0.0; });
-        pass<true, EX>(S, C, n, m, get, it.len, g.info, it.inst, it.t0, 2, no_pre, [&](int s) {
+        pass<true, EX, false, KEEP_GIVEN>(S, C, n, m, get, it.len, g.info, it.inst, it.t0, 2, no_pre, [&](int s) {
             T *d = base + (int64_t)s * R.per_stage();
-            return Rec<T>{d + R.P(), d + R.K(), d + R.V(), d + R.Lt(), d + R.L(), d + R.LT()};
-        });
+            return Rec<T>{d + R.P(), d + R.K(), d + R.V(), d + R.Lt(), d + R.L(), d + R.LT(), nullptr, nullptr};
+        }, y);
         store_V_transposed(C, out + SL.A(), n);
         copy_P(S, out + SL.Qx(), n);
         if (!g.ident) store_Q(C, out + SL.Qw(), n);
@@ -98,10 +99,10 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_leaf(GroupArgs g, int down) {
     } else {
         if (down) base += R.up();
         set_P(S, n, [&](int e) { return p.QxN[e]; });
-        pass<false, EX>(S, C, n, m, get, it.len, g.info, it.inst, it.t0, 2, no_pre, [&](int s) {
+        pass<false, EX, false, KEEP_GIVEN>(S, C, n, m, get, it.len, g.info, it.inst, it.t0, 2, no_pre, [&](int s) {
             T *d = base + (int64_t)s * R.per_stage();
-            return Rec<T>{d + R.P(), d + R.K(), nullptr, nullptr, d + R.L(), d + R.LT()};
-        });
+            return Rec<T>{d + R.P(), d + R.K(), nullptr, nullptr, d + R.L(), d + R.LT(), nullptr, nullptr};
+        }, y);
         if (!down) copy_P(S, out + SL.Qx(), n);
     }
 }
@@ -140,15 +141,16 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_tree(GroupArgs g) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         auto get = [&](int s) { return slot_stage(slot(it.first + s), n, g.ident); };
         Cols<double, NXT> C;
+        Vec y{};
         if (inst_skipped(g.probs, it.inst)) {
             // excluded instance: only its completion flag is published
         } else if (it.kind == ITEM_UP) {
             set_P(S, n, [](int) { return 0.0; });
-            pass<true, EX>(S, C, n, n, get, it.count, g.info, it.inst, -1, 3, [](int, int, int) {}, [&](int s) {
+            pass<true, EX, false, KEEP_GIVEN>(S, C, n, n, get, it.count, g.info, it.inst, -1, 3, [](int, int, int) {}, [&](int s) {
                 double *d = slot(it.first + s);
                 return Rec<double>{d + SL.uP(), d + SL.uK(), d + SL.uV(), g.superpose ? d + SL.dL() : nullptr,
-                                   d + SL.uL(), d + SL.uLT()};
-            });
+                                   d + SL.uL(), d + SL.uLT(), nullptr, nullptr};
+            }, y);
             double *out = slot(it.out_slot);
             store_V_transposed(C, out + SL.A(), n);
             copy_P(S, out + SL.Qx(), n);
@@ -169,17 +171,17 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_tree(GroupArgs g) {
             double *term = it.last ? slot(it.term_slot) : nullptr;
             const double *P0 = term ? term + SL.Qx() : msg + SL.P();
             set_P(S, n, [&](int e) { return P0[e]; });
-            pass<false, EX>(S, C, n, n, get, it.count, g.info, it.inst, -1, 3,
+            pass<false, EX, false, KEEP_GIVEN>(S, C, n, n, get, it.count, g.info, it.inst, -1, 3,
                             [&](int s, int t0, int t1) {      // M2 for child s: P at the end of master stage s
                                 if (!upl) copy_P(S, slot(it.first + s) + SL.P(), n, t0, t1);
                             },
                             [&](int s) {
                                 double *d = slot(it.first + s);
                                 return upl ? Rec<double>{d + SL.uP(), d + SL.uK(), nullptr, nullptr, d + SL.uL(),
-                                                         d + SL.uLT()}
+                                                         d + SL.uLT(), nullptr, nullptr}
                                            : Rec<double>{nullptr, d + SL.K(), nullptr, nullptr, d + SL.dL(),
-                                                         d + SL.dLT()};
-                            });
+                                                         d + SL.dLT(), nullptr, nullptr};
+                            }, y);
             // a level's last item: its reduced terminal; the top: P_0, for the optimal value
             double *d = upl ? slot(it.out_slot) + SL.Qx() : it.kind == ITEM_TOP ? term + SL.P() : nullptr;
             if (d) copy_P(S, d, n);
@@ -194,12 +196,12 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_tree(GroupArgs g) {
 
 inline int tiles(int d) { return (d + 15) / 16; }
 
-// EX: the shapes whose sizes fill the tiles have an instance without bounds
-// checks where that matters (n_x = 64).
+// Sizes that fill the tiles have an instance without bounds checks (the
+// shapes in use: n_x of 16, 32 and 64).
 template <class T, int A, int B>
 hipError_t leaf(const GroupArgs &g, hipStream_t st, int down) {
     const dim3 grid(g.nleaves), block(128 * A);
-    if constexpr (A == 4 && sizeof(T) == 8) {
+    if constexpr (A != 3 && (sizeof(T) == 8 || A < 4 || B < 3)) {
         if (g.nx == 16 * A && g.nu == 16 * B) {
             hipLaunchKernelGGL((kc_leaf<T, A, B, true>), grid, block, 0, st, g, down);
             return hipGetLastError();
