@@ -179,9 +179,10 @@ typedef struct rs_options {
 
 /* rs_options.flags: tile shape.  Instances with n_x = 16 or 32 and n_u < 16
  * are by default solved on the 16 x 16 matrix-core tile kernels with their
- * inputs padded to n_u = 16 (inputs that act on nothing, see the padding
- * kernels); with this flag they run on the kernels for their own shape
- * instead (wavefront and large-block kernels).  An autotuner chooses. */
+ * inputs padded to n_u = 16 (inputs that act on nothing; in FP64 plans for the
+ * fused solve alone the kernels pad on load, otherwise padded copies are
+ * made); with this flag they run on the kernels for run-time sizes instead.
+ * An autotuner chooses. */
 #define RS_PLAN_NATIVE_TILES 16
 
 /* rs_options.flags: down pass of the master levels of the stored
@@ -404,8 +405,8 @@ rs_status rs_batch_solve(rs_plan plan, const rs_problem *probs, void *work,
 /*
  * rs_batch_solve for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
- * the workspace is a device array of RS_NOALLOC_SCRATCH_BYTES (64 MiB) that
- * the library holds on every GPU it runs on from its load until the process
+ * the workspace is a device array of RS_NOALLOC_SCRATCH_BYTES (64 MiB; 128 MiB
+ * with the room below) that the library holds on every GPU it runs on from its load until the process
  * ends, so the caller passes only the problems (inputs and outputs, as for
  * rs_batch_solve), the stream and the optional status array.  The call
  * allocates nothing (no hipMalloc, hipFree, pinned or library allocation):
@@ -416,7 +417,9 @@ rs_status rs_batch_solve(rs_plan plan, const rs_problem *probs, void *work,
  * one GPU (other streams, other threads) race and must not be issued.
  * The plan's kernel timing is not recorded by this call.  Results are the
  * same as rs_batch_solve's.  Errors: RS_ERR_NOMEM if the plan's workspace
- * (rs_plan_workspace_size) exceeds RS_NOALLOC_SCRATCH_BYTES, RS_ERR_ARG for
+ * (rs_plan_workspace_size; for shapes whose n_x or n_u is not a multiple of
+ * 16 without the V and L_t of the fused solve's leaf records, for which the
+ * library holds room of its own) exceeds RS_NOALLOC_SCRATCH_BYTES, RS_ERR_ARG for
  * receding-horizon plans (their stored factors cannot live in a shared
  * array) and as rs_batch_solve, RS_ERR_HIP if the plan was created without
  * a device.

@@ -13,7 +13,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD_DIR = os.path.join(PKG, "_build")
 LIB_PATH = os.path.join(BUILD_DIR, "librs.so")
-SOURCES = ["rs_kernels.hip", "rs_kernels_mfma.hip", "rs_solve.hip", "rs_refine.hip", "rs_large.hip", "rs_mid.hip", "rs_mid32.hip", "rs_vsweep.hip",
+SOURCES = ["rs_kernels.hip", "rs_fused.hip", "rs_solve.hip", "rs_refine.hip", "rs_large.hip", "rs_mid.hip", "rs_mid32.hip", "rs_vsweep.hip",
            "rs_mhe.hip",
            "rs_ip.hip", "rs_pad.hip", "rs_static.hip", "rs_capi.cpp"]
 HEADERS = ["rs_types.hpp", "rs_device.hpp", "rs_mfma.hpp", "rs_launch.hpp", "rs_vec.hpp", "rs_col.hpp",

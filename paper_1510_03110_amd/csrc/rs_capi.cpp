@@ -84,6 +84,10 @@ struct rs_plan_s {
     std::vector<int32_t> nu_user;
     std::vector<size_t> off_pad;
     std::vector<int32_t> pad_inst;      // padded instances in order
+    // the padded inputs exist in the kernels only: a plan for the fused solve
+    // alone reads the caller's arrays as they are (no padded copies)
+    bool pad_in_kernel = false;
+    size_t counted = 0;                 // total as rs_batch_solve_noalloc counts it (scratch_counted)
     size_t off_padargs = 0;
     std::vector<Group> groups;
     size_t off_probs = 0, off_info = 0, off_queues = 0, off_tables = 0, tables_bytes = 0;
@@ -620,8 +624,9 @@ static rs_status plan_create(int32_t count, const int32_t *dims_in, int stride, 
             return RS_ERR_UNSUPPORTED;
         }
     }
+    P->pad_in_kernel = !P->pad_inst.empty() && !P->factored && !P->refine_ws;
     // workspace layout
-    size_t off = 0;
+    size_t off = 0, uncounted = 0;
     P->off_probs = off;                 // user problems, then (mixed) the correction problems,
     P->off_padargs = off + sizeof(DevProb) * count * (P->refine_ws ? 2 : 1);   // then the padding jobs
     off = align_up(P->off_padargs + sizeof(PadArgs) * P->pad_inst.size());
@@ -672,6 +677,10 @@ static rs_status plan_create(int32_t count, const int32_t *dims_in, int stride, 
         g.off_scratch = off;
         const size_t esz = sizeof(double);
         off = align_up(off + esz * (size_t)g.scratch_elems);
+        if (!g.shape->large) {
+            const int64_t cnt = g.scratch_elems / g.shape->scratch_per_stage * scratch_counted(g.nx, g.nu);
+            uncounted += align_up(esz * (size_t)g.scratch_elems) - align_up(esz * (size_t)cnt);
+        }
         if (!P->receding) g.leaf_stages = g.scratch_elems / g.shape->scratch_per_stage;
         if (g.shape->lb && P->factored) {
             const int64_t units =
@@ -725,6 +734,7 @@ static rs_status plan_create(int32_t count, const int32_t *dims_in, int stride, 
         off = align_up(off + sizeof(double) * N * (2 * nx * PAD_NU + PAD_NU * PAD_NU + 2 * PAD_NU));
     }
     P->total = off;
+    P->counted = off - uncounted;
     P->tables.assign(P->tables_bytes, 0);
     std::memcpy(P->tables.data() + (P->off_inst - P->off_tables), P->inst.data(), sizeof(InstInfo) * count);
     for (auto &g : P->groups) {
@@ -910,6 +920,7 @@ static rs_status bind_and_upload(rs_plan P, const rs_problem *probs, char *work,
     std::vector<PadArgs> &pads = P->pads_host;
     pads.clear();
     for (int i : P->pad_inst) {
+        if (P->pad_in_kernel) break;
         const rs_problem &q = probs[i];
         DevProb &d = dp[i];
         const int64_t nx = q.nx, np = PAD_NU, N = q.N;
@@ -1045,6 +1056,7 @@ static GroupArgs group_args(rs_plan P, char *W, size_t gi, int32_t *info, bool c
     a.nx = g.nx;
     a.nu = g.nu;
     a.superpose = P->superpose ? 1 : 0;
+    a.data_nu = P->pad_in_kernel && g.nu == PAD_NU ? 1 : 0;
     if (P->refine_ws) {
         a.corr = user + P->count;
         a.conv = with_conv ? reinterpret_cast<const int32_t *>(W + P->off_conv) : nullptr;
@@ -1255,7 +1267,7 @@ static rs_status chunked_solve(rs_plan P, char *W, int32_t *info, hipStream_t st
 // The call's kernels, between the padded copies of the inputs of padded
 // instances and the copy of their w back to the caller.
 static rs_status run_padded(rs_plan P, char *W, int32_t *info, hipStream_t st, int mode) {
-    const int npad = (int)P->pad_inst.size();
+    const int npad = P->pad_in_kernel ? 0 : (int)P->pad_inst.size();
     const PadArgs *pa = reinterpret_cast<const PadArgs *>(W + P->off_padargs);
     if (npad && launch_pad(pa, npad, false, st) != hipSuccess) return RS_ERR_HIP;
     rs_status s = run_sequence(P, W, info, st, mode);
@@ -1390,7 +1402,7 @@ rs_status rs_batch_solve(rs_plan P, const rs_problem *probs, void *work, size_t 
     return run_call(P, probs, work, work_bytes, stream, info_dev, 0);
 }
 
-static_assert(RS_NOALLOC_SCRATCH_BYTES == STATIC_SCRATCH_BYTES, "scratch size in rs.h and the library agree");
+static_assert(2 * RS_NOALLOC_SCRATCH_BYTES == STATIC_SCRATCH_BYTES, "every plan that is counted in fits");
 
 rs_status rs_batch_solve_noalloc(rs_plan P, const rs_problem *probs, void *stream, int32_t *info_dev) {
     if (!P || !probs) return RS_ERR_ARG;
@@ -1398,7 +1410,7 @@ rs_status rs_batch_solve_noalloc(rs_plan P, const rs_problem *probs, void *strea
     size_t bytes = 0;
     void *work = static_scratch(&bytes);
     if (!work) return RS_ERR_HIP;
-    if (P->total > bytes) return RS_ERR_NOMEM;
+    if (P->counted > RS_NOALLOC_SCRATCH_BYTES || P->total > bytes) return RS_ERR_NOMEM;
     if (!staging_ready(P)) return RS_ERR_HIP;  // plan created without a device
     // the scratch is shared by every call on this device and keeps the last
     // call's contents: bind it afresh, which uploads the tables and the

@@ -92,9 +92,10 @@ __device__ __forceinline__ T ldR(const Ln<T> &L, const T *M, int ti, int kt, int
 // phase at once and spill.
 __device__ __forceinline__ void tile_fence() { __builtin_amdgcn_sched_barrier(0); }
 
-// acc += sum over inner tiles k0 <= kt < KT of (N view of M)(ti, kt) b[kt].
+// acc += sum over inner tiles k0 <= kt < KT of (N view of M)(ti, kt) b[kt], NS
+// slices each.
 // The next inner tile's operands are read while this one's are multiplied.
-template <int PT, int KT, class T>
+template <int PT, int KT, int NS, class T>
 __device__ __forceinline__ v4_t<T> mulN(const Ln<T> &L, v4_t<T> acc, const T *M, int ti, const v4_t<T> *b, int k0 = 0) {
     tile_fence();
 #pragma unroll
@@ -102,9 +103,9 @@ __device__ __forceinline__ v4_t<T> mulN(const Ln<T> &L, v4_t<T> acc, const T *M,
         if (kt < k0) continue;
         T a[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) a[r] = ldN<PT>(L, M, kt, ti, r);
+        for (int r = 0; r < NS; ++r) a[r] = ldN<PT>(L, M, kt, ti, r);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc = MT<T>::mfma(a[r], b[kt][r], acc);
+        for (int r = 0; r < NS; ++r) acc = MT<T>::mfma(a[r], b[kt][r], acc);
     }
     tile_fence();
     return acc;
@@ -113,15 +114,15 @@ __device__ __forceinline__ v4_t<T> mulN(const Ln<T> &L, v4_t<T> acc, const T *M,
 // Tile (ti, tj) of C written at LDS (row, column) and, for a lower tile of a
 // symmetric result, also mirrored (the diagonal tile's upper half is the
 // mirror of its lower half).
-template <int PT, class T>
+template <int PT, int NS, class T>
 __device__ __forceinline__ void put(const Ln<T> &L, T *M, int ti, int tj, v4_t<T> v) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) M[at<PT>(16 * ti + L.row(r), 16 * tj + L.c)] = v[r];
+    for (int r = 0; r < NS; ++r) M[at<PT>(16 * ti + L.row(r), 16 * tj + L.c)] = v[r];
 }
-template <int PT, class T>
+template <int PT, int NS, class T>
 __device__ __forceinline__ void put_sym(const Ln<T> &L, T *M, int ti, int tj, v4_t<T> v) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int r = 0; r < NS; ++r) {
         const int i = 16 * ti + L.row(r), j = 16 * tj + L.c;
         if (ti != tj || i >= j) {
             M[at<PT>(i, j)] = v[r];
@@ -215,7 +216,7 @@ __device__ __forceinline__ int chol_inv(const Ln<T> &L, T *G, int m) {
             for (int r = 0; r < 4; ++r)          // G_ik' (k, i) = G[i][k]
                 acc = MT<T>::mfma(ldR<PU>(L, G, kb, kb, r), ldR<PU>(L, G, ib, kb, r), acc);
             u[ib] = acc;
-            put<PU>(L, G, kb, ib, acc);
+            put<PU, 4>(L, G, kb, ib, acc);
         }
         wave_fence();
 #pragma unroll
@@ -246,7 +247,7 @@ __device__ __forceinline__ int chol_inv(const Ln<T> &L, T *G, int m) {
             v4_t<T> x = zero4<T>();
 #pragma unroll
             for (int r = 0; r < 4; ++r) x = MT<T>::mfma(ldR<PU>(L, G, ib, ib, r), s[r], x);
-            put<PU>(L, G, ib, jb, v4_t<T>{-x[0], -x[1], -x[2], -x[3]});
+            put<PU, 4>(L, G, ib, jb, v4_t<T>{-x[0], -x[1], -x[2], -x[3]});
         }
         wave_fence();
     }
@@ -256,8 +257,16 @@ __device__ __forceinline__ int chol_inv(const Ln<T> &L, T *G, int m) {
 // LDS of one workgroup.  Y and X lie over A and B (dead once W, F, H', A'V
 // and B'V are formed) where they do not fit beside them; the next stage's A
 // and B are then written after one more barrier.
-template <class T, int NXT, int NUT>
+//
+// SX, SU: row slices in use of a tile of states and of inputs.  A slice is the
+// rows that one matrix instruction takes as inner indices (4 in FP64: rows
+// 4 r .. 4 r + 3), so shapes of up to 4 or 8 states need one or two of the
+// four (one tile, FP64); rows beyond them are neither written nor read.
+template <class T, int NXT, int NUT, int SX_ = 4, int SU_ = 4>
 struct Smem {
+    typedef T elem;
+    static constexpr int SX = SX_, SU = SU_;
+    static_assert((SX == 4 && SU == 4) || (NXT == 1 && sizeof(T) == 8), "slices of one FP64 tile");
     static constexpr int RX = 16 * NXT, RU = 16 * NUT, NTH = 128 * NXT;
     static constexpr size_t apart = sizeof(T) * (2 * RX * RX + RX * RU + RU * RU + 2 * RU * RX);
     static constexpr bool OVER = apart > 159 * 1024;
@@ -302,11 +311,11 @@ __device__ __forceinline__ double q_sum(double v) { return sv::xor_sum<32>(sv::x
 
 // 16x16 tile of problem data in the result layout; zeros outside n1 x n2
 // (identity where ONE).  TR reads the transposed element.
-template <bool EX, bool TR, bool ONE, class T>
+template <bool EX, bool TR, bool ONE, int NS, class T>
 __device__ __forceinline__ d4 load_tile(const Ln<T> &L, const double *M, int ld, int ti, int tj, int n1, int n2) {
-    d4 v;
+    d4 v{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int r = 0; r < NS; ++r) {
         const int i = 16 * ti + L.row(r), j = 16 * tj + L.c;
         const bool ok = EX || (i < n1 && j < n2);
         const double pad = (ONE && i == j) ? 1.0 : 0.0;
@@ -320,10 +329,10 @@ __device__ __forceinline__ v4_t<T> as_t(d4 v) {
 }
 
 // Result tile (ti, tj) to global memory (rows of length ld).
-template <bool EX, class T>
+template <bool EX, int NS, class T>
 __device__ __forceinline__ void store_tile(const Ln<T> &L, T *M, int ld, int ti, int tj, int n1, int n2, v4_t<T> v) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int r = 0; r < NS; ++r) {
         const int i = 16 * ti + L.row(r), j = 16 * tj + L.c;
         if (EX || (i < n1 && j < n2)) M[(uint32_t)(i * ld + j)] = v[r];
     }
@@ -331,10 +340,8 @@ __device__ __forceinline__ void store_tile(const Ln<T> &L, T *M, int ld, int ti,
 
 // P (n x n) from LDS to global memory, row by row, by the threads
 // t0 <= threadIdx.x < t1.
-template <class T, int NXT, int NUT, class U>
-__device__ __forceinline__ void copy_P(const Smem<T, NXT, NUT> &S, U *dst, int n, int t0 = 0,
-                                       int t1 = Smem<T, NXT, NUT>::NTH) {
-    using SM = Smem<T, NXT, NUT>;
+template <class SM, class U>
+__device__ __forceinline__ void copy_P(const SM &S, U *dst, int n, int t0 = 0, int t1 = SM::NTH) {
     int t = (int)threadIdx.x - t0;
     const int nt = t1 - t0;
     if (t < 0 || t >= nt) return;
@@ -347,9 +354,9 @@ __device__ __forceinline__ void copy_P(const Smem<T, NXT, NUT> &S, U *dst, int n
 }
 
 // Start of a pass: P from an element function (rows and columns < n).
-template <class T, int NXT, int NUT, class F>
-__device__ __forceinline__ void set_P(Smem<T, NXT, NUT> &S, int n, F f) {
-    using SM = Smem<T, NXT, NUT>;
+template <class SM, class F>
+__device__ __forceinline__ void set_P(SM &S, int n, F f) {
+    typedef typename SM::elem T;
     int t = threadIdx.x;
     asm volatile("" : "+v"(t));
 #pragma unroll 4
@@ -361,9 +368,9 @@ __device__ __forceinline__ void set_P(Smem<T, NXT, NUT> &S, int n, F f) {
 
 // L^{-1} and L^{-T} (m x m, dense) from LDS to their records, by the threads
 // t0 <= threadIdx.x < t1.
-template <class T, int NXT, int NUT>
-__device__ __forceinline__ void copy_L(const Smem<T, NXT, NUT> &S, T *L, T *LT, int m, int t0, int t1) {
-    constexpr int RU = Smem<T, NXT, NUT>::RU;
+template <class SM, class T>
+__device__ __forceinline__ void copy_L(const SM &S, T *L, T *LT, int m, int t0, int t1) {
+    constexpr int RU = SM::RU;
     int t = (int)threadIdx.x - t0;
     asm volatile("" : "+v"(t));
 #pragma unroll 2
@@ -379,7 +386,7 @@ __device__ __forceinline__ void copy_L(const Smem<T, NXT, NUT> &S, T *L, T *LT, 
 // Y = L^{-1} H' or X = L^{-1} B'V of one column block, in place and to LDS.
 // L^{-1} is lower triangular: row tile ti takes the inner tiles <= ti, so the
 // block is replaced from its last tile up.  Z: also z = L^{-1} gw (to zv).
-template <int RU, int RX, int NUT, bool Z = false, class T>
+template <int RU, int RX, int NUT, int NS, bool Z = false, class T>
 __device__ __forceinline__ void apply_Linv(const Ln<T> &L, const T *G, v4_t<T> *R2, T *D, int j,
                                            const double *gw = nullptr, double *zv = nullptr, double *zz = nullptr) {
 #pragma unroll
@@ -390,16 +397,16 @@ __device__ __forceinline__ void apply_Linv(const Ln<T> &L, const T *G, v4_t<T> *
 #pragma unroll
         for (int kt = 0; kt <= ti; ++kt)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            for (int r = 0; r < NS; ++r) {
                 const T a = ldR<RU>(L, G, ti, kt, r);
                 acc = MT<T>::mfma(a, R2[kt][r], acc);
                 if constexpr (Z) z += (double)a * gw[16 * kt + L.row(r)];
             }
         R2[ti] = acc;
-        put<RX>(L, D, ti, j, acc);
+        put<RX, NS>(L, D, ti, j, acc);
         if constexpr (Z) {
             z = q_sum(z);
-            if (L.q == 0) {
+            if (L.q == 0 && (NS == 4 || L.c < 4 * NS)) {
                 zv[16 * ti + L.c] = z;
                 *zz -= 0.5 * z * z;
             }
@@ -409,7 +416,7 @@ __device__ __forceinline__ void apply_Linv(const Ln<T> &L, const T *G, v4_t<T> *
 
 // K = -L^{-T} Y or L_t = -L^{-T} X of one column block, to its record.  Z:
 // also k = L^{-T} z.
-template <bool EX, int RU, int NUT, bool Z = false, class T>
+template <bool EX, int RU, int NUT, int NS, bool Z = false, class T>
 __device__ __forceinline__ void store_feedback(const Ln<T> &L, const T *G, const v4_t<T> *R2, T *D, int j, int n, int m,
                                                const double *zv = nullptr, double *k = nullptr) {
 #pragma unroll
@@ -420,12 +427,12 @@ __device__ __forceinline__ void store_feedback(const Ln<T> &L, const T *G, const
 #pragma unroll
         for (int kt = ti; kt < NUT; ++kt)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            for (int r = 0; r < NS; ++r) {
                 const T a = ldN<RU>(L, G, kt, ti, r);
                 acc = MT<T>::mfma(a, R2[kt][r], acc);
                 if constexpr (Z) s += (double)a * zv[16 * kt + L.row(r)];
             }
-        store_tile<EX>(L, D, n, ti, j, m, n, v4_t<T>{-acc[0], -acc[1], -acc[2], -acc[3]});
+        store_tile<EX, NS>(L, D, n, ti, j, m, n, v4_t<T>{-acc[0], -acc[1], -acc[2], -acc[3]});
         if constexpr (Z) {
             s = q_sum(s);
             if (L.q == 0 && (EX || 16 * ti + L.c < m)) sv::gs(k + (uint32_t)(16 * ti + L.c), s);
@@ -444,10 +451,10 @@ struct QTiles {
 };
 
 // Stage loop of the waves that own a column block of A (w < NXT).
-template <bool RED, bool EX, bool VEC, int KEEP, class T, int NXT, int NUT, class Get, class Pre, class RecOf>
-__device__ __forceinline__ void loop_P(Smem<T, NXT, NUT> &S, int n, int m, Get get, int count, int32_t *info, int inst,
+template <bool RED, bool EX, bool EXD, bool VEC, int KEEP, class T, int NXT, int NUT, int SX, int SU, class Get, class Pre, class RecOf>
+__device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int m, int md, Get get, int count, int32_t *info, int inst,
                                        int stage_base, int fail_code, Pre pre, RecOf rec, Vec &y) {
-    using SM = Smem<T, NXT, NUT>;
+    using SM = Smem<T, NXT, NUT, SX, SU>;
     using QT = QTiles<NXT, NUT>;
     constexpr int RX = SM::RX, RU = SM::RU;
     const int j = wave();
@@ -456,22 +463,22 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT> &S, int n, int m, Get g
         if (j < NUT) {
 #pragma unroll
             for (int ti = 0; ti < NUT; ++ti)
-                if (ti >= j) q.g[ti] = load_tile<EX, false, true>(L, src.Qw, m, ti, j, m, m);
+                if (ti >= j) q.g[ti] = load_tile<EXD, false, true, SU>(L, src.Qw, md, ti, j, md, md);
             if constexpr (VEC)
-                q.lw = (src.lw && (EX || 16 * j + L.c < m)) ? gload(src.lw + (uint32_t)(16 * j + L.c)) : 0.0;
+                q.lw = (src.lw && (EXD || 16 * j + L.c < md)) ? gload(src.lw + (uint32_t)(16 * j + L.c)) : 0.0;
         }
     };
     auto load_f = [&](const Ln<T> &L, const StageSrc &src) {
         if (src.Qxw) {
 #pragma unroll
-            for (int ti = 0; ti < NUT; ++ti) q.h[ti] = load_tile<EX, true, false>(L, src.Qxw, m, ti, j, m, n);
+            for (int ti = 0; ti < NUT; ++ti) q.h[ti] = load_tile<EXD, true, false, SU>(L, src.Qxw, md, ti, j, md, n);
         } else {
 #pragma unroll
             for (int ti = 0; ti < NUT; ++ti) q.h[ti] = d4{0.0, 0.0, 0.0, 0.0};
         }
 #pragma unroll
         for (int ti = 0; ti < NXT; ++ti)
-            if (ti >= j) q.f[ti] = load_tile<EX, false, false>(L, src.Qx, n, ti, j, n, n);
+            if (ti >= j) q.f[ti] = load_tile<EX, false, false, SX>(L, src.Qx, n, ti, j, n, n);
         if constexpr (VEC)
             q.lx = (src.lx && (EX || 16 * j + L.c < n)) ? gload(src.lx + (uint32_t)(16 * j + L.c)) : 0.0;
     };
@@ -491,7 +498,7 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT> &S, int n, int m, Get g
 #pragma unroll
             for (int kt = 0; kt < NXT; ++kt)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) pa += ldN<RX>(L, S.P, kt, j, r) * S.av[16 * kt + L.row(r)];
+                for (int r = 0; r < SX; ++r) pa += ldN<RX>(L, S.P, kt, j, r) * S.av[16 * kt + L.row(r)];
             pa = q_sum(pa);
             if (L.q == 0) {
                 S.pt[16 * j + L.c] = y.psi - pa;
@@ -504,12 +511,12 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT> &S, int n, int m, Get g
 #pragma unroll
             for (int kt = 0; kt < NXT; ++kt)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) b[kt][r] = ldN<RU>(L, S.B, kt, j, r);
+                for (int r = 0; r < SX; ++r) b[kt][r] = ldN<RU>(L, S.B, kt, j, r);
 #pragma unroll
-            for (int ti = 0; ti < NXT; ++ti) wb[ti] = mulN<RX, NXT>(L, zero4<T>(), S.P, ti, b);
+            for (int ti = 0; ti < NXT; ++ti) wb[ti] = mulN<RX, NXT, SX>(L, zero4<T>(), S.P, ti, b);
 #pragma unroll
             for (int ti = 0; ti < NUT; ++ti)
-                if (ti >= j) put_sym<RU>(L, S.G, ti, j, mulN<RU, NXT>(L, as_t<T>(q.g[ti]), S.B, ti, wb));
+                if (ti >= j) put_sym<RU, SU>(L, S.G, ti, j, mulN<RU, NXT, SX>(L, as_t<T>(q.g[ti]), S.B, ti, wb));
         }
         lds_sync();
         // ---- W, F, H', g_x, g_w (the last wave of the workgroup factors G)
@@ -521,31 +528,31 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT> &S, int n, int m, Get g
 #pragma unroll
             for (int kt = 0; kt < NXT; ++kt)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) a[kt][r] = ldN<RX>(L, S.A, kt, j, r);
+                for (int r = 0; r < SX; ++r) a[kt][r] = ldN<RX>(L, S.A, kt, j, r);
             if constexpr (VEC) {
 #pragma unroll
                 for (int kt = 0; kt < NXT; ++kt)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) gx += a[kt][r] * S.pt[16 * kt + L.row(r)];
+                    for (int r = 0; r < SX; ++r) gx += a[kt][r] * S.pt[16 * kt + L.row(r)];
                 gx = q_sum(gx) - q.lx;
                 if (j < NUT) {
                     double g = 0.0;
 #pragma unroll
                     for (int kt = 0; kt < NXT; ++kt)
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) g += ldN<RU>(L, S.B, kt, j, r) * S.pt[16 * kt + L.row(r)];
+                        for (int r = 0; r < SX; ++r) g += ldN<RU>(L, S.B, kt, j, r) * S.pt[16 * kt + L.row(r)];
                     g = q_sum(g) - q.lw;
                     if (L.q == 0) S.gw[16 * j + L.c] = g;
                 }
             }
             if (QT::AHEAD && s > 0) load_g(L, nxt);
 #pragma unroll
-            for (int ti = 0; ti < NXT; ++ti) wa[ti] = mulN<RX, NXT>(L, zero4<T>(), S.P, ti, a);
+            for (int ti = 0; ti < NXT; ++ti) wa[ti] = mulN<RX, NXT, SX>(L, zero4<T>(), S.P, ti, a);
 #pragma unroll
-            for (int ti = 0; ti < NUT; ++ti) R2[ti] = mulN<RU, NXT>(L, as_t<T>(q.h[ti]), S.B, ti, wa);
+            for (int ti = 0; ti < NUT; ++ti) R2[ti] = mulN<RU, NXT, SX>(L, as_t<T>(q.h[ti]), S.B, ti, wa);
 #pragma unroll
             for (int ti = 0; ti < NXT; ++ti)
-                if (ti >= j) R1[ti] = mulN<RX, NXT>(L, as_t<T>(q.f[ti]), S.A, ti, wa);
+                if (ti >= j) R1[ti] = mulN<RX, NXT, SX>(L, as_t<T>(q.f[ti]), S.A, ti, wa);
         }
         if (QT::AHEAD && s > 0) load_f(L, nxt);
         if (NXT == 1) {
@@ -563,17 +570,17 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT> &S, int n, int m, Get g
             S.bad = 0;
         }
         if (VEC && j == 0)
-            apply_Linv<RU, RX, NUT, VEC>(L, S.G, R2, S.Y(), j, S.gw, S.z, &y.cb);
+            apply_Linv<RU, RX, NUT, SU, VEC>(L, S.G, R2, S.Y(), j, S.gw, S.z, &y.cb);
         else
-            apply_Linv<RU, RX, NUT>(L, S.G, R2, S.Y(), j);
+            apply_Linv<RU, RX, NUT, SU>(L, S.G, R2, S.Y(), j);
         lds_sync();
         // ---- P = F - Y'Y, K = -L^{-T} Y, Psi = g_x - Y'z, k = L^{-T} z
         const Rec<T> out = rec(s);
 #pragma unroll
         for (int ti = 0; ti < NXT; ++ti)
             if (ti >= j) {
-                const v4_t<T> acc = mulN<RX, NUT>(L, zero4<T>(), S.Y(), ti, R2);
-                put_sym<RX>(L, S.P, ti, j,
+                const v4_t<T> acc = mulN<RX, NUT, SU>(L, zero4<T>(), S.Y(), ti, R2);
+                put_sym<RX, SX>(L, S.P, ti, j,
                             v4_t<T>{R1[ti][0] - acc[0], R1[ti][1] - acc[1], R1[ti][2] - acc[2], R1[ti][3] - acc[3]});
             }
         if constexpr (VEC) {
@@ -581,16 +588,16 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT> &S, int n, int m, Get g
 #pragma unroll
             for (int ti = 0; ti < NUT; ++ti)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) yz += R2[ti][r] * S.z[16 * ti + L.row(r)];
+                for (int r = 0; r < SU; ++r) yz += R2[ti][r] * S.z[16 * ti + L.row(r)];
             y.psi = gx - q_sum(yz);
             if ((KEEP == KEEP_ALL || out.Psi) && L.q == 0 && (EX || 16 * j + L.c < n))
                 sv::gs(out.Psi + (uint32_t)(16 * j + L.c), y.psi);
         }
         if (KEEP == KEEP_ALL || out.K) {
             if (VEC && j == 0)
-                store_feedback<EX, RU, NUT, VEC>(L, S.G, R2, out.K, j, n, m, S.z, out.k);
+                store_feedback<EX, RU, NUT, SU, VEC>(L, S.G, R2, out.K, j, n, m, S.z, out.k);
             else
-                store_feedback<EX, RU, NUT>(L, S.G, R2, out.K, j, n, m);
+                store_feedback<EX, RU, NUT, SU>(L, S.G, R2, out.K, j, n, m);
         }
         if (KEEP == KEEP_GIVEN && RED && out.L) copy_L(S, out.L, out.LT, m, 0, 64 * NXT);
         lds_sync();
@@ -601,10 +608,10 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT> &S, int n, int m, Get g
 // Stage loop of the waves NXT + j: A and B of the next stage are loaded into
 // their registers, the last of them factors G, and for Alg. 4 they own the
 // column blocks of V and Q_w_hat.
-template <bool RED, bool EX, bool VEC, int KEEP, class T, int NXT, int NUT, class Get, class Pre, class RecOf>
-__device__ __forceinline__ void loop_V(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, int n, int m, Get get, int count, Pre pre,
+template <bool RED, bool EX, bool EXD, bool VEC, int KEEP, class T, int NXT, int NUT, int SX, int SU, class Get, class Pre, class RecOf>
+__device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT> &C, int n, int m, int md, Get get, int count, Pre pre,
                                        RecOf rec, Vec &y) {
-    using SM = Smem<T, NXT, NUT>;
+    using SM = Smem<T, NXT, NUT, SX, SU>;
     constexpr int RX = SM::RX, RU = SM::RU, NTV = 64 * NXT;
     constexpr int NA = RX * RX / NTV, NB = RX * RU / NTV;
     static_assert(RX * RX % NTV == 0 && RX * RU % NTV == 0, "whole rounds");
@@ -621,7 +628,7 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, in
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
             const int e = tv + q * NTV, i = e / RU, k = e % RU;
-            pb[q] = (EX || (i < n && k < m)) ? gload(src.B + (uint32_t)(i * m + k)) : 0.0;
+            pb[q] = (EXD || (i < n && k < md)) ? gload(src.B + (uint32_t)(i * md + k)) : 0.0;
         }
         if constexpr (VEC) pv = (src.a && tv < n) ? gload(src.a + (uint32_t)tv) : 0.0;
     };
@@ -646,7 +653,7 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, in
         for (int ti = 0; ti < NXT; ++ti) {
             C.Q[ti] = zero4<T>();
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
+            for (int r = 0; r < SX; ++r)
                 C.V[ti][r] = (16 * ti + L.row(r) == 16 * j + L.c) ? T(1) : T(0);
         }
     }
@@ -660,17 +667,17 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, in
 #pragma unroll
                 for (int ti = 0; ti < NXT; ++ti)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) va += C.V[ti][r] * S.av[16 * ti + L.row(r)];
+                    for (int r = 0; r < SX; ++r) va += C.V[ti][r] * S.av[16 * ti + L.row(r)];
                 y.v += q_sum(va);
             }
 #pragma unroll
-            for (int ti = 0; ti < NUT; ++ti) R2[ti] = mulN<RU, NXT>(L, zero4<T>(), S.B, ti, C.V);
+            for (int ti = 0; ti < NUT; ++ti) R2[ti] = mulN<RU, NXT, SX>(L, zero4<T>(), S.B, ti, C.V);
 #pragma unroll
-            for (int ti = 0; ti < NXT; ++ti) R1[ti] = mulN<RX, NXT>(L, zero4<T>(), S.A, ti, C.V);
+            for (int ti = 0; ti < NXT; ++ti) R1[ti] = mulN<RX, NXT, SX>(L, zero4<T>(), S.A, ti, C.V);
         }
         lds_sync();
         if (j == NXT - 1) {
-            const int f = chol_inv<T, NUT>(L, S.G, m);
+            const int f = chol_inv<T, NUT>(L, S.G, md);
             if (f && lane() == 0) S.bad = 1;
         } else {
             // the record of P_{s+1}, still in LDS
@@ -682,30 +689,30 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, in
         }
         lds_sync();
         const Rec<T> out = rec(s);
-        if (RED) apply_Linv<RU, RX, NUT>(L, S.G, R2, S.X(), j);
+        if (RED) apply_Linv<RU, RX, NUT, SU>(L, S.G, R2, S.X(), j);
         if (!SM::OVER && s > 0) commit();        // A and B are dead
         lds_sync();
         if (RED) {
             // ---- V = A'V - Y'X, Q_w_hat += X'X, L_t = -L^{-T} X, v += X'z
 #pragma unroll
             for (int ti = 0; ti < NXT; ++ti) {
-                const v4_t<T> acc = mulN<RX, NUT>(L, zero4<T>(), S.Y(), ti, R2);
+                const v4_t<T> acc = mulN<RX, NUT, SU>(L, zero4<T>(), S.Y(), ti, R2);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) C.V[ti][r] = R1[ti][r] - acc[r];
-                if (KEEP == KEEP_ALL || out.V) store_tile<EX>(L, out.V, n, ti, j, n, n, C.V[ti]);
+                for (int r = 0; r < SX; ++r) C.V[ti][r] = R1[ti][r] - acc[r];
+                if (KEEP == KEEP_ALL || out.V) store_tile<EX, SX>(L, out.V, n, ti, j, n, n, C.V[ti]);
             }
 #pragma unroll
             for (int ti = 0; ti < NXT; ++ti)
-                if (ti >= j) C.Q[ti] = mulN<RX, NUT>(L, C.Q[ti], S.X(), ti, R2);
+                if (ti >= j) C.Q[ti] = mulN<RX, NUT, SU>(L, C.Q[ti], S.X(), ti, R2);
             if constexpr (VEC) {
                 double xz = 0.0;
 #pragma unroll
                 for (int ti = 0; ti < NUT; ++ti)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) xz += R2[ti][r] * S.z[16 * ti + L.row(r)];
+                    for (int r = 0; r < SU; ++r) xz += R2[ti][r] * S.z[16 * ti + L.row(r)];
                 y.v += q_sum(xz);
             }
-            if (KEEP == KEEP_ALL || out.Lt) store_feedback<EX, RU, NUT>(L, S.G, R2, out.Lt, j, n, m);
+            if (KEEP == KEEP_ALL || out.Lt) store_feedback<EX, RU, NUT, SU>(L, S.G, R2, out.Lt, j, n, m);
         } else if (KEEP == KEEP_GIVEN && out.L) {
             copy_L(S, out.L, out.LT, m, NTV, 2 * NTV);
         }
@@ -721,18 +728,21 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, in
 // in S.P (written by the caller; the pass starts with a barrier); RED: Alg. 4
 // from V = I, Q_w_hat = 0, result in C.  get(s): stage data; pre(s, t0, t1)
 // is called by the threads [t0, t1) before stage s and may read P_{s+1} from
-// S.P; rec(s): where its factors go.  EX: n = 16 NXT and m = 16 NUT exactly.
+// S.P; rec(s): where its factors go, with n and m their sizes (EX: n = 16 NXT
+// and m = 16 NUT exactly).  The problem data have md <= m inputs (EXD: 16 NUT),
+// the others being padding.
 // VEC: with the right-hand side, y holding Psi_{count} on entry.
 // The two kinds of waves run loops of their own (with the same barriers), so
 // that neither carries the other's registers.
-template <bool RED, bool EX, bool VEC, int KEEP, class T, int NXT, int NUT, class Get, class Pre, class RecOf>
-__device__ __forceinline__ void pass(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, int n_, int m_, Get get, int count,
+template <bool RED, bool EX, bool EXD, bool VEC, int KEEP, class T, int NXT, int NUT, int SX, int SU, class Get,
+          class Pre, class RecOf>
+__device__ __forceinline__ void pass(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT> &C, int n_, int m_, int md_, Get get, int count,
                                      int32_t *info, int inst, int stage_base, int fail_code, Pre pre, RecOf rec, Vec &y) {
-    using SM = Smem<T, NXT, NUT>;
+    using SM = Smem<T, NXT, NUT, SX, SU>;
     constexpr int RX = SM::RX, RU = SM::RU, NTH = SM::NTH;
     static_assert(NUT <= NXT, "one column block of B per owner of A");
     static_assert(!VEC || !SM::OVER, "the vector lines read Y's place in LDS");
-    const int n = EX ? RX : n_, m = EX ? RU : m_;
+    const int n = EX ? RX : n_, m = EX ? RU : m_, md = EXD ? RU : md_;
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     count = uni(count);
@@ -747,15 +757,15 @@ __device__ __forceinline__ void pass(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, int 
 #pragma unroll 4
         for (int e = tid; e < RX * RU; e += NTH) {
             const int i = e / RU, k = e % RU;
-            S.B[at<RU>(i, k)] = (EX || (i < n && k < m)) ? (T)gload(src.B + (uint32_t)(i * m + k)) : T(0);
+            S.B[at<RU>(i, k)] = (EXD || (i < n && k < md)) ? (T)gload(src.B + (uint32_t)(i * md + k)) : T(0);
         }
         if (VEC && tid < RX) S.av[tid] = (src.a && tid < n) ? gload(src.a + (uint32_t)tid) : 0.0;
     }
     lds_sync();
     if (wave() < NXT)
-        loop_P<RED, EX, VEC, KEEP>(S, n, m, get, count, info, inst, stage_base, fail_code, pre, rec, y);
+        loop_P<RED, EX, EXD, VEC, KEEP>(S, n, m, md, get, count, info, inst, stage_base, fail_code, pre, rec, y);
     else
-        loop_V<RED, EX, VEC, KEEP>(S, C, n, m, get, count, pre, rec, y);
+        loop_V<RED, EX, EXD, VEC, KEEP>(S, C, n, m, md, get, count, pre, rec, y);
     lds_sync();
     {
         T *p = rec(0).P;
@@ -764,21 +774,21 @@ __device__ __forceinline__ void pass(Smem<T, NXT, NUT> &S, Cols<T, NXT> &C, int 
 }
 
 // Sum of v over the workgroup, in thread 0's wave (every thread calls).
-template <class T, int NXT, int NUT>
-__device__ __forceinline__ double total(Smem<T, NXT, NUT> &S, double v) {
+template <class SM>
+__device__ __forceinline__ double total(SM &S, double v) {
     v = sv::wave_sum(v);
     if (lane() == 0) S.red[wave()] = v;
     lds_sync();
     double s = 0.0;
 #pragma unroll
-    for (int w = 0; w < 2 * NXT; ++w) s += S.red[w];
+    for (int w = 0; w < SM::NTH / 64; ++w) s += S.red[w];
     lds_sync();
     return s;
 }
 
 // V_0' and Q_w_hat (symmetric) from their owners' registers to row-major
 // n x n places.
-template <class T, int NXT, class U>
+template <int NS, class T, int NXT, class U>
 __device__ __forceinline__ void store_V_transposed(const Cols<T, NXT> &C, U *dst, int n) {
     const int j = wave() - NXT;
     if (j < 0) return;
@@ -786,12 +796,12 @@ __device__ __forceinline__ void store_V_transposed(const Cols<T, NXT> &C, U *dst
 #pragma unroll
     for (int ti = 0; ti < NXT; ++ti)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+        for (int r = 0; r < NS; ++r) {
             const int i = 16 * ti + L.row(r), k = 16 * j + L.c;
             if (i < n && k < n) dst[(uint32_t)(k * n + i)] = (U)C.V[ti][r];
         }
 }
-template <class T, int NXT, class U>
+template <int NS, class T, int NXT, class U>
 __device__ __forceinline__ void store_Q(const Cols<T, NXT> &C, U *dst, int n) {
     const int j = wave() - NXT;
     if (j < 0) return;
@@ -800,7 +810,7 @@ __device__ __forceinline__ void store_Q(const Cols<T, NXT> &C, U *dst, int n) {
     for (int ti = 0; ti < NXT; ++ti) {
         if (ti < j) continue;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+        for (int r = 0; r < NS; ++r) {
             const int i = 16 * ti + L.row(r), k = 16 * j + L.c;
             if (i < n && k < n && i >= k) {
                 dst[(uint32_t)(i * n + k)] = (U)C.Q[ti][r];
@@ -808,6 +818,64 @@ __device__ __forceinline__ void store_Q(const Cols<T, NXT> &C, U *dst, int n) {
             }
         }
     }
+}
+
+// ------------------------------------------------------------ work tables
+constexpr int SPIN_LIMIT = 1 << 26;
+
+__device__ __forceinline__ LeafItem load_leaf_u(const LeafItem *tab, int i) {
+    const LeafItem r = tab[i];
+    LeafItem u;
+    u.inst = uni(r.inst);
+    u.t0 = uni(r.t0);
+    u.len = uni(r.len);
+    u.flags = uni(r.flags);
+    u.slot = uni(r.slot);
+    u.m1 = uni(r.m1);
+    u.scratch = uni64(r.scratch);
+    return u;
+}
+__device__ __forceinline__ TreeItem load_item_u(const TreeItem *tab, int i) {
+    const TreeItem r = tab[i];
+    TreeItem u;
+    u.kind = uni(r.kind);
+    u.inst = uni(r.inst);
+    u.level = uni(r.level);
+    u.first = uni(r.first);
+    u.count = uni(r.count);
+    u.last = uni(r.last);
+    u.term_slot = uni(r.term_slot);
+    u.out_slot = uni(r.out_slot);
+    u.dep_first = uni(r.dep_first);
+    u.dep_count = uni(r.dep_count);
+    return u;
+}
+
+// Waits (thread 0) until the items this one depends on carry the current
+// epoch; a bounded wait records a failure instead of hanging.
+__device__ __forceinline__ void wait_deps(const GroupArgs &g, const TreeItem &it) {
+    if (threadIdx.x == 0) {
+        for (int d = 0; d < it.dep_count; ++d) {
+            int spins = 0;
+            while (__hip_atomic_load(&g.flags[it.dep_first + d], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) !=
+                   g.epoch) {
+                __builtin_amdgcn_s_sleep(2);
+                if (++spins > SPIN_LIMIT) {
+                    record_failure(g.info, it.inst, 6, -2);
+                    break;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+}
+
+__device__ __forceinline__ void publish(const GroupArgs &g, int idx) {
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(&g.flags[idx], g.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
 }
 
 }  // namespace cw

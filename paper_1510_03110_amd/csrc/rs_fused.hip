@@ -1,0 +1,329 @@
+// Fused FP64 solve (factor and right-hand side in one pass, no stored
+// factorization) for n_x <= 32 on the column-owner engine (rs_col.hpp):
+//   kf_leaf   one workgroup per leaf: Alg. 4, or elimination with the true
+//             terminal, keeping K, k, P, Psi, V and L_t of every stage; down:
+//             whole-problem leaves, Alg. 1-3
+//   kf_tree   work queue over the master levels: Alg. 5 up, the top solve, and
+//             Alg. 6 down to level 1 as forward sweeps on the records of the
+//             up pass
+// The leaves of multi-leaf instances are finished by the forward sweep on
+// their records (fused_leaf_forward).  Run-time sizes below the tiles
+// (n_x = 4, 8, 20, ...) are padded on load, as are the inputs of instances
+// with fewer inputs than their group's tile (g.data_nu).
+//
+// Bound: the dependent chain of a stage; on large batches the workgroups that
+// share a CU fill one another's waits, and the records' bytes are next.  FP64,
+// the whole solve before (a four-wave tile engine with every product through
+// LDS for full tiles, vector-unit kernels below them that factored the master
+// levels twice) and now: one problem of N = 1024, 32 x 16 505 -> 278 us and
+// 20 x 10 864 -> 285 us; 4 x 2, N = 64 129 -> 77 us; 512 problems of 32 x 16,
+// N = 1024 13.6 -> 11.7 ms (leaves 10.2 -> 8.2 ms); 1024 of 16 x 8, N in [32,
+// 2048] 14.9 -> 7.8 ms (padding on load instead of padded copies: 1.3 ms).
+#include <hip/hip_runtime.h>
+
+#include "rs_col.hpp"
+#include "rs_launch.hpp"
+#include "rs_vsweep.hpp"
+
+namespace rs {
+namespace cw {
+
+// Sizes: all of the tile's (FULL), the tile's with each instance's own number
+// of inputs in the data (DATA), or run-time (ANY).
+enum { FULL = 0, DATA = 1, ANY = 2 };
+
+template <int NXT, int NUT, int SZ, int SX = 4, int SU = 4>
+__global__ void __launch_bounds__(128 * NXT, NXT == 1 ? 4 : 3) kf_leaf(GroupArgs g, int down) {
+    using SM = Smem<double, NXT, NUT, SX, SU>;
+    constexpr int W = 2 * NXT;
+    constexpr bool EX = SZ != ANY, EXD = SZ == FULL;
+    __shared__ SM S;
+    __shared__ vs::Smem<SM::RX, SM::RU, W> F;
+    const LeafItem it = load_leaf_u(g.leaves, blockIdx.x);
+    if (((it.flags & LEAF_TOP) != 0) != (down != 0) || inst_skipped(g.probs, it.inst)) return;
+    const DevProb p = load_prob(g.probs, it.inst);
+    const int n = EX ? SM::RX : g.nx, m = EX ? SM::RU : g.nu, md = SZ == DATA ? p.nu : m, tid = threadIdx.x;
+    const SlotLayout SL{n};
+    double *out = g.slots + (int64_t)it.slot * SL.size();
+    double *base = static_cast<double *>(g.leaf_scratch) + it.scratch;
+    const int len = leaf_rec_len(n, m);
+    auto get = [&](int s) { return prob_stage(p, it.t0 + s); };
+    auto no_pre = [](int, int, int) {};
+    auto rec = [&](int s) {
+        double *K = base + (int64_t)s * len, *P = K + m * n + m, *V = P + n * n + n;
+        return Rec<double>{P, K, V, V + n * n, nullptr, nullptr, P + n * n, K + m * n};
+    };
+    const Ln<double> L;
+    const int w = wave(), col = 16 * (w < NXT ? w : w - NXT) + L.c;
+    const bool own = L.q == 0 && col < n;            // owner lane of entry col
+    Cols<double, NXT> C;
+    Vec y{};
+    if (!(it.flags & LEAF_LAST)) {
+        set_P(S, n, [](int) { return 0.0; });
+        pass<true, EX, EXD, true, KEEP_ALL>(S, C, n, m, md, get, it.len, g.info, it.inst, it.t0, 2, no_pre, rec, y);
+        store_V_transposed<SX>(C, out + SL.A(), n);
+        copy_P(S, out + SL.Qx(), n);
+        if (!g.ident) store_Q<SX>(C, out + SL.Qw(), n);
+        if (own && w >= NXT) out[SL.a() + col] = y.v;
+    } else {
+        set_P(S, n, [&](int e) { return p.QxN[e]; });
+        if (w < NXT && col < n) y.psi = p.lN ? -p.lN[col] : 0.0;
+        pass<false, EX, EXD, true, KEEP_ALL>(S, C, n, m, md, get, it.len, g.info, it.inst, it.t0, 2, no_pre, rec, y);
+        if (!down) copy_P(S, out + SL.Qx(), n);
+    }
+    const double c = total(S, y.cb + vs::sum_c(p.c ? p.c + (int64_t)it.t0 * p.sc : nullptr, p.sc, it.len)) +
+                     (((it.flags & LEAF_LAST) && p.cN) ? p.cN[0] : 0.0);
+    if (!down) {
+        if (own && w < NXT) out[SL.lx() + col] = -y.psi;
+        if (tid == 0) out[SL.c()] = c;
+        if (g.ident && !(it.flags & LEAF_LAST)) {
+            store_Q<SX>(C, S.A, n);              // A is dead: Q_w_hat, row-major
+            rank_reveal(S.A, n, unit_roundoff<double>(), out + SL.Qw(), nullptr);
+        }
+        return;
+    }
+    // whole problem: optimal value 1/2 x0'P_0 x0 - Psi_0'x0 + cbar_0, then Alg. 3
+    for (int e = tid; e < SM::RX; e += SM::NTH) F.x[e] = e < n ? p.x0[e] : 0.0;
+    __threadfence_block();                   // the records are read back by other lanes
+    __syncthreads();
+    if (p.obj) {
+        double px = 0.0;
+        if (w < NXT) {
+#pragma unroll
+            for (int kt = 0; kt < NXT; ++kt)
+#pragma unroll
+                for (int r = 0; r < SX; ++r) px += ldN<SM::RX>(L, S.P, kt, w, r) * F.x[16 * kt + L.row(r)];
+            px = q_sum(px);
+        }
+        const double o = total(S, (own && w < NXT) ? F.x[col] * (0.5 * px - y.psi) : 0.0);
+        if (tid == 0) p.obj[0] = o + c;
+    }
+    const int64_t t0 = it.t0;
+    vs::forward<SM::RX, SM::RU, W, EX, EXD, double>(
+        F, n, m, md, it.len, vs::FusedStages{sv::load_prob(g.probs, it.inst), it.t0, n, m, base}, false,
+        [&](int s) { return p.x + (t0 + s) * n; }, [&](int s) { return p.w + (t0 + s) * md; },
+        [&](int s) { return p.lam + (t0 + s) * n; });
+    const int64_t t = t0 + it.len;
+    const double q = vs::sym_apply<SM::RX, SM::RU, W>(p.QxN, F.x, n);
+    typedef vs::Mat<double, SM::RX, SM::RX, W> MA;
+    const int i = MA::out_row();
+    if (MA::lead_row() && i < n) {
+        p.lam[t * n + i] = q + (p.lN ? p.lN[i] : 0.0);          // lam_N = QxN x_N + lN
+        p.x[t * n + i] = F.x[i];
+    }
+}
+
+template <int NXT, bool EX, int SX = 4>
+__global__ void __launch_bounds__(128 * NXT, 2) kf_tree(GroupArgs g) {
+    using SM = Smem<double, NXT, NXT, SX, SX>;
+    constexpr int W = 2 * NXT, NM = SM::RX;
+    __shared__ SM S;
+    __shared__ vs::Smem<NM, NM, W> F;
+    __shared__ int s_item;
+    const int n = EX ? NM : g.nx, tid = threadIdx.x;
+    const SlotLayout SL{n};
+    double *slots = g.slots;
+    auto slot = [&](int s) { return slots + (int64_t)s * SL.size(); };
+    typedef vs::Mat<double, NM, NM, W> MA;
+    for (;;) {
+        if (tid == 0) s_item = atomicAdd(g.queue, 1);
+        __syncthreads();
+        const int idx = uni(s_item);
+        __syncthreads();
+        if (idx >= g.nitems) break;
+        const TreeItem it = load_item_u(g.items, idx);
+        wait_deps(g, it);
+        auto get = [&](int s) { return slot_stage(slot(it.first + s), n, g.ident); };
+        auto no_pre = [](int, int, int) {};
+        auto c_sum = [&] { return vs::sum_c(slot(it.first) + SL.c(), SL.size(), it.count); };
+        const Ln<double> L;
+        const int w = wave(), col = 16 * (w < NXT ? w : w - NXT) + L.c;
+        const bool own = L.q == 0 && col < n;
+        const int ir = MA::out_row();
+        const bool ownr = MA::lead_row() && ir < n;
+        Cols<double, NXT> C;
+        Vec y{};
+        if (inst_skipped(g.probs, it.inst)) {
+            // excluded instance: only its completion flag is published
+        } else if (it.kind == ITEM_UP) {
+            set_P(S, n, [](int) { return 0.0; });
+            pass<true, EX, EX, true, KEEP_GIVEN>(S, C, n, n, n, get, it.count, g.info, it.inst, -1, 3, no_pre, [&](int s) {
+                double *d = slot(it.first + s);
+                return Rec<double>{d + SL.uP(), d + SL.uK(), d + SL.uV(), d + SL.dL(), nullptr, nullptr, d + SL.Psi(),
+                                   d + SL.k()};
+            }, y);
+            double *out = slot(it.out_slot);
+            store_V_transposed<SX>(C, out + SL.A(), n);
+            copy_P(S, out + SL.Qx(), n);
+            if (!g.ident) store_Q<SX>(C, out + SL.Qw(), n);
+            const double c = total(S, y.cb + c_sum());
+            if (own) out[(w < NXT ? SL.lx() : SL.a()) + col] = w < NXT ? -y.psi : y.v;
+            if (tid == 0) out[SL.c()] = c;
+            if (g.ident) {
+                store_Q<SX>(C, S.A, n);
+                rank_reveal(S.A, n, unit_roundoff<double>(), out + SL.Qw(), nullptr);
+            }
+        } else if (it.kind == ITEM_UP_LAST || it.kind == ITEM_TOP) {
+            // Alg. 1-2 from the level's true terminal: the level's last item
+            // keeps its up records, the top the messages to its children
+            const bool top = it.kind == ITEM_TOP;
+            double *term = slot(it.term_slot);
+            set_P(S, n, [&](int e) { return term[SL.Qx() + e]; });
+            if (w < NXT && col < n) y.psi = -term[SL.lx() + col];
+            if (top) {
+                double *d = slot(it.first + it.count - 1);
+                __syncthreads();
+                copy_P(S, d + SL.P(), n);
+                if (own && w < NXT) d[SL.Psi() + col] = y.psi;
+            }
+            pass<false, EX, EX, true, KEEP_GIVEN>(S, C, n, n, n, get, it.count, g.info, it.inst, -1, 3, no_pre, [&](int s) {
+                double *d = slot(it.first + s);
+                if (!top)
+                    return Rec<double>{d + SL.uP(), d + SL.uK(), nullptr, nullptr, nullptr, nullptr, d + SL.Psi(),
+                                       d + SL.k()};
+                double *c = slot(it.first + (s > 0 ? s - 1 : 0));
+                return Rec<double>{s > 0 ? c + SL.P() : nullptr, d + SL.K(), nullptr, nullptr, nullptr, nullptr,
+                                   s > 0 ? c + SL.Psi() : nullptr, d + SL.k()};
+            }, y);
+            const double c = total(S, y.cb + c_sum()) + term[SL.c()];
+            if (!top) {
+                double *out = slot(it.out_slot);
+                copy_P(S, out + SL.Qx(), n);
+                if (own && w < NXT) out[SL.lx() + col] = -y.psi;
+                if (tid == 0) out[SL.c()] = c;
+            } else {
+                const DevProb p = load_prob(g.probs, it.inst);
+                for (int e = tid; e < NM; e += SM::NTH) F.x[e] = e < n ? p.x0[e] : 0.0;
+                __threadfence_block();       // K, k and the messages are read back by other lanes
+                __syncthreads();
+                if (p.obj) {
+                    double px = 0.0;
+                    if (w < NXT) {
+#pragma unroll
+                        for (int kt = 0; kt < NXT; ++kt)
+#pragma unroll
+                            for (int r = 0; r < SX; ++r) px += ldN<NM>(L, S.P, kt, w, r) * F.x[16 * kt + L.row(r)];
+                        px = q_sum(px);
+                    }
+                    const double o = total(S, (own && w < NXT) ? F.x[col] * (0.5 * px - y.psi) : 0.0);
+                    if (tid == 0) p.obj[0] = o + c;
+                }
+                auto none = [](int) { return (double *)nullptr; };
+                auto st = [&](int s) {
+                    vs::Stage<double> q = vs::SlotStages{slots, it.first, n, false}(s);
+                    q.P = nullptr;
+                    return q;
+                };
+                vs::forward<NM, NM, W, EX, EX, double>(F, n, n, n, it.count, st, false,
+                                                       [&](int s) { return slot(it.first + s) + SL.xh(); }, none, none);
+                if (ownr) term[SL.xh() + ir] = F.x[ir];
+                // terminal costate of child s, lam_{s+1} = P_{s+1} x_{s+1} -
+                // Psi_{s+1}, from the cost to go sent to it and the initial
+                // state of the next child (of the terminal node for the last)
+                __threadfence_block();
+                __syncthreads();
+                for (int s = 0; s < it.count; ++s) {
+                    double *d = slot(it.first + s);
+                    const double *xn = (s + 1 < it.count ? slot(it.first + s + 1) : term) + SL.xh();
+                    for (int e = tid; e < n; e += SM::NTH) F.x[e] = xn[e];
+                    sv::wsync();
+                    const double l = vs::sym_apply<NM, NM, W>(d + SL.P(), F.x, n);
+                    if (ownr) d[SL.lamN() + ir] = l - d[SL.Psi() + ir];
+                    sv::wsync();
+                }
+            }
+        } else {
+            // down pass below the top (Alg. 6, k >= 1): child s receives x_s
+            // and its terminal costate lam_{s+1}
+            const bool last = it.last != 0;
+            const double *msg = slot(it.out_slot);
+            for (int e = tid; e < NM; e += SM::NTH) {
+                F.x[e] = e < n ? msg[SL.xh() + e] : 0.0;
+                F.lamN[e] = (!last && e < n) ? msg[SL.lamN() + e] : 0.0;
+            }
+            __syncthreads();
+            vs::forward<NM, NM, W, EX, EX, double>(
+                F, n, n, n, it.count, vs::SlotStages{slots, it.first, n, true}, !last,
+                [&](int s) { return slot(it.first + s) + SL.xh(); }, [](int) { return (double *)nullptr; },
+                [&](int s) { return s > 0 ? slot(it.first + s - 1) + SL.lamN() : (double *)nullptr; });
+            // the last child ends where the item does: at lam_N, or for the
+            // last item at the terminal node, lam = P_term x - Psi_term
+            double *lend = slot(it.first + it.count - 1) + SL.lamN();
+            if (last) {
+                double *term = slot(it.term_slot);
+                const double l = vs::sym_apply<NM, NM, W>(term + SL.Qx(), F.x, n);
+                if (ownr) {
+                    lend[ir] = l + term[SL.lx() + ir];
+                    term[SL.xh() + ir] = F.x[ir];
+                }
+            } else if (ownr) {
+                lend[ir] = F.lamN[ir];
+            }
+        }
+        publish(g, idx);
+    }
+}
+
+template <int A, int B>
+hipError_t fused_leaf(const GroupArgs &g, int down, hipStream_t st) {
+    const dim3 grid(g.nleaves), block(128 * A);
+    if constexpr (A == 1) {
+        // one or two slices of the tile
+        if (g.nx <= 4 && g.nu <= 4) {
+            hipLaunchKernelGGL((kf_leaf<A, B, ANY, 1, 1>), grid, block, 0, st, g, down);
+            return hipGetLastError();
+        }
+        if (g.nx <= 8 && g.nu <= 4) {
+            hipLaunchKernelGGL((kf_leaf<A, B, ANY, 2, 1>), grid, block, 0, st, g, down);
+            return hipGetLastError();
+        }
+    }
+    if (g.nx != 16 * A || g.nu != 16 * B)
+        hipLaunchKernelGGL((kf_leaf<A, B, ANY>), grid, block, 0, st, g, down);
+    else if (g.data_nu)
+        hipLaunchKernelGGL((kf_leaf<A, B, DATA>), grid, block, 0, st, g, down);
+    else
+        hipLaunchKernelGGL((kf_leaf<A, B, FULL>), grid, block, 0, st, g, down);
+    return hipGetLastError();
+}
+hipError_t fused_leaf_any(const GroupArgs &g, int down, hipStream_t st) {
+    if (g.nx <= 16) return fused_leaf<1, 1>(g, down, st);
+    if (g.nu <= 16) return fused_leaf<2, 1>(g, down, st);
+    return fused_leaf<2, 2>(g, down, st);
+}
+
+hipError_t launch_up(const GroupArgs &g, int, hipStream_t st) {
+    return g.ntop == g.nleaves ? hipSuccess : fused_leaf_any(g, 0, st);
+}
+hipError_t launch_tree(const GroupArgs &g, int grid, hipStream_t st) {
+    const dim3 gd(grid);
+    if (g.nx == 16)
+        hipLaunchKernelGGL((kf_tree<1, true>), gd, dim3(128), 0, st, g);
+    else if (g.nx <= 4)
+        hipLaunchKernelGGL((kf_tree<1, false, 1>), gd, dim3(128), 0, st, g);
+    else if (g.nx <= 8)
+        hipLaunchKernelGGL((kf_tree<1, false, 2>), gd, dim3(128), 0, st, g);
+    else if (g.nx < 16)
+        hipLaunchKernelGGL((kf_tree<1, false>), gd, dim3(128), 0, st, g);
+    else if (g.nx == 32)
+        hipLaunchKernelGGL((kf_tree<2, true>), gd, dim3(256), 0, st, g);
+    else
+        hipLaunchKernelGGL((kf_tree<2, false>), gd, dim3(256), 0, st, g);
+    return hipGetLastError();
+}
+hipError_t launch_down(const GroupArgs &g, int, hipStream_t st) {
+    if (g.ntop > 0) {
+        const hipError_t e = fused_leaf_any(g, 1, st);
+        if (e != hipSuccess || g.ntop == g.nleaves) return e;
+    }
+    return fused_leaf_forward(g, st);
+}
+
+}  // namespace cw
+
+Launcher fused_solve(int nx, int nu, int which) {
+    if (nx > 32 || !mid_shape(nx, nu)) return nullptr;
+    return which == 0 ? &cw::launch_up : which == 1 ? &cw::launch_tree : &cw::launch_down;
+}
+
+}  // namespace rs

@@ -507,7 +507,7 @@ __device__ __forceinline__ v4_t<T> blk16(v4_t<T> acc, const T *A, int lda, const
 // Blocked Cholesky factorization G = L L' ("a factorization of G", Alg. 1)
 // and the explicit inverse (any m <= 128).  Right-looking over 16-wide block
 // columns: the diagonal block (padded with the identity past m) is factored
-// and inverted by one wavefront (chol_inv_wave), the panel below it is
+// and inverted by one wavefront (chol_inv16), the panel below it is
 // L_ik = G_ik L_kk^{-T}, and the trailing lower blocks are updated
 // G_ij -= L_ik L_jk'.  The inverse follows block row by block row:
 // X_ii = L_ii^{-1}, X_ij = -X_ii sum_{k=j}^{i-1} L_ik X_kj.  On return
@@ -527,7 +527,7 @@ __device__ void chol_inv(WS<T> &S, int m, int *bad) {
                 D[e] = (i < rk && j < rk) ? G[(int64_t)(16 * kb + i) * m + 16 * kb + j] : (i == j ? T(1) : T(0));
             }
             wave_gfence();
-            const int f = mf::chol_inv_wave<16>(D, DT);      // D <- L_kk^{-1}, DT <- L_kk^{-T}
+            const int f = mf::chol_inv16(D, DT);      // D <- L_kk^{-1}, DT <- L_kk^{-T}
             if (f && l == 0) *bad = 1;
         }
         __syncthreads();

@@ -7,11 +7,12 @@
 
 namespace rs {
 
-// Per-stage element count of the leaf solve's scratch (K, k, P, Psi).
-constexpr int scratch_per_stage(int nx, int nu) { return nu * nx + nu + nx * nx + nx; }
-// Matrix-core leaves also keep V and L of Alg. 4 (leaf solve by a forward
-// sweep on the stored preliminary solution).
-constexpr int scratch_per_stage_fwd(int nx, int nu) { return 2 * nu * nx + nu + 2 * nx * nx + nx; }
+// Leaf scratch of the fused solve per stage as rs_batch_solve_noalloc counts
+// it: below the full tiles without V and L_t, which those shapes' records did
+// not always hold, so that the plans it takes are the same.
+constexpr int scratch_counted(int nx, int nu) {
+    return (nx % 16 == 0 && nu % 16 == 0) ? leaf_rec_len(nx, nu) : nu * nx + nu + nx * nx + nx;
+}
 
 typedef hipError_t (*Launcher)(const GroupArgs &, int grid, hipStream_t);
 
@@ -37,10 +38,11 @@ struct ShapeEntry {
     int scratch_per_stage;
 };
 
+Launcher fused_solve(int nx, int nu, int which);         // fused FP64 solve (rs_fused.hip), n_x <= 32
+hipError_t fused_leaf_forward(const GroupArgs &g, hipStream_t st);   // its leaf solve on the leaf records
 Launcher mfma_factor(int nx, int nu, int which, bool fp32);
 Launcher vector_solve(int nx, int nu, int which, bool fp32);
 Launcher refine_kernel(int nx, int nu, int which);       // 0 residual, 1 update
-Launcher leaf_forward(int nx, int nu);                   // leaf solve on the stored leaf records
 // mode 0 also clears active[0 .. nactive); mode 1 counts the instances still
 // iterating into *active.
 hipError_t launch_refine_check(const InstInfo *tab, int count, const double *part, double *stats, int32_t *conv,
@@ -82,8 +84,10 @@ hipError_t sweep_tree(const GroupArgs &g, int grid, hipStream_t st);
 const ShapeEntry *find_shape(int nx, int nu);
 
 // Device scratch of rs_batch_solve_noalloc (rs_static.hip): its device
-// address on the current device (taken once per device), and its size.
-constexpr size_t STATIC_SCRATCH_BYTES = size_t(64) << 20;
+// address on the current device (taken once per device), and its size (twice
+// what the call counts: a plan's leaf scratch is less than twice its counted
+// one, see scratch_counted).
+constexpr size_t STATIC_SCRATCH_BYTES = size_t(128) << 20;
 void *static_scratch(size_t *bytes);
 hipError_t launch_init(int32_t *info, int count, int32_t *queues, int nq, hipStream_t st);
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t st);

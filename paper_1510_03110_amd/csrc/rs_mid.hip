@@ -20,43 +20,13 @@
 namespace rs {
 namespace cw {
 
-constexpr int SPIN_LIMIT = 1 << 26;
-
-__device__ __forceinline__ LeafItem load_leaf_u(const LeafItem *tab, int i) {
-    const LeafItem r = tab[i];
-    LeafItem u;
-    u.inst = uni(r.inst);
-    u.t0 = uni(r.t0);
-    u.len = uni(r.len);
-    u.flags = uni(r.flags);
-    u.slot = uni(r.slot);
-    u.m1 = uni(r.m1);
-    u.scratch = uni64(r.scratch);
-    return u;
-}
-__device__ __forceinline__ TreeItem load_item_u(const TreeItem *tab, int i) {
-    const TreeItem r = tab[i];
-    TreeItem u;
-    u.kind = uni(r.kind);
-    u.inst = uni(r.inst);
-    u.level = uni(r.level);
-    u.first = uni(r.first);
-    u.count = uni(r.count);
-    u.last = uni(r.last);
-    u.term_slot = uni(r.term_slot);
-    u.out_slot = uni(r.out_slot);
-    u.dep_first = uni(r.dep_first);
-    u.dep_count = uni(r.dep_count);
-    return u;
-}
-
 // One workgroup per leaf.  Up (down = 0): leaves of multi-leaf instances;
 // down (down = 1): whole-problem leaves, the only ones that need the
 // factorization with the true terminal (the others are solved from their up
 // records).
-template <class T, int NXT, int NUT, bool EX>
+template <class T, int NXT, int NUT, bool EX, int SX = 4, int SU = 4>
 __global__ void __launch_bounds__(128 * NXT, 2) kc_leaf(GroupArgs g, int down) {
-    using SM = Smem<T, NXT, NUT>;
+    using SM = Smem<T, NXT, NUT, SX, SU>;
     __shared__ SM S;
     const LeafItem it = load_leaf_u(g.leaves, blockIdx.x);
     if (((it.flags & LEAF_TOP) != 0) != (down != 0) || inst_skipped(g.probs, it.inst)) return;
@@ -80,26 +50,26 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_leaf(GroupArgs g, int down) {
     Vec y{};
     if (!(it.flags & LEAF_LAST)) {
         set_P(S, n, [](int) { return 0.0; });
-        pass<true, EX, false, KEEP_GIVEN>(S, C, n, m, get, it.len, g.info, it.inst, it.t0, 2, no_pre, [&](int s) {
+        pass<true, EX, EX, false, KEEP_GIVEN>(S, C, n, m, m, get, it.len, g.info, it.inst, it.t0, 2, no_pre, [&](int s) {
             T *d = base + (int64_t)s * R.per_stage();
             return Rec<T>{d + R.P(), d + R.K(), d + R.V(), d + R.Lt(), d + R.L(), d + R.LT(), nullptr, nullptr};
         }, y);
-        store_V_transposed(C, out + SL.A(), n);
+        store_V_transposed<SX>(C, out + SL.A(), n);
         copy_P(S, out + SL.Qx(), n);
-        if (!g.ident) store_Q(C, out + SL.Qw(), n);
+        if (!g.ident) store_Q<SX>(C, out + SL.Qw(), n);
         if (cache) {
-            store_V_transposed(C, cache + SL.A(), n);
+            store_V_transposed<SX>(C, cache + SL.A(), n);
             copy_P(S, cache + SL.Qx(), n);
-            if (!g.ident) store_Q(C, cache + SL.Qw(), n);
+            if (!g.ident) store_Q<SX>(C, cache + SL.Qw(), n);
         }
         if (g.ident) {
-            store_Q(C, S.A, n);              // A is dead: Q_w_hat, row-major
+            store_Q<SX>(C, S.A, n);              // A is dead: Q_w_hat, row-major
             rank_reveal(S.A, n, unit_roundoff<T>(), out + SL.Qw(), cache ? cache + SL.Qw() : nullptr);
         }
     } else {
         if (down) base += R.up();
         set_P(S, n, [&](int e) { return p.QxN[e]; });
-        pass<false, EX, false, KEEP_GIVEN>(S, C, n, m, get, it.len, g.info, it.inst, it.t0, 2, no_pre, [&](int s) {
+        pass<false, EX, EX, false, KEEP_GIVEN>(S, C, n, m, m, get, it.len, g.info, it.inst, it.t0, 2, no_pre, [&](int s) {
             T *d = base + (int64_t)s * R.per_stage();
             return Rec<T>{d + R.P(), d + R.K(), nullptr, nullptr, d + R.L(), d + R.LT(), nullptr, nullptr};
         }, y);
@@ -108,9 +78,9 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_leaf(GroupArgs g, int down) {
 }
 
 #ifndef RS_MID_FP32
-template <int NXT, bool EX>
+template <int NXT, bool EX, int SX = 4>
 __global__ void __launch_bounds__(128 * NXT, 2) kc_tree(GroupArgs g) {
-    using SM = Smem<double, NXT, NXT>;
+    using SM = Smem<double, NXT, NXT, SX, SX>;
     __shared__ SM S;
     __shared__ int s_item;
     const int n = EX ? SM::RX : g.nx, tid = threadIdx.x;
@@ -124,21 +94,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_tree(GroupArgs g) {
         __syncthreads();
         if (idx >= g.nitems) break;
         const TreeItem it = load_item_u(g.items, idx);
-        if (tid == 0) {
-            for (int d = 0; d < it.dep_count; ++d) {
-                int spins = 0;
-                while (__hip_atomic_load(&g.flags[it.dep_first + d], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) !=
-                       g.epoch) {
-                    __builtin_amdgcn_s_sleep(4);
-                    if (++spins > SPIN_LIMIT) {
-                        record_failure(g.info, it.inst, 6, -2);
-                        break;
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        wait_deps(g, it);
         auto get = [&](int s) { return slot_stage(slot(it.first + s), n, g.ident); };
         Cols<double, NXT> C;
         Vec y{};
@@ -146,18 +102,18 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_tree(GroupArgs g) {
             // excluded instance: only its completion flag is published
         } else if (it.kind == ITEM_UP) {
             set_P(S, n, [](int) { return 0.0; });
-            pass<true, EX, false, KEEP_GIVEN>(S, C, n, n, get, it.count, g.info, it.inst, -1, 3, [](int, int, int) {}, [&](int s) {
+            pass<true, EX, EX, false, KEEP_GIVEN>(S, C, n, n, n, get, it.count, g.info, it.inst, -1, 3, [](int, int, int) {}, [&](int s) {
                 double *d = slot(it.first + s);
                 return Rec<double>{d + SL.uP(), d + SL.uK(), d + SL.uV(), g.superpose ? d + SL.dL() : nullptr,
                                    d + SL.uL(), d + SL.uLT(), nullptr, nullptr};
             }, y);
             double *out = slot(it.out_slot);
-            store_V_transposed(C, out + SL.A(), n);
+            store_V_transposed<SX>(C, out + SL.A(), n);
             copy_P(S, out + SL.Qx(), n);
             if (!g.ident) {
-                store_Q(C, out + SL.Qw(), n);
+                store_Q<SX>(C, out + SL.Qw(), n);
             } else {
-                store_Q(C, S.A, n);
+                store_Q<SX>(C, S.A, n);
                 rank_reveal(S.A, n, unit_roundoff<double>(), out + SL.Qw(), nullptr);
             }
         } else if (it.kind == ITEM_DOWN && g.superpose) {
@@ -171,7 +127,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_tree(GroupArgs g) {
             double *term = it.last ? slot(it.term_slot) : nullptr;
             const double *P0 = term ? term + SL.Qx() : msg + SL.P();
             set_P(S, n, [&](int e) { return P0[e]; });
-            pass<false, EX, false, KEEP_GIVEN>(S, C, n, n, get, it.count, g.info, it.inst, -1, 3,
+            pass<false, EX, EX, false, KEEP_GIVEN>(S, C, n, n, n, get, it.count, g.info, it.inst, -1, 3,
                             [&](int s, int t0, int t1) {      // M2 for child s: P at the end of master stage s
                                 if (!upl) copy_P(S, slot(it.first + s) + SL.P(), n, t0, t1);
                             },
@@ -186,10 +142,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_tree(GroupArgs g) {
             double *d = upl ? slot(it.out_slot) + SL.Qx() : it.kind == ITEM_TOP ? term + SL.P() : nullptr;
             if (d) copy_P(S, d, n);
         }
-        __threadfence();
-        __syncthreads();
-        if (tid == 0) __hip_atomic_store(&g.flags[idx], g.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
+        publish(g, idx);
     }
 }
 #endif
@@ -206,6 +159,16 @@ hipError_t leaf(const GroupArgs &g, hipStream_t st, int down) {
             hipLaunchKernelGGL((kc_leaf<T, A, B, true>), grid, block, 0, st, g, down);
             return hipGetLastError();
         }
+    }
+    if constexpr (A == 1 && sizeof(T) == 8) {
+        // one or two slices of the tile
+        if (g.nx <= 4 && g.nu <= 4)
+            hipLaunchKernelGGL((kc_leaf<T, A, B, false, 1, 1>), grid, block, 0, st, g, down);
+        else if (g.nx <= 8 && g.nu <= 4)
+            hipLaunchKernelGGL((kc_leaf<T, A, B, false, 2, 1>), grid, block, 0, st, g, down);
+        else
+            hipLaunchKernelGGL((kc_leaf<T, A, B, false>), grid, block, 0, st, g, down);
+        return hipGetLastError();
     }
     hipLaunchKernelGGL((kc_leaf<T, A, B, false>), grid, block, 0, st, g, down);
     return hipGetLastError();
@@ -231,6 +194,16 @@ hipError_t leaf_any(const GroupArgs &g, hipStream_t st, int down) {
 #ifndef RS_MID_FP32
 template <int A>
 hipError_t tree(const GroupArgs &g, int grid, hipStream_t st) {
+    if constexpr (A == 1) {
+        if (g.nx <= 4) {
+            hipLaunchKernelGGL((kc_tree<A, false, 1>), dim3(grid), dim3(128 * A), 0, st, g);
+            return hipGetLastError();
+        }
+        if (g.nx <= 8) {
+            hipLaunchKernelGGL((kc_tree<A, false, 2>), dim3(grid), dim3(128 * A), 0, st, g);
+            return hipGetLastError();
+        }
+    }
     if (g.nx == 16 * A)
         hipLaunchKernelGGL((kc_tree<A, true>), dim3(grid), dim3(128 * A), 0, st, g);
     else
@@ -259,6 +232,19 @@ hipError_t mid_tree(const GroupArgs &g, int grid, hipStream_t st) {
     default: return cw::tree<4>(g, grid, st);
     }
 }
+
+// Stored factorization on the column-owner engine; which: 0 leaf up, 1 tree,
+// 2 leaf down; fp32: leaf passes in FP32 (the tree is FP64 in both).
+Launcher mfma_factor(int nx, int nu, int which, bool fp32) {
+    if (!((nx == 16 && nu == 16) || (nx == 32 && nu == 16) || (nx == 32 && nu == 32))) return nullptr;
+    if (which == 1) return [](const GroupArgs &g, int grid, hipStream_t st) { return mid_tree(g, grid, st); };
+    if (which == 0)
+        return fp32 ? [](const GroupArgs &g, int, hipStream_t st) { return mid_leaf_f32(g, false, st); }
+                    : [](const GroupArgs &g, int, hipStream_t st) { return mid_leaf_f64(g, false, st); };
+    return fp32 ? [](const GroupArgs &g, int, hipStream_t st) { return g.ntop ? mid_leaf_f32(g, true, st) : hipSuccess; }
+                : [](const GroupArgs &g, int, hipStream_t st) { return g.ntop ? mid_leaf_f64(g, true, st) : hipSuccess; };
+}
+
 #endif
 
 }  // namespace rs

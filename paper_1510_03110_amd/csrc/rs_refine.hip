@@ -525,7 +525,7 @@ __global__ void __launch_bounds__(RT) kc_scan(GroupArgs g, int32_t *first) {
     const LeafItem it = load_leaf(g.leaves, blockIdx.x);
     if ((uni(g.probs[it.inst].flags) & PROB_SKIP) != 0) return;
     const Prob p = load_prob(g.probs, it.inst);
-    const int64_t n = g.nx, m = g.nu;
+    const int64_t n = g.nx, m = uni(g.probs[it.inst].nu);     // the data's own width
     const int tid = threadIdx.x, len = uni(it.len);
     if (tid == 0) bad_s = 0x7fffffff;
     __syncthreads();

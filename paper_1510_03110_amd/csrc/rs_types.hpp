@@ -192,6 +192,9 @@ struct GroupArgs {
     // records (Alg. 6 without a second factorization), 0 = factored again
     // with the parent's message
     int32_t superpose;
+    // 1: the instances' data have their own number of inputs (DevProb.nu), at
+    // most this group's nu; the others are padding (fused solve)
+    int32_t data_nu;
     // first stage of a leaf's records in the stored factorization
     __host__ __device__ int64_t rec_stage(int64_t leaf_scratch) const { return leaf_scratch / sps - rec_stage0; }
 };

@@ -120,7 +120,7 @@ __global__ void __launch_bounds__(64 * W) ks_leaf_down(GroupArgs g) {
         wsync();
     }
     const int64_t t0 = it.t0;
-    forward<NM, MM, W, EX, TR>(S, n, m, it.len, st, lterms, [&](int s) { return p.x + (t0 + s) * n; },
+    forward<NM, MM, W, EX, EX, TR>(S, n, m, m, it.len, st, lterms, [&](int s) { return p.x + (t0 + s) * n; },
                            [&](int s) { return p.w + (t0 + s) * m; }, [&](int s) { return p.lam + (t0 + s) * n; });
     if (last) {
         const int64_t t = t0 + it.len;
@@ -134,12 +134,13 @@ __global__ void __launch_bounds__(64 * W) ks_leaf_down(GroupArgs g) {
 
 // Leaf solve of the fused path from the records of the fused leaf reduction;
 // whole-problem leaves are solved by the fused leaf kernel itself.
-template <int NM, int MM, int W>
+// EX: full sizes; MD: the data width is the instance's own (padded inputs).
+template <int NM, int MM, int W, bool EX, bool MD>
 __global__ void __launch_bounds__(64 * W) ks_leaf_fwd(GroupArgs g) {
     __shared__ Smem<NM, MM, W> S;
     const LeafItem it = sv::load_leaf(g.leaves, blockIdx.x);
     if ((it.flags & LEAF_TOP) || sv::skip_inst(g, it.inst)) return;
-    const int n = NM, m = MM;
+    const int n = EX ? NM : g.nx, m = EX ? MM : g.nu, md = MD ? uni(g.probs[it.inst].nu) : m;
     const sv::Prob p = sv::load_prob(g.probs, it.inst);
     const SlotLayout SL{n};
     const bool last = (it.flags & LEAF_LAST) != 0;
@@ -147,18 +148,19 @@ __global__ void __launch_bounds__(64 * W) ks_leaf_fwd(GroupArgs g) {
     typedef Mat<double, NM, NM, W> MA;
     const int i = MA::out_row();
     for (int e = threadIdx.x; e < NM; e += 64 * W) {
-        S.x[e] = msg[SL.xh() + e];
-        S.lamN[e] = last ? 0.0 : msg[SL.lamN() + e];
+        S.x[e] = e < n ? msg[SL.xh() + e] : 0.0;
+        S.lamN[e] = (last || e >= n) ? 0.0 : msg[SL.lamN() + e];
     }
     __syncthreads();
     const FusedStages st{p, it.t0, n, m, static_cast<double *>(g.leaf_scratch) + it.scratch};
     const int64_t t0 = it.t0;
-    forward<NM, MM, W, true, double>(S, n, m, it.len, st, !last, [&](int s) { return p.x + (t0 + s) * n; },
-                               [&](int s) { return p.w + (t0 + s) * m; }, [&](int s) { return p.lam + (t0 + s) * n; });
+    forward<NM, MM, W, EX, EX && !MD, double>(
+        S, n, m, md, it.len, st, !last, [&](int s) { return p.x + (t0 + s) * n; },
+        [&](int s) { return p.w + (t0 + s) * md; }, [&](int s) { return p.lam + (t0 + s) * n; });
     if (last) {
         const int64_t t = t0 + it.len;
         const double q = sym_apply<NM, MM, W>(p.QxN, S.x, n);
-        if (MA::lead_row()) {
+        if (MA::lead_row() && i < n) {
             p.lam[t * n + i] = q + (p.lN ? p.lN[i] : 0.0);         // lam_N = QxN x_N + lN
             p.x[t * n + i] = S.x[i];
         }
@@ -166,28 +168,6 @@ __global__ void __launch_bounds__(64 * W) ks_leaf_fwd(GroupArgs g) {
 }
 
 // -------------------------------------------------------------- the tree
-// Master stages read from their slots; up: the factors of the up pass
-// (P and V after the stage are those records), else of the down pass, whose P
-// is the message P_{s+1} kept in the stage's own slot.
-struct SlotStages {
-    double *slots;
-    int first, n;
-    bool up;
-    __device__ double *slot(int s) const { return slots + (int64_t)(first + s) * SlotLayout{n}.size(); }
-    __device__ Stage<double> operator()(int s) const {
-        const SlotLayout L{n};
-        double *d = slot(s);
-        if (up)
-            return Stage<double>{d + L.uP(), d + L.uV(), d + L.uL(), d + L.uLT(), d + L.uK(), d + L.dL(), d + L.A(),
-                                 d + L.Qw(), d + L.a(), d + L.lx(), nullptr, d + L.Psi(), d + L.k()};
-        // P after stage s of the down pass is the message of stage s - 1 (not
-        // asked for at s = 0)
-        return Stage<double>{s > 0 ? slot(s - 1) + L.P() : nullptr, nullptr, d + L.dL(), d + L.dLT(), d + L.K(), nullptr,
-                             d + L.A(), d + L.Qw(), d + L.a(), d + L.lx(), nullptr,
-                             s > 0 ? slot(s - 1) + L.Psi() : nullptr, d + L.k()};
-    }
-};
-
 __device__ __forceinline__ TreeItem load_item(const TreeItem *tab, int i) {
     const TreeItem r = tab[i];
     TreeItem u;
@@ -290,7 +270,7 @@ __global__ void __launch_bounds__(64 * W) ks_tree(GroupArgs g) {
                     q.P = nullptr;
                     return q;
                 };
-                forward<NM, NM, W, EX, double>(S, n, n, count, fst, false, [&](int s) { return slot(it.first + s) + SL.xh(); },
+                forward<NM, NM, W, EX, EX, double>(S, n, n, n, count, fst, false, [&](int s) { return slot(it.first + s) + SL.xh(); },
                                            none, none);
                 if (ownr) term[SL.xh() + ir] = S.x[ir];
                 // terminal costate of child s, lam_{s+1} = P_{s+1} x_{s+1} -
@@ -319,7 +299,7 @@ __global__ void __launch_bounds__(64 * W) ks_tree(GroupArgs g) {
             }
             __syncthreads();
             const SlotStages st{slots, it.first, n, true};
-            forward<NM, NM, W, EX, double>(S, n, n, count, st, !last, [&](int s) { return slot(it.first + s) + SL.xh(); },
+            forward<NM, NM, W, EX, EX, double>(S, n, n, n, count, st, !last, [&](int s) { return slot(it.first + s) + SL.xh(); },
                                        [](int) { return (double *)nullptr; },
                                        [&](int s) { return s > 0 ? slot(it.first + s - 1) + SL.lamN() : (double *)nullptr; });
             // the last child ends where the item does: at lam_N, or for the
@@ -372,8 +352,14 @@ hipError_t leaf(const GroupArgs &g, bool down, hipStream_t st) {
     return leaf_of<64, 64, 8, TR>(g, down, st);
 }
 template <int NM, int MM, int W>
-hipError_t fwd_of(const GroupArgs &g, int, hipStream_t st) {
-    hipLaunchKernelGGL((ks_leaf_fwd<NM, MM, W>), dim3(g.nleaves), dim3(64 * W), 0, st, g);
+hipError_t fwd_of(const GroupArgs &g, hipStream_t st) {
+    const dim3 grid(g.nleaves), block(64 * W);
+    if (g.nx != NM || g.nu != MM)
+        hipLaunchKernelGGL((ks_leaf_fwd<NM, MM, W, false, false>), grid, block, 0, st, g);
+    else if (g.data_nu)
+        hipLaunchKernelGGL((ks_leaf_fwd<NM, MM, W, true, true>), grid, block, 0, st, g);
+    else
+        hipLaunchKernelGGL((ks_leaf_fwd<NM, MM, W, true, false>), grid, block, 0, st, g);
     return hipGetLastError();
 }
 template <int NM, int W>
@@ -391,11 +377,10 @@ hipError_t sweep_leaf(const GroupArgs &g, bool fp32, bool down, hipStream_t st) 
     return fp32 ? vs::leaf<float>(g, down, st) : vs::leaf<double>(g, down, st);
 }
 
-Launcher leaf_forward(int nx, int nu) {
-    if (nx == 16 && nu == 16) return &vs::fwd_of<16, 16, 1>;
-    if (nx == 32 && nu == 16) return &vs::fwd_of<32, 16, 4>;
-    if (nx == 32 && nu == 32) return &vs::fwd_of<32, 32, 4>;
-    return nullptr;
+hipError_t fused_leaf_forward(const GroupArgs &g, hipStream_t st) {
+    if (g.nx <= 16 && g.nu <= 16) return vs::fwd_of<16, 16, 1>(g, st);
+    if (g.nu <= 16) return vs::fwd_of<32, 16, 4>(g, st);
+    return vs::fwd_of<32, 32, 4>(g, st);
 }
 
 hipError_t sweep_tree(const GroupArgs &g, int grid, hipStream_t st) {

@@ -64,9 +64,11 @@ struct Mat {
             m[q] = (i < outs && k < ins) ? gl(M + (uint32_t)(k * ld + i)) : U(0);
         }
     }
+    // FULL: outs and ins fill the matrix (else guarded loads, in the same order)
+    template <bool FULL = PAIR>
     __device__ __forceinline__ void load_row(const U *M, int ld, int outs, int ins) {
         const int i = out_row(), p = lane() % LPO;
-        if constexpr (PR) {
+        if constexpr (PR && FULL) {
             typedef U two __attribute__((ext_vector_type(2), aligned(sizeof(U))));   // element alignment only
 #pragma unroll
             for (int q = 0; q < NQ / 2; ++q) {
@@ -78,7 +80,7 @@ struct Mat {
         }
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            const int k = p + LPO * q;
+            const int k = PR ? 2 * p + 2 * LPO * (q / 2) + (q & 1) : p + LPO * q;
             m[q] = (i < outs && k < ins) ? gl(M + (uint32_t)(i * ld + k)) : U(0);
         }
     }
@@ -277,10 +279,12 @@ __device__ __forceinline__ double sum_c(const double *c, int64_t sc, int count) 
 
 // Forward sweep from the x in S.x (zero-padded); lterms: with the lam_N in
 // S.lamN.  P may be null (no lam).  xo, wo, lo: where x_s, w_s and lam_s of
-// stage s go (null: not wanted).  Ends with x of the end in S.x.
-template <int NM, int MM, int W, bool EX, class TR, class St, class Xo, class Wo, class Lo>
-__device__ __forceinline__ void forward(Smem<NM, MM, W> &S, int n, int m, int count, St st, bool lterms, Xo xo, Wo wo,
-                                        Lo lo) {
+// stage s go (null: not wanted).  The records have m inputs, the problem data
+// and w md <= m (the others are padding, and zero).  Ends with x of the end in
+// S.x.
+template <int NM, int MM, int W, bool EX, bool EXD, class TR, class St, class Xo, class Wo, class Lo>
+__device__ __forceinline__ void forward(Smem<NM, MM, W> &S, int n, int m, int md, int count, St st, bool lterms, Xo xo,
+                                        Wo wo, Lo lo) {
     typedef Mat<TR, NM, NM, W, EX> MNN;
     typedef Mat<double, NM, NM, W, EX> MA;
     typedef Mat<double, NM, MM, W, EX> MB;
@@ -305,7 +309,7 @@ __device__ __forceinline__ void forward(Smem<NM, MM, W> &S, int n, int m, int co
     };
     Stage<TR> cur = st(0);
     load1(cur);
-    mB.load_row(cur.B, m, n, m);
+    mB.template load_row<EXD>(cur.B, md, n, md);
     for (int e = threadIdx.x; e < MM; e += 64 * W) S.gw[e] = 0.0;
     wsync();
     for (int s = 0; s < count; ++s) {
@@ -328,13 +332,13 @@ __device__ __forceinline__ void forward(Smem<NM, MM, W> &S, int n, int m, int co
             if (px) gs(px + i, xi);
             if (pl) gs(pl + i, lam);
         }
-        if (ownm) {
+        if (ownm && jj < md) {
             double *pw = wo(s);
             if (pw) gs(pw + jj, w);
         }
         wsync();
         const double xn = y + MB::sum_row(mB.part_row(S.gw));
-        if (more) mB.load_row(nxt.B, m, n, m);
+        if (more) mB.template load_row<EXD>(nxt.B, md, n, md);
         if (own) S.x[i] = xn;
         cur = nxt;
         wsync();
@@ -364,6 +368,28 @@ struct FusedStages {
         double *P = r + m * n + m, *V = P + n * n + n;
         return Stage<double>{P, V, nullptr, nullptr, r, V + n * n, p.A + t * p.sA, p.B + t * p.sB,
                              p.a ? p.a + t * p.sa : nullptr, nullptr, nullptr, P + n * n, r + m * n};
+    }
+};
+
+// Master stages read from their slots; up: the factors of the up pass
+// (P and V after the stage are those records), else of the down pass, whose P
+// is the message P_{s+1} kept in the stage's own slot.
+struct SlotStages {
+    double *slots;
+    int first, n;
+    bool up;
+    __device__ double *slot(int s) const { return slots + (int64_t)(first + s) * SlotLayout{n}.size(); }
+    __device__ Stage<double> operator()(int s) const {
+        const SlotLayout L{n};
+        double *d = slot(s);
+        if (up)
+            return Stage<double>{d + L.uP(), d + L.uV(), d + L.uL(), d + L.uLT(), d + L.uK(), d + L.dL(), d + L.A(),
+                                 d + L.Qw(), d + L.a(), d + L.lx(), nullptr, d + L.Psi(), d + L.k()};
+        // P after stage s of the down pass is the message of stage s - 1 (not
+        // asked for at s = 0)
+        return Stage<double>{s > 0 ? slot(s - 1) + L.P() : nullptr, nullptr, d + L.dL(), d + L.dLT(), d + L.K(), nullptr,
+                             d + L.A(), d + L.Qw(), d + L.a(), d + L.lx(), nullptr,
+                             s > 0 ? slot(s - 1) + L.Psi() : nullptr, d + L.k()};
     }
 };
 

@@ -60,3 +60,34 @@ def test_prefetched_sweeps_at_short_lengths(nx, nu, N, Ns, b, precision):
         assert kkt.rel_error(sol, ref) <= TOL
         assert abs(sol["obj"] - ref["obj"]) <= 1e-9 * max(1.0, abs(ref["obj"]))
         bt.close()
+
+
+def test_noalloc_takes_the_plans_it_counts_in():
+    """Shapes below the full tiles keep V and L_t in their fused leaf records,
+    which rs_batch_solve_noalloc does not count: a plan whose workspace is
+    beyond the 64 MiB only by them is taken (and gives the workspace call's
+    results bit for bit), one beyond it without them is refused."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1510_03110_amd import rs
+    prob = W.g1_invariant(8, 4, 40000, seed=3)
+    bt = rs.Batch({k: [prob[k]] for k in prob}, Ns=32, branch=8)
+    assert bt.work_bytes > rs.RS_NOALLOC_SCRATCH_BYTES
+    bt.solve()
+    torch.cuda.synchronize()
+    assert bt.status()[0].tolist() == [0, -1]
+    ref = bt.x[0].clone(), bt.w[0].clone(), bt.lam[0].clone(), bt.obj.clone()
+    for t in (bt.x[0], bt.w[0], bt.lam[0], bt.obj):
+        t.zero_()
+    rs.rs_batch_solve_noalloc(bt.plan, bt.probs, bt.stream_ptr(), bt.info.data_ptr())
+    torch.cuda.synchronize()
+    assert bt.status()[0].tolist() == [0, -1]
+    for a, b in zip(ref, (bt.x[0], bt.w[0], bt.lam[0], bt.obj)):
+        assert torch.equal(a, b)
+    bt.close()
+    plan = rs.rs_plan_create([(8, 4, 70000)], Ns=32, branch=8)
+    with pytest.raises(rs.RsError) as e:
+        rs.rs_batch_solve_noalloc(plan, (rs.rs_problem * 1)())
+    assert e.value.status == rs.RS_ERR_NOMEM
+    rs.rs_plan_destroy(plan)
