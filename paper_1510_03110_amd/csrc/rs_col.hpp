@@ -89,15 +89,18 @@ __device__ __forceinline__ T ldR(const Ln<T> &L, const T *M, int ti, int kt, int
 
 // Keeps the operand reads of one tile product from being moved across the
 // products before it: the compiler would otherwise issue the reads of a whole
-// phase at once and spill.
-__device__ __forceinline__ void tile_fence() { __builtin_amdgcn_sched_barrier(0); }
+// phase at once and spill.  Up to two tiles a side there is room for them.
+template <int PITCH>
+__device__ __forceinline__ void tile_fence() {
+    if (PITCH > 32) __builtin_amdgcn_sched_barrier(0);
+}
 
 // acc += sum over inner tiles k0 <= kt < KT of (N view of M)(ti, kt) b[kt], NS
 // slices each.
 // The next inner tile's operands are read while this one's are multiplied.
 template <int PT, int KT, int NS, class T>
 __device__ __forceinline__ v4_t<T> mulN(const Ln<T> &L, v4_t<T> acc, const T *M, int ti, const v4_t<T> *b, int k0 = 0) {
-    tile_fence();
+    tile_fence<(PT > 16 * KT ? PT : 16 * KT)>();
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt) {
         if (kt < k0) continue;
@@ -107,7 +110,7 @@ __device__ __forceinline__ v4_t<T> mulN(const Ln<T> &L, v4_t<T> acc, const T *M,
 #pragma unroll
         for (int r = 0; r < NS; ++r) acc = MT<T>::mfma(a[r], b[kt][r], acc);
     }
-    tile_fence();
+    tile_fence<(PT > 16 * KT ? PT : 16 * KT)>();
     return acc;
 }
 
@@ -133,30 +136,54 @@ __device__ __forceinline__ void put_sym(const Ln<T> &L, T *M, int ti, int tj, v4
 
 __device__ __forceinline__ double rcp_est(double d) { return __builtin_amdgcn_rcp(d); }
 __device__ __forceinline__ float rcp_est(float d) { return __builtin_amdgcn_rcpf(d); }
+// Positive and finite.
+__device__ __forceinline__ bool usable_pivot(double d) { return __builtin_amdgcn_class(d, 0x180); }
+__device__ __forceinline__ bool usable_pivot(float d) { return __builtin_amdgcn_classf(d, 0x180); }
+
+// Value of lane 16 H + i in the lanes i of all four rows of 16: two swaps
+// between rows (the pairs of rows, then the halves of the wave).
+template <int H>
+__device__ __forceinline__ unsigned row_to_all(unsigned v) {
+    const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    const unsigned u = p[H & 1];
+    const auto q = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return q[H >> 1];
+}
+template <int H>
+__device__ __forceinline__ double row_to_all(double v) {
+    return __hiloint2double((int)row_to_all<H>((unsigned)__double2hiint(v)),
+                            (int)row_to_all<H>((unsigned)__double2loint(v)));
+}
+template <int H>
+__device__ __forceinline__ float row_to_all(float v) {
+    return __uint_as_float(row_to_all<H>(__float_as_uint(v)));
+}
 
 // Step K of the in-place elimination below: column K of the block becomes
-// column K of L_u^{-1}.  r = 1 / d_K comes from the hardware estimate and two
-// Newton steps; the square roots are left to the end.
+// column K of L_u^{-1}.  The lanes that hold column K (row group H = K / 4)
+// form the multipliers from the pivot, which reaches them by DPP, and hand
+// them to the other groups by row swaps, so that no step waits for LDS or for
+// a scalar register.  1 / d_K comes from the hardware estimate and two Newton
+// steps; the square roots are left to the end.
 template <int K, class T>
 __device__ __forceinline__ void elim_step(T (&a)[4], int i, int h, T &piv, int &fail, int steps) {
     if constexpr (K % 4 == 0 && K > 0) {
         if (K >= steps) return;                       // padding: unit pivots, nothing to eliminate
     }
-    constexpr int kh = K >> 2, kc = K & 3;
-    T d = bcast_lane(a[kc], 16 * kh + K);            // pivot d_K (wave-uniform)
-    const T f = __shfl(a[kc], 16 * kh + i, 64);       // entry (i, K) of this lane's row
-    const bool bad = !(d > T(0)) || !__builtin_isfinite(d);
-    fail |= bad ? 1 : 0;
-    d = bad ? T(1) : d;
+    constexpr int H = K >> 2, kc = K & 3;
+    T d = mf::row_bcast<K>(a[kc]);                    // the pivot, in row group H
+    const bool ok = usable_pivot(d);
+    fail |= (!ok && h == H) ? 1 : 0;
+    d = ok ? d : T(1);
     T r = rcp_est(d);
     r = r + r * (T(1) - d * r);
     r = r + r * (T(1) - d * r);
-    if (i == K) piv = d;
-    const T m = i > K ? f * r : T(0);                 // rows above the pivot keep their values
+    if (h == H && i == K) piv = d;
+    const T m = row_to_all<H>(i > K ? a[kc] * r : T(0));    // rows above the pivot keep their values
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         const T t = a[c] - m * mf::row_bcast<K>(a[c]);
-        a[c] = (c == kc && h == kh && i > K) ? -m : t;
+        a[c] = (c == kc && h == H && i > K) ? -m : t;
     }
     if constexpr (K + 1 < 16) elim_step<K + 1>(a, i, h, piv, fail, steps);
 }
@@ -167,8 +194,10 @@ __device__ __forceinline__ void elim_step(T (&a)[4], int i, int h, T &piv, int &
 // block into D L_u' on and above the diagonal and L_u^{-1} below it, with
 // G = L_u D L_u', so that L^{-1} = D^{-1/2} L_u^{-1}: the same factorization
 // and forward substitution as the textbook sweep, in the 256 elements of the
-// block itself.  `steps`: rows that are not padding.  (On [G | I], twice the
-// elements and a square root in every step, a block took 5 to 6 k cycles.)
+// block itself.  `steps`: rows that are not padding.  (On [G | I], with twice
+// the elements, a square root in every step and the pivot through scalar
+// registers, a block took 5 to 6 k cycles; in place with the column through
+// LDS 4.2 k.)
 template <int PU, class T>
 __device__ __forceinline__ int chol_block(T *G, int kb, int steps) {
     int l = lane();
@@ -180,6 +209,7 @@ __device__ __forceinline__ int chol_block(T *G, int kb, int steps) {
     int fail = 0;
     T piv = T(1);
     elim_step<0>(a, i, h, piv, fail, steps);
+    piv = __shfl(piv, 16 * (i >> 2) + i, 64);        // row i's pivot was in row group i / 4
     T is = mf::rsq_est(piv);
     is = is * (T(1.5) - T(0.5) * piv * is * is);
     is = is * (T(1.5) - T(0.5) * piv * is * is);
@@ -188,7 +218,7 @@ __device__ __forceinline__ int chol_block(T *G, int kb, int steps) {
         const int j = 4 * h + c;
         G[at<PU>(16 * kb + i, 16 * kb + j)] = j < i ? a[c] * is : j == i ? is : T(0);
     }
-    return fail;
+    return __any(fail) ? 1 : 0;
 }
 
 // Cholesky factorization and inverse of the NB x NB blocks of G (lower part
@@ -391,7 +421,7 @@ __device__ __forceinline__ void apply_Linv(const Ln<T> &L, const T *G, v4_t<T> *
                                            const double *gw = nullptr, double *zv = nullptr, double *zz = nullptr) {
 #pragma unroll
     for (int ti = NUT - 1; ti >= 0; --ti) {
-        tile_fence();
+        tile_fence<RX>();
         v4_t<T> acc = zero4<T>();
         double z = 0.0;
 #pragma unroll
@@ -421,7 +451,7 @@ __device__ __forceinline__ void store_feedback(const Ln<T> &L, const T *G, const
                                                const double *zv = nullptr, double *k = nullptr) {
 #pragma unroll
     for (int ti = 0; ti < NUT; ++ti) {
-        tile_fence();
+        tile_fence<RU>();
         v4_t<T> acc = zero4<T>();
         double s = 0.0;
 #pragma unroll
@@ -451,8 +481,8 @@ struct QTiles {
 };
 
 // Stage loop of the waves that own a column block of A (w < NXT).
-template <bool RED, bool EX, bool EXD, bool VEC, int KEEP, class T, int NXT, int NUT, int SX, int SU, class Get, class Pre, class RecOf>
-__device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int m, int md, Get get, int count, int32_t *info, int inst,
+template <bool RED, bool EX, bool EXD, bool VEC, int KEEP, class T, int NXT, int NUT, int SX, int SU, class Pre, class RecOf>
+__device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int m, int md, StageWalk wk, int count, int32_t *info, int inst,
                                        int stage_base, int fail_code, Pre pre, RecOf rec, Vec &y) {
     using SM = Smem<T, NXT, NUT, SX, SU>;
     using QT = QTiles<NXT, NUT>;
@@ -482,16 +512,14 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
         if constexpr (VEC)
             q.lx = (src.lx && (EX || 16 * j + L.c < n)) ? gload(src.lx + (uint32_t)(16 * j + L.c)) : 0.0;
     };
-    StageSrc src = get(count - 1);
     if (QT::AHEAD) {
         const Ln<T> L;
-        load_g(L, src);
-        load_f(L, src);
+        load_g(L, wk.s);
+        load_f(L, wk.s);
     }
     for (int s = count - 1; s >= 0; --s) {
         const Ln<T> L;
-        const StageSrc nxt = s > 0 ? get(s - 1) : StageSrc{};
-        if (!QT::AHEAD) load_g(L, src);
+        if (!QT::AHEAD) load_g(L, wk.s);
         double pa = 0.0;
         if constexpr (VEC) {
             // ---- pt = Psi - P a, cbar += 1/2 a'Pa - Psi'a
@@ -522,7 +550,8 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
         // ---- W, F, H', g_x, g_w (the last wave of the workgroup factors G)
         v4_t<T> R1[NXT], R2[NUT];
         double gx = 0.0;
-        if (!QT::AHEAD) load_f(L, src);
+        if (!QT::AHEAD) load_f(L, wk.s);
+        if (s > 0) wk.back();           // the next stage
         {
             v4_t<T> a[NXT], wa[NXT];
 #pragma unroll
@@ -545,7 +574,7 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
                     if (L.q == 0) S.gw[16 * j + L.c] = g;
                 }
             }
-            if (QT::AHEAD && s > 0) load_g(L, nxt);
+            if (QT::AHEAD && s > 0) load_g(L, wk.s);
 #pragma unroll
             for (int ti = 0; ti < NXT; ++ti) wa[ti] = mulN<RX, NXT, SX>(L, zero4<T>(), S.P, ti, a);
 #pragma unroll
@@ -554,7 +583,7 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
             for (int ti = 0; ti < NXT; ++ti)
                 if (ti >= j) R1[ti] = mulN<RX, NXT, SX>(L, as_t<T>(q.f[ti]), S.A, ti, wa);
         }
-        if (QT::AHEAD && s > 0) load_f(L, nxt);
+        if (QT::AHEAD && s > 0) load_f(L, wk.s);
         if (NXT == 1) {
             // the record of P_{s+1}, still in LDS (the other wave factors G)
             pre(s, 0, 64);
@@ -563,7 +592,6 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
                 if (KEEP == KEEP_ALL || p) copy_P(S, p, n, 0, 64);
             }
         }
-        src = nxt;
         lds_sync();
         if (threadIdx.x == 0 && S.bad) {
             record_failure(info, inst, fail_code, stage_base < 0 ? -1 : stage_base + s);
@@ -608,8 +636,8 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
 // Stage loop of the waves NXT + j: A and B of the next stage are loaded into
 // their registers, the last of them factors G, and for Alg. 4 they own the
 // column blocks of V and Q_w_hat.
-template <bool RED, bool EX, bool EXD, bool VEC, int KEEP, class T, int NXT, int NUT, int SX, int SU, class Get, class Pre, class RecOf>
-__device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT> &C, int n, int m, int md, Get get, int count, Pre pre,
+template <bool RED, bool EX, bool EXD, bool VEC, int KEEP, class T, int NXT, int NUT, int SX, int SU, class Pre, class RecOf>
+__device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT> &C, int n, int m, int md, StageWalk wk, int count, Pre pre,
                                        RecOf rec, Vec &y) {
     using SM = Smem<T, NXT, NUT, SX, SU>;
     constexpr int RX = SM::RX, RU = SM::RU, NTV = 64 * NXT;
@@ -659,7 +687,10 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
     }
     for (int s = count - 1; s >= 0; --s) {
         const Ln<T> L;
-        if (s > 0) fetch(get(s - 1));
+        if (s > 0) {
+            wk.back();
+            fetch(wk.s);
+        }
         v4_t<T> R1[NXT], R2[NUT];
         if (RED) {
             if constexpr (VEC) {
@@ -726,7 +757,7 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
 
 // Backward pass over `count` >= 1 stages (local s = count-1 .. 0).  P_{count}
 // in S.P (written by the caller; the pass starts with a barrier); RED: Alg. 4
-// from V = I, Q_w_hat = 0, result in C.  get(s): stage data; pre(s, t0, t1)
+// from V = I, Q_w_hat = 0, result in C.  wk: the data of stage count-1; pre(s, t0, t1)
 // is called by the threads [t0, t1) before stage s and may read P_{s+1} from
 // S.P; rec(s): where its factors go, with n and m their sizes (EX: n = 16 NXT
 // and m = 16 NUT exactly).  The problem data have md <= m inputs (EXD: 16 NUT),
@@ -734,9 +765,9 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
 // VEC: with the right-hand side, y holding Psi_{count} on entry.
 // The two kinds of waves run loops of their own (with the same barriers), so
 // that neither carries the other's registers.
-template <bool RED, bool EX, bool EXD, bool VEC, int KEEP, class T, int NXT, int NUT, int SX, int SU, class Get,
-          class Pre, class RecOf>
-__device__ __forceinline__ void pass(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT> &C, int n_, int m_, int md_, Get get, int count,
+template <bool RED, bool EX, bool EXD, bool VEC, int KEEP, class T, int NXT, int NUT, int SX, int SU, class Pre,
+          class RecOf>
+__device__ __forceinline__ void pass(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT> &C, int n_, int m_, int md_, StageWalk wk, int count,
                                      int32_t *info, int inst, int stage_base, int fail_code, Pre pre, RecOf rec, Vec &y) {
     using SM = Smem<T, NXT, NUT, SX, SU>;
     constexpr int RX = SM::RX, RU = SM::RU, NTH = SM::NTH;
@@ -748,7 +779,7 @@ __device__ __forceinline__ void pass(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT> 
     count = uni(count);
     if (tid == 0) S.bad = 0;
     {
-        const StageSrc src = get(count - 1);
+        const StageSrc &src = wk.s;
 #pragma unroll 4
         for (int e = tid; e < RX * RX; e += NTH) {
             const int i = e / RX, k = e % RX;
@@ -763,9 +794,9 @@ __device__ __forceinline__ void pass(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT> 
     }
     lds_sync();
     if (wave() < NXT)
-        loop_P<RED, EX, EXD, VEC, KEEP>(S, n, m, md, get, count, info, inst, stage_base, fail_code, pre, rec, y);
+        loop_P<RED, EX, EXD, VEC, KEEP>(S, n, m, md, wk, count, info, inst, stage_base, fail_code, pre, rec, y);
     else
-        loop_V<RED, EX, EXD, VEC, KEEP>(S, C, n, m, md, get, count, pre, rec, y);
+        loop_V<RED, EX, EXD, VEC, KEEP>(S, C, n, m, md, wk, count, pre, rec, y);
     lds_sync();
     {
         T *p = rec(0).P;

@@ -148,6 +148,33 @@ __device__ __forceinline__ StageSrc slot_stage(const double *slot, int n, const 
     return s;
 }
 
+// The stages of a pass from its last one backwards: one subtraction per
+// pointer and stage (formed from the stage index, the addresses cost some
+// hundred scalar instructions a stage in every wave, on the chain of the small
+// shapes).
+struct StageWalk {
+    StageSrc s;
+    int64_t dQx, dQw, dQxw, dA, dB, da, dlx, dlw;     // elements per stage (0 for absent arrays)
+    __device__ __forceinline__ void back() {
+        s.Qx -= dQx;
+        s.Qw -= dQw;
+        s.Qxw -= dQxw;
+        s.A -= dA;
+        s.B -= dB;
+        s.a -= da;
+        s.lx -= dlx;
+        s.lw -= dlw;
+    }
+};
+__device__ __forceinline__ StageWalk prob_walk(const DevProb &p, int last) {
+    return StageWalk{prob_stage(p, last), p.sQx, p.sQw, p.Qxw ? p.sQxw : 0, p.sA, p.sB, p.a ? p.sa : 0,
+                     p.lx ? p.slx : 0, p.lw ? p.slw : 0};
+}
+__device__ __forceinline__ StageWalk slot_walk(const double *last, int n, const double *ident) {
+    const int64_t d = SlotLayout{n}.size();
+    return StageWalk{slot_stage(last, n, ident), d, ident ? 0 : d, 0, d, d, d, d, 0};
+}
+
 // Rank-revealing form of a reduced subproblem (Sec. 4.2, eqs. Bh_def and
 // Gh_Hh_def).  The reduction (Alg. 4) leaves M = S Qbar^{-1} S' in `M`
 // (n x n, row-major, positive semidefinite of rank n_uo = rank(S')).  This

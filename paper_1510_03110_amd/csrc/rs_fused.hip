@@ -33,7 +33,7 @@ namespace cw {
 enum { FULL = 0, DATA = 1, ANY = 2 };
 
 template <int NXT, int NUT, int SZ, int SX = 4, int SU = 4>
-__global__ void __launch_bounds__(128 * NXT, NXT == 1 ? 4 : 3) kf_leaf(GroupArgs g, int down) {
+__global__ void __launch_bounds__(128 * NXT, NXT == 1 ? 4 : NUT == 1 ? 3 : 2) kf_leaf(GroupArgs g, int down) {
     using SM = Smem<double, NXT, NUT, SX, SU>;
     constexpr int W = 2 * NXT;
     constexpr bool EX = SZ != ANY, EXD = SZ == FULL;
@@ -47,7 +47,7 @@ __global__ void __launch_bounds__(128 * NXT, NXT == 1 ? 4 : 3) kf_leaf(GroupArgs
     double *out = g.slots + (int64_t)it.slot * SL.size();
     double *base = static_cast<double *>(g.leaf_scratch) + it.scratch;
     const int len = leaf_rec_len(n, m);
-    auto get = [&](int s) { return prob_stage(p, it.t0 + s); };
+    const StageWalk wk = prob_walk(p, it.t0 + it.len - 1);
     auto no_pre = [](int, int, int) {};
     auto rec = [&](int s) {
         double *K = base + (int64_t)s * len, *P = K + m * n + m, *V = P + n * n + n;
@@ -60,7 +60,7 @@ __global__ void __launch_bounds__(128 * NXT, NXT == 1 ? 4 : 3) kf_leaf(GroupArgs
     Vec y{};
     if (!(it.flags & LEAF_LAST)) {
         set_P(S, n, [](int) { return 0.0; });
-        pass<true, EX, EXD, true, KEEP_ALL>(S, C, n, m, md, get, it.len, g.info, it.inst, it.t0, 2, no_pre, rec, y);
+        pass<true, EX, EXD, true, KEEP_ALL>(S, C, n, m, md, wk, it.len, g.info, it.inst, it.t0, 2, no_pre, rec, y);
         store_V_transposed<SX>(C, out + SL.A(), n);
         copy_P(S, out + SL.Qx(), n);
         if (!g.ident) store_Q<SX>(C, out + SL.Qw(), n);
@@ -68,7 +68,7 @@ __global__ void __launch_bounds__(128 * NXT, NXT == 1 ? 4 : 3) kf_leaf(GroupArgs
     } else {
         set_P(S, n, [&](int e) { return p.QxN[e]; });
         if (w < NXT && col < n) y.psi = p.lN ? -p.lN[col] : 0.0;
-        pass<false, EX, EXD, true, KEEP_ALL>(S, C, n, m, md, get, it.len, g.info, it.inst, it.t0, 2, no_pre, rec, y);
+        pass<false, EX, EXD, true, KEEP_ALL>(S, C, n, m, md, wk, it.len, g.info, it.inst, it.t0, 2, no_pre, rec, y);
         if (!down) copy_P(S, out + SL.Qx(), n);
     }
     const double c = total(S, y.cb + vs::sum_c(p.c ? p.c + (int64_t)it.t0 * p.sc : nullptr, p.sc, it.len)) +
@@ -133,7 +133,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kf_tree(GroupArgs g) {
         if (idx >= g.nitems) break;
         const TreeItem it = load_item_u(g.items, idx);
         wait_deps(g, it);
-        auto get = [&](int s) { return slot_stage(slot(it.first + s), n, g.ident); };
+        const StageWalk wk = slot_walk(slot(it.first + it.count - 1), n, g.ident);
         auto no_pre = [](int, int, int) {};
         auto c_sum = [&] { return vs::sum_c(slot(it.first) + SL.c(), SL.size(), it.count); };
         const Ln<double> L;
@@ -147,7 +147,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kf_tree(GroupArgs g) {
             // excluded instance: only its completion flag is published
         } else if (it.kind == ITEM_UP) {
             set_P(S, n, [](int) { return 0.0; });
-            pass<true, EX, EX, true, KEEP_GIVEN>(S, C, n, n, n, get, it.count, g.info, it.inst, -1, 3, no_pre, [&](int s) {
+            pass<true, EX, EX, true, KEEP_GIVEN>(S, C, n, n, n, wk, it.count, g.info, it.inst, -1, 3, no_pre, [&](int s) {
                 double *d = slot(it.first + s);
                 return Rec<double>{d + SL.uP(), d + SL.uK(), d + SL.uV(), d + SL.dL(), nullptr, nullptr, d + SL.Psi(),
                                    d + SL.k()};
@@ -176,7 +176,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kf_tree(GroupArgs g) {
                 copy_P(S, d + SL.P(), n);
                 if (own && w < NXT) d[SL.Psi() + col] = y.psi;
             }
-            pass<false, EX, EX, true, KEEP_GIVEN>(S, C, n, n, n, get, it.count, g.info, it.inst, -1, 3, no_pre, [&](int s) {
+            pass<false, EX, EX, true, KEEP_GIVEN>(S, C, n, n, n, wk, it.count, g.info, it.inst, -1, 3, no_pre, [&](int s) {
                 double *d = slot(it.first + s);
                 if (!top)
                     return Rec<double>{d + SL.uP(), d + SL.uK(), nullptr, nullptr, nullptr, nullptr, d + SL.Psi(),

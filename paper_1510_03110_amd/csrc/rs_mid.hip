@@ -44,13 +44,13 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_leaf(GroupArgs g, int down) {
     const DevProb p = load_prob(g.probs, it.inst);
     double *cache = (g.m1cache && it.m1 >= 0) ? g.m1cache + (int64_t)it.m1 * 3 * n * n : nullptr;
     T *base = reinterpret_cast<T *>(g.fstore) + g.rec_stage(it.scratch) * (int64_t)R.per_stage();
-    auto get = [&](int s) { return prob_stage(p, it.t0 + s); };
+    const StageWalk wk = prob_walk(p, it.t0 + it.len - 1);
     auto no_pre = [](int, int, int) {};
     Cols<T, NXT> C;
     Vec y{};
     if (!(it.flags & LEAF_LAST)) {
         set_P(S, n, [](int) { return 0.0; });
-        pass<true, EX, EX, false, KEEP_GIVEN>(S, C, n, m, m, get, it.len, g.info, it.inst, it.t0, 2, no_pre, [&](int s) {
+        pass<true, EX, EX, false, KEEP_GIVEN>(S, C, n, m, m, wk, it.len, g.info, it.inst, it.t0, 2, no_pre, [&](int s) {
             T *d = base + (int64_t)s * R.per_stage();
             return Rec<T>{d + R.P(), d + R.K(), d + R.V(), d + R.Lt(), d + R.L(), d + R.LT(), nullptr, nullptr};
         }, y);
@@ -69,7 +69,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_leaf(GroupArgs g, int down) {
     } else {
         if (down) base += R.up();
         set_P(S, n, [&](int e) { return p.QxN[e]; });
-        pass<false, EX, EX, false, KEEP_GIVEN>(S, C, n, m, m, get, it.len, g.info, it.inst, it.t0, 2, no_pre, [&](int s) {
+        pass<false, EX, EX, false, KEEP_GIVEN>(S, C, n, m, m, wk, it.len, g.info, it.inst, it.t0, 2, no_pre, [&](int s) {
             T *d = base + (int64_t)s * R.per_stage();
             return Rec<T>{d + R.P(), d + R.K(), nullptr, nullptr, d + R.L(), d + R.LT(), nullptr, nullptr};
         }, y);
@@ -95,14 +95,14 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_tree(GroupArgs g) {
         if (idx >= g.nitems) break;
         const TreeItem it = load_item_u(g.items, idx);
         wait_deps(g, it);
-        auto get = [&](int s) { return slot_stage(slot(it.first + s), n, g.ident); };
+        const StageWalk wk = slot_walk(slot(it.first + it.count - 1), n, g.ident);
         Cols<double, NXT> C;
         Vec y{};
         if (inst_skipped(g.probs, it.inst)) {
             // excluded instance: only its completion flag is published
         } else if (it.kind == ITEM_UP) {
             set_P(S, n, [](int) { return 0.0; });
-            pass<true, EX, EX, false, KEEP_GIVEN>(S, C, n, n, n, get, it.count, g.info, it.inst, -1, 3, [](int, int, int) {}, [&](int s) {
+            pass<true, EX, EX, false, KEEP_GIVEN>(S, C, n, n, n, wk, it.count, g.info, it.inst, -1, 3, [](int, int, int) {}, [&](int s) {
                 double *d = slot(it.first + s);
                 return Rec<double>{d + SL.uP(), d + SL.uK(), d + SL.uV(), g.superpose ? d + SL.dL() : nullptr,
                                    d + SL.uL(), d + SL.uLT(), nullptr, nullptr};
@@ -127,7 +127,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_tree(GroupArgs g) {
             double *term = it.last ? slot(it.term_slot) : nullptr;
             const double *P0 = term ? term + SL.Qx() : msg + SL.P();
             set_P(S, n, [&](int e) { return P0[e]; });
-            pass<false, EX, EX, false, KEEP_GIVEN>(S, C, n, n, n, get, it.count, g.info, it.inst, -1, 3,
+            pass<false, EX, EX, false, KEEP_GIVEN>(S, C, n, n, n, wk, it.count, g.info, it.inst, -1, 3,
                             [&](int s, int t0, int t1) {      // M2 for child s: P at the end of master stage s
                                 if (!upl) copy_P(S, slot(it.first + s) + SL.P(), n, t0, t1);
                             },
