@@ -159,33 +159,44 @@ __device__ __forceinline__ float row_to_all(float v) {
     return __uint_as_float(row_to_all<H>(__float_as_uint(v)));
 }
 
+// Value of lane N of this lane's row of 16 (every lane has a source: the old
+// value of the destination is not used).
+template <int N>
+__device__ __forceinline__ double row16(double v) {
+    return __longlong_as_double(__builtin_amdgcn_mov_dpp(__double_as_longlong(v), 0x150 + N, 0xF, 0xF, true));
+}
+template <int N>
+__device__ __forceinline__ float row16(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + N, 0xF, 0xF, true));
+}
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
 // Step K of the in-place elimination below: column K of the block becomes
 // column K of L_u^{-1}.  The lanes that hold column K (row group H = K / 4)
 // form the multipliers from the pivot, which reaches them by DPP, and hand
 // them to the other groups by row swaps, so that no step waits for LDS or for
-// a scalar register.  1 / d_K comes from the hardware estimate and two Newton
-// steps; the square roots are left to the end.
+// a scalar register.  a / d from the hardware's estimate r of 1 / d:
+// a r (1 + e + e^2) with e = 1 - d r (e^3 is below the rounding).  The pivots
+// stay on the diagonal: they are checked, and their square roots taken, at
+// the end.
 template <int K, class T>
-__device__ __forceinline__ void elim_step(T (&a)[4], int i, int h, T &piv, int &fail, int steps) {
+__device__ __forceinline__ void elim_step(T (&a)[4], int i, int h, int steps) {
     if constexpr (K % 4 == 0 && K > 0) {
         if (K >= steps) return;                       // padding: unit pivots, nothing to eliminate
     }
     constexpr int H = K >> 2, kc = K & 3;
-    T d = mf::row_bcast<K>(a[kc]);                    // the pivot, in row group H
-    const bool ok = usable_pivot(d);
-    fail |= (!ok && h == H) ? 1 : 0;
-    d = ok ? d : T(1);
-    T r = rcp_est(d);
-    r = r + r * (T(1) - d * r);
-    r = r + r * (T(1) - d * r);
-    if (h == H && i == K) piv = d;
-    const T m = row_to_all<H>(i > K ? a[kc] * r : T(0));    // rows above the pivot keep their values
+    T pr[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) pr[c] = row16<K>(a[c]);     // row K; pr[kc] in row group H: the pivot
+    const T r = rcp_est(pr[kc]), e = fma_t(-pr[kc], r, T(1)), f = -a[kc] * r;
+    const T nm = row_to_all<H>(i > K ? fma_t(f, fma_t(e, e, e), f) : T(0));    // rows above the pivot keep their values
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        const T t = a[c] - m * mf::row_bcast<K>(a[c]);
-        a[c] = (c == kc && h == H && i > K) ? -m : t;
+        const T t = fma_t(nm, pr[c], a[c]);
+        a[c] = (c == kc && h == H && i > K) ? nm : t;
     }
-    if constexpr (K + 1 < 16) elim_step<K + 1>(a, i, h, piv, fail, steps);
+    if constexpr (K + 1 < 16) elim_step<K + 1>(a, i, h, steps);
 }
 
 // Inverse Cholesky factor of the 16 x 16 diagonal block kb of G, in place
@@ -198,18 +209,21 @@ __device__ __forceinline__ void elim_step(T (&a)[4], int i, int h, T &piv, int &
 // the elements, a square root in every step and the pivot through scalar
 // registers, a block took 5 to 6 k cycles; in place with the column through
 // LDS 4.2 k.)
-template <int PU, class T>
+template <int PU, int GS = 1, class T>
 __device__ __forceinline__ int chol_block(T *G, int kb, int steps) {
     int l = lane();
     asm volatile("" : "+v"(l));          // lane constants are not kept across stages
     const int i = l & 15, h = l >> 4;
     T a[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) a[c] = G[at<PU>(16 * kb + i, 16 * kb + 4 * h + c)];
-    int fail = 0;
-    T piv = T(1);
-    elim_step<0>(a, i, h, piv, fail, steps);
-    piv = __shfl(piv, 16 * (i >> 2) + i, 64);        // row i's pivot was in row group i / 4
+    for (int c = 0; c < 4; ++c) {
+        a[c] = G[at<PU>(16 * kb + i, 16 * kb + 4 * h + c)];
+#pragma unroll
+        for (int g = 1; g < GS; ++g) a[c] += G[g * PU * PU + at<PU>(16 * kb + i, 16 * kb + 4 * h + c)];
+    }
+    elim_step<0>(a, i, h, steps);
+    const T p01 = (i & 1) ? a[1] : a[0], p23 = (i & 1) ? a[3] : a[2];
+    const T piv = __shfl((i & 2) ? p23 : p01, 16 * (i >> 2) + i, 64);        // row i's pivot, from row group i / 4
     T is = mf::rsq_est(piv);
     is = is * (T(1.5) - T(0.5) * piv * is * is);
     is = is * (T(1.5) - T(0.5) * piv * is * is);
@@ -218,7 +232,7 @@ __device__ __forceinline__ int chol_block(T *G, int kb, int steps) {
         const int j = 4 * h + c;
         G[at<PU>(16 * kb + i, 16 * kb + j)] = j < i ? a[c] * is : j == i ? is : T(0);
     }
-    return __any(fail) ? 1 : 0;
+    return __any(i < steps && !usable_pivot(piv)) ? 1 : 0;
 }
 
 // Cholesky factorization and inverse of the NB x NB blocks of G (lower part
@@ -227,14 +241,25 @@ __device__ __forceinline__ int chol_block(T *G, int kb, int steps) {
 // ones with a zero upper half), the upper ones the off-diagonal blocks of L'.
 // Right-looking over 16-wide blocks: L_kk^{-1}, L_ik' = L_kk^{-1} G_ik',
 // G_ij -= L_ik L_jk'; then block row by block row of the inverse,
-// X_ij = -X_ii sum_k L_ik X_kj.  Returns nonzero if a pivot failed.
-template <class T, int NB>
+// X_ij = -X_ii sum_k L_ik X_kj.  Returns nonzero if a pivot failed.  GS: G is
+// the sum of so many matrices, one after the other.
+template <class T, int NB, int GS>
 __device__ __forceinline__ int chol_inv(const Ln<T> &L, T *G, int m) {
     constexpr int PU = 16 * NB;
     int fail = 0;
+    if constexpr (NB > 1 && GS > 1) {
+#pragma unroll 4
+        for (int e = lane(); e < PU * PU; e += 64) {
+            T v = G[e];
+#pragma unroll
+            for (int g = 1; g < GS; ++g) v += G[g * PU * PU + e];
+            G[e] = v;
+        }
+        wave_fence();
+    }
 #pragma unroll
     for (int kb = 0; kb < NB; ++kb) {
-        fail |= chol_block<PU>(G, kb, m - 16 * kb);
+        fail |= chol_block<PU, NB == 1 ? GS : 1>(G, kb, m - 16 * kb);
         if constexpr (NB == 1) return fail;
         wave_fence();
         // L_ik' into the upper block (k, i)
@@ -300,7 +325,11 @@ struct Smem {
     static constexpr int RX = 16 * NXT, RU = 16 * NUT, NTH = 128 * NXT;
     static constexpr size_t apart = sizeof(T) * (2 * RX * RX + RX * RU + RU * RU + 2 * RU * RX);
     static constexpr bool OVER = apart > 159 * 1024;
-    T P[RX * RX], A[RX * RX], B[RX * RU], G[RU * RU];
+    // Waves per column block of G (each takes NUT of the inner tiles of B'W_B
+    // where fewer than half of the owners of A's columns would have one).
+    static constexpr int GS = (NUT < NXT && NXT % NUT == 0) ? NXT / NUT : 1;
+    static constexpr int WT = GS > 1 ? NUT : NXT;       // row tiles of W_B per wave
+    T P[RX * RX], A[RX * RX], B[RX * RU], G[GS * RU * RU];
     T YX[OVER ? 1 : 2 * RU * RX];
     double av[RX], pt[RX], gw[RU], z[RU];      // VEC
     double red[2 * NXT];
@@ -472,10 +501,12 @@ __device__ __forceinline__ void store_feedback(const Ln<T> &L, const T *G, const
 
 // The inputs a wave that owns a column block of A adds to its products,
 // loaded one stage ahead at n_x <= 32 (where a stage is shorter than a memory
-// latency) and at the start of their phase otherwise.
+// latency; F's and H''s with one tile as soon as this stage's are in use,
+// EARLY, with two once this stage has left the registers) and at the start of
+// their phase otherwise.
 template <int NXT, int NUT>
 struct QTiles {
-    static constexpr bool AHEAD = NXT <= 2;
+    static constexpr bool AHEAD = NXT <= 2, EARLY = NXT == 1;
     d4 g[NUT], f[NXT], h[NUT];
     double lx, lw;
 };
@@ -486,8 +517,9 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
                                        int stage_base, int fail_code, Pre pre, RecOf rec, Vec &y) {
     using SM = Smem<T, NXT, NUT, SX, SU>;
     using QT = QTiles<NXT, NUT>;
-    constexpr int RX = SM::RX, RU = SM::RU;
+    constexpr int RX = SM::RX, RU = SM::RU, GS = SM::GS, WT = SM::WT;
     const int j = wave();
+    const bool zs = j == NXT - 1;           // owner of z and k (with the fewest tiles of F and P)
     QT q;
     auto load_g = [&](const Ln<T> &L, const StageSrc &src) {
         if (j < NUT) {
@@ -533,18 +565,23 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
                 y.cb += S.av[16 * j + L.c] * (0.5 * pa - y.psi);
             }
         }
-        // ---- G = Qw + B'PB by the owners of B's columns
-        if (j < NUT) {
-            v4_t<T> b[NXT], wb[NXT];
+        // ---- G = Qw + B'PB: column block jb by GS waves, each with its row
+        // tiles of W_B = P B
+        if (j < GS * NUT) {
+            const int jb = GS > 1 ? j % NUT : j, h = GS > 1 ? j / NUT : 0;
+            v4_t<T> b[NXT], wb[WT];
 #pragma unroll
             for (int kt = 0; kt < NXT; ++kt)
 #pragma unroll
-                for (int r = 0; r < SX; ++r) b[kt][r] = ldN<RU>(L, S.B, kt, j, r);
+                for (int r = 0; r < SX; ++r) b[kt][r] = ldN<RU>(L, S.B, kt, jb, r);
 #pragma unroll
-            for (int ti = 0; ti < NXT; ++ti) wb[ti] = mulN<RX, NXT, SX>(L, zero4<T>(), S.P, ti, b);
+            for (int ti = 0; ti < WT; ++ti) wb[ti] = mulN<RX, NXT, SX>(L, zero4<T>(), S.P, h * WT + ti, b);
 #pragma unroll
             for (int ti = 0; ti < NUT; ++ti)
-                if (ti >= j) put_sym<RU, SU>(L, S.G, ti, j, mulN<RU, NXT, SX>(L, as_t<T>(q.g[ti]), S.B, ti, wb));
+                if (ti >= jb)
+                    put_sym<RU, SU>(L, S.G + h * RU * RU, ti, jb,
+                                    mulN<RU, WT, SX>(L, h == 0 ? as_t<T>(q.g[ti]) : zero4<T>(),
+                                                     S.B + 16 * WT * h * RU, ti, wb));
         }
         lds_sync();
         // ---- W, F, H', g_x, g_w (the last wave of the workgroup factors G)
@@ -583,7 +620,7 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
             for (int ti = 0; ti < NXT; ++ti)
                 if (ti >= j) R1[ti] = mulN<RX, NXT, SX>(L, as_t<T>(q.f[ti]), S.A, ti, wa);
         }
-        if (QT::AHEAD && s > 0) load_f(L, wk.s);
+        if (QT::EARLY && s > 0) load_f(L, wk.s);
         if (NXT == 1) {
             // the record of P_{s+1}, still in LDS (the other wave factors G)
             pre(s, 0, 64);
@@ -597,7 +634,7 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
             record_failure(info, inst, fail_code, stage_base < 0 ? -1 : stage_base + s);
             S.bad = 0;
         }
-        if (VEC && j == 0)
+        if (VEC && zs)
             apply_Linv<RU, RX, NUT, SU, VEC>(L, S.G, R2, S.Y(), j, S.gw, S.z, &y.cb);
         else
             apply_Linv<RU, RX, NUT, SU>(L, S.G, R2, S.Y(), j);
@@ -622,21 +659,22 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
                 sv::gs(out.Psi + (uint32_t)(16 * j + L.c), y.psi);
         }
         if (KEEP == KEEP_ALL || out.K) {
-            if (VEC && j == 0)
+            if (VEC && zs)
                 store_feedback<EX, RU, NUT, SU, VEC>(L, S.G, R2, out.K, j, n, m, S.z, out.k);
             else
                 store_feedback<EX, RU, NUT, SU>(L, S.G, R2, out.K, j, n, m);
         }
         if (KEEP == KEEP_GIVEN && RED && out.L) copy_L(S, out.L, out.LT, m, 0, 64 * NXT);
+        if (QT::AHEAD && !QT::EARLY && s > 0) load_f(L, wk.s);
         lds_sync();
         if (SM::OVER) lds_sync();
     }
 }
 
 // Stage loop of the waves NXT + j: A and B of the next stage are loaded into
-// their registers, the last of them factors G, and for Alg. 4 they own the
+// their registers, the last of them (CH) factors G, and for Alg. 4 they own the
 // column blocks of V and Q_w_hat.
-template <bool RED, bool EX, bool EXD, bool VEC, int KEEP, class T, int NXT, int NUT, int SX, int SU, class Pre, class RecOf>
+template <bool CH, bool RED, bool EX, bool EXD, bool VEC, int KEEP, class T, int NXT, int NUT, int SX, int SU, class Pre, class RecOf>
 __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT> &C, int n, int m, int md, StageWalk wk, int count, Pre pre,
                                        RecOf rec, Vec &y) {
     using SM = Smem<T, NXT, NUT, SX, SU>;
@@ -685,13 +723,27 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
                 C.V[ti][r] = (16 * ti + L.row(r) == 16 * j + L.c) ? T(1) : T(0);
         }
     }
+    // What is not on the chain of a stage is left to the waves that wait for
+    // the factor of G: A'V, and Q_w_hat += X'X of the stage before (X keeps its
+    // place in LDS unless that is B's).
+    constexpr bool QD = RED && !CH && !SM::OVER;
+    v4_t<T> Xp[QD ? NUT : 1];
+    auto add_Q = [&](const Ln<T> &L, const v4_t<T> *X) {
+#pragma unroll
+        for (int ti = 0; ti < NXT; ++ti)
+            if (ti >= j) C.Q[ti] = mulN<RX, NUT, SU>(L, C.Q[ti], S.X(), ti, X);
+    };
     for (int s = count - 1; s >= 0; --s) {
         const Ln<T> L;
-        if (s > 0) {
+        v4_t<T> R1[NXT], R2[NUT];
+        auto mul_A = [&] {
+#pragma unroll
+            for (int ti = 0; ti < NXT; ++ti) R1[ti] = mulN<RX, NXT, SX>(L, zero4<T>(), S.A, ti, C.V);
+        };
+        if (NXT == 1 && s > 0) {
             wk.back();
             fetch(wk.s);
         }
-        v4_t<T> R1[NXT], R2[NUT];
         if (RED) {
             if constexpr (VEC) {
                 double va = 0.0;
@@ -703,14 +755,19 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
             }
 #pragma unroll
             for (int ti = 0; ti < NUT; ++ti) R2[ti] = mulN<RU, NXT, SX>(L, zero4<T>(), S.B, ti, C.V);
-#pragma unroll
-            for (int ti = 0; ti < NXT; ++ti) R1[ti] = mulN<RX, NXT, SX>(L, zero4<T>(), S.A, ti, C.V);
+            if (CH) mul_A();
         }
         lds_sync();
-        if (j == NXT - 1) {
-            const int f = chol_inv<T, NUT>(L, S.G, md);
+        if (NXT > 1 && s > 0) wk.back();
+        if (CH) {
+            if (NXT > 1 && s > 0) fetch(wk.s);
+            const int f = chol_inv<T, NUT, SM::GS>(L, S.G, md);
             if (f && lane() == 0) S.bad = 1;
         } else {
+            if (QD && s + 1 < count) add_Q(L, Xp);
+            if (RED) mul_A();
+            tile_fence<RX>();
+            if (NXT > 1 && s > 0) fetch(wk.s);
             // the record of P_{s+1}, still in LDS
             pre(s, NTV, 2 * NTV - 64);
             if (s + 1 < count) {
@@ -724,7 +781,7 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
         if (!SM::OVER && s > 0) commit();        // A and B are dead
         lds_sync();
         if (RED) {
-            // ---- V = A'V - Y'X, Q_w_hat += X'X, L_t = -L^{-T} X, v += X'z
+            // ---- V = A'V - Y'X, Q_w_hat += X'X (or X kept for it), L_t = -L^{-T} X, v += X'z
 #pragma unroll
             for (int ti = 0; ti < NXT; ++ti) {
                 const v4_t<T> acc = mulN<RX, NUT, SU>(L, zero4<T>(), S.Y(), ti, R2);
@@ -732,9 +789,12 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
                 for (int r = 0; r < SX; ++r) C.V[ti][r] = R1[ti][r] - acc[r];
                 if (KEEP == KEEP_ALL || out.V) store_tile<EX, SX>(L, out.V, n, ti, j, n, n, C.V[ti]);
             }
+            if (QD) {
 #pragma unroll
-            for (int ti = 0; ti < NXT; ++ti)
-                if (ti >= j) C.Q[ti] = mulN<RX, NUT, SU>(L, C.Q[ti], S.X(), ti, R2);
+                for (int ti = 0; ti < NUT; ++ti) Xp[QD ? ti : 0] = R2[ti];
+            } else {
+                add_Q(L, R2);
+            }
             if constexpr (VEC) {
                 double xz = 0.0;
 #pragma unroll
@@ -753,6 +813,7 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
             lds_sync();
         }
     }
+    if (QD) add_Q(Ln<T>(), Xp);
 }
 
 // Backward pass over `count` >= 1 stages (local s = count-1 .. 0).  P_{count}
@@ -763,7 +824,7 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
 // and m = 16 NUT exactly).  The problem data have md <= m inputs (EXD: 16 NUT),
 // the others being padding.
 // VEC: with the right-hand side, y holding Psi_{count} on entry.
-// The two kinds of waves run loops of their own (with the same barriers), so
+// The three kinds of waves run loops of their own (with the same barriers), so
 // that neither carries the other's registers.
 template <bool RED, bool EX, bool EXD, bool VEC, int KEEP, class T, int NXT, int NUT, int SX, int SU, class Pre,
           class RecOf>
@@ -795,8 +856,10 @@ __device__ __forceinline__ void pass(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT> 
     lds_sync();
     if (wave() < NXT)
         loop_P<RED, EX, EXD, VEC, KEEP>(S, n, m, md, wk, count, info, inst, stage_base, fail_code, pre, rec, y);
+    else if (NXT > 1 && wave() < 2 * NXT - 1)
+        loop_V<false, RED, EX, EXD, VEC, KEEP>(S, C, n, m, md, wk, count, pre, rec, y);
     else
-        loop_V<RED, EX, EXD, VEC, KEEP>(S, C, n, m, md, wk, count, pre, rec, y);
+        loop_V<true, RED, EX, EXD, VEC, KEEP>(S, C, n, m, md, wk, count, pre, rec, y);
     lds_sync();
     {
         T *p = rec(0).P;
