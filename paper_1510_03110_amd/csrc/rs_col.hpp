@@ -345,19 +345,13 @@ struct Cols {
     v4_t<T> V[NXT], Q[NXT];
 };
 
-// Where the factors of a stage go (row-major; nullptr: not kept), and Psi_t
-// and k_{t+1} (VEC).
+// Where the factors of a stage go (row-major; nullptr: not kept; K and, with
+// VEC, L_t always are), and Psi_t and k_{t+1} (VEC).
 template <class T>
 struct Rec {
     T *P, *K, *V, *Lt, *L, *LT;
     double *Psi, *k;
 };
-// What of it a pass keeps: decided per stage by the pointers (KEEP_GIVEN), or
-// at compile time all of it but L^{-1} and L^{-T} (KEEP_ALL, the records of
-// the fused solve; the loop then has no branches around its stores, and a
-// wait for a load need not assume anything about them).
-enum { KEEP_GIVEN = 0, KEEP_ALL = 1 };
-
 // Running right-hand side of a pass (VEC) in its owners' lanes: entry 16 j +
 // lane % 16 of Psi (waves j) and of v (waves NXT + j), and this lane's part of
 // cbar (without the constants c).
@@ -368,17 +362,56 @@ struct Vec {
 // Sum over the four lanes that hold one column of a result tile.
 __device__ __forceinline__ double q_sum(double v) { return sv::xor_sum<32>(sv::xor_sum<16>(v)); }
 
-// 16x16 tile of problem data in the result layout; zeros outside n1 x n2
-// (identity where ONE).  TR reads the transposed element.
+// Accesses to global memory in the stage loops go through buffer descriptors:
+// a load beyond the array gives zero and a store beyond it is dropped, so
+// bounds, absent arrays and the last stage need no branch.  Without branches
+// around them the number of accesses in flight is known wherever a loaded
+// value is used, and a wait for it does not also wait for the record stores
+// and the next loads issued since (stores and loads share one counter; with
+// branches the waits of a stage were for an empty counter).
+constexpr uint32_t BEYOND = 0x40000000u;      // a byte offset outside every array
+typedef __amdgpu_buffer_rsrc_t Buf;
+// `count` elements from p (uniform), none if p is null or !on.
+template <class U>
+__device__ __forceinline__ Buf buf(const U *p, int count, bool on = true) {
+    void *q = const_cast<double *>(uni_ptr(reinterpret_cast<const double *>(p)));
+    return __builtin_amdgcn_make_buffer_rsrc(q, 0, q && on ? count * (int)sizeof(U) : 0, 0x00020000);
+}
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+// byte: this lane's offset, the bounded part; sbyte: a uniform offset on top
+// (full tiles, where nothing is out of bounds: it takes no vector register).
+__device__ __forceinline__ double buf_ld(Buf b, uint32_t byte, uint32_t sbyte = 0) {
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(b, (int)byte, (int)sbyte, 0));
+}
+__device__ __forceinline__ void buf_st(Buf b, uint32_t byte, double v, uint32_t sbyte = 0) {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), b, (int)byte, (int)sbyte, 0);
+}
+__device__ __forceinline__ void buf_st(Buf b, uint32_t byte, float v, uint32_t sbyte = 0) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), b, (int)byte, (int)sbyte, 0);
+}
+// Drains this wave's global accesses.
+__device__ __forceinline__ void drain() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
+// 16x16 tile of problem data (n1 x n2 in all, rows of length ld) in the result
+// layout; zeros outside (identity where ONE).  TR: the array holds the
+// transpose.
 template <bool EX, bool TR, bool ONE, int NS, class T>
-__device__ __forceinline__ d4 load_tile(const Ln<T> &L, const double *M, int ld, int ti, int tj, int n1, int n2) {
+__device__ __forceinline__ d4 load_tile(const Ln<T> &L, Buf M, int ld, int ti, int tj, int n1, int n2) {
     d4 v{0.0, 0.0, 0.0, 0.0};
+    const int j = 16 * tj + L.c;
+    const bool in = EX || TR || j < n2;        // the other index is bounded by the array's length
 #pragma unroll
     for (int r = 0; r < NS; ++r) {
-        const int i = 16 * ti + L.row(r), j = 16 * tj + L.c;
-        const bool ok = EX || (i < n1 && j < n2);
-        const double pad = (ONE && i == j) ? 1.0 : 0.0;
-        v[r] = ok ? gload(M + (uint32_t)(TR ? j * ld + i : i * ld + j)) : pad;
+        const int i = 16 * ti + L.row(r);
+        if (EX) {
+            const int si = 16 * ti + L.row(r) - L.row(0), sj = 16 * tj;
+            v[r] = buf_ld(M, 8u * (uint32_t)(TR ? L.c * ld + L.row(0) : L.row(0) * ld + L.c),
+                          8u * (uint32_t)(TR ? sj * ld + si : si * ld + sj));
+            continue;
+        }
+        const uint32_t e = 8u * (uint32_t)(TR ? j * ld + i : i * ld + j);
+        v[r] = buf_ld(M, (TR ? i < n1 : in) ? e : BEYOND);
+        if (ONE && !EX) v[r] = (i == j && i >= n1) ? 1.0 : v[r];
     }
     return v;
 }
@@ -387,13 +420,18 @@ __device__ __forceinline__ v4_t<T> as_t(d4 v) {
     return v4_t<T>{(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
 }
 
-// Result tile (ti, tj) to global memory (rows of length ld).
+// Result tile (ti, tj) to global memory (rows of length ld, n2 columns in use).
 template <bool EX, int NS, class T>
-__device__ __forceinline__ void store_tile(const Ln<T> &L, T *M, int ld, int ti, int tj, int n1, int n2, v4_t<T> v) {
+__device__ __forceinline__ void store_tile(const Ln<T> &L, Buf M, int ld, int ti, int tj, int n2, v4_t<T> v) {
+    const int j = 16 * tj + L.c;
 #pragma unroll
     for (int r = 0; r < NS; ++r) {
-        const int i = 16 * ti + L.row(r), j = 16 * tj + L.c;
-        if (EX || (i < n1 && j < n2)) M[(uint32_t)(i * ld + j)] = v[r];
+        constexpr uint32_t B = sizeof(T);
+        if (EX)
+            buf_st(M, B * (uint32_t)(L.row(0) * ld + L.c), v[r],
+                   B * (uint32_t)((16 * ti + L.row(r) - L.row(0)) * ld + 16 * tj));
+        else
+            buf_st(M, j < n2 ? B * (uint32_t)((16 * ti + L.row(r)) * ld + j) : BEYOND, v[r]);
     }
 }
 
@@ -411,6 +449,25 @@ __device__ __forceinline__ void copy_P(const SM &S, U *dst, int n, int t0 = 0, i
         if (i < n && j < n) dst[(uint32_t)(i * n + j)] = (U)S.P[at<SM::RX>(i, j)];
     }
 }
+// The same by NT threads (t their index) inside a stage loop, where it may be
+// switched off without a branch.
+template <bool EX, int NT, class SM, class U>
+__device__ __forceinline__ void put_P(const SM &S, U *dst, int n, int t, bool on) {
+    constexpr int RX = SM::RX, W = (4 * SM::SX < 16 && RX == 16) ? 4 * SM::SX : RX;    // rows and columns in use
+    const Buf b = buf(dst, n * n, on);
+    asm volatile("" : "+v"(t));
+#pragma unroll
+    for (int q = 0; q < (W * W + NT - 1) / NT; ++q) {
+        const int e = t + q * NT, i = e / W, j = e % W;
+        const uint32_t o = (uint32_t)sizeof(U) * (uint32_t)(i * n + j);
+        const bool all = W * W % NT == 0;
+        const U v = (U)S.P[at<RX>(all || i < W ? i : 0, j)];
+        if (EX && all)
+            buf_st(b, (uint32_t)sizeof(U) * (uint32_t)t, v, (uint32_t)sizeof(U) * (uint32_t)(q * NT));
+        else
+            buf_st(b, (EX || j < n) && (all || i < W) ? o : BEYOND, v);
+    }
+}
 
 // Start of a pass: P from an element function (rows and columns < n).
 template <class SM, class F>
@@ -425,20 +482,21 @@ __device__ __forceinline__ void set_P(SM &S, int n, F f) {
     }
 }
 
-// L^{-1} and L^{-T} (m x m, dense) from LDS to their records, by the threads
-// t0 <= threadIdx.x < t1.
-template <class SM, class T>
-__device__ __forceinline__ void copy_L(const SM &S, T *L, T *LT, int m, int t0, int t1) {
-    constexpr int RU = SM::RU;
-    int t = (int)threadIdx.x - t0;
+// L^{-1} and L^{-T} (m x m, dense) from LDS to their records, by NT threads (t
+// their index).
+template <bool EX, int NT, class SM, class T>
+__device__ __forceinline__ void put_L(const SM &S, T *L, T *LT, int m, int t) {
+    constexpr int RU = SM::RU, W = (4 * SM::SU < 16 && RU == 16) ? 4 * SM::SU : RU;
+    const Buf b = buf(L, m * m), bt = buf(LT, m * m);
     asm volatile("" : "+v"(t));
-#pragma unroll 2
-    for (int e = t; e < RU * RU; e += t1 - t0) {
-        const int i = e / RU, k = e % RU;
-        if (i < m && k < m) {
-            L[(uint32_t)(i * m + k)] = k <= i ? S.G[at<RU>(i, k)] : T(0);
-            LT[(uint32_t)(i * m + k)] = i <= k ? S.G[at<RU>(k, i)] : T(0);
-        }
+#pragma unroll
+    for (int q = 0; q < (W * W + NT - 1) / NT; ++q) {
+        const int e = t + q * NT, i = e / W, k = e % W;
+        const bool in = (EX || k < m) && (W * W % NT == 0 || e < W * W);
+        const uint32_t o = in ? (uint32_t)sizeof(T) * (uint32_t)(i * m + k) : BEYOND;
+        const int is = W * W % NT == 0 || i < W ? i : 0;
+        buf_st(b, o, k <= i ? S.G[at<RU>(is, k)] : T(0));
+        buf_st(bt, o, i <= k ? S.G[at<RU>(k, is)] : T(0));
     }
 }
 
@@ -475,12 +533,13 @@ __device__ __forceinline__ void apply_Linv(const Ln<T> &L, const T *G, v4_t<T> *
 
 // K = -L^{-T} Y or L_t = -L^{-T} X of one column block, to its record.  Z:
 // also k = L^{-T} z.
-template <bool EX, int RU, int NUT, int NS, bool Z = false, class T>
+template <bool EX, int RU, int RX, int NUT, int NS, bool Z = false, class T>
 __device__ __forceinline__ void store_feedback(const Ln<T> &L, const T *G, const v4_t<T> *R2, T *D, int j, int n, int m,
                                                const double *zv = nullptr, double *k = nullptr) {
+    const Buf bd = buf(D, n * m), bk = buf(k, m);
 #pragma unroll
     for (int ti = 0; ti < NUT; ++ti) {
-        tile_fence<RU>();
+        tile_fence<RX>();
         v4_t<T> acc = zero4<T>();
         double s = 0.0;
 #pragma unroll
@@ -491,28 +550,27 @@ __device__ __forceinline__ void store_feedback(const Ln<T> &L, const T *G, const
                 acc = MT<T>::mfma(a, R2[kt][r], acc);
                 if constexpr (Z) s += (double)a * zv[16 * kt + L.row(r)];
             }
-        store_tile<EX, NS>(L, D, n, ti, j, m, n, v4_t<T>{-acc[0], -acc[1], -acc[2], -acc[3]});
+        store_tile<EX, NS>(L, bd, n, ti, j, n, v4_t<T>{-acc[0], -acc[1], -acc[2], -acc[3]});
         if constexpr (Z) {
             s = q_sum(s);
-            if (L.q == 0 && (EX || 16 * ti + L.c < m)) sv::gs(k + (uint32_t)(16 * ti + L.c), s);
+            buf_st(bk, 8u * (uint32_t)(16 * ti + L.c), s);       // (the four lanes of a column hold the same sum)
         }
     }
 }
 
-// The inputs a wave that owns a column block of A adds to its products,
-// loaded one stage ahead at n_x <= 32 (where a stage is shorter than a memory
-// latency; F's and H''s with one tile as soon as this stage's are in use,
-// EARLY, with two once this stage has left the registers) and at the start of
-// their phase otherwise.
+// The inputs a wave that owns a column block of A adds to its products, loaded
+// one stage ahead: G's during W, F's and H''s with one tile as soon as this
+// stage's are in use (EARLY), otherwise when this stage's P has left their
+// registers.
 template <int NXT, int NUT>
 struct QTiles {
-    static constexpr bool AHEAD = NXT <= 2, EARLY = NXT == 1;
+    static constexpr bool EARLY = NXT == 1;
     d4 g[NUT], f[NXT], h[NUT];
     double lx, lw;
 };
 
 // Stage loop of the waves that own a column block of A (w < NXT).
-template <bool RED, bool EX, bool EXD, bool VEC, int KEEP, class T, int NXT, int NUT, int SX, int SU, class Pre, class RecOf>
+template <bool RED, bool EX, bool EXD, bool VEC, class T, int NXT, int NUT, int SX, int SU, class Pre, class RecOf>
 __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int m, int md, StageWalk wk, int count, int32_t *info, int inst,
                                        int stage_base, int fail_code, Pre pre, RecOf rec, Vec &y) {
     using SM = Smem<T, NXT, NUT, SX, SU>;
@@ -521,37 +579,30 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
     const int j = wave();
     const bool zs = j == NXT - 1;           // owner of z and k (with the fewest tiles of F and P)
     QT q;
-    auto load_g = [&](const Ln<T> &L, const StageSrc &src) {
-        if (j < NUT) {
+    auto load_g = [&](const Ln<T> &L, const StageSrc &src, bool on) {
 #pragma unroll
-            for (int ti = 0; ti < NUT; ++ti)
-                if (ti >= j) q.g[ti] = load_tile<EXD, false, true, SU>(L, src.Qw, md, ti, j, md, md);
-            if constexpr (VEC)
-                q.lw = (src.lw && (EXD || 16 * j + L.c < md)) ? gload(src.lw + (uint32_t)(16 * j + L.c)) : 0.0;
-        }
+        for (int ti = 0; ti < NUT; ++ti)
+            q.g[ti] = load_tile<EXD, false, true, SU>(L, buf(src.Qw, md * md, on && j <= ti), md, ti, j, md, md);
+        if constexpr (VEC) q.lw = buf_ld(buf(src.lw, md, on), 8u * (uint32_t)(16 * j + L.c));
     };
-    auto load_f = [&](const Ln<T> &L, const StageSrc &src) {
-        if (src.Qxw) {
+    auto load_f = [&](const Ln<T> &L, const StageSrc &src, bool on) {
+        const Buf bh = buf(src.Qxw, n * md, on);
 #pragma unroll
-            for (int ti = 0; ti < NUT; ++ti) q.h[ti] = load_tile<EXD, true, false, SU>(L, src.Qxw, md, ti, j, md, n);
-        } else {
-#pragma unroll
-            for (int ti = 0; ti < NUT; ++ti) q.h[ti] = d4{0.0, 0.0, 0.0, 0.0};
-        }
+        for (int ti = 0; ti < NUT; ++ti) q.h[ti] = load_tile<EXD, true, false, SU>(L, bh, md, ti, j, md, n);
 #pragma unroll
         for (int ti = 0; ti < NXT; ++ti)
-            if (ti >= j) q.f[ti] = load_tile<EX, false, false, SX>(L, src.Qx, n, ti, j, n, n);
-        if constexpr (VEC)
-            q.lx = (src.lx && (EX || 16 * j + L.c < n)) ? gload(src.lx + (uint32_t)(16 * j + L.c)) : 0.0;
+            q.f[ti] = load_tile<EX, false, false, SX>(L, buf(src.Qx, n * n, on && ti >= j), n, ti, j, n, n);
+        if constexpr (VEC) q.lx = buf_ld(buf(src.lx, n, on), 8u * (uint32_t)(16 * j + L.c));
     };
-    if (QT::AHEAD) {
+    {
         const Ln<T> L;
-        load_g(L, wk.s);
-        load_f(L, wk.s);
+        load_g(L, wk.s, true);
+        load_f(L, wk.s, true);
+        drain();
     }
+    lds_sync();
     for (int s = count - 1; s >= 0; --s) {
         const Ln<T> L;
-        if (!QT::AHEAD) load_g(L, wk.s);
         double pa = 0.0;
         if constexpr (VEC) {
             // ---- pt = Psi - P a, cbar += 1/2 a'Pa - Psi'a
@@ -587,7 +638,6 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
         // ---- W, F, H', g_x, g_w (the last wave of the workgroup factors G)
         v4_t<T> R1[NXT], R2[NUT];
         double gx = 0.0;
-        if (!QT::AHEAD) load_f(L, wk.s);
         if (s > 0) wk.back();           // the next stage
         {
             v4_t<T> a[NXT], wa[NXT];
@@ -611,7 +661,7 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
                     if (L.q == 0) S.gw[16 * j + L.c] = g;
                 }
             }
-            if (QT::AHEAD && s > 0) load_g(L, wk.s);
+            load_g(L, wk.s, s > 0);
 #pragma unroll
             for (int ti = 0; ti < NXT; ++ti) wa[ti] = mulN<RX, NXT, SX>(L, zero4<T>(), S.P, ti, a);
 #pragma unroll
@@ -620,14 +670,11 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
             for (int ti = 0; ti < NXT; ++ti)
                 if (ti >= j) R1[ti] = mulN<RX, NXT, SX>(L, as_t<T>(q.f[ti]), S.A, ti, wa);
         }
-        if (QT::EARLY && s > 0) load_f(L, wk.s);
-        if (NXT == 1) {
+        if (QT::EARLY) load_f(L, wk.s, s > 0);
+        if constexpr (NXT == 1) {
             // the record of P_{s+1}, still in LDS (the other wave factors G)
             pre(s, 0, 64);
-            if (s + 1 < count) {
-                T *p = rec(s + 1).P;
-                if (KEEP == KEEP_ALL || p) copy_P(S, p, n, 0, 64);
-            }
+            put_P<EX, 64>(S, rec(s + 1 < count ? s + 1 : s).P, n, threadIdx.x, s + 1 < count);
         }
         lds_sync();
         if (threadIdx.x == 0 && S.bad) {
@@ -648,6 +695,7 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
                 put_sym<RX, SX>(L, S.P, ti, j,
                             v4_t<T>{R1[ti][0] - acc[0], R1[ti][1] - acc[1], R1[ti][2] - acc[2], R1[ti][3] - acc[3]});
             }
+        if (!QT::EARLY) load_f(L, wk.s, s > 0);
         if constexpr (VEC) {
             double yz = 0.0;
 #pragma unroll
@@ -655,17 +703,10 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
 #pragma unroll
                 for (int r = 0; r < SU; ++r) yz += R2[ti][r] * S.z[16 * ti + L.row(r)];
             y.psi = gx - q_sum(yz);
-            if ((KEEP == KEEP_ALL || out.Psi) && L.q == 0 && (EX || 16 * j + L.c < n))
-                sv::gs(out.Psi + (uint32_t)(16 * j + L.c), y.psi);
+            buf_st(buf(out.Psi, n), 8u * (uint32_t)(16 * j + L.c), y.psi);
         }
-        if (KEEP == KEEP_ALL || out.K) {
-            if (VEC && zs)
-                store_feedback<EX, RU, NUT, SU, VEC>(L, S.G, R2, out.K, j, n, m, S.z, out.k);
-            else
-                store_feedback<EX, RU, NUT, SU>(L, S.G, R2, out.K, j, n, m);
-        }
-        if (KEEP == KEEP_GIVEN && RED && out.L) copy_L(S, out.L, out.LT, m, 0, 64 * NXT);
-        if (QT::AHEAD && !QT::EARLY && s > 0) load_f(L, wk.s);
+        store_feedback<EX, RU, RX, NUT, SU, VEC>(L, S.G, R2, out.K, j, n, m, S.z, zs ? out.k : nullptr);
+        if (RED && !VEC) put_L<EX, 64 * NXT>(S, out.L, out.LT, m, threadIdx.x);
         lds_sync();
         if (SM::OVER) lds_sync();
     }
@@ -674,7 +715,7 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
 // Stage loop of the waves NXT + j: A and B of the next stage are loaded into
 // their registers, the last of them (CH) factors G, and for Alg. 4 they own the
 // column blocks of V and Q_w_hat.
-template <bool CH, bool RED, bool EX, bool EXD, bool VEC, int KEEP, class T, int NXT, int NUT, int SX, int SU, class Pre, class RecOf>
+template <bool CH, bool RED, bool EX, bool EXD, bool VEC, class T, int NXT, int NUT, int SX, int SU, class Pre, class RecOf>
 __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT> &C, int n, int m, int md, StageWalk wk, int count, Pre pre,
                                        RecOf rec, Vec &y) {
     using SM = Smem<T, NXT, NUT, SX, SU>;
@@ -683,20 +724,23 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
     static_assert(RX * RX % NTV == 0 && RX * RU % NTV == 0, "whole rounds");
     const int j = wave() - NXT;
     double pa[NA], pb[NB], pv = 0.0;
-    auto fetch = [&](const StageSrc &src) {
+    auto fetch = [&](const StageSrc &src, bool on) {
         int tv = (int)threadIdx.x - NTV;
         asm volatile("" : "+v"(tv));
+        const Buf ba = buf(src.A, n * n, on), bb = buf(src.B, n * md, on);
 #pragma unroll
         for (int q = 0; q < NA; ++q) {
             const int e = tv + q * NTV, i = e / RX, k = e % RX;
-            pa[q] = (EX || (i < n && k < n)) ? gload(src.A + (uint32_t)(i * n + k)) : 0.0;
+            pa[q] = EX ? buf_ld(ba, 8u * (uint32_t)tv, 8u * (uint32_t)(q * NTV))
+                       : buf_ld(ba, k < n ? 8u * (uint32_t)(i * n + k) : BEYOND);
         }
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
             const int e = tv + q * NTV, i = e / RU, k = e % RU;
-            pb[q] = (EXD || (i < n && k < md)) ? gload(src.B + (uint32_t)(i * md + k)) : 0.0;
+            pb[q] = EXD ? buf_ld(bb, 8u * (uint32_t)tv, 8u * (uint32_t)(q * NTV))
+                        : buf_ld(bb, k < md ? 8u * (uint32_t)(i * md + k) : BEYOND);
         }
-        if constexpr (VEC) pv = (src.a && tv < n) ? gload(src.a + (uint32_t)tv) : 0.0;
+        if constexpr (VEC) pv = buf_ld(buf(src.a, n, on), 8u * (uint32_t)tv);
     };
     auto commit = [&]() {
         int tv = (int)threadIdx.x - NTV;
@@ -727,12 +771,22 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
     // the factor of G: A'V, and Q_w_hat += X'X of the stage before (X keeps its
     // place in LDS unless that is B's).
     constexpr bool QD = RED && !CH && !SM::OVER;
-    v4_t<T> Xp[QD ? NUT : 1];
     auto add_Q = [&](const Ln<T> &L, const v4_t<T> *X) {
 #pragma unroll
         for (int ti = 0; ti < NXT; ++ti)
             if (ti >= j) C.Q[ti] = mulN<RX, NUT, SU>(L, C.Q[ti], S.X(), ti, X);
     };
+    auto add_Q_late = [&](const Ln<T> &L) {
+        v4_t<T> X[NUT];
+#pragma unroll
+        for (int kt = 0; kt < NUT; ++kt)
+#pragma unroll
+            for (int r = 0; r < SU; ++r) X[kt][r] = ldN<RX>(L, S.X(), kt, j, r);
+        add_Q(L, X);
+    };
+    fetch(wk.s, true);
+    commit();
+    lds_sync();
     for (int s = count - 1; s >= 0; --s) {
         const Ln<T> L;
         v4_t<T> R1[NXT], R2[NUT];
@@ -740,10 +794,8 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
 #pragma unroll
             for (int ti = 0; ti < NXT; ++ti) R1[ti] = mulN<RX, NXT, SX>(L, zero4<T>(), S.A, ti, C.V);
         };
-        if (NXT == 1 && s > 0) {
-            wk.back();
-            fetch(wk.s);
-        }
+        if (s > 0) wk.back();
+        if (NXT == 1) fetch(wk.s, s > 0);
         if (RED) {
             if constexpr (VEC) {
                 double va = 0.0;
@@ -758,43 +810,35 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
             if (CH) mul_A();
         }
         lds_sync();
-        if (NXT > 1 && s > 0) wk.back();
-        if (CH) {
-            if (NXT > 1 && s > 0) fetch(wk.s);
+        if constexpr (CH) {
             const int f = chol_inv<T, NUT, SM::GS>(L, S.G, md);
             if (f && lane() == 0) S.bad = 1;
+            tile_fence<RX>();
+            if (NXT > 1) fetch(wk.s, s > 0);
         } else {
-            if (QD && s + 1 < count) add_Q(L, Xp);
+            if (QD && s + 1 < count) add_Q_late(L);
             if (RED) mul_A();
             tile_fence<RX>();
-            if (NXT > 1 && s > 0) fetch(wk.s);
+            if (NXT > 1) fetch(wk.s, s > 0);
             // the record of P_{s+1}, still in LDS
             pre(s, NTV, 2 * NTV - 64);
-            if (s + 1 < count) {
-                T *p = rec(s + 1).P;
-                if (KEEP == KEEP_ALL || p) copy_P(S, p, n, NTV, 2 * NTV - 64);
-            }
+            put_P<EX, NTV - 64>(S, rec(s + 1 < count ? s + 1 : s).P, n, (int)threadIdx.x - NTV, s + 1 < count);
         }
         lds_sync();
         const Rec<T> out = rec(s);
         if (RED) apply_Linv<RU, RX, NUT, SU>(L, S.G, R2, S.X(), j);
-        if (!SM::OVER && s > 0) commit();        // A and B are dead
         lds_sync();
         if (RED) {
-            // ---- V = A'V - Y'X, Q_w_hat += X'X (or X kept for it), L_t = -L^{-T} X, v += X'z
+            const Buf bv = buf(out.V, n * n);
+            // ---- V = A'V - Y'X, Q_w_hat += X'X, L_t = -L^{-T} X, v += X'z
 #pragma unroll
             for (int ti = 0; ti < NXT; ++ti) {
                 const v4_t<T> acc = mulN<RX, NUT, SU>(L, zero4<T>(), S.Y(), ti, R2);
 #pragma unroll
                 for (int r = 0; r < SX; ++r) C.V[ti][r] = R1[ti][r] - acc[r];
-                if (KEEP == KEEP_ALL || out.V) store_tile<EX, SX>(L, out.V, n, ti, j, n, n, C.V[ti]);
+                store_tile<EX, SX>(L, bv, n, ti, j, n, C.V[ti]);
             }
-            if (QD) {
-#pragma unroll
-                for (int ti = 0; ti < NUT; ++ti) Xp[QD ? ti : 0] = R2[ti];
-            } else {
-                add_Q(L, R2);
-            }
+            if (!QD) add_Q(L, R2);
             if constexpr (VEC) {
                 double xz = 0.0;
 #pragma unroll
@@ -803,17 +847,18 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
                     for (int r = 0; r < SU; ++r) xz += R2[ti][r] * S.z[16 * ti + L.row(r)];
                 y.v += q_sum(xz);
             }
-            if (KEEP == KEEP_ALL || out.Lt) store_feedback<EX, RU, NUT, SU>(L, S.G, R2, out.Lt, j, n, m);
-        } else if (KEEP == KEEP_GIVEN && out.L) {
-            copy_L(S, out.L, out.LT, m, NTV, 2 * NTV);
+            if (VEC || out.Lt) store_feedback<EX, RU, RX, NUT, SU>(L, S.G, R2, out.Lt, j, n, m);
+        } else if (!VEC) {
+            put_L<EX, NTV>(S, out.L, out.LT, m, (int)threadIdx.x - NTV);
         }
+        if (!SM::OVER) commit();                 // A and B are dead since the factorization
         lds_sync();
         if (SM::OVER) {
-            if (s > 0) commit();
+            commit();
             lds_sync();
         }
     }
-    if (QD) add_Q(Ln<T>(), Xp);
+    if (QD) add_Q_late(Ln<T>());
 }
 
 // Backward pass over `count` >= 1 stages (local s = count-1 .. 0).  P_{count}
@@ -826,7 +871,7 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
 // VEC: with the right-hand side, y holding Psi_{count} on entry.
 // The three kinds of waves run loops of their own (with the same barriers), so
 // that neither carries the other's registers.
-template <bool RED, bool EX, bool EXD, bool VEC, int KEEP, class T, int NXT, int NUT, int SX, int SU, class Pre,
+template <bool RED, bool EX, bool EXD, bool VEC, class T, int NXT, int NUT, int SX, int SU, class Pre,
           class RecOf>
 __device__ __forceinline__ void pass(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT> &C, int n_, int m_, int md_, StageWalk wk, int count,
                                      int32_t *info, int inst, int stage_base, int fail_code, Pre pre, RecOf rec, Vec &y) {
@@ -839,31 +884,16 @@ __device__ __forceinline__ void pass(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT> 
     asm volatile("" : "+v"(tid));
     count = uni(count);
     if (tid == 0) S.bad = 0;
-    {
-        const StageSrc &src = wk.s;
-#pragma unroll 4
-        for (int e = tid; e < RX * RX; e += NTH) {
-            const int i = e / RX, k = e % RX;
-            S.A[at<RX>(i, k)] = (EX || (i < n && k < n)) ? (T)gload(src.A + (uint32_t)(i * n + k)) : T(0);
-        }
-#pragma unroll 4
-        for (int e = tid; e < RX * RU; e += NTH) {
-            const int i = e / RU, k = e % RU;
-            S.B[at<RU>(i, k)] = (EXD || (i < n && k < md)) ? (T)gload(src.B + (uint32_t)(i * md + k)) : T(0);
-        }
-        if (VEC && tid < RX) S.av[tid] = (src.a && tid < n) ? gload(src.a + (uint32_t)tid) : 0.0;
-    }
-    lds_sync();
     if (wave() < NXT)
-        loop_P<RED, EX, EXD, VEC, KEEP>(S, n, m, md, wk, count, info, inst, stage_base, fail_code, pre, rec, y);
-    else if (NXT > 1 && wave() < 2 * NXT - 1)
-        loop_V<false, RED, EX, EXD, VEC, KEEP>(S, C, n, m, md, wk, count, pre, rec, y);
-    else
-        loop_V<true, RED, EX, EXD, VEC, KEEP>(S, C, n, m, md, wk, count, pre, rec, y);
+        loop_P<RED, EX, EXD, VEC>(S, n, m, md, wk, count, info, inst, stage_base, fail_code, pre, rec, y);
+    else if (wave() == 2 * NXT - 1)
+        loop_V<true, RED, EX, EXD, VEC>(S, C, n, m, md, wk, count, pre, rec, y);
+    else if constexpr (NXT > 1)
+        loop_V<false, RED, EX, EXD, VEC>(S, C, n, m, md, wk, count, pre, rec, y);
     lds_sync();
     {
         T *p = rec(0).P;
-        if (KEEP == KEEP_ALL || p) copy_P(S, p, n);
+        if (p) copy_P(S, p, n);
     }
 }
 

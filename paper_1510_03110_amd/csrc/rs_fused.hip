@@ -60,7 +60,7 @@ __global__ void __launch_bounds__(128 * NXT, NXT == 1 ? 4 : NUT == 1 ? 3 : 2) kf
     Vec y{};
     if (!(it.flags & LEAF_LAST)) {
         set_P(S, n, [](int) { return 0.0; });
-        pass<true, EX, EXD, true, KEEP_ALL>(S, C, n, m, md, wk, it.len, g.info, it.inst, it.t0, 2, no_pre, rec, y);
+        pass<true, EX, EXD, true>(S, C, n, m, md, wk, it.len, g.info, it.inst, it.t0, 2, no_pre, rec, y);
         store_V_transposed<SX>(C, out + SL.A(), n);
         copy_P(S, out + SL.Qx(), n);
         if (!g.ident) store_Q<SX>(C, out + SL.Qw(), n);
@@ -68,7 +68,7 @@ __global__ void __launch_bounds__(128 * NXT, NXT == 1 ? 4 : NUT == 1 ? 3 : 2) kf
     } else {
         set_P(S, n, [&](int e) { return p.QxN[e]; });
         if (w < NXT && col < n) y.psi = p.lN ? -p.lN[col] : 0.0;
-        pass<false, EX, EXD, true, KEEP_ALL>(S, C, n, m, md, wk, it.len, g.info, it.inst, it.t0, 2, no_pre, rec, y);
+        pass<false, EX, EXD, true>(S, C, n, m, md, wk, it.len, g.info, it.inst, it.t0, 2, no_pre, rec, y);
         if (!down) copy_P(S, out + SL.Qx(), n);
     }
     const double c = total(S, y.cb + vs::sum_c(p.c ? p.c + (int64_t)it.t0 * p.sc : nullptr, p.sc, it.len)) +
@@ -147,7 +147,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kf_tree(GroupArgs g) {
             // excluded instance: only its completion flag is published
         } else if (it.kind == ITEM_UP) {
             set_P(S, n, [](int) { return 0.0; });
-            pass<true, EX, EX, true, KEEP_GIVEN>(S, C, n, n, n, wk, it.count, g.info, it.inst, -1, 3, no_pre, [&](int s) {
+            pass<true, EX, EX, true>(S, C, n, n, n, wk, it.count, g.info, it.inst, -1, 3, no_pre, [&](int s) {
                 double *d = slot(it.first + s);
                 return Rec<double>{d + SL.uP(), d + SL.uK(), d + SL.uV(), d + SL.dL(), nullptr, nullptr, d + SL.Psi(),
                                    d + SL.k()};
@@ -176,7 +176,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kf_tree(GroupArgs g) {
                 copy_P(S, d + SL.P(), n);
                 if (own && w < NXT) d[SL.Psi() + col] = y.psi;
             }
-            pass<false, EX, EX, true, KEEP_GIVEN>(S, C, n, n, n, wk, it.count, g.info, it.inst, -1, 3, no_pre, [&](int s) {
+            pass<false, EX, EX, true>(S, C, n, n, n, wk, it.count, g.info, it.inst, -1, 3, no_pre, [&](int s) {
                 double *d = slot(it.first + s);
                 if (!top)
                     return Rec<double>{d + SL.uP(), d + SL.uK(), nullptr, nullptr, nullptr, nullptr, d + SL.Psi(),

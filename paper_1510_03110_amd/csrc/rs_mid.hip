@@ -50,7 +50,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_leaf(GroupArgs g, int down) {
     Vec y{};
     if (!(it.flags & LEAF_LAST)) {
         set_P(S, n, [](int) { return 0.0; });
-        pass<true, EX, EX, false, KEEP_GIVEN>(S, C, n, m, m, wk, it.len, g.info, it.inst, it.t0, 2, no_pre, [&](int s) {
+        pass<true, EX, EX, false>(S, C, n, m, m, wk, it.len, g.info, it.inst, it.t0, 2, no_pre, [&](int s) {
             T *d = base + (int64_t)s * R.per_stage();
             return Rec<T>{d + R.P(), d + R.K(), d + R.V(), d + R.Lt(), d + R.L(), d + R.LT(), nullptr, nullptr};
         }, y);
@@ -69,7 +69,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_leaf(GroupArgs g, int down) {
     } else {
         if (down) base += R.up();
         set_P(S, n, [&](int e) { return p.QxN[e]; });
-        pass<false, EX, EX, false, KEEP_GIVEN>(S, C, n, m, m, wk, it.len, g.info, it.inst, it.t0, 2, no_pre, [&](int s) {
+        pass<false, EX, EX, false>(S, C, n, m, m, wk, it.len, g.info, it.inst, it.t0, 2, no_pre, [&](int s) {
             T *d = base + (int64_t)s * R.per_stage();
             return Rec<T>{d + R.P(), d + R.K(), nullptr, nullptr, d + R.L(), d + R.LT(), nullptr, nullptr};
         }, y);
@@ -102,7 +102,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_tree(GroupArgs g) {
             // excluded instance: only its completion flag is published
         } else if (it.kind == ITEM_UP) {
             set_P(S, n, [](int) { return 0.0; });
-            pass<true, EX, EX, false, KEEP_GIVEN>(S, C, n, n, n, wk, it.count, g.info, it.inst, -1, 3, [](int, int, int) {}, [&](int s) {
+            pass<true, EX, EX, false>(S, C, n, n, n, wk, it.count, g.info, it.inst, -1, 3, [](int, int, int) {}, [&](int s) {
                 double *d = slot(it.first + s);
                 return Rec<double>{d + SL.uP(), d + SL.uK(), d + SL.uV(), g.superpose ? d + SL.dL() : nullptr,
                                    d + SL.uL(), d + SL.uLT(), nullptr, nullptr};
@@ -127,7 +127,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_tree(GroupArgs g) {
             double *term = it.last ? slot(it.term_slot) : nullptr;
             const double *P0 = term ? term + SL.Qx() : msg + SL.P();
             set_P(S, n, [&](int e) { return P0[e]; });
-            pass<false, EX, EX, false, KEEP_GIVEN>(S, C, n, n, n, wk, it.count, g.info, it.inst, -1, 3,
+            pass<false, EX, EX, false>(S, C, n, n, n, wk, it.count, g.info, it.inst, -1, 3,
                             [&](int s, int t0, int t1) {      // M2 for child s: P at the end of master stage s
                                 if (!upl) copy_P(S, slot(it.first + s) + SL.P(), n, t0, t1);
                             },
