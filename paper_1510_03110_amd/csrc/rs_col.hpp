@@ -383,6 +383,13 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ double buf_ld(Buf b, uint32_t byte, uint32_t sbyte = 0) {
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(b, (int)byte, (int)sbyte, 0));
 }
+template <class T>
+__device__ __forceinline__ T buf_get(Buf b, uint32_t byte) {
+    if constexpr (sizeof(T) == 8)
+        return buf_ld(b, byte);
+    else
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(b, (int)byte, 0, 0));
+}
 __device__ __forceinline__ void buf_st(Buf b, uint32_t byte, double v, uint32_t sbyte = 0) {
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), b, (int)byte, (int)sbyte, 0);
 }

@@ -46,9 +46,11 @@
 
 #include <algorithm>
 
+#include "rs_col.hpp"
 #include "rs_launch.hpp"
 #include "rs_mfma.hpp"
 #include "rs_vec.hpp"
+#include "rs_wide.hpp"
 
 namespace rs {
 namespace lb {
@@ -57,6 +59,11 @@ using mf::lane;
 using mf::MT;
 using mf::v4_t;
 using mf::wave;
+using cw::BEYOND;
+using cw::Buf;
+using cw::buf;
+using cw::buf_get;
+using cw::buf_st;
 
 constexpr int SPIN_LIMIT = 1 << 26;
 
@@ -79,16 +86,16 @@ __device__ __forceinline__ TreeItem load_item(const TreeItem *tab, int i) {
 // ------------------------------------------------------------- workspace
 // Matrices of one work unit, row-major, elements of T:
 //   P V Qh F AV (n x n) | AB W (n x (n+m)) | H HY (n x m) | BV X (m x n) |
-//   G Li LiT Lp (m x m) | D DT (16 x 16) | Tm (m x 16)
+//   G (m x m)
 template <class T>
 struct WS {
     int n, m, nw;
-    T *P, *V, *Qh, *F, *AV, *AB, *W, *H, *HY, *BV, *X, *G, *Li, *LiT, *Lp, *D, *DT, *Tm;
+    T *P, *V, *Qh, *F, *AV, *AB, *W, *H, *HY, *BV, *X, *G;
     __device__ void bind(T *b, int n_, int m_) {
         n = n_;
         m = m_;
         nw = n + m;
-        const int64_t nn = (int64_t)n * n, nm = (int64_t)n * m, mm = (int64_t)m * m, nwn = (int64_t)n * nw;
+        const int64_t nn = (int64_t)n * n, nm = (int64_t)n * m, nwn = (int64_t)n * nw;
         P = b;
         V = P + nn;
         Qh = V + nn;
@@ -101,12 +108,6 @@ struct WS {
         BV = HY + nm;
         X = BV + nm;
         G = X + nm;
-        Li = G + mm;
-        LiT = Li + mm;
-        Lp = LiT + mm;
-        D = Lp + mm;
-        DT = D + 256;
-        Tm = DT + 256;
     }
 };
 
@@ -116,7 +117,7 @@ size_t large_unit_bytes(int nx, int nu) {
     // the master levels factor n x n blocks (m = n), so a unit holds the
     // larger of the two working sets
     auto elems = [](int64_t n, int64_t m) {
-        return 5 * n * n + 2 * n * (n + m) + 4 * n * m + 4 * m * m + 512 + 16 * m;
+        return 5 * n * n + 2 * n * (n + m) + 4 * n * m + m * m;
     };
     const int64_t e = std::max(elems(nx, nu), elems(nx, nx));
     return (size_t)(((e * 8) + 255) & ~(int64_t)255);
@@ -130,14 +131,6 @@ namespace lb {
 constexpr int LB_MT = 512;
 __device__ __forceinline__ int nthr() { return (int)blockDim.x; }
 __device__ __forceinline__ int nwav() { return (int)(blockDim.x >> 6); }
-
-// Orders one wavefront's global-memory traffic (stores of some lanes before
-// loads of others).
-__device__ __forceinline__ void wave_gfence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // Where the result of a large-block product goes: element (i, j) of
 // v = sgn * opA(A) opB(B) + D is stored to C and, when given, to the record R;
@@ -185,181 +178,195 @@ __device__ __forceinline__ void put(const Ep<T> &e, int i, int j, T c) {
     }
 }
 
-// Operand panels of the large-block products, staged in LDS: a 16-wide
-// inner panel of A (up to 128 rows, row pitch 17) and of B (16 rows of up to
-// 128 columns, pitch 144), shared by every wavefront of the workgroup.  The
-// pitches keep the MFMA operand reads nearly free of bank conflicts: rows of
-// the A panel 17 doubles apart fall on distinct banks for the 16 lanes of a
-// row group, and the two row groups of a half-wave read B rows 32 banks apart.
+// Operand panels of the large-block products, staged in LDS: a 16-wide inner
+// panel of A (128 rows, row pitch 17) and of B (16 rows of 128 columns, pitch
+// 144), shared by every wavefront of the workgroup, twice.  The pitches keep
+// the MFMA operand reads nearly free of bank conflicts: rows of the A panel 17
+// doubles apart fall on distinct banks for the 16 lanes of a row group, and
+// the two row groups of a half-wave read B rows 32 banks apart.
 constexpr int GP_K = 16, GP_M = 128, GP_N = 128, GP_AP = GP_K + 1, GP_BP = GP_N + 16;
 constexpr int GP_ELEMS = GP_M * GP_AP + GP_K * GP_BP;
 // products with fewer 16 x 16 tiles than this take the per-tile form
 constexpr int GP_MIN_TILES = 32;
-__shared__ double gp_sm[GP_ELEMS];
+// LDS elements of a matrix kernel: the two pairs of panels (PANEL), or G at
+// pitch PU while it is factored
+template <int PU, bool PANEL>
+constexpr int lds_elems() {
+    return PANEL && 2 * GP_ELEMS > PU * PU ? 2 * GP_ELEMS : PU * PU;
+}
+template <class T>
+using LdsPtr = __attribute__((address_space(3))) T *;
 
-// C = opA(A) opB(B): M x N (M <= 128, any N; with `lower` square and
-// N <= 128), inner size K; the result goes through the epilogue `ep`.
-// opA(i,k) = TA ? A[k*lda+i] : A[i*lda+k], opB(k,j) = TB ? B[j*ldb+k] :
-// B[k*ldb+j].  The result is formed in column chunks of up to 128; for each
-// chunk the workgroup walks the inner dimension in panels of 16: its threads
-// load the A and B panels (zero-padded to whole 16 x 16 tiles, loads laid out
-// along the operand's contiguous direction) into LDS, and each wavefront
-// accumulates its 16 x 16 tiles (tile t goes to wave t mod 8, at most 8 per
-// wave) from there while the next panel's loads are in flight: one memory
-// round trip per panel of 16 for every tile of the chunk at once, where a
-// tile that read its own operand strips needed one per 32 of inner size.
-// With `lower` only the tiles on and below the diagonal are formed and only
-// the elements with i >= j are put.  Small products (fewer than
+// C = opA(A) opB(B): M x N (M, N <= 128; with `lower` square), inner size K;
+// the result goes through the epilogue `ep`.  opA(i,k) = TA ? A[k*lda+i] :
+// A[i*lda+k], opB(k,j) = TB ? B[j*ldb+k] : B[k*ldb+j].  The workgroup walks
+// the inner dimension in panels of 16: its threads load the A and B panels
+// (loads laid out along the operand's contiguous direction, zero outside by
+// buffer bounds) into one of two LDS pairs, and each wavefront accumulates its
+// 16 x 16 tiles (tile t goes to wave t mod 8, at most 8 per wave) from there
+// while the next panel's loads are in flight, with one barrier per panel.  The
+// addend D enters as the accumulators' start: all its elements are in flight
+// at once with the first panel.  (Added element by element behind the product,
+// each read waiting for the store before it, it took longer than the product:
+// 128 x 128 x 64 with an addend 107 k cycles, of which 16 k on the matrix
+// cores.)  With `lower` only the tiles on and below the diagonal are formed
+// and only the elements with i >= j are put.  Small products (fewer than
 // GP_MIN_TILES tiles, such as G at n_u <= 64) skip the panels, and each wave
 // reads its tiles' operand strips itself.  One out-of-line body per operand
 // layout keeps the stage's code within the instruction cache.  Every thread
-// of the workgroup must call it (it synchronizes the workgroup).
+// of the workgroup must call it; it synchronizes LDS, not global memory.
 template <bool TA, bool TB, class T>
-__device__ __attribute__((noinline)) void gemm_panel(int M, int N, int K, const T *A, int lda, const T *B, int ldb,
-                                                     bool lower, Ep<T> ep) {
-    static_assert(LB_MT == 512, "eight wavefronts: at most eight 16 x 16 tiles of a chunk per wave");
+__device__ __attribute__((noinline)) void gemm_panel(LdsPtr<T> sm, int M, int N, int K, const T *A, int lda, const T *B,
+                                                     int ldb, bool lower, Ep<T> ep) {
+    static_assert(LB_MT == 512, "eight wavefronts: at most eight 16 x 16 tiles per wave");
     constexpr int QMAX = (GP_M / 16) * (GP_N / 16) / (LB_MT / 64);
     constexpr int EA = GP_M * GP_K / LB_MT, EB = GP_K * GP_N / LB_MT;
-    const auto gA = gview(A);
-    const auto gB = gview(B);
-    T *As = reinterpret_cast<T *>(gp_sm), *Bs = As + GP_M * GP_AP;
+    constexpr uint32_t SZ = sizeof(T);
+    M = uni(M);
+    N = uni(N);
+    K = uni(K);
+    lda = uni(lda);
+    ldb = uni(ldb);
+    const bool low = uni(lower) != 0, neg = uni(ep.sgn < T(0)) != 0, sym = uni(ep.sym) != 0;
+    const int ldc = uni(ep.ldc), ldd = uni(ep.ldd), ldr = uni(ep.ldr);
+    const Buf bA = buf(A, TA ? (K - 1) * lda + M : (M - 1) * lda + K);
+    const Buf bB = buf(B, TB ? (N - 1) * ldb + K : (K - 1) * ldb + N);
+    const Buf bD64 = buf(ep.D64, (M - 1) * ldd + N), bDT = buf(ep.DT, (M - 1) * ldd + N);
+    const Buf bC = buf(ep.C, (M - 1) * ldc + N), bR = buf(ep.R, (M - 1) * ldr + N);
+    const bool d64 = uni_ptr(ep.D64) != nullptr, hasC = uni_ptr(reinterpret_cast<const double *>(ep.C)) != nullptr,
+               dt = uni_ptr(reinterpret_cast<const double *>(ep.DT)) != nullptr,
+               hasR = uni_ptr(reinterpret_cast<const double *>(ep.R)) != nullptr;
     const int tid = threadIdx.x, w = wave(), l = lane(), r16 = l & 15, k4 = l >> 4;
-    const int tm = (M + 15) >> 4, Mp = 16 * tm;
-    if ((lower ? tm * (tm + 1) / 2 : tm * ((N + 15) >> 4)) < GP_MIN_TILES) {
+    const int tm = (M + 15) >> 4, tn = (N + 15) >> 4, nt = low ? tm * (tm + 1) / 2 : tm * tn;
+    auto tile = [&](int t, int &ti, int &tj) {
+        if (low) {
+            mf::lower_tile(t, ti, tj);
+        } else {
+            ti = t / tn;
+            tj = t - ti * tn;
+        }
+    };
+    // element offset of result row r of a lane in tile (ti, tj), or none
+    auto at = [&](int ti, int tj, int r, int ld) {
+        const int i = mf::trow<T>(ti, r), j = mf::tcol(tj);
+        return i < M && j < N && (!low || i >= j) ? (uint32_t)(i * ld + j) : ~0u;
+    };
+    auto byte = [](uint32_t e, uint32_t size) { return e == ~0u ? BEYOND : e * size; };
+    auto start = [&](int ti, int tj) {
+        v4_t<T> v = mf::zero4<T>();
+        if (d64) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = (T)buf_get<double>(bD64, byte(at(ti, tj, r, ldd), 8));
+        } else if (dt) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = buf_get<T>(bDT, byte(at(ti, tj, r, ldd), SZ));
+        }
+        if (neg)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = -v[r];
+        return v;
+    };
+    auto finish = [&](int ti, int tj, v4_t<T> v) {
+        if (neg)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = -v[r];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = mf::trow<T>(ti, r), j = mf::tcol(tj);
+            const bool in = i < M && j < N && (!low || i >= j);
+            if (hasC) {
+                buf_st(bC, in ? SZ * (uint32_t)(i * ldc + j) : BEYOND, v[r]);
+                if (sym) buf_st(bC, in ? SZ * (uint32_t)(j * ldc + i) : BEYOND, v[r]);
+            }
+            if (hasR) {
+                buf_st(bR, in ? SZ * (uint32_t)(i * ldr + j) : BEYOND, v[r]);
+                if (sym) buf_st(bR, in ? SZ * (uint32_t)(j * ldr + i) : BEYOND, v[r]);
+            }
+        }
+    };
+    if (nt < GP_MIN_TILES) {
         // small product: each wave forms its tiles from operand strips read
         // straight from memory (no barriers; the panels would cost more in
         // synchronization than they save)
-        const int tn = (N + 15) >> 4, nt = lower ? tm * (tm + 1) / 2 : tm * tn;
         for (int t = w; t < nt; t += LB_MT / 64) {
             int ti, tj;
-            if (lower) {
-                mf::lower_tile(t, ti, tj);
-            } else {
-                ti = t / tn;
-                tj = t - ti * tn;
-            }
+            tile(t, ti, tj);
             const int i = 16 * ti + r16, j = 16 * tj + r16;
             const bool iv = i < M, jv = j < N;
-            v4_t<T> acc = mf::zero4<T>();
-#pragma unroll 2
-            for (int k0 = 0; k0 < K; k0 += 16) {
-                T a[4], b[4];
+            v4_t<T> acc = start(ti, tj);
+            for (int k0 = 0; k0 < K; k0 += 32) {
+                T a[8], b[8];
 #pragma unroll
-                for (int s = 0; s < 4; ++s) {
+                for (int s = 0; s < 8; ++s) {
                     const int k = k0 + 4 * s + k4;
-                    a[s] = (iv && k < K) ? (TA ? gA[(int64_t)k * lda + i] : gA[(int64_t)i * lda + k]) : T(0);
-                    b[s] = (jv && k < K) ? (TB ? gB[(int64_t)j * ldb + k] : gB[(int64_t)k * ldb + j]) : T(0);
+                    a[s] = buf_get<T>(bA, iv && k < K ? SZ * (uint32_t)(TA ? k * lda + i : i * lda + k) : BEYOND);
+                    b[s] = buf_get<T>(bB, jv && k < K ? SZ * (uint32_t)(TB ? j * ldb + k : k * ldb + j) : BEYOND);
                 }
 #pragma unroll
-                for (int s = 0; s < 4; ++s) acc = MT<T>::mfma(a[s], b[s], acc);
+                for (int s = 0; s < 8; ++s) acc = MT<T>::mfma(a[s], b[s], acc);
             }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int ii = mf::trow<T>(ti, r), jj = mf::tcol(tj);
-                if (ii < M && jj < N && (!lower || ii >= jj)) put(ep, ii, jj, acc[r]);
-            }
+            finish(ti, tj, acc);
         }
         return;
     }
-    for (int n0 = 0; n0 < N; n0 += GP_N) {
-        const int NC = N - n0 < GP_N ? N - n0 : GP_N, tn = (NC + 15) >> 4, Np = 16 * tn;
-        const int nt = lower ? tm * (tm + 1) / 2 : tm * tn;
-        int ti[QMAX], tj[QMAX];
+    int ti[QMAX], tj[QMAX];
+    v4_t<T> acc[QMAX];
 #pragma unroll
-        for (int q = 0; q < QMAX; ++q) {
-            const int t = w + 8 * q;
-            if (lower) {
-                mf::lower_tile(t < nt ? t : 0, ti[q], tj[q]);
-            } else {
-                ti[q] = t / tn;
-                tj[q] = t - ti[q] * tn;
-            }
+    for (int q = 0; q < QMAX; ++q) {
+        tile(w + 8 * q < nt ? w + 8 * q : 0, ti[q], tj[q]);
+        ti[q] = uni(ti[q]);
+        tj[q] = uni(tj[q]);
+    }
+    T ra[EA], rb[EB];
+    // panel element e of A: (row, inner index) along A's contiguous
+    // direction; of B: (inner index, column) along B's
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < EA; ++u) {
+            const int e = tid + u * LB_MT, m = TA ? e & 127 : e >> 4, k = k0 + (TA ? e >> 7 : e & 15);
+            ra[u] = buf_get<T>(bA, m < M && k < K ? SZ * (uint32_t)(TA ? k * lda + m : m * lda + k) : BEYOND);
         }
-        v4_t<T> acc[QMAX];
 #pragma unroll
-        for (int q = 0; q < QMAX; ++q) acc[q] = mf::zero4<T>();
-        // panel element e of A: (row, inner index) along A's contiguous
-        // direction; of B: (inner index, column) along B's
-        auto a_at = [&](int e, int &m, int &kk) {
-            if (TA) {
-                kk = e / Mp;
-                m = e - kk * Mp;
-            } else {
-                m = e >> 4;
-                kk = e & 15;
-            }
-        };
-        auto b_at = [&](int e, int &kk, int &n) {
-            if (TB) {
-                n = e >> 4;
-                kk = e & 15;
-            } else {
-                kk = e / Np;
-                n = e - kk * Np;
-            }
-        };
-        T ra[EA], rb[EB];
-        auto fetch = [&](int k0) {
-#pragma unroll
-            for (int u = 0; u < EA; ++u) {
-                const int e = tid + u * LB_MT;
-                int m, kk;
-                a_at(e, m, kk);
-                const int k = k0 + kk;
-                ra[u] = (e < Mp * GP_K && m < M && k < K) ? (TA ? gA[(int64_t)k * lda + m] : gA[(int64_t)m * lda + k])
-                                                          : T(0);
-            }
-#pragma unroll
-            for (int u = 0; u < EB; ++u) {
-                const int e = tid + u * LB_MT;
-                int kk, n;
-                b_at(e, kk, n);
-                const int k = k0 + kk, j = n0 + n;
-                rb[u] = (e < Np * GP_K && n < NC && k < K) ? (TB ? gB[(int64_t)j * ldb + k] : gB[(int64_t)k * ldb + j])
-                                                           : T(0);
-            }
-        };
-        fetch(0);
-        for (int k0 = 0; k0 < K; k0 += GP_K) {
-            __syncthreads();      // every wave is done with the previous panel
-#pragma unroll
-            for (int u = 0; u < EA; ++u) {
-                const int e = tid + u * LB_MT;
-                int m, kk;
-                a_at(e, m, kk);
-                if (e < Mp * GP_K) As[m * GP_AP + kk] = ra[u];
-            }
-#pragma unroll
-            for (int u = 0; u < EB; ++u) {
-                const int e = tid + u * LB_MT;
-                int kk, n;
-                b_at(e, kk, n);
-                if (e < Np * GP_K) Bs[kk * GP_BP + n] = rb[u];
-            }
-            __syncthreads();
-            if (k0 + GP_K < K) fetch(k0 + GP_K);
-#pragma unroll
-            for (int q = 0; q < QMAX; ++q) {
-                if (w + 8 * q < nt) {
-                    const T *ap = As + (16 * ti[q] + r16) * GP_AP + k4;
-                    const T *bp = Bs + k4 * GP_BP + 16 * tj[q] + r16;
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) acc[q] = MT<T>::mfma(ap[4 * s], bp[4 * s * GP_BP], acc[q]);
-                }
-            }
+        for (int u = 0; u < EB; ++u) {
+            const int e = tid + u * LB_MT, n = TB ? e >> 4 : e & 127, k = k0 + (TB ? e & 15 : e >> 7);
+            rb[u] = buf_get<T>(bB, n < N && k < K ? SZ * (uint32_t)(TB ? n * ldb + k : k * ldb + n) : BEYOND);
         }
+    };
+    fetch(0);
+#pragma unroll
+    for (int q = 0; q < QMAX; ++q) acc[q] = w + 8 * q < nt ? start(ti[q], tj[q]) : mf::zero4<T>();
+    LdsPtr<T> As = sm, Bs = sm + GP_M * GP_AP;
+    int other = GP_ELEMS;                 // offset of the other pair of panels
+    for (int k0 = 0; k0 < K; k0 += GP_K) {
+#pragma unroll
+        for (int u = 0; u < EA; ++u) {
+            const int e = tid + u * LB_MT, m = TA ? e & 127 : e >> 4, kk = TA ? e >> 7 : e & 15;
+            As[m * GP_AP + kk] = ra[u];
+        }
+#pragma unroll
+        for (int u = 0; u < EB; ++u) {
+            const int e = tid + u * LB_MT, n = TB ? e >> 4 : e & 127, kk = TB ? e & 15 : e >> 7;
+            Bs[kk * GP_BP + n] = rb[u];
+        }
+        lds_sync();       // the panel is complete, and the other pair is free
+        if (k0 + GP_K < K) fetch(k0 + GP_K);
 #pragma unroll
         for (int q = 0; q < QMAX; ++q) {
             if (w + 8 * q < nt) {
+                const auto ap = As + (16 * ti[q] + r16) * GP_AP + k4;
+                const auto bp = Bs + k4 * GP_BP + 16 * tj[q] + r16;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int i = mf::trow<T>(ti[q], r), j = n0 + mf::tcol(tj[q]);
-                    if (i < M && j < N && (!lower || i >= j)) put(ep, i, j, acc[q][r]);
-                }
+                for (int s = 0; s < 4; ++s) acc[q] = MT<T>::mfma(ap[4 * s], bp[4 * s * GP_BP], acc[q]);
             }
         }
+        As += other;
+        Bs += other;
+        other = -other;
     }
-    __syncthreads();      // the results are visible to the workgroup
+#pragma unroll
+    for (int q = 0; q < QMAX; ++q)
+        if (w + 8 * q < nt) finish(ti[q], tj[q], acc[q]);
+    lds_sync();           // the panels are free for the next product
 }
 
 // Stages with n_x <= 64 (products of at most 24 tiles), inline with the
@@ -465,14 +472,14 @@ __device__ __forceinline__ void gemm_big(int M, int N, int K, const T *A, int ld
         gemm_tile<TA, TB>(M, N, K, A, lda, B, ldb, lower, epi);
 }
 template <bool BF, bool TA, bool TB, class T>
-__device__ __forceinline__ void gemm_big_panel(int M, int N, int K, const T *A, int lda, const T *B, int ldb,
+__device__ __forceinline__ void gemm_big_panel(LdsPtr<T> sm, int M, int N, int K, const T *A, int lda, const T *B, int ldb,
                                                bool lower, const Ep<T> &ep) {
     if constexpr (BF)
         gemm_bf16<TA, TB>(M, N, K, A, lda, B, ldb, lower, [&](int i, int j, float c) {
             if (!lower || i >= j) put(ep, i, j, c);
         });
     else
-        gemm_panel<TA, TB>(M, N, K, A, lda, B, ldb, lower, ep);
+        gemm_panel<TA, TB>(sm, M, N, K, A, lda, B, ldb, lower, ep);
 }
 
 // Epilogue descriptors: store to C (leading dimension ldc); plus a
@@ -485,104 +492,96 @@ __device__ __forceinline__ Ep<T> to(T *C, int ldc) {
     return e;
 }
 
-// acc += opA(A) opB(B) for one 16 x 16 x 16 block with only the first ri
-// rows, rk inner indices and rj columns taken (the rest read as zero).
-// opA(i,k) = A[i*lda+k]; opB(k,j) = TB ? B[j*ldb+k] : B[k*ldb+j].
-template <bool TB, class T>
-__device__ __forceinline__ v4_t<T> blk16(v4_t<T> acc, const T *A, int lda, const T *B, int ldb, int ri, int rk,
-                                         int rj) {
-    const int l = lane(), r16 = l & 15, k4 = l >> 4;
-    T a[4], b[4];
+// Cholesky factorization G = L L' ("a factorization of G", Alg. 1) and the
+// explicit inverse (m <= PU), in LDS, by the whole workgroup: right-looking
+// over 16-wide blocks, the diagonal block (identity past m) factored and
+// inverted by wave 0 (chol_block), L_ik' = L_kk^{-1} G_ik' and the trailing
+// updates G_ij -= L_ik L_jk' one tile per wave; wave 0 updates the next
+// diagonal block first and factors it behind the others' tiles.  Then block
+// row by block row of the inverse, X_ij = -X_ii sum_k L_ik X_kj.  L^{-1} and L^{-T}
+// go straight to their records Li and LiT (zeros above / below the diagonal),
+// from which the products read them.  (With every block passing through global
+// memory 100 k cycles at m = 64 and 265 k at m = 128; here 21 and 57 k.)
+// *bad is set if a pivot failed.  Every thread calls it; it ends with a
+// workgroup barrier.
+template <int PU, class T>
+__device__ __forceinline__ void chol_lds(T *S, int m, T *Li, T *LiT, int *bad) {
+    using namespace cw;
+    const int nb = (m + 15) >> 4, tid = threadIdx.x, w = wave(), nw = LB_MT / 64;
+    const Ln<T> L;
+    if (w == 0 && chol_block<PU>(S, 0, m) && lane() == 0) *bad = 1;
+    lds_sync();
+    for (int kb = 0; kb + 1 < nb; ++kb) {
+        const int np = nb - kb - 1, nt = np * (np + 1) / 2;
+        for (int t = w; t < np; t += nw) {
+            v4_t<T> acc = mf::zero4<T>();
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const int k = 4 * s + k4;
-        a[s] = (r16 < ri && k < rk) ? A[(int64_t)r16 * lda + k] : T(0);
-        b[s] = (r16 < rj && k < rk) ? (TB ? B[(int64_t)r16 * ldb + k] : B[(int64_t)k * ldb + r16]) : T(0);
-    }
-#pragma unroll
-    for (int s = 0; s < 4; ++s) acc = MT<T>::mfma(a[s], b[s], acc);
-    return acc;
-}
-
-// Blocked Cholesky factorization G = L L' ("a factorization of G", Alg. 1)
-// and the explicit inverse (any m <= 128).  Right-looking over 16-wide block
-// columns: the diagonal block (padded with the identity past m) is factored
-// and inverted by one wavefront (chol_inv16), the panel below it is
-// L_ik = G_ik L_kk^{-T}, and the trailing lower blocks are updated
-// G_ij -= L_ik L_jk'.  The inverse follows block row by block row:
-// X_ii = L_ii^{-1}, X_ij = -X_ii sum_{k=j}^{i-1} L_ik X_kj.  On return
-// Li = L^{-1} and LiT = L^{-T} (row-major, zeros above / below the
-// diagonal); G is overwritten.  *bad is set if a pivot failed.  Every thread
-// must call it; it ends with a workgroup barrier.
-template <class T>
-__device__ void chol_inv(WS<T> &S, int m, int *bad) {
-    const int nb = (m + 15) >> 4, tid = threadIdx.x, w = wave(), l = lane();
-    T *G = S.G, *Li = S.Li, *Lp = S.Lp, *D = S.D, *DT = S.DT;
-    auto rows = [&](int b) { return m - 16 * b < 16 ? m - 16 * b : 16; };
-    for (int kb = 0; kb < nb; ++kb) {
-        const int rk = rows(kb);
-        if (w == 0) {
-            for (int e = l; e < 256; e += 64) {
-                const int i = e / 16, j = e % 16;
-                D[e] = (i < rk && j < rk) ? G[(int64_t)(16 * kb + i) * m + 16 * kb + j] : (i == j ? T(1) : T(0));
-            }
-            wave_gfence();
-            const int f = mf::chol_inv16(D, DT);      // D <- L_kk^{-1}, DT <- L_kk^{-T}
-            if (f && l == 0) *bad = 1;
+            for (int r = 0; r < 4; ++r)
+                acc = MT<T>::mfma(ldR<PU>(L, S, kb, kb, r), ldR<PU>(L, S, kb + 1 + t, kb, r), acc);
+            cw::put<PU, 4>(L, S, kb, kb + 1 + t, acc);
         }
-        __syncthreads();
-        // panel below the diagonal block, then the trailing lower blocks
-        const int np = nb - kb - 1;
-        for (int t = w; t < np; t += nwav()) {
-            const int ib = kb + 1 + t, ri = rows(ib);
-            const v4_t<T> acc = blk16<false>(mf::zero4<T>(), G + (int64_t)16 * ib * m + 16 * kb, m, DT, 16, ri, rk, rk);
-            mf::tile_for<T>(0, 0, [&](int r, int i, int j) {
-                if (i < ri && j < rk) Lp[(int64_t)(16 * ib + i) * m + 16 * kb + j] = acc[r];
-            });
-        }
-        for (int e = tid; e < 256; e += nthr()) {
-            const int i = e / 16, j = e % 16;
-            if (i < rk && j < rk) Li[(int64_t)(16 * kb + i) * m + 16 * kb + j] = D[e];
-        }
-        __syncthreads();
-        const int nt = np * (np + 1) / 2;
-        for (int t = w; t < nt; t += nwav()) {
+        lds_sync();
+        for (int t = w; t < nt; t += w == 0 ? nt : nw - 1) {
             int a, b;
             mf::lower_tile(t, a, b);
-            const int ib = kb + 1 + a, jb = kb + 1 + b, ri = rows(ib), rj = rows(jb);
-            const v4_t<T> acc = blk16<true>(mf::zero4<T>(), Lp + (int64_t)16 * ib * m + 16 * kb, m,
-                                            Lp + (int64_t)16 * jb * m + 16 * kb, m, ri, rk, rj);
-            mf::tile_for<T>(0, 0, [&](int r, int i, int j) {
-                if (i < ri && j < rj) G[(int64_t)(16 * ib + i) * m + 16 * jb + j] -= acc[r];
-            });
-        }
-        __syncthreads();
-    }
-    // block rows of the inverse
-    for (int ib = 1; ib < nb; ++ib) {
-        const int ri = rows(ib);
-        for (int jb = w; jb < ib; jb += nwav()) {
+            const int ib = kb + 1 + a, jb = kb + 1 + b;
             v4_t<T> acc = mf::zero4<T>();
-            for (int kb = jb; kb < ib; ++kb)
-                acc = blk16<false>(acc, Lp + (int64_t)16 * ib * m + 16 * kb, m, Li + (int64_t)16 * kb * m + 16 * jb, m,
-                                   ri, 16, 16);
-            T *tm = S.Tm + 256 * jb;
-            mf::tile_for<T>(0, 0, [&](int r, int i, int j) { tm[i * 16 + j] = acc[r]; });
-            wave_gfence();
-            acc = blk16<false>(mf::zero4<T>(), Li + (int64_t)16 * ib * m + 16 * ib, m, tm, 16, ri, ri, 16);
-            mf::tile_for<T>(0, 0, [&](int r, int i, int j) {
-                if (i < ri) Li[(int64_t)(16 * ib + i) * m + 16 * jb + j] = -acc[r];
-            });
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc = MT<T>::mfma(ldN<PU>(L, S, kb, ib, r), ldN<PU>(L, S, kb, jb, r), acc);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) S[at<PU>(16 * ib + L.row(r), 16 * jb + L.c)] -= acc[r];
         }
-        __syncthreads();
+        if (w == 0) {
+            mf::wave_fence();
+            if (chol_block<PU>(S, kb + 1, m - 16 * (kb + 1)) && lane() == 0) *bad = 1;
+        }
+        lds_sync();
     }
-    for (int e = tid; e < m * m; e += nthr()) {
-        const int i = e / m, j = e - (e / m) * m;
-        const T v = j <= i ? Li[e] : T(0);
-        Li[e] = v;
-        S.LiT[(int64_t)j * m + i] = v;
+    for (int ib = 1; ib < nb; ++ib) {
+        for (int jb = w; jb < ib; jb += nw) {
+            v4_t<T> s = mf::zero4<T>(), x = mf::zero4<T>();
+            for (int kb = jb; kb < ib; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    s = MT<T>::mfma(ldN<PU>(L, S, kb, ib, r), ldN<PU>(L, S, kb, jb, r), s);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x = MT<T>::mfma(ldR<PU>(L, S, ib, ib, r), s[r], x);
+            cw::put<PU, 4>(L, S, ib, jb, v4_t<T>{-x[0], -x[1], -x[2], -x[3]});
+        }
+        lds_sync();
+    }
+    const Buf bL = buf(Li, m * m), bT = buf(LiT, m * m);
+    for (int e = tid; e < m * PU; e += LB_MT) {
+        const int i = e / PU, k = e % PU;
+        const uint32_t o = k < m ? (uint32_t)sizeof(T) * (uint32_t)(i * m + k) : BEYOND;
+        buf_st(bL, o, k <= i ? S[at<PU>(i, k)] : T(0));
+        buf_st(bT, o, i <= k ? S[at<PU>(k, i)] : T(0));
     }
     __syncthreads();
+}
+
+// The same with G (m x m, row-major, complete) read from global memory.
+template <int PU, class T>
+__device__ __forceinline__ void chol_inv(T *S, const T *G, int m, T *Li, T *LiT, int *bad) {
+    using cw::at;
+    const int nb = (m + 15) >> 4, tid = threadIdx.x;
+    constexpr int UN = PU * PU / LB_MT < 16 ? PU * PU / LB_MT : 16;
+    const Buf bG = buf(G, m * m);
+    for (int e0 = tid; e0 < 16 * nb * PU; e0 += UN * LB_MT) {
+        T v[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int e = e0 + u * LB_MT, i = e / PU, k = e % PU;
+            v[u] = buf_get<T>(bG, i < m && k < m ? (uint32_t)sizeof(T) * (uint32_t)(i * m + k) : BEYOND);
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int e = e0 + u * LB_MT, i = e / PU, k = e % PU;
+            if (i < 16 * nb) S[at<PU>(i, k)] = (i >= m && i == k) ? T(1) : v[u];
+        }
+    }
+    lds_sync();
+    chol_lds<PU>(S, m, Li, LiT, bad);
 }
 
 // Where a pass's per-stage factors go.
@@ -605,14 +604,8 @@ struct LeafOut {
     __device__ T *Krec(int s) const { return at(s) + LeafRec{n, m}.K(); }
     __device__ T *Vrec(int s) const { return up ? at(s) + LeafRec{n, m}.V() : nullptr; }
     __device__ T *Ltrec(int s) const { return up ? at(s) + LeafRec{n, m}.Lt() : nullptr; }
-    __device__ void L(int s, const T *Li, const T *LiT) const {
-        T *d = at(s);
-        const LeafRec R{n, m};
-        for (int e = threadIdx.x; e < m * m; e += nthr()) {
-            d[R.L() + e] = Li[e];
-            d[R.LT() + e] = LiT[e];
-        }
-    }
+    __device__ T *Lrec(int s) const { return at(s) + LeafRec{n, m}.L(); }
+    __device__ T *LTrec(int s) const { return at(s) + LeafRec{n, m}.LT(); }
 };
 
 // Master-slot factors (SlotLayout): up pass uK, uP, uV, uL, uLT (and, for
@@ -641,15 +634,8 @@ struct SlotOut {
     __device__ double *Krec(int s) const { return at(s) + (up ? SlotLayout{n}.uK() : SlotLayout{n}.K()); }
     __device__ double *Vrec(int s) const { return up ? at(s) + SlotLayout{n}.uV() : nullptr; }
     __device__ double *Ltrec(int s) const { return lt ? at(s) + SlotLayout{n}.dL() : nullptr; }
-    __device__ void L(int s, const double *Li, const double *LiT) const {
-        double *d = at(s);
-        const SlotLayout SL{n};
-        const int oL = up ? SL.uL() : SL.dL(), oT = up ? SL.uLT() : SL.dLT();
-        for (int e = threadIdx.x; e < n * n; e += nthr()) {
-            d[oL + e] = Li[e];
-            d[oT + e] = LiT[e];
-        }
-    }
+    __device__ double *Lrec(int s) const { return at(s) + (up ? SlotLayout{n}.uL() : SlotLayout{n}.dL()); }
+    __device__ double *LTrec(int s) const { return at(s) + (up ? SlotLayout{n}.uLT() : SlotLayout{n}.dLT()); }
 };
 
 // [A B] of a stage into the workspace (n x (n + m), row-major, element
@@ -676,14 +662,15 @@ __device__ __forceinline__ void load_ab(WS<T> &S, const StageSrc &src) {
 // only.  RED: Alg. 4 (state P, V, Q_w_hat in the workspace); otherwise Alg. 1
 // from the P in the workspace.  pre(s) runs before stage s and sees P_{s+1}.
 // BF: P [A B], A'W_A, A'W_B and B'W_B (A'PA, A'PB, B'PB) on BF16 operands.
-template <class T, bool RED, bool BF, class Get, class Pre, class Out>
-__device__ void mpass_tile(WS<T> &S, Get get, int count, int32_t *info, int inst, int stage_base, int fail_code, Pre pre,
+template <class T, bool RED, bool BF, int PU, class Get, class Pre, class Out>
+__device__ __forceinline__ void mpass_tile(T *sm, WS<T> &S, Get get, int count, int32_t *info, int inst, int stage_base, int fail_code, Pre pre,
                       const Out &out, int *bad) {
     static_assert(!BF || sizeof(T) == 4, "BF16 products accumulate in FP32");
     const int n = S.n, m = S.m, nw = S.nw, tid = threadIdx.x;
     count = uni(count);
     for (int s = count - 1; s >= 0; --s) {
         pre(s);
+        T *Li = out.Lrec(s), *LiT = out.LTrec(s);
         const StageSrc src = get(s);
         for (int e = tid; e < n * nw; e += nthr()) {
             const int i = e / nw, j = e - (e / nw) * nw;
@@ -718,16 +705,15 @@ __device__ void mpass_tile(WS<T> &S, Get get, int count, int32_t *info, int inst
             }
         });
         __syncthreads();
-        chol_inv(S, m, bad);
+        chol_inv<PU>(sm, S.G, m, Li, LiT, bad);
         if (tid == 0 && *bad) {
             record_failure(info, inst, fail_code, stage_base < 0 ? -1 : stage_base + s);
             *bad = 0;
         }
-        out.L(s, S.Li, S.LiT);
         // Y' = H L^{-T}; Alg. 4: X = L^{-1} B'V
-        gemm_tile<false, false>(n, m, m, S.H, m, S.LiT, m, false, [&](int i, int j, T c) { S.HY[(int64_t)i * m + j] = c; });
+        gemm_tile<false, false>(n, m, m, S.H, m, LiT, m, false, [&](int i, int j, T c) { S.HY[(int64_t)i * m + j] = c; });
         if constexpr (RED) {
-            gemm_tile<false, false>(m, n, m, S.Li, m, S.BV, n, false, [&](int i, int j, T c) { S.X[(int64_t)i * n + j] = c; });
+            gemm_tile<false, false>(m, n, m, Li, m, S.BV, n, false, [&](int i, int j, T c) { S.X[(int64_t)i * n + j] = c; });
         }
         __syncthreads();
         // P = F - Y'Y (symmetric), K = -L^{-T} Y
@@ -740,7 +726,7 @@ __device__ void mpass_tile(WS<T> &S, Get get, int count, int32_t *info, int inst
                 out.P(s, j, i, v);
             }
         });
-        gemm_tile<false, true>(m, n, m, S.LiT, m, S.HY, m, false, [&](int i, int j, T c) { out.K(s, i, j, -c); });
+        gemm_tile<false, true>(m, n, m, LiT, m, S.HY, m, false, [&](int i, int j, T c) { out.K(s, i, j, -c); });
         if constexpr (RED) {
             // Q_w_hat += X'X, V = A'V - Y'X, L_t = -L^{-T} X
             gemm_tile<true, false>(n, n, m, S.X, n, S.X, n, true, [&](int i, int j, T c) {
@@ -755,7 +741,7 @@ __device__ void mpass_tile(WS<T> &S, Get get, int count, int32_t *info, int inst
                 S.V[(int64_t)i * n + j] = v;
                 out.V(s, i, j, v);
             });
-            gemm_tile<false, false>(m, n, m, S.LiT, m, S.X, n, false, [&](int i, int j, T c) { out.Lt(s, i, j, -c); });
+            gemm_tile<false, false>(m, n, m, LiT, m, S.X, n, false, [&](int i, int j, T c) { out.Lt(s, i, j, -c); });
         }
         __syncthreads();
     }
@@ -763,22 +749,38 @@ __device__ void mpass_tile(WS<T> &S, Get get, int count, int32_t *info, int inst
 
 // The same pass with the products on LDS panels (gemm_panel) and their
 // results through epilogue descriptors: the stages with n_x > 64.
-template <class T, bool RED, bool BF, class Get, class Pre, class Out>
-__device__ void mpass_panel(WS<T> &S, Get get, int count, int32_t *info, int inst, int stage_base, int fail_code, Pre pre,
+template <class T, bool RED, bool BF, int PU, class Get, class Pre, class Out>
+__device__ __forceinline__ void mpass_panel(T *sm_, WS<T> &S, Get get, int count, int32_t *info, int inst, int stage_base, int fail_code, Pre pre,
                       const Out &out, int *bad) {
     static_assert(!BF || sizeof(T) == 4, "BF16 products accumulate in FP32");
     const int n = S.n, m = S.m, nw = S.nw, tid = threadIdx.x;
     count = uni(count);
+    const LdsPtr<T> sm = (LdsPtr<T>)sm_;
     for (int s = count - 1; s >= 0; --s) {
         pre(s);
+        T *Li = out.Lrec(s), *LiT = out.LTrec(s);
         const StageSrc src = get(s);
-        load_ab(S, src);
-        __syncthreads();
+        // FP64: the data where they are; FP32: [A B] converted
+        const T *A, *B;
+        int lda, ldb;
+        if constexpr (sizeof(T) == 8) {
+            A = src.A;
+            B = src.B;
+            lda = n;
+            ldb = m;
+        } else {
+            load_ab(S, src);
+            __syncthreads();
+            A = S.AB;
+            B = S.AB + n;
+            lda = ldb = nw;
+        }
         // W = P [A B]; Alg. 4: B'V, A'V
-        gemm_big_panel<BF, false, false>(n, nw, n, S.P, n, S.AB, nw, false, to(S.W, nw));
+        gemm_big_panel<BF, false, false>(sm, n, n, n, S.P, n, A, lda, false, to(S.W, nw));
+        gemm_big_panel<BF, false, false>(sm, n, m, n, S.P, n, B, ldb, false, to(S.W + n, nw));
         if constexpr (RED) {
-            gemm_panel<true, false>(m, n, n, S.AB + n, nw, S.V, n, false, to(S.BV, n));
-            gemm_panel<true, false>(n, n, n, S.AB, nw, S.V, n, false, to(S.AV, n));
+            gemm_panel<true, false>(sm, m, n, n, B, ldb, S.V, n, false, to(S.BV, n));
+            gemm_panel<true, false>(sm, n, n, n, A, lda, S.V, n, false, to(S.AV, n));
         }
         __syncthreads();
         // F = Qx + A'W_A (symmetric), H = Qxw + A'W_B, G = Qw + B'W_B (symmetric)
@@ -787,31 +789,30 @@ __device__ void mpass_panel(WS<T> &S, Get get, int count, int32_t *info, int ins
             e.D64 = src.Qx;
             e.ldd = n;
             e.sym = true;
-            gemm_big_panel<BF, true, false>(n, n, n, S.AB, nw, S.W, nw, true, e);
+            gemm_big_panel<BF, true, false>(sm, n, n, n, A, lda, S.W, nw, true, e);
         }
         {
             Ep<T> e = to(S.H, m);
             e.D64 = src.Qxw;
             e.ldd = m;
-            gemm_big_panel<BF, true, false>(n, m, n, S.AB, nw, S.W + n, nw, false, e);
+            gemm_big_panel<BF, true, false>(sm, n, m, n, A, lda, S.W + n, nw, false, e);
         }
         {
             Ep<T> e = to(S.G, m);
             e.D64 = src.Qw;
             e.ldd = m;
             e.sym = true;
-            gemm_big_panel<BF, true, false>(m, m, n, S.AB + n, nw, S.W + n, nw, true, e);
+            gemm_big_panel<BF, true, false>(sm, m, m, n, B, ldb, S.W + n, nw, true, e);
         }
         __syncthreads();
-        chol_inv(S, m, bad);
+        chol_inv<PU>(sm_, S.G, m, Li, LiT, bad);
         if (tid == 0 && *bad) {
             record_failure(info, inst, fail_code, stage_base < 0 ? -1 : stage_base + s);
             *bad = 0;
         }
-        out.L(s, S.Li, S.LiT);
         // Y' = H L^{-T}; Alg. 4: X = L^{-1} B'V
-        gemm_panel<false, false>(n, m, m, S.H, m, S.LiT, m, false, to(S.HY, m));
-        if constexpr (RED) gemm_panel<false, false>(m, n, m, S.Li, m, S.BV, n, false, to(S.X, n));
+        gemm_panel<false, false>(sm, n, m, m, S.H, m, LiT, m, false, to(S.HY, m));
+        if constexpr (RED) gemm_panel<false, false>(sm, m, n, m, Li, m, S.BV, n, false, to(S.X, n));
         __syncthreads();
         // P = F - Y'Y (symmetric), K = -L^{-T} Y
         {
@@ -822,12 +823,12 @@ __device__ void mpass_panel(WS<T> &S, Get get, int count, int32_t *info, int ins
             e.sym = true;
             e.R = out.Prec(s);
             e.ldr = n;
-            gemm_panel<false, true>(n, n, m, S.HY, m, S.HY, m, true, e);
+            gemm_panel<false, true>(sm, n, n, m, S.HY, m, S.HY, m, true, e);
         }
         {
             Ep<T> e = to(out.Krec(s), n);
             e.sgn = T(-1);
-            gemm_panel<false, true>(m, n, m, S.LiT, m, S.HY, m, false, e);
+            gemm_panel<false, true>(sm, m, n, m, LiT, m, S.HY, m, false, e);
         }
         if constexpr (RED) {
             // Q_w_hat += X'X, V = A'V - Y'X, L_t = -L^{-T} X
@@ -836,7 +837,7 @@ __device__ void mpass_panel(WS<T> &S, Get get, int count, int32_t *info, int ins
                 e.DT = S.Qh;
                 e.ldd = n;
                 e.sym = true;
-                gemm_panel<true, false>(n, n, m, S.X, n, S.X, n, true, e);
+                gemm_panel<true, false>(sm, n, n, m, S.X, n, S.X, n, true, e);
             }
             {
                 Ep<T> e = to(S.V, n);
@@ -845,27 +846,55 @@ __device__ void mpass_panel(WS<T> &S, Get get, int count, int32_t *info, int ins
                 e.sgn = T(-1);
                 e.R = out.Vrec(s);
                 e.ldr = n;
-                gemm_panel<false, false>(n, n, m, S.HY, m, S.X, n, false, e);
+                gemm_panel<false, false>(sm, n, n, m, S.HY, m, S.X, n, false, e);
             }
             {
                 Ep<T> e = to(out.Ltrec(s), n);
                 e.sgn = T(-1);
-                gemm_panel<false, false>(m, n, m, S.LiT, m, S.X, n, false, e);
+                gemm_panel<false, false>(sm, m, n, m, LiT, m, S.X, n, false, e);
             }
         }
         __syncthreads();
     }
 }
 
-// A pass over `count` stages: LDS-panel products out of line for the large
-// stages (BIG: n_x > 64), the inline per-tile products otherwise.
-template <class T, bool RED, bool BF, bool BIG, class Get, class Pre, class Out>
-__device__ __forceinline__ void mpass(WS<T> &S, Get get, int count, int32_t *info, int inst, int stage_base,
+// The same pass on column owners: the stages with n_x > 64 but for the BF16
+// products.
+template <class T, bool RED, int PU, class Get, class Pre, class Out>
+__device__ __forceinline__ void mpass_cols(T *sm, WS<T> &S, Get get, int count, int32_t *info, int inst, int stage_base,
+                                           int fail_code, Pre pre, const Out &out, int *bad) {
+    const int n = S.n, m = S.m;
+    count = uni(count);
+    wd::Work<T> W{S.P, S.V, S.Qh, S.HY, S.X};
+    for (int s = count - 1; s >= 0; --s) {
+        S.P = W.P;
+        pre(s);
+        const StageSrc src = get(s);
+        const wd::Rec<T> r{out.Prec(s), out.Krec(s), out.Vrec(s), out.Ltrec(s), out.Lrec(s), out.LTrec(s)};
+        wd::stage<RED, PU / 16>(sm, W, src, n, m, r, s == 0, [&](T *G, int mm, T *Li, T *LiT) {
+            chol_lds<PU>(G, mm, Li, LiT, bad);
+            if (threadIdx.x == 0 && *bad) {
+                record_failure(info, inst, fail_code, stage_base < 0 ? -1 : stage_base + s);
+                *bad = 0;
+            }
+        });
+    }
+    S.P = W.P;
+    S.V = W.V;
+}
+
+// A pass over `count` stages: column owners for the large stages (BIG: n_x >
+// 64; LDS-panel products out of line with BF16 products), the inline per-tile
+// products otherwise.  With BIG it leaves S.P and S.V pointing to the results.
+template <class T, bool RED, bool BF, bool BIG, int PU, class Get, class Pre, class Out>
+__device__ __forceinline__ void mpass(T *sm, WS<T> &S, Get get, int count, int32_t *info, int inst, int stage_base,
                                       int fail_code, Pre pre, const Out &out, int *bad) {
-    if constexpr (BIG)
-        mpass_panel<T, RED, BF>(S, get, count, info, inst, stage_base, fail_code, pre, out, bad);
+    if constexpr (BIG && !BF)
+        mpass_cols<T, RED, PU>(sm, S, get, count, info, inst, stage_base, fail_code, pre, out, bad);
+    else if constexpr (BIG)
+        mpass_panel<T, RED, BF, PU>(sm, S, get, count, info, inst, stage_base, fail_code, pre, out, bad);
     else
-        mpass_tile<T, RED, BF>(S, get, count, info, inst, stage_base, fail_code, pre, out, bad);
+        mpass_tile<T, RED, BF, PU>(sm, S, get, count, info, inst, stage_base, fail_code, pre, out, bad);
 }
 
 __device__ __forceinline__ StageSrc leaf_stage(const DevProb &p, int t) { return prob_stage(p, t); }
@@ -888,15 +917,16 @@ __device__ T *unit_ws(const GroupArgs &g) {
 }
 
 // ------------------------------------------------------------ matrix side
-template <class T, bool BF, bool BIG>
+template <class T, bool BF, bool BIG, int PU>
 __global__ void __launch_bounds__(LB_MT) kl_leaf_up(GroupArgs g) {
     __shared__ int bad;
+    __shared__ T sm[BIG && !BF ? wd::lds_elems<PU / 16>() : lds_elems<PU, BIG>()];
     const int n = g.nx, m = g.nu, tid = threadIdx.x;
     WS<T> S;
-    S.bind(unit_ws<T>(g), n, m);
     if (tid == 0) bad = 0;
     const SlotLayout SL{n};
     for (int li = blockIdx.x; li < g.nleaves; li += gridDim.x) {
+        S.bind(unit_ws<T>(g), n, m);
         const LeafItem it = sv::load_leaf(g.leaves, li);
         if ((it.flags & LEAF_TOP) || inst_skipped(g.probs, it.inst)) continue;
         const DevProb p = load_prob(g.probs, it.inst);
@@ -914,7 +944,7 @@ __global__ void __launch_bounds__(LB_MT) kl_leaf_up(GroupArgs g) {
         const LeafOut<T> o{base, n, m, true};
         if (!(it.flags & LEAF_LAST)) {
             init_red(S);
-            mpass<T, true, BF, BIG>(S, get, it.len, g.info, it.inst, it.t0, 2, [](int) {}, o, &bad);
+            mpass<T, true, BF, BIG, PU>(sm, S, get, it.len, g.info, it.inst, it.t0, 2, [](int) {}, o, &bad);
             for (int e = tid; e < n * n; e += nthr()) {
                 const int i = e / n, j = e % n;
                 const double a = (double)S.V[(int64_t)j * n + i], q = (double)S.Qh[e], x = (double)S.P[e];
@@ -931,21 +961,22 @@ __global__ void __launch_bounds__(LB_MT) kl_leaf_up(GroupArgs g) {
         } else {
             for (int e = tid; e < n * n; e += nthr()) S.P[e] = (T)p.QxN[e];
             __syncthreads();
-            mpass<T, false, BF, BIG>(S, get, it.len, g.info, it.inst, it.t0, 2, [](int) {}, o, &bad);
+            mpass<T, false, BF, BIG, PU>(sm, S, get, it.len, g.info, it.inst, it.t0, 2, [](int) {}, o, &bad);
             for (int e = tid; e < n * n; e += nthr()) out[SL.Qx() + e] = (double)S.P[e];
         }
         __syncthreads();
     }
 }
 
-template <class T, bool BF, bool BIG>
+template <class T, bool BF, bool BIG, int PU>
 __global__ void __launch_bounds__(LB_MT) kl_leaf_down(GroupArgs g) {
     __shared__ int bad;
+    __shared__ T sm[BIG && !BF ? wd::lds_elems<PU / 16>() : lds_elems<PU, BIG>()];
     const int n = g.nx, m = g.nu, tid = threadIdx.x;
     WS<T> S;
-    S.bind(unit_ws<T>(g), n, m);
     if (tid == 0) bad = 0;
     for (int li = blockIdx.x; li < g.nleaves; li += gridDim.x) {
+        S.bind(unit_ws<T>(g), n, m);
         const LeafItem it = sv::load_leaf(g.leaves, li);
         // only whole-problem leaves need the factorization with the true
         // terminal; the others are solved from their up records
@@ -955,7 +986,7 @@ __global__ void __launch_bounds__(LB_MT) kl_leaf_down(GroupArgs g) {
         for (int e = tid; e < n * n; e += nthr()) S.P[e] = (T)p.QxN[e];
         __syncthreads();
         auto get = [&](int s) { return leaf_stage(p, it.t0 + s); };
-        mpass<T, false, BF, BIG>(S, get, it.len, g.info, it.inst, it.t0, 2, [](int) {}, LeafOut<T>{base, n, m, false},
+        mpass<T, false, BF, BIG, PU>(sm, S, get, it.len, g.info, it.inst, it.t0, 2, [](int) {}, LeafOut<T>{base, n, m, false},
                             &bad);
         __syncthreads();
     }
@@ -989,11 +1020,12 @@ __device__ void publish(const GroupArgs &g, int idx) {
 }
 
 __global__ void __launch_bounds__(LB_MT) kl_tree(GroupArgs g) {
+    constexpr int PU = 128;
     __shared__ int s_item, bad;
+    __shared__ double sm[wd::lds_elems<PU / 16>()];
     const int n = g.nx, tid = threadIdx.x;
     const SlotLayout SL{n};
     WS<double> S;
-    S.bind(unit_ws<double>(g), n, n);
     if (tid == 0) bad = 0;
     double *slots = g.slots;
     auto slot = [&](int s) { return slots + (int64_t)s * SL.size(); };
@@ -1003,6 +1035,7 @@ __global__ void __launch_bounds__(LB_MT) kl_tree(GroupArgs g) {
         const int idx = uni(s_item);
         __syncthreads();
         if (idx >= g.nitems) break;
+        S.bind(unit_ws<double>(g), n, n);
         const TreeItem it = load_item(g.items, idx);
         wait_deps(g, it);
         auto get = [&](int s) { return slot_stage(slot(it.first + s), n, g.ident); };
@@ -1010,7 +1043,7 @@ __global__ void __launch_bounds__(LB_MT) kl_tree(GroupArgs g) {
             // excluded instance: only its completion flag is published
         } else if (it.kind == ITEM_UP) {
             init_red(S);
-            mpass<double, true, false, true>(S, get, it.count, g.info, it.inst, -1, 3, [](int) {},
+            mpass<double, true, false, true, PU>(sm, S, get, it.count, g.info, it.inst, -1, 3, [](int) {},
                                        SlotOut{slots, it.first, n, true, g.superpose != 0}, &bad);
             double *out = slot(it.out_slot);
             for (int e = tid; e < n * n; e += nthr()) {
@@ -1031,8 +1064,8 @@ __global__ void __launch_bounds__(LB_MT) kl_tree(GroupArgs g) {
             double *term = it.last ? slot(it.term_slot) : nullptr;
             for (int e = tid; e < n * n; e += nthr()) S.P[e] = term ? term[SL.Qx() + e] : msg[SL.P() + e];
             __syncthreads();
-            mpass<double, false, false, true>(
-                S, get, it.count, g.info, it.inst, -1, 3,
+            mpass<double, false, false, true, PU>(
+                sm, S, get, it.count, g.info, it.inst, -1, 3,
                 [&](int s) {      // M2 for child s: P at the end of master stage s
                     if (!upl) {
                         double *d = slot(it.first + s) + SL.P();
@@ -1814,10 +1847,15 @@ inline bool big_stage(const GroupArgs &g) { return g.nx > 64; }
 template <class T, bool BF = false>
 hipError_t launch_leaf_up(const GroupArgs &g, int, hipStream_t st) {
     if (!BF && mid_shape(g.nx, g.nu)) return sizeof(T) == 4 ? mid_leaf_f32(g, false, st) : mid_leaf_f64(g, false, st);
-    if (big_stage(g))
-        hipLaunchKernelGGL((kl_leaf_up<T, BF, true>), dim3(leaf_units(g)), dim3(LB_MT), 0, st, g);
+    const dim3 grid(leaf_units(g)), block(LB_MT);
+    if (big_stage(g) && g.nu > 64)
+        hipLaunchKernelGGL((kl_leaf_up<T, BF, true, 128>), grid, block, 0, st, g);
+    else if (big_stage(g))
+        hipLaunchKernelGGL((kl_leaf_up<T, BF, true, 64>), grid, block, 0, st, g);
+    else if (g.nu > 64)
+        hipLaunchKernelGGL((kl_leaf_up<T, BF, false, 128>), grid, block, 0, st, g);
     else
-        hipLaunchKernelGGL((kl_leaf_up<T, BF, false>), dim3(leaf_units(g)), dim3(LB_MT), 0, st, g);
+        hipLaunchKernelGGL((kl_leaf_up<T, BF, false, 64>), grid, block, 0, st, g);
     return hipGetLastError();
 }
 hipError_t launch_tree(const GroupArgs &g, int grid, hipStream_t st) {
@@ -1829,10 +1867,15 @@ template <class T, bool BF = false>
 hipError_t launch_leaf_down(const GroupArgs &g, int, hipStream_t st) {
     if (g.ntop == 0) return hipSuccess;
     if (!BF && mid_shape(g.nx, g.nu)) return sizeof(T) == 4 ? mid_leaf_f32(g, true, st) : mid_leaf_f64(g, true, st);
-    if (big_stage(g))
-        hipLaunchKernelGGL((kl_leaf_down<T, BF, true>), dim3(leaf_units(g)), dim3(LB_MT), 0, st, g);
+    const dim3 grid(leaf_units(g)), block(LB_MT);
+    if (big_stage(g) && g.nu > 64)
+        hipLaunchKernelGGL((kl_leaf_down<T, BF, true, 128>), grid, block, 0, st, g);
+    else if (big_stage(g))
+        hipLaunchKernelGGL((kl_leaf_down<T, BF, true, 64>), grid, block, 0, st, g);
+    else if (g.nu > 64)
+        hipLaunchKernelGGL((kl_leaf_down<T, BF, false, 128>), grid, block, 0, st, g);
     else
-        hipLaunchKernelGGL((kl_leaf_down<T, BF, false>), dim3(leaf_units(g)), dim3(LB_MT), 0, st, g);
+        hipLaunchKernelGGL((kl_leaf_down<T, BF, false, 64>), grid, block, 0, st, g);
     return hipGetLastError();
 }
 template <class TR>

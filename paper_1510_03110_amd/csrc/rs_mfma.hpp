@@ -79,63 +79,5 @@ __device__ __forceinline__ float row_bcast(float v) {
 __device__ __forceinline__ double rsq_est(double d) { return __builtin_amdgcn_rsq(d); }
 __device__ __forceinline__ float rsq_est(float d) { return __builtin_amdgcn_rsqf(d); }
 
-// Step K of chol_inv16: eliminate column K below the pivot in [G | I].
-template <int K, class T>
-__device__ __forceinline__ void chol16_step(T (&a)[8], int i, T &sdi, int &fail) {
-    constexpr int kh = K >> 3, kc = K & 7;
-    T d = bcast_lane(a[kc], 16 * kh + K);              // pivot d_K (wave-uniform)
-    if (!(d > T(0)) || !__builtin_isfinite(d)) {
-        fail = 1;
-        d = T(1);
-    }
-    T is = rsq_est(d);
-    is = is * (T(1.5) - T(0.5) * d * is * is);
-    is = is * (T(1.5) - T(0.5) * d * is * is);
-    if (i == K) sdi = is;
-    const T f = __shfl(a[kc], 16 * kh + i, 64);       // entry (i, K) of this lane's row
-    const T m = i > K ? f * (is * is) : T(0);           // rows above the pivot keep their values
-#pragma unroll
-    for (int c = 0; c < 8; ++c) a[c] -= m * row_bcast<K>(a[c]);
-    if constexpr (K + 1 < 16) chol16_step<K + 1>(a, i, sdi, fail);
-}
-
-// Inverse Cholesky factor of a 16 x 16 block by one wavefront: Gaussian
-// elimination without pivoting on the 16 x 32 matrix [G | I] turns it into
-// [D L_u' | L_u^{-1}] with G = L_u D L_u' (L_u unit lower triangular), i.e.
-// the Cholesky factor L = L_u D^{1/2} and L^{-1} = D^{-1/2} L_u^{-1}, the
-// same factorization and forward substitution as the row-per-lane sweep.
-// Lane l holds row l % 16 of [G | I], columns 8 (l / 16) .. 8 (l / 16) + 7;
-// the pivot row reaches the other lanes of each row of 16 by DPP, the pivot
-// column by one bpermute, the pivot by readlane.
-// The lane's row and column block are taken through an opaque copy: the
-// compare masks formed from them (one per step) are the same in every stage,
-// and the compiler would otherwise hoist all of them out of the caller's
-// stage loop and keep them live in scalar registers (spilled to vector lanes).
-template <class T>
-__device__ __forceinline__ int chol_inv16(T *G, T *LiT) {
-    int l = lane();
-    asm volatile("" : "+v"(l));
-    const int i = l & 15, h = l >> 4;
-    T a[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        const T g = G[i * 16 + ((8 * h + c) & 15)];
-        a[c] = h < 2 ? g : (8 * (h - 2) + c == i ? T(1) : T(0));
-    }
-    int fail = 0;
-    T sdi = T(0);
-    chol16_step<0>(a, i, sdi, fail);
-    if (h >= 2) {
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const int j = 8 * (h - 2) + c;
-            const T v = a[c] * sdi;
-            G[i * 16 + j] = v;       // L^{-1}[i][j]
-            LiT[j * 16 + i] = v;     // L^{-T}[j][i]
-        }
-    }
-    return fail;
-}
-
 }  // namespace mf
 }  // namespace rs
