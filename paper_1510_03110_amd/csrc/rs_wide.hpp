@@ -52,9 +52,12 @@ struct Mat {
 };
 
 // body(kt, P0, P1) for the panels kt of 16 rows of M0 and M1 (same number of
-// rows; M1.p null: none), from LDS; pre(kt) issues what body(kt) wants loaded.
-template <class T, class U0, class U1, class Pre, class Body>
-__device__ __forceinline__ void sweep(T *sm, Mat<U0> M0, Mat<U1> M1, bool two, Pre pre, Body body) {
+// rows; M1.p null: none), from LDS.  pre(kt) issues what body(kt) wants loaded
+// and adv() takes it over from there once it has arrived.  The loop is rolled:
+// unrolled, with its register arrays indexed by kt, a stage is 200 KB of code,
+// and a panel spent as long on instruction fetches as on its products.
+template <class T, class U0, class U1, class Pre, class Adv, class Body>
+__device__ __forceinline__ void sweep(T *sm, Mat<U0> M0, Mat<U1> M1, bool two, Pre pre, Adv adv, Body body) {
     constexpr int E = 16 * 16 * NT / NTHR;
     const Buf b0 = buf(M0.p, (M0.rows - 1) * M0.ld + M0.cols), b1 = buf(M1.p, (M1.rows - 1) * M1.ld + M1.cols);
     int tid = threadIdx.x;
@@ -78,21 +81,31 @@ __device__ __forceinline__ void sweep(T *sm, Mat<U0> M0, Mat<U1> M1, bool two, P
     };
     const int nk = (M0.rows + 15) >> 4;
     fetch(0);
-#pragma unroll
-    for (int kt = 0; kt < NT; ++kt) {
-        if (kt >= nk) break;
+#pragma unroll 1
+    for (int kt = 0; kt < nk; ++kt) {
         T *P0 = sm + 2 * PANEL * (kt & 1), *P1 = P0 + PANEL;
 #pragma unroll
         for (int u = 0; u < E; ++u) {
             P0[(row + 4 * u) * PITCH + col] = (T)r0[u];
             if (two) P1[(row + 4 * u) * PITCH + col] = (T)r1[u];
         }
+        adv();
         lds_sync();           // the panel is complete, and the other pair is free
         if (kt + 1 < nk) fetch(kt + 1);
         body(kt, P0, P1);
         fence();
     }
     lds_sync();
+}
+
+// The first of N column tiles, which goes to the end.
+template <int N, class V>
+__device__ __forceinline__ V rotate(V (&v)[N]) {
+    const V f = v[0];
+#pragma unroll
+    for (int t = 0; t + 1 < N; ++t) v[t] = v[t + 1];
+    v[N - 1] = f;
+    return f;
 }
 
 // acc += (tile ti of the panel)' b
@@ -176,30 +189,34 @@ __device__ __forceinline__ void stage(T *sm, Work<T> &S, const StageSrc &src, in
     const Mat<double> A{src.A, n, n, n}, B{src.B, n, m, m};
     const Mat<T> P{S.P, n, n, n};
     auto no_pre = [](int) {};
+    auto no_adv = [] {};
     // ---- G = Qw + B'PB: column block c by NT / NUT waves, each with WT row
     // tiles of W_B = P B
     {
         const Ln<T> L;
         const int c = j % NUT, h = j / NUT;
-        v4_t<T> wb[WT], g[NUT], b[2];
+        v4_t<T> wb[WT], g[NUT], b, bn;
 #pragma unroll
         for (int t = 0; t < WT; ++t) wb[t] = zero4<T>();
-        sweep(sm, P, none, false, [&](int kt) { b[kt & 1] = tile<false, false, T>(L, src.B, m, kt, c, n, m); },
+        sweep(sm, P, none, false, [&](int kt) { bn = tile<false, false, T>(L, src.B, m, kt, c, n, m); },
+              [&] { b = bn; },
               [&](int kt, const T *P0, const T *) {
 #pragma unroll
                   for (int t = 0; t < WT; ++t)
-                      if (h * WT + t < nt && c < mt) wb[t] = mul(L, wb[t], P0, h * WT + t, b[kt & 1]);
+                      if (h * WT + t < nt && c < mt) wb[t] = mul(L, wb[t], P0, h * WT + t, b);
               });
 #pragma unroll
         for (int t = 0; t < NUT; ++t) g[t] = tile<false, true, T>(L, src.Qw, m, t, c, m, m, h == 0 && t >= c);
         if (h != 0)
 #pragma unroll
             for (int t = 0; t < NUT; ++t) g[t] = zero4<T>();
-        sweep(sm, B, none, false, no_pre, [&](int kt, const T *P0, const T *) {
-            if (kt / WT == h)
+        sweep(sm, B, none, false, no_pre, no_adv, [&](int kt, const T *P0, const T *) {
+            if (kt / WT == h) {
+                const v4_t<T> b = rotate(wb);
 #pragma unroll
                 for (int t = 0; t < NUT; ++t)
-                    if (t >= c && t < mt) g[t] = mul(L, g[t], P0, t, wb[kt % WT]);
+                    if (t >= c && t < mt) g[t] = mul(L, g[t], P0, t, b);
+            }
         });
         if (h == 0)
 #pragma unroll
@@ -225,37 +242,39 @@ __device__ __forceinline__ void stage(T *sm, Work<T> &S, const StageSrc &src, in
         const Ln<T> L;
         v4_t<T> F[NT], H[NUT];
         {
-            v4_t<T> w[NT], a[2];
+            v4_t<T> w[NT], a, an;
 #pragma unroll
             for (int t = 0; t < NT; ++t) w[t] = zero4<T>();
-            sweep(sm, P, none, false, [&](int kt) { a[kt & 1] = tile<false, false, T>(L, src.A, n, kt, j, n, n); },
+            sweep(sm, P, none, false, [&](int kt) { an = tile<false, false, T>(L, src.A, n, kt, j, n, n); }, [&] { a = an; },
                   [&](int kt, const T *P0, const T *) {
 #pragma unroll
                       for (int t = 0; t < NT; ++t)
-                          if (t < nt) w[t] = mul(L, w[t], P0, t, a[kt & 1]);
+                          if (t < nt) w[t] = mul(L, w[t], P0, t, a);
                   });
             // ---- F = Qx + A'W (lower tiles), H' = Qxw' + B'W
 #pragma unroll
             for (int t = 0; t < NT; ++t) F[t] = tile<false, false, T>(L, src.Qx, n, t, j, n, n, t >= j);
 #pragma unroll
             for (int t = 0; t < NUT; ++t) H[t] = tile<true, false, T>(L, src.Qxw, m, t, j, m, n);
-            sweep(sm, A, B, true, no_pre, [&](int kt, const T *P0, const T *P1) {
+            sweep(sm, A, B, true, no_pre, no_adv, [&](int, const T *P0, const T *P1) {
+                const v4_t<T> b = rotate(w);
 #pragma unroll
                 for (int t = 0; t < NUT; ++t)
-                    if (t < mt) H[t] = mul(L, H[t], P1, t, w[kt]);
+                    if (t < mt) H[t] = mul(L, H[t], P1, t, b);
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
-                    if (t >= j && t < nt) F[t] = mul(L, F[t], P0, t, w[kt]);
+                    if (t >= j && t < nt) F[t] = mul(L, F[t], P0, t, b);
             });
         }
         // ---- Y = L^{-1} H'
         v4_t<T> y[NUT];
 #pragma unroll
         for (int t = 0; t < NUT; ++t) y[t] = zero4<T>();
-        sweep(sm, LT, none, false, no_pre, [&](int kt, const T *P0, const T *) {
+        sweep(sm, LT, none, false, no_pre, no_adv, [&](int kt, const T *P0, const T *) {
+            const v4_t<T> b = rotate(H);
 #pragma unroll
             for (int t = 0; t < NUT; ++t)
-                if (kt < NUT && t >= kt && t < mt) y[t] = mul(L, y[t], P0, t, H[kt < NUT ? kt : 0]);
+                if (t >= kt && t < mt) y[t] = mul(L, y[t], P0, t, b);
         });
         const Buf by = buf(S.Y, m * n);
 #pragma unroll
@@ -265,8 +284,8 @@ __device__ __forceinline__ void stage(T *sm, Work<T> &S, const StageSrc &src, in
         v4_t<T> k[NUT];
 #pragma unroll
         for (int t = 0; t < NUT; ++t) k[t] = zero4<T>();
-        sweep(sm, Y, LI, true, no_pre, [&](int kt, const T *P0, const T *P1) {
-            const v4_t<T> b = neg<T>(y[kt < NUT ? kt : 0]);
+        sweep(sm, Y, LI, true, no_pre, no_adv, [&](int kt, const T *P0, const T *P1) {
+            const v4_t<T> b = neg<T>(rotate(y));
 #pragma unroll
             for (int t = 0; t < NUT; ++t)
                 if (t <= kt) k[t] = mul(L, k[t], P1, t, b);
@@ -287,25 +306,28 @@ __device__ __forceinline__ void stage(T *sm, Work<T> &S, const StageSrc &src, in
         const Ln<T> L;
         v4_t<T> av[NT], x[NUT];
         {
-            v4_t<T> bv[NUT], v[2];
+            v4_t<T> bv[NUT], v, vn;
 #pragma unroll
             for (int t = 0; t < NT; ++t) av[t] = zero4<T>();
 #pragma unroll
-            for (int t = 0; t < NUT; ++t) bv[t] = x[t] = zero4<T>();
-            sweep(sm, A, B, true, [&](int kt) { v[kt & 1] = tile<false, false, T>(L, S.V, n, kt, j, n, n); },
+            for (int t = 0; t < NUT; ++t) bv[t] = zero4<T>();
+            sweep(sm, A, B, true, [&](int kt) { vn = tile<false, false, T>(L, S.V, n, kt, j, n, n); }, [&] { v = vn; },
                   [&](int kt, const T *P0, const T *P1) {
 #pragma unroll
                       for (int t = 0; t < NUT; ++t)
-                          if (t < mt) bv[t] = mul(L, bv[t], P1, t, v[kt & 1]);
+                          if (t < mt) bv[t] = mul(L, bv[t], P1, t, v);
 #pragma unroll
                       for (int t = 0; t < NT; ++t)
-                          if (t < nt) av[t] = mul(L, av[t], P0, t, v[kt & 1]);
+                          if (t < nt) av[t] = mul(L, av[t], P0, t, v);
                   });
             // ---- X = L^{-1} B'V
-            sweep(sm, LT, none, false, no_pre, [&](int kt, const T *P0, const T *) {
+#pragma unroll
+            for (int t = 0; t < NUT; ++t) x[t] = zero4<T>();
+            sweep(sm, LT, none, false, no_pre, no_adv, [&](int kt, const T *P0, const T *) {
+                const v4_t<T> b = rotate(bv);
 #pragma unroll
                 for (int t = 0; t < NUT; ++t)
-                    if (kt < NUT && t >= kt && t < mt) x[t] = mul(L, x[t], P0, t, bv[kt < NUT ? kt : 0]);
+                    if (t >= kt && t < mt) x[t] = mul(L, x[t], P0, t, b);
             });
         }
         const Buf bx = buf(S.X, m * n);
@@ -317,8 +339,8 @@ __device__ __forceinline__ void stage(T *sm, Work<T> &S, const StageSrc &src, in
             v4_t<T> l[NUT];
 #pragma unroll
             for (int t = 0; t < NUT; ++t) l[t] = zero4<T>();
-            sweep(sm, Y, LI, out.Lt != nullptr, no_pre, [&](int kt, const T *P0, const T *P1) {
-                const v4_t<T> b = neg<T>(x[kt < NUT ? kt : 0]);
+            sweep(sm, Y, LI, out.Lt != nullptr, no_pre, no_adv, [&](int kt, const T *P0, const T *P1) {
+                const v4_t<T> b = neg<T>(rotate(x));
                 if (out.Lt)
 #pragma unroll
                     for (int t = 0; t < NUT; ++t)
@@ -337,13 +359,15 @@ __device__ __forceinline__ void stage(T *sm, Work<T> &S, const StageSrc &src, in
 #pragma unroll
         for (int t = 0; t < NT; ++t) store(L, bv, n, t, j, n, n, av[t]);
         S.V = dst;
+        for (int t = mt; t < NUT; ++t) rotate(x);      // back in order
         // ---- Q_w_hat += X'X (lower tiles; the whole matrix after the last)
 #pragma unroll
         for (int t = 0; t < NT; ++t) av[t] = tile<false, false, T>(L, S.Q, n, t, j, n, n, t >= j);
-        sweep(sm, X, none, false, no_pre, [&](int kt, const T *P0, const T *) {
+        sweep(sm, X, none, false, no_pre, no_adv, [&](int, const T *P0, const T *) {
+            const v4_t<T> b = rotate(x);
 #pragma unroll
             for (int t = 0; t < NT; ++t)
-                if (t >= j && t < nt) av[t] = mul(L, av[t], P0, t, x[kt < NUT ? kt : 0]);
+                if (t >= j && t < nt) av[t] = mul(L, av[t], P0, t, b);
         });
         const Buf bq = buf(S.Q, n * n);
 #pragma unroll
