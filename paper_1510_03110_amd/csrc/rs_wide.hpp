@@ -108,16 +108,29 @@ __device__ __forceinline__ V rotate(V (&v)[N]) {
     return f;
 }
 
-// acc += (tile ti of the panel)' b
-template <class T>
-__device__ __forceinline__ v4_t<T> mul(const Ln<T> &L, v4_t<T> acc, const T *P, int ti, v4_t<T> b) {
-    T a[4];
-    fence();
+// acc[t] += (tile t0 + t of the panel)' b for lo <= t < hi (uniform).  The
+// operands of the next tile are read before this one is multiplied (in the
+// order of the source, the reads of a tile waited behind the products of its
+// own first half: the matrix cores idled for twice the LDS latency a tile).
+template <int N, class T>
+__device__ __forceinline__ void mul(const Ln<T> &L, v4_t<T> (&acc)[N], const T *P, int t0, v4_t<T> b, int lo, int hi) {
+    const T *q = P + L.row(0) * PITCH + 16 * t0 + L.c;
+    T a[2][4];
+    auto read = [&](int t) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) a[r] = P[L.row(r) * PITCH + 16 * ti + L.c];
+        for (int r = 0; r < 4; ++r) a[t & 1][r] = q[(L.row(r) - L.row(0)) * PITCH + 16 * t];
+    };
+    read(0);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) acc = MT<T>::mfma(a[r], b[r], acc);
-    return acc;
+    for (int t = 0; t < N; ++t) {
+        if (t + 1 < N) read(t + 1);
+        fence();
+        if (t >= lo && t < hi) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[t] = MT<T>::mfma(a[t & 1][r], b[r], acc[t]);
+        }
+        fence();
+    }
 }
 template <class T>
 __device__ __forceinline__ v4_t<T> neg(v4_t<T> v) {
@@ -190,20 +203,32 @@ __device__ __forceinline__ void stage(T *sm, Work<T> &S, const StageSrc &src, in
     const Mat<T> P{S.P, n, n, n};
     auto no_pre = [](int) {};
     auto no_adv = [] {};
-    // ---- G = Qw + B'PB: column block c by NT / NUT waves, each with WT row
-    // tiles of W_B = P B
+    // ---- W = P A and, for G = Qw + B'PB (column block c by NT / NUT waves),
+    // each wave's WT row tiles of W_B = P B: one sweep over P where the
+    // registers hold both
+    constexpr bool ONE = NUT < NT;
+    v4_t<T> w[NT];
     {
         const Ln<T> L;
         const int c = j % NUT, h = j / NUT;
-        v4_t<T> wb[WT], g[NUT], b, bn;
+        v4_t<T> wb[WT], g[NUT], a, an, b, bn;
 #pragma unroll
         for (int t = 0; t < WT; ++t) wb[t] = zero4<T>();
-        sweep(sm, P, none, false, [&](int kt) { bn = tile<false, false, T>(L, src.B, m, kt, c, n, m); },
-              [&] { b = bn; },
-              [&](int kt, const T *P0, const T *) {
+        if (ONE)
 #pragma unroll
-                  for (int t = 0; t < WT; ++t)
-                      if (h * WT + t < nt && c < mt) wb[t] = mul(L, wb[t], P0, h * WT + t, b);
+            for (int t = 0; t < NT; ++t) w[t] = zero4<T>();
+        sweep(sm, P, none, false,
+              [&](int kt) {
+                  bn = tile<false, false, T>(L, src.B, m, kt, c, n, m);
+                  if (ONE) an = tile<false, false, T>(L, src.A, n, kt, j, n, n);
+              },
+              [&] {
+                  b = bn;
+                  a = an;
+              },
+              [&](int, const T *P0, const T *) {
+                  mul(L, wb, P0, h * WT, b, 0, c < mt ? nt - h * WT : 0);
+                  if (ONE) mul(L, w, P0, 0, a, 0, nt);
               });
 #pragma unroll
         for (int t = 0; t < NUT; ++t) g[t] = tile<false, true, T>(L, src.Qw, m, t, c, m, m, h == 0 && t >= c);
@@ -213,9 +238,7 @@ __device__ __forceinline__ void stage(T *sm, Work<T> &S, const StageSrc &src, in
         sweep(sm, B, none, false, no_pre, no_adv, [&](int kt, const T *P0, const T *) {
             if (kt / WT == h) {
                 const v4_t<T> b = rotate(wb);
-#pragma unroll
-                for (int t = 0; t < NUT; ++t)
-                    if (t >= c && t < mt) g[t] = mul(L, g[t], P0, t, b);
+                mul(L, g, P0, 0, b, c, mt);
             }
         });
         if (h == 0)
@@ -238,19 +261,27 @@ __device__ __forceinline__ void stage(T *sm, Work<T> &S, const StageSrc &src, in
         chol(sm, m, out.L, out.LT);
     }
     const Mat<T> LI{out.L, m, m, m}, LT{out.LT, m, m, m}, Y{S.Y, m, n, n}, X{S.X, m, n, n};
+    // k -= L^{-T} y, in a sweep of its own
+    auto feedback = [&](v4_t<T>(&k)[NUT], v4_t<T>(&y)[NUT], const Ln<T> &L) {
+        sweep(sm, LI, none, false, no_pre, no_adv, [&](int kt, const T *P0, const T *) {
+            const v4_t<T> b = neg<T>(rotate(y));
+            mul(L, k, P0, 0, b, 0, kt + 1);
+        });
+    };
     {
         const Ln<T> L;
         v4_t<T> F[NT], H[NUT];
         {
-            v4_t<T> w[NT], a, an;
+            if constexpr (!ONE) {
+                v4_t<T> a, an;
 #pragma unroll
-            for (int t = 0; t < NT; ++t) w[t] = zero4<T>();
-            sweep(sm, P, none, false, [&](int kt) { an = tile<false, false, T>(L, src.A, n, kt, j, n, n); }, [&] { a = an; },
-                  [&](int kt, const T *P0, const T *) {
-#pragma unroll
-                      for (int t = 0; t < NT; ++t)
-                          if (t < nt) w[t] = mul(L, w[t], P0, t, a);
-                  });
+                for (int t = 0; t < NT; ++t) w[t] = zero4<T>();
+                sweep(sm, P, none, false, [&](int kt) { an = tile<false, false, T>(L, src.A, n, kt, j, n, n); },
+                      [&] { a = an; },
+                      [&](int, const T *P0, const T *) {
+                          mul(L, w, P0, 0, a, 0, nt);
+                      });
+            }
             // ---- F = Qx + A'W (lower tiles), H' = Qxw' + B'W
 #pragma unroll
             for (int t = 0; t < NT; ++t) F[t] = tile<false, false, T>(L, src.Qx, n, t, j, n, n, t >= j);
@@ -258,12 +289,8 @@ __device__ __forceinline__ void stage(T *sm, Work<T> &S, const StageSrc &src, in
             for (int t = 0; t < NUT; ++t) H[t] = tile<true, false, T>(L, src.Qxw, m, t, j, m, n);
             sweep(sm, A, B, true, no_pre, no_adv, [&](int, const T *P0, const T *P1) {
                 const v4_t<T> b = rotate(w);
-#pragma unroll
-                for (int t = 0; t < NUT; ++t)
-                    if (t < mt) H[t] = mul(L, H[t], P1, t, b);
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    if (t >= j && t < nt) F[t] = mul(L, F[t], P0, t, b);
+                mul(L, H, P1, 0, b, 0, mt);
+                mul(L, F, P0, 0, b, j, nt);
             });
         }
         // ---- Y = L^{-1} H'
@@ -272,9 +299,7 @@ __device__ __forceinline__ void stage(T *sm, Work<T> &S, const StageSrc &src, in
         for (int t = 0; t < NUT; ++t) y[t] = zero4<T>();
         sweep(sm, LT, none, false, no_pre, no_adv, [&](int kt, const T *P0, const T *) {
             const v4_t<T> b = rotate(H);
-#pragma unroll
-            for (int t = 0; t < NUT; ++t)
-                if (t >= kt && t < mt) y[t] = mul(L, y[t], P0, t, b);
+            mul(L, y, P0, 0, b, kt, mt);
         });
         const Buf by = buf(S.Y, m * n);
 #pragma unroll
@@ -282,22 +307,25 @@ __device__ __forceinline__ void stage(T *sm, Work<T> &S, const StageSrc &src, in
         __syncthreads();
         // ---- P = F - Y'Y, K = -L^{-T} Y
         v4_t<T> k[NUT];
+        if (ONE)
 #pragma unroll
-        for (int t = 0; t < NUT; ++t) k[t] = zero4<T>();
-        sweep(sm, Y, LI, true, no_pre, no_adv, [&](int kt, const T *P0, const T *P1) {
+            for (int t = 0; t < NUT; ++t) k[t] = zero4<T>();
+        sweep(sm, Y, LI, ONE, no_pre, no_adv, [&](int kt, const T *P0, const T *P1) {
             const v4_t<T> b = neg<T>(rotate(y));
-#pragma unroll
-            for (int t = 0; t < NUT; ++t)
-                if (t <= kt) k[t] = mul(L, k[t], P1, t, b);
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-                if (t >= j && t < nt) F[t] = mul(L, F[t], P0, t, b);
+            if (ONE) mul(L, k, P1, 0, b, 0, kt + 1);
+            mul(L, F, P0, 0, b, j, nt);
         });
         T *dst = out.P ? out.P : S.P;
         const Buf bp = buf(dst, n * n), bk = buf(out.K, m * n);
 #pragma unroll
         for (int t = 0; t < NT; ++t)
             if (t >= j) store_sym(L, bp, n, t, j, F[t], true);
+        if constexpr (!ONE) {
+            for (int t = mt; t < NUT; ++t) rotate(y);      // back in order
+#pragma unroll
+            for (int t = 0; t < NUT; ++t) k[t] = zero4<T>();
+            feedback(k, y, L);
+        }
 #pragma unroll
         for (int t = 0; t < NUT; ++t) store(L, bk, n, t, j, m, n, k[t]);
         S.P = dst;
@@ -312,22 +340,16 @@ __device__ __forceinline__ void stage(T *sm, Work<T> &S, const StageSrc &src, in
 #pragma unroll
             for (int t = 0; t < NUT; ++t) bv[t] = zero4<T>();
             sweep(sm, A, B, true, [&](int kt) { vn = tile<false, false, T>(L, S.V, n, kt, j, n, n); }, [&] { v = vn; },
-                  [&](int kt, const T *P0, const T *P1) {
-#pragma unroll
-                      for (int t = 0; t < NUT; ++t)
-                          if (t < mt) bv[t] = mul(L, bv[t], P1, t, v);
-#pragma unroll
-                      for (int t = 0; t < NT; ++t)
-                          if (t < nt) av[t] = mul(L, av[t], P0, t, v);
+                  [&](int, const T *P0, const T *P1) {
+                      mul(L, bv, P1, 0, v, 0, mt);
+                      mul(L, av, P0, 0, v, 0, nt);
                   });
             // ---- X = L^{-1} B'V
 #pragma unroll
             for (int t = 0; t < NUT; ++t) x[t] = zero4<T>();
             sweep(sm, LT, none, false, no_pre, no_adv, [&](int kt, const T *P0, const T *) {
                 const v4_t<T> b = rotate(bv);
-#pragma unroll
-                for (int t = 0; t < NUT; ++t)
-                    if (t >= kt && t < mt) x[t] = mul(L, x[t], P0, t, b);
+                mul(L, x, P0, 0, b, kt, mt);
             });
         }
         const Buf bx = buf(S.X, m * n);
@@ -337,37 +359,37 @@ __device__ __forceinline__ void stage(T *sm, Work<T> &S, const StageSrc &src, in
         // ---- V = A'V - Y'X, L_t = -L^{-T} X
         {
             v4_t<T> l[NUT];
+            if (ONE)
 #pragma unroll
-            for (int t = 0; t < NUT; ++t) l[t] = zero4<T>();
-            sweep(sm, Y, LI, out.Lt != nullptr, no_pre, no_adv, [&](int kt, const T *P0, const T *P1) {
+                for (int t = 0; t < NUT; ++t) l[t] = zero4<T>();
+            sweep(sm, Y, LI, ONE && out.Lt, no_pre, no_adv, [&](int kt, const T *P0, const T *P1) {
                 const v4_t<T> b = neg<T>(rotate(x));
-                if (out.Lt)
-#pragma unroll
-                    for (int t = 0; t < NUT; ++t)
-                        if (t <= kt) l[t] = mul(L, l[t], P1, t, b);
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    if (t < nt) av[t] = mul(L, av[t], P0, t, b);
+                if (ONE && out.Lt) mul(L, l, P1, 0, b, 0, kt + 1);
+                mul(L, av, P0, 0, b, 0, nt);
             });
+            T *dst = out.V ? out.V : S.V;
+            const Buf bv = buf(dst, n * n);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) store(L, bv, n, t, j, n, n, av[t]);
+            S.V = dst;
+            for (int t = mt; t < NUT; ++t) rotate(x);      // back in order
+            if (!ONE && out.Lt) {
+#pragma unroll
+                for (int t = 0; t < NUT; ++t) l[t] = zero4<T>();
+                feedback(l, x, L);
+                for (int t = mt; t < NUT; ++t) rotate(x);
+            }
             const Buf bl = buf(out.Lt, m * n);
             if (out.Lt)
 #pragma unroll
                 for (int t = 0; t < NUT; ++t) store(L, bl, n, t, j, m, n, l[t]);
         }
-        T *dst = out.V ? out.V : S.V;
-        const Buf bv = buf(dst, n * n);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) store(L, bv, n, t, j, n, n, av[t]);
-        S.V = dst;
-        for (int t = mt; t < NUT; ++t) rotate(x);      // back in order
         // ---- Q_w_hat += X'X (lower tiles; the whole matrix after the last)
 #pragma unroll
         for (int t = 0; t < NT; ++t) av[t] = tile<false, false, T>(L, S.Q, n, t, j, n, n, t >= j);
         sweep(sm, X, none, false, no_pre, no_adv, [&](int, const T *P0, const T *) {
             const v4_t<T> b = rotate(x);
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-                if (t >= j && t < nt) av[t] = mul(L, av[t], P0, t, b);
+            mul(L, av, P0, 0, b, j, nt);
         });
         const Buf bq = buf(S.Q, n * n);
 #pragma unroll
