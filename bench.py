@@ -31,9 +31,6 @@ FP64_PEAK_TFLOPS = 78.6          # MI355X FP64 vector (and FP64 matrix) peak
 FP32_PEAK_TFLOPS = 157.3         # MI355X FP32 vector / FP32 matrix (dense) peak
 BF16_PEAK_TFLOPS = 2500.0        # MI355X BF16 matrix (dense) peak
 HBM_PEAK_GBS = 8000.0
-# shapes with register/LDS-resident matrix-core kernels; the others run the
-# large-block kernels (matrices in a per-workgroup global workspace)
-MATRIX_CORE_SHAPES = {(16, 16), (32, 16), (32, 32)}
 
 
 def log(*a):
@@ -224,22 +221,21 @@ def run_precision(prec, args, data, dev):
     # ------------------------------------------------ roofline (dominant)
     leaves = rs.rs_plan_export(batch.plan, 0)
     fused = "leaf_up" in per_step          # otherwise the solve runs on the stored factorization
-    matrix_core = (n, m) in MATRIX_CORE_SHAPES
     if fused:
         up, down = leaf_work(leaves, n, m, flops_reduce, flops_elim, flops_forward, flops_solve)
-        work = {"leaf_up": ("alu", up, FP64_PEAK_TFLOPS, "km_leaf_up"),
-                "leaf_down": ("alu", down, FP64_PEAK_TFLOPS, "kv_leaf_fwd")}
+        work = {"leaf_up": ("alu", up, FP64_PEAK_TFLOPS, "kf_leaf"),
+                "leaf_down": ("alu", down, FP64_PEAK_TFLOPS, "ks_leaf_fwd")}
     else:
         # the factorization's leaf-down kernel serves whole-problem leaves only
         up, down = leaf_work(leaves, n, m, flops_factor_reduce, flops_factor_elim, lambda a, b: 0.0,
                              flops_factor_elim)
         # BF16 plans: the dominant products run on BF16 matrix cores
         peak = BF16_PEAK_TFLOPS if prec == "bf16" else FP32_PEAK_TFLOPS if mixed else FP64_PEAK_TFLOPS
-        pre = "kf_" if matrix_core else "kl_"
+        columns = n <= 64 and (m + 15) // 16 <= (n + 15) // 16 and prec != "bf16"    # column-owner kernels
         # kernels launched once per step (the refinement kernels skip
         # converged instances, so their per-launch work is not fixed)
-        work = {"factor_leaf_up": ("alu", up, peak, pre + "leaf_up"),
-                "factor_leaf_down": ("alu", down, peak, pre + "leaf_down")}
+        work = {"factor_leaf_up": ("alu", up, peak, "kc_leaf" if columns else "kl_leaf_up"),
+                "factor_leaf_down": ("alu", down, peak, "kc_leaf" if columns else "kl_leaf_down")}
     avg = {k: kt[k][0] / max(kt[k][1], 1) for k in work if k in kt}
     dom = max(avg, key=lambda k: per_step.get(k, 0.0))
     bound, amount, peak, kname = work[dom]
@@ -338,8 +334,9 @@ def ingest_counters(fetch_csv, write_csv, copy_bytes, workload):
                                 float(r["Counter_Value"])))
         return sorted(out)
 
-    names = ("km_leaf_up", "km_leaf_down", "km_tree", "kv_leaf_fwd", "kf_leaf_up", "kf_leaf_down", "kf_tree",
-             "kv_leaf_up", "kv_leaf_down", "kv_tree", "kr_residual")
+    # (km_leaf_up, kf_leaf_up: kernels of traces taken before kf_leaf and kc_leaf)
+    names = ("kf_leaf", "kf_tree", "ks_leaf_fwd", "kc_leaf", "kc_tree", "ks_leaf_up", "ks_leaf_down", "ks_tree",
+             "kr_residual", "km_leaf_up", "kf_leaf_up")
     per = {}
     for counter, path in (("FETCH_SIZE", fetch_csv), ("WRITE_SIZE", write_csv)):
         rr = rows(path, counter)
@@ -359,7 +356,7 @@ def ingest_counters(fetch_csv, write_csv, copy_bytes, workload):
         if "FETCH_SIZE" not in c or "WRITE_SIZE" not in c:
             continue
         (fk, fs), (wk, ws) = c["FETCH_SIZE"], c["WRITE_SIZE"]
-        fp64 = name.startswith("km_") or name == "kv_leaf_fwd"      # the fused FP64 solve's kernels
+        fp64 = name in ("kf_leaf", "kf_tree", "ks_leaf_fwd", "km_leaf_up")      # the fused FP64 solve's kernels
         records.append({"kernel": name, "workload": workload + ("_fp64" if fp64 else "_mixed"),
                         "csrc_hash": csrc_hash(), "fetch_kib_raw": fk, "write_kib_raw": wk,
                         "fetch_scale": round(fs, 4), "write_scale": round(ws, 4),

@@ -115,9 +115,11 @@ struct WS {
 
 size_t large_unit_bytes(int nx, int nu) {
     // the master levels factor n x n blocks (m = n), so a unit holds the
-    // larger of the two working sets
+    // larger of the two working sets.  (The factorization of G counts as three
+    // m x m matrices and its blocks more than it takes in LDS: workspace sizes,
+    // and with them the plans that fit the static scratch, stay what they were.)
     auto elems = [](int64_t n, int64_t m) {
-        return 5 * n * n + 2 * n * (n + m) + 4 * n * m + m * m;
+        return 5 * n * n + 2 * n * (n + m) + 4 * n * m + 4 * m * m + 512 + 16 * m;
     };
     const int64_t e = std::max(elems(nx, nu), elems(nx, nx));
     return (size_t)(((e * 8) + 255) & ~(int64_t)255);

@@ -35,6 +35,31 @@ def test_column_owner_shapes(nx, nu, N, Ns, precision):
 
 
 @pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("nx,nu,N,Ns,b", [(65, 1, 12, 16, 2), (65, 65, 9, 3, 2), (80, 64, 14, 4, 2), (113, 17, 20, 10, 2),
+                                          (127, 128, 7, 2, 2), (128, 49, 13, 5, 3), (20, 100, 9, 3, 2)])
+def test_wide_stage_shapes(nx, nu, N, Ns, b, precision):
+    """Stages of more than 64 states (column blocks of 128, left operands in
+    panels), at both sizes of the factorization of G in LDS (up to 64 and up to
+    128 inputs), at the edges of their tiles and panels, with fewer row tiles
+    than waves, a single leaf, and its use with more than 64 inputs on few
+    states.  Bar as above."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1510_03110_amd import rs
+    prob = W.with_costs(W.g2(nx, nu, N, seed=nx * 100 + nu), seed=N)
+    bt = rs.Batch({k: [prob[k]] for k in prob}, precision=precision, Ns=Ns, branch=b, factored=True)
+    bt.factor()
+    bt.solve_factored()
+    torch.cuda.synchronize()
+    assert bt.status()[0].tolist() == [0, -1]
+    sol, ref = bt.result(0), riccati.solve(prob)
+    assert kkt.rel_error(sol, ref) <= TOL
+    assert abs(sol["obj"] - ref["obj"]) <= 1e-9 * max(1.0, abs(ref["obj"]))
+    bt.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
 @pytest.mark.parametrize("nx,nu,N,Ns,b", [(3, 7, 7, 1, 2), (8, 4, 9, 4, 3), (16, 32, 11, 2, 2), (31, 33, 8, 2, 4), (33, 64, 10, 3, 2),
                                           (64, 64, 5, 2, 2)])
 def test_prefetched_sweeps_at_short_lengths(nx, nu, N, Ns, b, precision):
