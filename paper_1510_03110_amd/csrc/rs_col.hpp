@@ -18,16 +18,19 @@
 //   V(:,j) = A'V - Y'X(:,j)   Q_w_hat(:,j) += X'X(:,j)
 //
 // Only left-hand operands (P, A, B, L^{-1}, Y, X) live in LDS; V and Q_w_hat
-// never leave their owner's registers.  G = Qw + B'PB is formed by the waves
-// j < n_u / 16 (column block j of B) and factored by the last wave while the
-// others form W, F and H'.  P, F and Q_w_hat are formed on the lower tiles
-// and mirrored, so they are exactly symmetric.  Four workgroup barriers a
+// never leave their owner's registers.  G = Qw + B'PB is formed by the owners of
+// A's columns (a column block of B each, its inner tiles split over two or more
+// waves where there are fewer of them) and factored by the last wave while the
+// others form W, F, H', A'V and the last stage's part of Q_w_hat.  (In that
+// order, with the loads counted, a stage of 32 states and 16 inputs alone on its
+// CU went from 13.6 to 11.0 k cycles.)  P, F and Q_w_hat are formed on the lower
+// tiles and mirrored, so they are exactly symmetric.  Four workgroup barriers a
 // stage; the next stage's A and B wait in registers.
 //
 // The vector lines ride on the same registers: the owner of a column block
 // also owns those entries of Psi, v and g_x, whose products with a column
 // block are sums over its own lanes (P a, A'pt, V'a, Y'z, X'z), and the owner
-// of column block 0 forms z = L^{-1} g_w and k = L^{-T} z from the operands it
+// of the last column block forms z = L^{-1} g_w and k = L^{-T} z from the operands it
 // reads for Y and K anyway.
 //
 // Sizes that are not multiples of 16 are padded with zeros on load (an
@@ -208,7 +211,7 @@ __device__ __forceinline__ void elim_step(T (&a)[4], int i, int h, int steps) {
 // block itself.  `steps`: rows that are not padding.  (On [G | I], with twice
 // the elements, a square root in every step and the pivot through scalar
 // registers, a block took 5 to 6 k cycles; in place with the column through
-// LDS 4.2 k.)
+// LDS 4.2 k; here 3.0 k.)
 template <int PU, int GS = 1, class T>
 __device__ __forceinline__ int chol_block(T *G, int kb, int steps) {
     int l = lane();

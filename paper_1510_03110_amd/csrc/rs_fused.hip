@@ -15,10 +15,10 @@
 // share a CU fill one another's waits, and the records' bytes are next.  FP64,
 // the whole solve before (a four-wave tile engine with every product through
 // LDS for full tiles, vector-unit kernels below them that factored the master
-// levels twice) and now: one problem of N = 1024, 32 x 16 505 -> 278 us and
-// 20 x 10 864 -> 285 us; 4 x 2, N = 64 129 -> 77 us; 512 problems of 32 x 16,
-// N = 1024 13.6 -> 11.7 ms (leaves 10.2 -> 8.2 ms); 1024 of 16 x 8, N in [32,
-// 2048] 14.9 -> 7.8 ms (padding on load instead of padded copies: 1.3 ms).
+// levels twice) and now: one problem of N = 1024, 32 x 16 505 -> 250 us and
+// 20 x 10 864 -> 275 us; 4 x 2, N = 64 129 -> 69 us; 512 problems of 32 x 16,
+// N = 1024 13.6 -> 10.1 ms (leaves 10.2 -> 6.5 ms); 1024 of 16 x 8, N in [32,
+// 2048] 14.9 -> 7.0 ms (padding on load instead of padded copies: 1.3 ms).
 #include <hip/hip_runtime.h>
 
 #include "rs_col.hpp"
@@ -39,7 +39,7 @@ __global__ void __launch_bounds__(128 * NXT, NXT == 1 ? 4 : NUT == 1 ? 3 : 2) kf
     constexpr bool EX = SZ != ANY, EXD = SZ == FULL;
     __shared__ SM S;
     __shared__ vs::Smem<SM::RX, SM::RU, W> F;
-    const LeafItem it = load_leaf_u(g.leaves, blockIdx.x);
+    const LeafItem it = load_leaf_u(g.leaves, my_leaf(g));
     if (((it.flags & LEAF_TOP) != 0) != (down != 0) || inst_skipped(g.probs, it.inst)) return;
     const DevProb p = load_prob(g.probs, it.inst);
     const int n = EX ? SM::RX : g.nx, m = EX ? SM::RU : g.nu, md = SZ == DATA ? p.nu : m, tid = threadIdx.x;

@@ -29,11 +29,12 @@
 //   kw_residual / kw_update
 //                  FP64 KKT residual and update of iterative refinement
 //
-// Every dense product of a stage is a list of 16x16 output tiles on the
-// matrix cores (v_mfma_f64_16x16x4f64, or the f32 form for FP32 factors),
-// tile t of a product going to wave t mod 8; at n_x > 64 the operands come
-// through LDS panels shared by the workgroup (gemm_panel), at n_x <= 64 each
-// tile reads its own strips (gemm_tile).  Products of one phase are
+// At n_x > 64 a stage runs on column owners (rs_wide.hpp).  With BF16 products,
+// and at n_x <= 64, every dense product of a stage is a list of 16x16 output
+// tiles on the matrix cores (v_mfma_f64_16x16x4f64, or the f32 form for FP32
+// factors), tile t of a product going to wave t mod 8; at n_x > 64 the operands
+// come through LDS panels shared by the workgroup (gemm_panel), at n_x <= 64
+// each tile reads its own strips (gemm_tile).  Products of one phase are
 // independent, and a workgroup barrier separates phases.  Per stage:
 //   W = P [A B];  (Alg. 4) B'V, A'V
 //   F = Qx + A'W_A,  H = Qxw + A'W_B,  G = Qw + B'W_B                 (Alg. 1)

@@ -28,7 +28,7 @@ template <class T, int NXT, int NUT, bool EX, int SX = 4, int SU = 4>
 __global__ void __launch_bounds__(128 * NXT, 2) kc_leaf(GroupArgs g, int down) {
     using SM = Smem<T, NXT, NUT, SX, SU>;
     __shared__ SM S;
-    const LeafItem it = load_leaf_u(g.leaves, blockIdx.x);
+    const LeafItem it = load_leaf_u(g.leaves, my_leaf(g));
     if (((it.flags & LEAF_TOP) != 0) != (down != 0) || inst_skipped(g.probs, it.inst)) return;
     const int n = EX ? SM::RX : g.nx, m = EX ? SM::RU : g.nu, tid = threadIdx.x;
     const SlotLayout SL{n};

@@ -39,7 +39,8 @@ struct LeafItem {
     int32_t flags;     // LEAF_LAST: holds the terminal cost; LEAF_TOP: whole problem
     int32_t slot;      // level-1 slot: receives its reduced form (up), holds the
                        // parent's solution for it (down)
-    int32_t m1;        // receding-horizon plans: M1 cache block of an interior leaf (-1: none)
+    int32_t m1;        // receding-horizon plans: M1 cache block of an interior leaf (-1: none);
+                       // GroupArgs.ordered: leaf that the workgroup of this item's index takes
     int64_t scratch;   // element offset of its per-stage factor storage
 };
 // LEAF_REUSE: its stored factorization and reduced form (M1 cache) are
@@ -195,6 +196,8 @@ struct GroupArgs {
     // 1: the instances' data have their own number of inputs (DevProb.nu), at
     // most this group's nu; the others are padding (fused solve)
     int32_t data_nu;
+    // 1: workgroup b of a leaf pass takes leaf leaves[b].m1 (longest first)
+    int32_t ordered;
     // first stage of a leaf's records in the stored factorization
     __host__ __device__ int64_t rec_stage(int64_t leaf_scratch) const { return leaf_scratch / sps - rec_stage0; }
 };

@@ -7,6 +7,12 @@
 #include "rs_types.hpp"
 
 namespace rs {
+
+// Leaf of this workgroup: in plans whose leaves do not all start at once the
+// longest go first, so that the last workgroups to start are the shortest.
+__device__ __forceinline__ int my_leaf(const GroupArgs &g) {
+    return g.ordered ? __builtin_amdgcn_readfirstlane(g.leaves[blockIdx.x].m1) : (int)blockIdx.x;
+}
 namespace sv {
 
 constexpr int WT = 64;

@@ -47,7 +47,7 @@ template <int NM, int MM, int W, bool EX, class TR>
 __global__ void __launch_bounds__(64 * W) ks_leaf_up(GroupArgs g) {
     __shared__ Smem<NM, MM, W> S;
     if (sv::pass_idle(g)) return;
-    const LeafItem it = sv::load_leaf(g.leaves, blockIdx.x);
+    const LeafItem it = sv::load_leaf(g.leaves, my_leaf(g));
     if ((it.flags & LEAF_TOP) || sv::skip_inst(g, it.inst)) return;
     const int n = EX ? NM : g.nx, m = EX ? MM : g.nu;
     const sv::Prob p = sv::load_prob(g.probs, it.inst);
@@ -74,7 +74,7 @@ template <int NM, int MM, int W, bool EX, class TR>
 __global__ void __launch_bounds__(64 * W) ks_leaf_down(GroupArgs g) {
     __shared__ Smem<NM, MM, W> S;
     if (sv::pass_idle(g)) return;
-    const LeafItem it = sv::load_leaf(g.leaves, blockIdx.x);
+    const LeafItem it = sv::load_leaf(g.leaves, my_leaf(g));
     if (sv::skip_inst(g, it.inst)) return;
     const int n = EX ? NM : g.nx, m = EX ? MM : g.nu;
     const sv::Prob p = sv::load_prob(g.probs, it.inst);
@@ -138,7 +138,7 @@ __global__ void __launch_bounds__(64 * W) ks_leaf_down(GroupArgs g) {
 template <int NM, int MM, int W, bool EX, bool MD>
 __global__ void __launch_bounds__(64 * W) ks_leaf_fwd(GroupArgs g) {
     __shared__ Smem<NM, MM, W> S;
-    const LeafItem it = sv::load_leaf(g.leaves, blockIdx.x);
+    const LeafItem it = sv::load_leaf(g.leaves, my_leaf(g));
     if ((it.flags & LEAF_TOP) || sv::skip_inst(g, it.inst)) return;
     const int n = EX ? NM : g.nx, m = EX ? MM : g.nu, md = MD ? uni(g.probs[it.inst].nu) : m;
     const sv::Prob p = sv::load_prob(g.probs, it.inst);

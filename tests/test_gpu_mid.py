@@ -116,3 +116,28 @@ def test_noalloc_takes_the_plans_it_counts_in():
         rs.rs_batch_solve_noalloc(plan, (rs.rs_problem * 1)())
     assert e.value.status == rs.RS_ERR_NOMEM
     rs.rs_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("precision,factored", [(0, False), (0, True), (1, False)])
+def test_many_leaves_run_longest_first(precision, factored):
+    """Plans of more leaves than workgroups that start together take them by
+    length: horizons below, at and above whole leaves, every leaf once (its
+    instance equals the oracle's, bar as above)."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1510_03110_amd import rs
+    Ns = [1 + (7 * i) % 23 for i in range(150)]
+    probs = [W.with_costs(W.g2(6, 3, N, seed=900 + i), seed=i) for i, N in enumerate(Ns)]
+    bt = rs.Batch({k: [p[k] for p in probs] for k in probs[0]}, precision=precision, Ns=4, branch=4, factored=factored)
+    assert len(rs.rs_plan_export(bt.plan, 0)) > 256
+    if factored:
+        bt.factor()
+        bt.solve_factored()
+    else:
+        bt.solve()
+    torch.cuda.synchronize()
+    assert (bt.status()[:, 0] == 0).all()
+    for i in range(150):
+        assert kkt.rel_error(bt.result(i), riccati.solve(probs[i])) <= TOL
+    bt.close()
