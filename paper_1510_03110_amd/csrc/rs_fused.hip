@@ -17,7 +17,7 @@
 // LDS for full tiles, vector-unit kernels below them that factored the master
 // levels twice) and now: one problem of N = 1024, 32 x 16 505 -> 250 us and
 // 20 x 10 864 -> 275 us; 4 x 2, N = 64 129 -> 69 us; 512 problems of 32 x 16,
-// N = 1024 13.6 -> 10.1 ms (leaves 10.2 -> 6.5 ms); 1024 of 16 x 8, N in [32,
+// N = 1024 13.6 -> 10.1 ms (leaves 10.2 -> 6.8 ms); 1024 of 16 x 8, N in [32,
 // 2048] 14.9 -> 7.0 ms (padding on load instead of padded copies: 1.3 ms).
 #include <hip/hip_runtime.h>
 

@@ -6,7 +6,7 @@
 //
 // Bound: the dependent chain of a stage (G, its Cholesky factorization, Y, P)
 // on one workgroup per CU at n_x = 64 (123 KB of LDS), then the matrix cores.
-// (64, 32), FP64, 1024 leaves of 64 stages: 24 us a stage, 36 TFLOP/s (98 us
+// (64, 32), FP64, 1024 leaves of 64 stages: 22 us a stage, 39 TFLOP/s (98 us
 // with every operand read through the L2); a 64 x 64 master stage takes about
 // 55 us (161 us); 8 x 4 stages (one tile, two wavefronts) 4 us (13.6 us).
 //   kc_leaf   one workgroup per leaf: Alg. 4 or the last-leaf elimination (up),
