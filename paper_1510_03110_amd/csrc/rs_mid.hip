@@ -1,6 +1,6 @@
-// Stored factorization of the shapes without compile-time matrix-core kernels
-// up to n_x = 64 (n_u <= n_x in tiles of 16): the column-owner stage engine
-// (rs_col.hpp) with run-time sizes, in place of the global-memory workspace
+// Stored factorization up to n_x = 64 (n_u <= n_x in tiles of 16): the
+// column-owner stage engine (rs_col.hpp), with run-time sizes or sizes that
+// fill the tiles, in place of the global-memory workspace
 // of the large-block kernels.  Same records, slots and work tables, so the
 // vector passes of the large-block family solve on them.
 //
