@@ -781,10 +781,15 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
     // the factor of G: A'V, and Q_w_hat += X'X of the stage before (X keeps its
     // place in LDS unless that is B's).
     constexpr bool QD = RED && !CH && !SM::OVER;
+    // The product is summed by itself and added once: with the running sum as
+    // the matrix instructions' addend every inner step rounds at its size, and
+    // the FP32 reductions lost a factor of 2 to 6 of their accuracy (mixed
+    // plans took one more correction; 64 problems of 64 x 32 in FP64 run 1 %
+    // longer this way).
     auto add_Q = [&](const Ln<T> &L, const v4_t<T> *X) {
 #pragma unroll
         for (int ti = 0; ti < NXT; ++ti)
-            if (ti >= j) C.Q[ti] = mulN<RX, NUT, SU>(L, C.Q[ti], S.X(), ti, X);
+            if (ti >= j) C.Q[ti] += mulN<RX, NUT, SU>(L, zero4<T>(), S.X(), ti, X);
     };
     auto add_Q_late = [&](const Ln<T> &L) {
         v4_t<T> X[NUT];

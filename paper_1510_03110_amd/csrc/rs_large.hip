@@ -208,11 +208,12 @@ using LdsPtr = __attribute__((address_space(3))) T *;
 // buffer bounds) into one of two LDS pairs, and each wavefront accumulates its
 // 16 x 16 tiles (tile t goes to wave t mod 8, at most 8 per wave) from there
 // while the next panel's loads are in flight, with one barrier per panel.  The
-// addend D enters as the accumulators' start: all its elements are in flight
-// at once with the first panel.  (Added element by element behind the product,
-// each read waiting for the store before it, it took longer than the product:
-// 128 x 128 x 64 with an addend 107 k cycles, of which 16 k on the matrix
-// cores.)  With `lower` only the tiles on and below the diagonal are formed
+// addend D waits in registers, its elements in flight at once with the first
+// panel, and is added once to the finished product (as the accumulators' start
+// every inner step would round at its size).  (Read element by element behind
+// the product, each read waiting for the store before it, it took longer than
+// the product: 128 x 128 x 64 with an addend 107 k cycles, of which 16 k on the
+// matrix cores.)  With `lower` only the tiles on and below the diagonal are formed
 // and only the elements with i >= j are put.  Small products (fewer than
 // GP_MIN_TILES tiles, such as G at n_u <= 64) skip the panels, and each wave
 // reads its tiles' operand strips itself.  One out-of-line body per operand
@@ -264,15 +265,13 @@ __device__ __attribute__((noinline)) void gemm_panel(LdsPtr<T> sm, int M, int N,
 #pragma unroll
             for (int r = 0; r < 4; ++r) v[r] = buf_get<T>(bDT, byte(at(ti, tj, r, ldd), SZ));
         }
-        if (neg)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = -v[r];
         return v;
     };
-    auto finish = [&](int ti, int tj, v4_t<T> v) {
+    auto finish = [&](int ti, int tj, v4_t<T> d, v4_t<T> v) {
         if (neg)
 #pragma unroll
             for (int r = 0; r < 4; ++r) v[r] = -v[r];
+        v += d;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int i = mf::trow<T>(ti, r), j = mf::tcol(tj);
@@ -296,7 +295,8 @@ __device__ __attribute__((noinline)) void gemm_panel(LdsPtr<T> sm, int M, int N,
             tile(t, ti, tj);
             const int i = 16 * ti + r16, j = 16 * tj + r16;
             const bool iv = i < M, jv = j < N;
-            v4_t<T> acc = start(ti, tj);
+            const v4_t<T> d = start(ti, tj);
+            v4_t<T> acc = mf::zero4<T>();
             for (int k0 = 0; k0 < K; k0 += 32) {
                 T a[8], b[8];
 #pragma unroll
@@ -308,12 +308,12 @@ __device__ __attribute__((noinline)) void gemm_panel(LdsPtr<T> sm, int M, int N,
 #pragma unroll
                 for (int s = 0; s < 8; ++s) acc = MT<T>::mfma(a[s], b[s], acc);
             }
-            finish(ti, tj, acc);
+            finish(ti, tj, d, acc);
         }
         return;
     }
     int ti[QMAX], tj[QMAX];
-    v4_t<T> acc[QMAX];
+    v4_t<T> acc[QMAX], d[QMAX];
 #pragma unroll
     for (int q = 0; q < QMAX; ++q) {
         tile(w + 8 * q < nt ? w + 8 * q : 0, ti[q], tj[q]);
@@ -337,7 +337,10 @@ __device__ __attribute__((noinline)) void gemm_panel(LdsPtr<T> sm, int M, int N,
     };
     fetch(0);
 #pragma unroll
-    for (int q = 0; q < QMAX; ++q) acc[q] = w + 8 * q < nt ? start(ti[q], tj[q]) : mf::zero4<T>();
+    for (int q = 0; q < QMAX; ++q) {
+        d[q] = w + 8 * q < nt ? start(ti[q], tj[q]) : mf::zero4<T>();
+        acc[q] = mf::zero4<T>();
+    }
     LdsPtr<T> As = sm, Bs = sm + GP_M * GP_AP;
     int other = GP_ELEMS;                 // offset of the other pair of panels
     for (int k0 = 0; k0 < K; k0 += GP_K) {
@@ -368,7 +371,7 @@ __device__ __attribute__((noinline)) void gemm_panel(LdsPtr<T> sm, int M, int N,
     }
 #pragma unroll
     for (int q = 0; q < QMAX; ++q)
-        if (w + 8 * q < nt) finish(ti[q], tj[q], acc[q]);
+        if (w + 8 * q < nt) finish(ti[q], tj[q], d[q], acc[q]);
     lds_sync();           // the panels are free for the next product
 }
 

@@ -384,13 +384,16 @@ __device__ __forceinline__ void stage(T *sm, Work<T> &S, const StageSrc &src, in
 #pragma unroll
                 for (int t = 0; t < NUT; ++t) store(L, bl, n, t, j, m, n, l[t]);
         }
-        // ---- Q_w_hat += X'X (lower tiles; the whole matrix after the last)
+        // ---- Q_w_hat += X'X (lower tiles; the whole matrix after the last):
+        // the product by itself, added once (see add_Q in rs_col.hpp)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) av[t] = tile<false, false, T>(L, S.Q, n, t, j, n, n, t >= j);
+        for (int t = 0; t < NT; ++t) av[t] = zero4<T>();
         sweep(sm, X, none, false, no_pre, no_adv, [&](int, const T *P0, const T *) {
             const v4_t<T> b = rotate(x);
             mul(L, av, P0, 0, b, j, nt);
         });
+#pragma unroll
+        for (int t = 0; t < NT; ++t) av[t] += tile<false, false, T>(L, S.Q, n, t, j, n, n, t >= j);
         const Buf bq = buf(S.Q, n * n);
 #pragma unroll
         for (int t = 0; t < NT; ++t)
