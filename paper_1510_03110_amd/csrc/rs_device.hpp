@@ -262,35 +262,45 @@ __device__ __attribute__((noinline)) void rank_reveal(T *M, int n, double eps, d
         for (int cc = c; cc < n; ++cc) put(tid, cc, 0.0);
 }
 
-// The same factorization for n <= NM <= 64 (NM known at compile time): the
-// thread of row i keeps that row in registers, the pivot column goes through
-// a short LDS vector, and M is only read.
+// The same factorization for n <= NM <= 64 (NM known at compile time): four
+// threads hold a row of the remaining Schur complement in registers, in 64
+// bits whatever T, a quarter of it each; the pivot column goes through a short
+// LDS vector, and M is only read.  A dependent chain of n pivots; 32 states of
+// rank 32 take 34 us (one thread a row 68 us, and so many registers that other
+// workgroups find no room; rows in LDS at pitch n, where they collide, 150 us).
+// Out of line, it takes no register from the stage loops.  At least 4 NM
+// threads.
 template <int NM, class T>
 __device__ __attribute__((noinline)) void rank_reveal_rows(const T *M, int n, double eps, double *out,
                                                            double *cache) {
-    static_assert(NM >= 1 && NM <= 64, "one register row of at most 64");
-    __shared__ double s_val[16], s_l[NM];
-    __shared__ int s_idx[16];
-    const int tid = threadIdx.x, nw = (int)(blockDim.x + 63) >> 6, w = tid >> 6, l = tid & 63;
-    const bool own = tid < n;
-    auto put = [&](int i, int c, double v) {
+    static_assert(NM % 16 == 0 && NM <= 64, "whole wavefronts of rows");
+    constexpr int C = NM / 4, NW = NM / 16;   // columns of a thread, wavefronts that hold rows
+    __shared__ double s_val[NW], s_l[NM];
+    __shared__ int s_idx[NW];
+    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, i = tid % NM, q = tid / NM;
+    const bool own = w < NW && i < n;
+    auto put = [&](int c, double v) {
         out[i * n + c] = v;
         if (cache) cache[i * n + c] = v;
     };
-    double r[NM];
+    double r[C];
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < NM; ++k) r[k] = (own && k < n) ? (double)M[tid * n + k] : 0.0;
+    for (int k = 0; k < C; ++k) r[k] = (own && C * q + k < n) ? (double)M[i * n + C * q + k] : 0.0;
+    // element k of this thread's quarter
+    auto pick = [&](int k) {
+        double d = 0.0;
+#pragma unroll
+        for (int e = 0; e < C; ++e) d = (e == k) ? r[e] : d;
+        return d;
+    };
     uint64_t done = 0;                        // pivots taken (the same in every thread)
     double tol = 0.0;
     int c = 0;
     for (; c < n; ++c) {
-        const bool live = own && !((done >> tid) & 1);
-        double d = 0.0;
-#pragma unroll
-        for (int k = 0; k < NM; ++k) d = (k == tid) ? r[k] : d;
-        double v = live ? d : -1.0;
-        int p = tid;
+        const bool live = own && !((done >> i) & 1);
+        double v = (live && q == i / C) ? pick(i % C) : -1.0;
+        int p = i;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
             const double v2 = __shfl_xor(v, o, 64);
@@ -300,14 +310,15 @@ __device__ __attribute__((noinline)) void rank_reveal_rows(const T *M, int n, do
                 p = p2;
             }
         }
-        if (l == 0) {
+        if (l == 0 && w < NW) {
             s_val[w] = v;
             s_idx[w] = p;
         }
         __syncthreads();
         v = s_val[0];
         p = s_idx[0];
-        for (int u = 1; u < nw; ++u) {
+#pragma unroll
+        for (int u = 1; u < NW; ++u) {
             const double v2 = s_val[u];
             const int p2 = s_idx[u];
             if (v2 > v || (v2 == v && p2 < p)) {
@@ -318,21 +329,21 @@ __device__ __attribute__((noinline)) void rank_reveal_rows(const T *M, int n, do
         if (c == 0) tol = (double)n * eps * v;
         if (!(v > tol)) break;                // rank reached (also an all-zero M)
         const double s = 1.0 / sqrt(v);
-        double rp = 0.0;
-#pragma unroll
-        for (int k = 0; k < NM; ++k) rp = (k == p) ? r[k] : rp;
-        const double li = (live && tid != p) ? rp * s : 0.0;
-        if (own) put(tid, c, !live ? 0.0 : (tid == p ? v * s : li));
-        if (tid < NM) s_l[tid] = li;          // 0 for the pivot row and rows already taken
+        if (w < NW && q == p / C) {
+            const double li = (live && i != p) ? pick(p % C) * s : 0.0;
+            if (own) put(c, !live ? 0.0 : (i == p ? v * s : li));
+            s_l[i] = li;                      // 0 for the pivot row and rows already taken
+        }
         __syncthreads();
-        if (live && tid != p) {
+        if (live && i != p) {
+            const double li = s_l[i];
 #pragma unroll
-            for (int k = 0; k < NM; ++k) r[k] -= li * s_l[k];
+            for (int k = 0; k < C; ++k) r[k] -= li * s_l[C * q + k];
         }
         done |= 1ull << p;
     }
-    if (own)
-        for (int cc = c; cc < n; ++cc) put(tid, cc, 0.0);
+    if (own && q == 0)
+        for (int cc = c; cc < n; ++cc) put(cc, 0.0);
 }
 
 template <class T>

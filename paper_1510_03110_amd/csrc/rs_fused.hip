@@ -78,7 +78,7 @@ __global__ void __launch_bounds__(128 * NXT, NXT == 1 ? 4 : NUT == 1 ? 3 : 2) kf
         if (tid == 0) out[SL.c()] = c;
         if (g.ident && !(it.flags & LEAF_LAST)) {
             store_Q<SX>(C, S.A, n);              // A is dead: Q_w_hat, row-major
-            rank_reveal(S.A, n, unit_roundoff<double>(), out + SL.Qw(), nullptr);
+            rank_reveal_rows<SM::RX>(S.A, n, unit_roundoff<double>(), out + SL.Qw(), nullptr);
         }
         return;
     }
@@ -161,7 +161,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kf_tree(GroupArgs g) {
             if (tid == 0) out[SL.c()] = c;
             if (g.ident) {
                 store_Q<SX>(C, S.A, n);
-                rank_reveal(S.A, n, unit_roundoff<double>(), out + SL.Qw(), nullptr);
+                rank_reveal_rows<SM::RX>(S.A, n, unit_roundoff<double>(), out + SL.Qw(), nullptr);
             }
         } else if (it.kind == ITEM_UP_LAST || it.kind == ITEM_TOP) {
             // Alg. 1-2 from the level's true terminal: the level's last item

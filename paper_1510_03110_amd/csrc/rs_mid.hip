@@ -64,7 +64,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_leaf(GroupArgs g, int down) {
         }
         if (g.ident) {
             store_Q<SX>(C, S.A, n);              // A is dead: Q_w_hat, row-major
-            rank_reveal(S.A, n, unit_roundoff<T>(), out + SL.Qw(), cache ? cache + SL.Qw() : nullptr);
+            rank_reveal_rows<SM::RX>(S.A, n, unit_roundoff<T>(), out + SL.Qw(), cache ? cache + SL.Qw() : nullptr);
         }
     } else {
         if (down) base += R.up();
@@ -114,7 +114,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_tree(GroupArgs g) {
                 store_Q<SX>(C, out + SL.Qw(), n);
             } else {
                 store_Q<SX>(C, S.A, n);
-                rank_reveal(S.A, n, unit_roundoff<double>(), out + SL.Qw(), nullptr);
+                rank_reveal_rows<SM::RX>(S.A, n, unit_roundoff<double>(), out + SL.Qw(), nullptr);
             }
         } else if (it.kind == ITEM_DOWN && g.superpose) {
             // solved by the vector pass from the up records: nothing to factor

@@ -1,4 +1,4 @@
-"""Accuracy of what the reductions hold in 32 bits, on data whose FP32 leaf
+"""Accuracy of the reductions of mixed plans, on data whose FP32 leaf
 factorization is exact, so that the first solve of a mixed plan is as accurate
 as an FP64 one and its first correction shows any rounding added to it."""
 import numpy as np
@@ -58,3 +58,22 @@ def test_reduced_input_weight_is_summed_once_a_stage(n, m, precision):
     n = m = 8)."""
     dz = _first_correction(_sums_of_inputs(n, m, 33, 3, n), precision=precision, Ns=33, branch=2)
     assert dz <= 1e-6, "first correction %.2e" % dz
+
+
+@pytest.mark.parametrize("n,m", [(8, 3), (16, 8), (20, 10), (32, 16), (48, 8), (64, 16)])
+def test_rank_revealing_factor_keeps_64_bits(n, m):
+    """One-stage leaves of small whole numbers with Q_w = I, Q_xw = 0 (P = 0
+    before them, so K = 0, L = I, V = A' and Q_w_hat = B B', all exact in
+    FP32) and Q_xN = 0.  The pivoted factor of B B' holds its remaining rows
+    in 64 bits, as the master levels do.  Bound: a 64th of one rounding to
+    FP32 (2^-24 / 64); FP64 roundings leave about 1e-13, a factor held in 32
+    bits 5e-11 and more."""
+    rng = np.random.default_rng(n)
+    N = 24
+    ints = lambda *s: rng.integers(-3, 4, s).astype(float)  # noqa: E731
+    prob = dict(Qx=np.tile(4.0 * np.eye(n), (N, 1, 1)), Qw=np.tile(np.eye(m), (N, 1, 1)), Qxw=np.zeros((N, n, m)),
+                A=ints(N, n, n) * (rng.random((N, n, n)) < 2.0 / n) / 4, B=ints(N, n, m), a=ints(N, n),
+                lx=ints(N, n), lw=ints(N, m), c=np.zeros(N), QxN=np.zeros((n, n)), lN=ints(n),
+                cN=np.float64(0.0), x0=ints(n))
+    dz = _first_correction(prob, precision=1, Ns=1, branch=3, rank_reveal=True)
+    assert dz <= 2.0 ** -30, "first correction %.2e" % dz
