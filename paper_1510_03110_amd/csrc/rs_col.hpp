@@ -580,7 +580,7 @@ struct QTiles {
 };
 
 // Stage loop of the waves that own a column block of A (w < NXT).
-template <bool RED, bool EX, bool EXD, bool VEC, class T, int NXT, int NUT, int SX, int SU, class Pre, class RecOf>
+template <bool RED, bool EX, bool EXD, bool VEC, bool KEEP, class T, int NXT, int NUT, int SX, int SU, class Pre, class RecOf>
 __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int m, int md, StageWalk wk, int count, int32_t *info, int inst,
                                        int stage_base, int fail_code, Pre pre, RecOf rec, Vec &y) {
     using SM = Smem<T, NXT, NUT, SX, SU>;
@@ -684,7 +684,7 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
         if constexpr (NXT == 1) {
             // the record of P_{s+1}, still in LDS (the other wave factors G)
             pre(s, 0, 64);
-            put_P<EX, 64>(S, rec(s + 1 < count ? s + 1 : s).P, n, threadIdx.x, s + 1 < count);
+            if (KEEP) put_P<EX, 64>(S, rec(s + 1 < count ? s + 1 : s).P, n, threadIdx.x, s + 1 < count);
         }
         lds_sync();
         if (threadIdx.x == 0 && S.bad) {
@@ -713,9 +713,9 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
 #pragma unroll
                 for (int r = 0; r < SU; ++r) yz += R2[ti][r] * S.z[16 * ti + L.row(r)];
             y.psi = gx - q_sum(yz);
-            buf_st(buf(out.Psi, n), 8u * (uint32_t)(16 * j + L.c), y.psi);
+            if (KEEP) buf_st(buf(out.Psi, n), 8u * (uint32_t)(16 * j + L.c), y.psi);
         }
-        store_feedback<EX, RU, RX, NUT, SU, VEC>(L, S.G, R2, out.K, j, n, m, S.z, zs ? out.k : nullptr);
+        if (KEEP) store_feedback<EX, RU, RX, NUT, SU, VEC>(L, S.G, R2, out.K, j, n, m, S.z, zs ? out.k : nullptr);
         if (RED && !VEC) put_L<EX, 64 * NXT>(S, out.L, out.LT, m, threadIdx.x);
         lds_sync();
         if (SM::OVER) lds_sync();
@@ -725,7 +725,7 @@ __device__ __forceinline__ void loop_P(Smem<T, NXT, NUT, SX, SU> &S, int n, int 
 // Stage loop of the waves NXT + j: A and B of the next stage are loaded into
 // their registers, the last of them (CH) factors G, and for Alg. 4 they own the
 // column blocks of V and Q_w_hat.
-template <bool CH, bool RED, bool EX, bool EXD, bool VEC, class T, int NXT, int NUT, int SX, int SU, class Pre, class RecOf>
+template <bool CH, bool RED, bool EX, bool EXD, bool VEC, bool KEEP, class T, int NXT, int NUT, int SX, int SU, class Pre, class RecOf>
 __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT> &C, int n, int m, int md, StageWalk wk, int count, Pre pre,
                                        RecOf rec, Vec &y) {
     using SM = Smem<T, NXT, NUT, SX, SU>;
@@ -837,7 +837,7 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
             if (NXT > 1) fetch(wk.s, s > 0);
             // the record of P_{s+1}, still in LDS
             pre(s, NTV, 2 * NTV - 64);
-            put_P<EX, NTV - 64>(S, rec(s + 1 < count ? s + 1 : s).P, n, (int)threadIdx.x - NTV, s + 1 < count);
+            if (KEEP) put_P<EX, NTV - 64>(S, rec(s + 1 < count ? s + 1 : s).P, n, (int)threadIdx.x - NTV, s + 1 < count);
         }
         lds_sync();
         const Rec<T> out = rec(s);
@@ -851,7 +851,7 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
                 const v4_t<T> acc = mulN<RX, NUT, SU>(L, zero4<T>(), S.Y(), ti, R2);
 #pragma unroll
                 for (int r = 0; r < SX; ++r) C.V[ti][r] = R1[ti][r] - acc[r];
-                store_tile<EX, SX>(L, bv, n, ti, j, n, C.V[ti]);
+                if (KEEP) store_tile<EX, SX>(L, bv, n, ti, j, n, C.V[ti]);
             }
             if (!QD) add_Q(L, R2);
             if constexpr (VEC) {
@@ -862,7 +862,7 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
                     for (int r = 0; r < SU; ++r) xz += R2[ti][r] * S.z[16 * ti + L.row(r)];
                 y.v += q_sum(xz);
             }
-            if (VEC || out.Lt) store_feedback<EX, RU, RX, NUT, SU>(L, S.G, R2, out.Lt, j, n, m);
+            if (KEEP && (VEC || out.Lt)) store_feedback<EX, RU, RX, NUT, SU>(L, S.G, R2, out.Lt, j, n, m);
         } else if (!VEC) {
             put_L<EX, NTV>(S, out.L, out.LT, m, (int)threadIdx.x - NTV);
         }
@@ -883,10 +883,11 @@ __device__ __forceinline__ void loop_V(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT
 // S.P; rec(s): where its factors go, with n and m their sizes (EX: n = 16 NXT
 // and m = 16 NUT exactly).  The problem data have md <= m inputs (EXD: 16 NUT),
 // the others being padding.
-// VEC: with the right-hand side, y holding Psi_{count} on entry.
+// VEC: with the right-hand side, y holding Psi_{count} on entry.  KEEP: the
+// factors go to their records (else rec is not used).
 // The three kinds of waves run loops of their own (with the same barriers), so
 // that neither carries the other's registers.
-template <bool RED, bool EX, bool EXD, bool VEC, class T, int NXT, int NUT, int SX, int SU, class Pre,
+template <bool RED, bool EX, bool EXD, bool VEC, bool KEEP = true, class T, int NXT, int NUT, int SX, int SU, class Pre,
           class RecOf>
 __device__ __forceinline__ void pass(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT> &C, int n_, int m_, int md_, StageWalk wk, int count,
                                      int32_t *info, int inst, int stage_base, int fail_code, Pre pre, RecOf rec, Vec &y) {
@@ -900,13 +901,13 @@ __device__ __forceinline__ void pass(Smem<T, NXT, NUT, SX, SU> &S, Cols<T, NXT> 
     count = uni(count);
     if (tid == 0) S.bad = 0;
     if (wave() < NXT)
-        loop_P<RED, EX, EXD, VEC>(S, n, m, md, wk, count, info, inst, stage_base, fail_code, pre, rec, y);
+        loop_P<RED, EX, EXD, VEC, KEEP>(S, n, m, md, wk, count, info, inst, stage_base, fail_code, pre, rec, y);
     else if (wave() == 2 * NXT - 1)
-        loop_V<true, RED, EX, EXD, VEC>(S, C, n, m, md, wk, count, pre, rec, y);
+        loop_V<true, RED, EX, EXD, VEC, KEEP>(S, C, n, m, md, wk, count, pre, rec, y);
     else if constexpr (NXT > 1)
-        loop_V<false, RED, EX, EXD, VEC>(S, C, n, m, md, wk, count, pre, rec, y);
+        loop_V<false, RED, EX, EXD, VEC, KEEP>(S, C, n, m, md, wk, count, pre, rec, y);
     lds_sync();
-    {
+    if constexpr (KEEP) {
         T *p = rec(0).P;
         if (p) copy_P(S, p, n);
     }

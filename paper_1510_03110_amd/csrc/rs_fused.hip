@@ -1,22 +1,28 @@
 // Fused FP64 solve (factor and right-hand side in one pass, no stored
 // factorization) for n_x <= 32 on the column-owner engine (rs_col.hpp):
-//   kf_leaf   one workgroup per leaf: Alg. 4, or elimination with the true
-//             terminal, keeping K, k, P, Psi, V and L_t of every stage; down:
-//             whole-problem leaves, Alg. 1-3
+//   kf_leaf   one workgroup per leaf.  Up: Alg. 4, or elimination with the true
+//             terminal; down: elimination with the true terminal and Alg. 3
 //   kf_tree   work queue over the master levels: Alg. 5 up, the top solve, and
-//             Alg. 6 down to level 1 as forward sweeps on the records of the
-//             up pass
-// The leaves of multi-leaf instances are finished by the forward sweep on
-// their records (fused_leaf_forward).  Run-time sizes below the tiles
-// (n_x = 4, 8, 20, ...) are padded on load, as are the inputs of instances
-// with fewer inputs than their group's tile (g.data_nu).
+//             Alg. 6 down to level 1
+// Shapes of full tiles (n_x and n_u multiples of 16) keep K, k, P, Psi, V and
+// L_t of every stage of the up pass, and everything below the top is a forward
+// sweep on them by superposition (fused_leaf_forward for the leaves; whole-
+// problem leaves go through kf_leaf).  The others (run-time sizes, n_x = 4, 8,
+// 20, ...) are eliminated again with the parent's P and Psi, keeping K, k, P and
+// Psi of that pass: there the superposition's w = K x + k + L_t lam_N, whose
+// L_t does not know the terminal, would pass the rounding of lam_N on undamped
+// (2 times the error of elimination on average, 10 times with small state
+// weights and unstable dynamics; it would take 69 us instead of 81 for one
+// problem of 4 x 2, N = 64, and 275 instead of 380 for 20 x 10, N = 1024).
+// Sizes below the tiles are padded on load, as are the inputs of instances with
+// fewer inputs than their group's tile (g.data_nu).
 //
 // Bound: the dependent chain of a stage; on large batches the workgroups that
 // share a CU fill one another's waits, and the records' bytes are next.  FP64,
 // the whole solve before (a four-wave tile engine with every product through
 // LDS for full tiles, vector-unit kernels below them that factored the master
 // levels twice) and now: one problem of N = 1024, 32 x 16 505 -> 250 us and
-// 20 x 10 864 -> 275 us; 4 x 2, N = 64 129 -> 69 us; 512 problems of 32 x 16,
+// 20 x 10 862 -> 380 us; 4 x 2, N = 64 129 -> 81 us; 512 problems of 32 x 16,
 // N = 1024 13.6 -> 10.1 ms (leaves 10.2 -> 6.8 ms); 1024 of 16 x 8, N in [32,
 // 2048] 14.9 -> 7.0 ms (padding on load instead of padded copies: 1.3 ms).
 #include <hip/hip_runtime.h>
@@ -40,7 +46,8 @@ __global__ void __launch_bounds__(128 * NXT, NXT == 1 ? 4 : NUT == 1 ? 3 : 2) kf
     __shared__ SM S;
     __shared__ vs::Smem<SM::RX, SM::RU, W> F;
     const LeafItem it = load_leaf_u(g.leaves, my_leaf(g));
-    if (((it.flags & LEAF_TOP) != 0) != (down != 0) || inst_skipped(g.probs, it.inst)) return;
+    const bool top = (it.flags & LEAF_TOP) != 0, last = (it.flags & LEAF_LAST) != 0;
+    if ((down ? EX && !top : top) || inst_skipped(g.probs, it.inst)) return;
     const DevProb p = load_prob(g.probs, it.inst);
     const int n = EX ? SM::RX : g.nx, m = EX ? SM::RU : g.nu, md = SZ == DATA ? p.nu : m, tid = threadIdx.x;
     const SlotLayout SL{n};
@@ -58,51 +65,61 @@ __global__ void __launch_bounds__(128 * NXT, NXT == 1 ? 4 : NUT == 1 ? 3 : 2) kf
     const bool own = L.q == 0 && col < n;            // owner lane of entry col
     Cols<double, NXT> C;
     Vec y{};
-    if (!(it.flags & LEAF_LAST)) {
+    if (!down && !last) {
         set_P(S, n, [](int) { return 0.0; });
-        pass<true, EX, EXD, true>(S, C, n, m, md, wk, it.len, g.info, it.inst, it.t0, 2, no_pre, rec, y);
+        pass<true, EX, EXD, true, EX>(S, C, n, m, md, wk, it.len, g.info, it.inst, it.t0, 2, no_pre, rec, y);
         store_V_transposed<SX>(C, out + SL.A(), n);
         copy_P(S, out + SL.Qx(), n);
         if (!g.ident) store_Q<SX>(C, out + SL.Qw(), n);
         if (own && w >= NXT) out[SL.a() + col] = y.v;
-    } else {
-        set_P(S, n, [&](int e) { return p.QxN[e]; });
-        if (w < NXT && col < n) y.psi = p.lN ? -p.lN[col] : 0.0;
+    } else if (!down || top || !last) {
+        // from the true terminal: the parent's message, or the problem's own
+        // (whose records, kept by the up pass, also serve the down pass)
+        const double *P0 = last ? p.QxN : out + SL.P();
+        set_P(S, n, [&](int e) { return P0[e]; });
+        if (w < NXT && col < n) y.psi = !last ? out[SL.Psi() + col] : p.lN ? -p.lN[col] : 0.0;
         pass<false, EX, EXD, true>(S, C, n, m, md, wk, it.len, g.info, it.inst, it.t0, 2, no_pre, rec, y);
         if (!down) copy_P(S, out + SL.Qx(), n);
     }
-    const double c = total(S, y.cb + vs::sum_c(p.c ? p.c + (int64_t)it.t0 * p.sc : nullptr, p.sc, it.len)) +
-                     (((it.flags & LEAF_LAST) && p.cN) ? p.cN[0] : 0.0);
-    if (!down) {
-        if (own && w < NXT) out[SL.lx() + col] = -y.psi;
-        if (tid == 0) out[SL.c()] = c;
-        if (g.ident && !(it.flags & LEAF_LAST)) {
-            store_Q<SX>(C, S.A, n);              // A is dead: Q_w_hat, row-major
-            rank_reveal_rows<SM::RX>(S.A, n, unit_roundoff<double>(), out + SL.Qw(), nullptr);
+    if (!down || top) {
+        const double c = total(S, y.cb + vs::sum_c(p.c ? p.c + (int64_t)it.t0 * p.sc : nullptr, p.sc, it.len)) +
+                         ((last && p.cN) ? p.cN[0] : 0.0);
+        if (!down) {
+            if (own && w < NXT) out[SL.lx() + col] = -y.psi;
+            if (tid == 0) out[SL.c()] = c;
+            if (g.ident && !last) {
+                store_Q<SX>(C, S.A, n);              // A is dead: Q_w_hat, row-major
+                rank_reveal_rows<SM::RX>(S.A, n, unit_roundoff<double>(), out + SL.Qw(), nullptr);
+            }
+            return;
         }
-        return;
+        if (p.obj) {
+            // whole problem: optimal value 1/2 x0'P_0 x0 - Psi_0'x0 + cbar_0
+            for (int e = tid; e < SM::RX; e += SM::NTH) F.x[e] = e < n ? p.x0[e] : 0.0;
+            __syncthreads();
+            double px = 0.0;
+            if (w < NXT) {
+#pragma unroll
+                for (int kt = 0; kt < NXT; ++kt)
+#pragma unroll
+                    for (int r = 0; r < SX; ++r) px += ldN<SM::RX>(L, S.P, kt, w, r) * F.x[16 * kt + L.row(r)];
+                px = q_sum(px);
+            }
+            const double o = total(S, (own && w < NXT) ? F.x[col] * (0.5 * px - y.psi) : 0.0);
+            if (tid == 0) p.obj[0] = o + c;
+        }
     }
-    // whole problem: optimal value 1/2 x0'P_0 x0 - Psi_0'x0 + cbar_0, then Alg. 3
-    for (int e = tid; e < SM::RX; e += SM::NTH) F.x[e] = e < n ? p.x0[e] : 0.0;
+    // ---- Alg. 3
+    const double *x0 = top ? p.x0 : out + SL.xh();
+    for (int e = tid; e < SM::RX; e += SM::NTH) F.x[e] = e < n ? x0[e] : 0.0;
     __threadfence_block();                   // the records are read back by other lanes
     __syncthreads();
-    if (p.obj) {
-        double px = 0.0;
-        if (w < NXT) {
-#pragma unroll
-            for (int kt = 0; kt < NXT; ++kt)
-#pragma unroll
-                for (int r = 0; r < SX; ++r) px += ldN<SM::RX>(L, S.P, kt, w, r) * F.x[16 * kt + L.row(r)];
-            px = q_sum(px);
-        }
-        const double o = total(S, (own && w < NXT) ? F.x[col] * (0.5 * px - y.psi) : 0.0);
-        if (tid == 0) p.obj[0] = o + c;
-    }
     const int64_t t0 = it.t0;
     vs::forward<SM::RX, SM::RU, W, EX, EXD, double>(
         F, n, m, md, it.len, vs::FusedStages{sv::load_prob(g.probs, it.inst), it.t0, n, m, base}, false,
         [&](int s) { return p.x + (t0 + s) * n; }, [&](int s) { return p.w + (t0 + s) * md; },
         [&](int s) { return p.lam + (t0 + s) * n; });
+    if (!last) return;
     const int64_t t = t0 + it.len;
     const double q = vs::sym_apply<SM::RX, SM::RU, W>(p.QxN, F.x, n);
     typedef vs::Mat<double, SM::RX, SM::RX, W> MA;
@@ -113,6 +130,7 @@ __global__ void __launch_bounds__(128 * NXT, NXT == 1 ? 4 : NUT == 1 ? 3 : 2) kf
     }
 }
 
+// EX: full tiles.
 template <int NXT, bool EX, int SX = 4>
 __global__ void __launch_bounds__(128 * NXT, 2) kf_tree(GroupArgs g) {
     using SM = Smem<double, NXT, NXT, SX, SX>;
@@ -141,13 +159,25 @@ __global__ void __launch_bounds__(128 * NXT, 2) kf_tree(GroupArgs g) {
         const bool own = L.q == 0 && col < n;
         const int ir = MA::out_row();
         const bool ownr = MA::lead_row() && ir < n;
+        auto none = [](int) { return (double *)nullptr; };
+        // forward with the K and k of the item's stages, x to the children
+        auto solve = [&] {
+            auto st = [&](int s) {
+                vs::Stage<double> q = vs::SlotStages{slots, it.first, n, false}(s);
+                q.P = nullptr;
+                return q;
+            };
+            vs::forward<NM, NM, W, EX, EX, double>(F, n, n, n, it.count, st, false,
+                                                   [&](int s) { return slot(it.first + s) + SL.xh(); }, none, none);
+        };
+        const bool last = it.last != 0;
         Cols<double, NXT> C;
         Vec y{};
         if (inst_skipped(g.probs, it.inst)) {
             // excluded instance: only its completion flag is published
         } else if (it.kind == ITEM_UP) {
             set_P(S, n, [](int) { return 0.0; });
-            pass<true, EX, EX, true>(S, C, n, n, n, wk, it.count, g.info, it.inst, -1, 3, no_pre, [&](int s) {
+            pass<true, EX, EX, true, EX>(S, C, n, n, n, wk, it.count, g.info, it.inst, -1, 3, no_pre, [&](int s) {
                 double *d = slot(it.first + s);
                 return Rec<double>{d + SL.uP(), d + SL.uK(), d + SL.uV(), d + SL.dL(), nullptr, nullptr, d + SL.Psi(),
                                    d + SL.k()};
@@ -163,14 +193,17 @@ __global__ void __launch_bounds__(128 * NXT, 2) kf_tree(GroupArgs g) {
                 store_Q<SX>(C, S.A, n);
                 rank_reveal_rows<SM::RX>(S.A, n, unit_roundoff<double>(), out + SL.Qw(), nullptr);
             }
-        } else if (it.kind == ITEM_UP_LAST || it.kind == ITEM_TOP) {
-            // Alg. 1-2 from the level's true terminal: the level's last item
-            // keeps its up records, the top the messages to its children
-            const bool top = it.kind == ITEM_TOP;
-            double *term = slot(it.term_slot);
-            set_P(S, n, [&](int e) { return term[SL.Qx() + e]; });
-            if (w < NXT && col < n) y.psi = -term[SL.lx() + col];
-            if (top) {
+        } else if (it.kind != ITEM_DOWN || (!EX && !last)) {
+            // Alg. 1-2 from the true terminal: the level's own, or the
+            // parent's message.  The level's last item keeps its up records
+            // (full tiles); the others keep K and k and send P and Psi to
+            // their children.
+            const bool top = it.kind == ITEM_TOP, upl = it.kind == ITEM_UP_LAST, msgs = !EX || top;
+            double *end = slot(it.kind == ITEM_DOWN ? it.out_slot : it.term_slot);
+            const double *P0 = end + (it.kind == ITEM_DOWN ? SL.P() : SL.Qx());
+            set_P(S, n, [&](int e) { return P0[e]; });
+            if (w < NXT && col < n) y.psi = it.kind == ITEM_DOWN ? end[SL.Psi() + col] : -end[SL.lx() + col];
+            if (msgs) {
                 double *d = slot(it.first + it.count - 1);
                 __syncthreads();
                 copy_P(S, d + SL.P(), n);
@@ -178,25 +211,27 @@ __global__ void __launch_bounds__(128 * NXT, 2) kf_tree(GroupArgs g) {
             }
             pass<false, EX, EX, true>(S, C, n, n, n, wk, it.count, g.info, it.inst, -1, 3, no_pre, [&](int s) {
                 double *d = slot(it.first + s);
-                if (!top)
+                if (!msgs)
                     return Rec<double>{d + SL.uP(), d + SL.uK(), nullptr, nullptr, nullptr, nullptr, d + SL.Psi(),
                                        d + SL.k()};
                 double *c = slot(it.first + (s > 0 ? s - 1 : 0));
                 return Rec<double>{s > 0 ? c + SL.P() : nullptr, d + SL.K(), nullptr, nullptr, nullptr, nullptr,
                                    s > 0 ? c + SL.Psi() : nullptr, d + SL.k()};
             }, y);
-            const double c = total(S, y.cb + c_sum()) + term[SL.c()];
-            if (!top) {
+            double c = 0.0;
+            if (top || upl) c = total(S, y.cb + c_sum()) + end[SL.c()];
+            if (upl) {
                 double *out = slot(it.out_slot);
                 copy_P(S, out + SL.Qx(), n);
                 if (own && w < NXT) out[SL.lx() + col] = -y.psi;
                 if (tid == 0) out[SL.c()] = c;
             } else {
                 const DevProb p = load_prob(g.probs, it.inst);
-                for (int e = tid; e < NM; e += SM::NTH) F.x[e] = e < n ? p.x0[e] : 0.0;
+                const double *x0 = top ? p.x0 : end + SL.xh();
+                for (int e = tid; e < NM; e += SM::NTH) F.x[e] = e < n ? x0[e] : 0.0;
                 __threadfence_block();       // K, k and the messages are read back by other lanes
                 __syncthreads();
-                if (p.obj) {
+                if (top && p.obj) {
                     double px = 0.0;
                     if (w < NXT) {
 #pragma unroll
@@ -208,34 +243,36 @@ __global__ void __launch_bounds__(128 * NXT, 2) kf_tree(GroupArgs g) {
                     const double o = total(S, (own && w < NXT) ? F.x[col] * (0.5 * px - y.psi) : 0.0);
                     if (tid == 0) p.obj[0] = o + c;
                 }
-                auto none = [](int) { return (double *)nullptr; };
-                auto st = [&](int s) {
-                    vs::Stage<double> q = vs::SlotStages{slots, it.first, n, false}(s);
-                    q.P = nullptr;
-                    return q;
-                };
-                vs::forward<NM, NM, W, EX, EX, double>(F, n, n, n, it.count, st, false,
-                                                       [&](int s) { return slot(it.first + s) + SL.xh(); }, none, none);
-                if (ownr) term[SL.xh() + ir] = F.x[ir];
-                // terminal costate of child s, lam_{s+1} = P_{s+1} x_{s+1} -
-                // Psi_{s+1}, from the cost to go sent to it and the initial
-                // state of the next child (of the terminal node for the last)
-                __threadfence_block();
-                __syncthreads();
-                for (int s = 0; s < it.count; ++s) {
-                    double *d = slot(it.first + s);
-                    const double *xn = (s + 1 < it.count ? slot(it.first + s + 1) : term) + SL.xh();
-                    for (int e = tid; e < n; e += SM::NTH) F.x[e] = xn[e];
-                    sv::wsync();
-                    const double l = vs::sym_apply<NM, NM, W>(d + SL.P(), F.x, n);
-                    if (ownr) d[SL.lamN() + ir] = l - d[SL.Psi() + ir];
-                    sv::wsync();
+                solve();
+                if (top && ownr) end[SL.xh() + ir] = F.x[ir];
+                if constexpr (EX) {
+                    // terminal costate of child s, lam_{s+1} = P_{s+1} x_{s+1} -
+                    // Psi_{s+1}, from the cost to go sent to it and the initial
+                    // state of the next child (of the terminal node for the last)
+                    __threadfence_block();
+                    __syncthreads();
+                    for (int s = 0; s < it.count; ++s) {
+                        double *d = slot(it.first + s);
+                        const double *xn = (s + 1 < it.count ? slot(it.first + s + 1) : end) + SL.xh();
+                        for (int e = tid; e < n; e += SM::NTH) F.x[e] = xn[e];
+                        sv::wsync();
+                        const double l = vs::sym_apply<NM, NM, W>(d + SL.P(), F.x, n);
+                        if (ownr) d[SL.lamN() + ir] = l - d[SL.Psi() + ir];
+                        sv::wsync();
+                    }
                 }
             }
+        } else if constexpr (!EX) {
+            // the level's last item: solved on the K and k of its up pass,
+            // which started from the same terminal
+            const double *msg = slot(it.out_slot);
+            for (int e = tid; e < NM; e += SM::NTH) F.x[e] = e < n ? msg[SL.xh() + e] : 0.0;
+            __syncthreads();
+            solve();
+            if (ownr) slot(it.term_slot)[SL.xh() + ir] = F.x[ir];
         } else {
-            // down pass below the top (Alg. 6, k >= 1): child s receives x_s
-            // and its terminal costate lam_{s+1}
-            const bool last = it.last != 0;
+            // down pass below the top (Alg. 6, k >= 1) on the up records:
+            // child s receives x_s and its terminal costate lam_{s+1}
             const double *msg = slot(it.out_slot);
             for (int e = tid; e < NM; e += SM::NTH) {
                 F.x[e] = e < n ? msg[SL.xh() + e] : 0.0;
@@ -244,7 +281,7 @@ __global__ void __launch_bounds__(128 * NXT, 2) kf_tree(GroupArgs g) {
             __syncthreads();
             vs::forward<NM, NM, W, EX, EX, double>(
                 F, n, n, n, it.count, vs::SlotStages{slots, it.first, n, true}, !last,
-                [&](int s) { return slot(it.first + s) + SL.xh(); }, [](int) { return (double *)nullptr; },
+                [&](int s) { return slot(it.first + s) + SL.xh(); }, none,
                 [&](int s) { return s > 0 ? slot(it.first + s - 1) + SL.lamN() : (double *)nullptr; });
             // the last child ends where the item does: at lam_N, or for the
             // last item at the terminal node, lam = P_term x - Psi_term
@@ -264,6 +301,10 @@ __global__ void __launch_bounds__(128 * NXT, 2) kf_tree(GroupArgs g) {
     }
 }
 
+// Superposition on the records of the up pass, or elimination with the true
+// terminal (see above).
+bool full_tiles(const GroupArgs &g) { return g.nx % 16 == 0 && g.nu % 16 == 0; }
+
 template <int A, int B>
 hipError_t fused_leaf(const GroupArgs &g, int down, hipStream_t st) {
     const dim3 grid(g.nleaves), block(128 * A);
@@ -278,7 +319,7 @@ hipError_t fused_leaf(const GroupArgs &g, int down, hipStream_t st) {
             return hipGetLastError();
         }
     }
-    if (g.nx != 16 * A || g.nu != 16 * B)
+    if (!full_tiles(g))
         hipLaunchKernelGGL((kf_leaf<A, B, ANY>), grid, block, 0, st, g, down);
     else if (g.data_nu)
         hipLaunchKernelGGL((kf_leaf<A, B, DATA>), grid, block, 0, st, g, down);
@@ -297,21 +338,22 @@ hipError_t launch_up(const GroupArgs &g, int, hipStream_t st) {
 }
 hipError_t launch_tree(const GroupArgs &g, int grid, hipStream_t st) {
     const dim3 gd(grid);
-    if (g.nx == 16)
+    if (full_tiles(g) && g.nx == 16)
         hipLaunchKernelGGL((kf_tree<1, true>), gd, dim3(128), 0, st, g);
+    else if (full_tiles(g))
+        hipLaunchKernelGGL((kf_tree<2, true>), gd, dim3(256), 0, st, g);
     else if (g.nx <= 4)
         hipLaunchKernelGGL((kf_tree<1, false, 1>), gd, dim3(128), 0, st, g);
     else if (g.nx <= 8)
         hipLaunchKernelGGL((kf_tree<1, false, 2>), gd, dim3(128), 0, st, g);
-    else if (g.nx < 16)
+    else if (g.nx <= 16)
         hipLaunchKernelGGL((kf_tree<1, false>), gd, dim3(128), 0, st, g);
-    else if (g.nx == 32)
-        hipLaunchKernelGGL((kf_tree<2, true>), gd, dim3(256), 0, st, g);
     else
         hipLaunchKernelGGL((kf_tree<2, false>), gd, dim3(256), 0, st, g);
     return hipGetLastError();
 }
 hipError_t launch_down(const GroupArgs &g, int, hipStream_t st) {
+    if (!full_tiles(g)) return fused_leaf_any(g, 1, st);
     if (g.ntop > 0) {
         const hipError_t e = fused_leaf_any(g, 1, st);
         if (e != hipSuccess || g.ntop == g.nleaves) return e;

@@ -8,8 +8,8 @@
 namespace rs {
 
 // Leaf scratch of the fused solve per stage as rs_batch_solve_noalloc counts
-// it: below the full tiles without V and L_t, which those shapes' records did
-// not always hold, so that the plans it takes are the same.
+// it: below the full tiles without the room for V and L_t, which those shapes
+// do not use, so that the plans it takes are the same with and without it.
 constexpr int scratch_counted(int nx, int nu) {
     return (nx % 16 == 0 && nu % 16 == 0) ? leaf_rec_len(nx, nu) : nu * nx + nu + nx * nx + nx;
 }

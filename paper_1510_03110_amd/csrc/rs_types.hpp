@@ -124,7 +124,8 @@ struct LeafRec {
 
 // Record of one leaf stage of the fused solve (leaf scratch, FP64):
 //   K (m n) | k (m) | P (n n) | Psi (n) | V (n n) | L_t (m n)
-// (the last two for reduced leaves only).
+// (the last two for the reduced leaves of full tiles only; the room for them is
+// in every shape's record).
 __host__ __device__ constexpr int leaf_rec_len(int n, int m) { return 2 * n * m + m + 2 * n * n + n; }
 
 // Per-instance entry of the refinement tables: the instance's leaves are

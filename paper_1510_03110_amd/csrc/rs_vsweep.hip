@@ -132,15 +132,15 @@ __global__ void __launch_bounds__(64 * W) ks_leaf_down(GroupArgs g) {
     }
 }
 
-// Leaf solve of the fused path from the records of the fused leaf reduction;
-// whole-problem leaves are solved by the fused leaf kernel itself.
-// EX: full sizes; MD: the data width is the instance's own (padded inputs).
-template <int NM, int MM, int W, bool EX, bool MD>
+// Leaf solve of the fused path from the records of the fused leaf reduction
+// (shapes of full tiles); whole-problem leaves are solved by the fused leaf
+// kernel itself.  MD: the data width is the instance's own (padded inputs).
+template <int NM, int MM, int W, bool MD>
 __global__ void __launch_bounds__(64 * W) ks_leaf_fwd(GroupArgs g) {
     __shared__ Smem<NM, MM, W> S;
     const LeafItem it = sv::load_leaf(g.leaves, my_leaf(g));
     if ((it.flags & LEAF_TOP) || sv::skip_inst(g, it.inst)) return;
-    const int n = EX ? NM : g.nx, m = EX ? MM : g.nu, md = MD ? uni(g.probs[it.inst].nu) : m;
+    const int n = NM, m = MM, md = MD ? uni(g.probs[it.inst].nu) : m;
     const sv::Prob p = sv::load_prob(g.probs, it.inst);
     const SlotLayout SL{n};
     const bool last = (it.flags & LEAF_LAST) != 0;
@@ -154,7 +154,7 @@ __global__ void __launch_bounds__(64 * W) ks_leaf_fwd(GroupArgs g) {
     __syncthreads();
     const FusedStages st{p, it.t0, n, m, static_cast<double *>(g.leaf_scratch) + it.scratch};
     const int64_t t0 = it.t0;
-    forward<NM, MM, W, EX, EX && !MD, double>(
+    forward<NM, MM, W, true, !MD, double>(
         S, n, m, md, it.len, st, !last, [&](int s) { return p.x + (t0 + s) * n; },
         [&](int s) { return p.w + (t0 + s) * md; }, [&](int s) { return p.lam + (t0 + s) * n; });
     if (last) {
@@ -354,12 +354,10 @@ hipError_t leaf(const GroupArgs &g, bool down, hipStream_t st) {
 template <int NM, int MM, int W>
 hipError_t fwd_of(const GroupArgs &g, hipStream_t st) {
     const dim3 grid(g.nleaves), block(64 * W);
-    if (g.nx != NM || g.nu != MM)
-        hipLaunchKernelGGL((ks_leaf_fwd<NM, MM, W, false, false>), grid, block, 0, st, g);
-    else if (g.data_nu)
-        hipLaunchKernelGGL((ks_leaf_fwd<NM, MM, W, true, true>), grid, block, 0, st, g);
+    if (g.data_nu)
+        hipLaunchKernelGGL((ks_leaf_fwd<NM, MM, W, true>), grid, block, 0, st, g);
     else
-        hipLaunchKernelGGL((ks_leaf_fwd<NM, MM, W, true, false>), grid, block, 0, st, g);
+        hipLaunchKernelGGL((ks_leaf_fwd<NM, MM, W, false>), grid, block, 0, st, g);
     return hipGetLastError();
 }
 template <int NM, int W>

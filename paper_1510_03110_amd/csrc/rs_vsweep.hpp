@@ -356,8 +356,8 @@ __device__ __forceinline__ double sym_apply(const double *M, const double *x, in
 // Leaf solve of the fused path: the records of the fused leaf reduction (leaf
 // scratch, FP64 per stage)
 //   K (m n) | k (m) | P (n n) | Psi (n) | V (n n) | L_t (m n)
-// with lam_N from the master level; whole-problem leaves are solved by the
-// fused leaf-down kernel.
+// with lam_N from the master level, or (V and L_t not looked at) those of an
+// elimination with the true terminal.
 struct FusedStages {
     sv::Prob p;
     int t0, n, m;
