@@ -1102,7 +1102,7 @@ static rs_status launch_pass(rs_plan P, char *W, int32_t *info, hipStream_t st, 
         Group &g = P->groups[gi];
         GroupArgs a = group_args(P, W, gi, info, corr, with_conv, iter);
         const Launcher *L = pass == 0 ? g.shape->fp64 : pass == 1 ? g.shape->factor[fac] : g.shape->vsolve[f32];
-        // the vector passes run one wavefront per work item
+        // the vector passes run one wavefront per work item (up to 32 states and many items)
         const int cap = pass == 2 ? 1024 : 256;
         const int tree_grid = std::max(1, std::min<int>((int)g.items.size(), cap));
         if (a.nleaves > 0) {

@@ -43,7 +43,8 @@ __device__ __forceinline__ LeafStages<TR> leaf_stages(const GroupArgs &g, const 
     return LeafStages<TR>{p, it.t0, n, m, rec, g.fvec + s0 * (int64_t)R.vec()};
 }
 
-template <int NM, int MM, int W, bool EX, class TR>
+// LT: the form of v (see backward).
+template <int NM, int MM, int W, bool EX, bool LT, class TR>
 __global__ void __launch_bounds__(64 * W) ks_leaf_up(GroupArgs g) {
     __shared__ Smem<NM, MM, W> S;
     if (sv::pass_idle(g)) return;
@@ -60,10 +61,10 @@ __global__ void __launch_bounds__(64 * W) ks_leaf_up(GroupArgs g) {
     double psi = (last && p.lN && i < n) ? -p.lN[i] : 0.0, v = 0.0, cb;
     const auto st = leaf_stages<TR>(g, p, it, n, m, false);
     if (!last) {
-        cb = backward<NM, MM, W, true, TR>(S, n, m, it.len, st, nullptr, psi, v);
+        cb = backward<NM, MM, W, true, LT, TR>(S, n, m, it.len, st, nullptr, psi, v);
         if (own) out[SL.a() + i] = v;
     } else {
-        cb = backward<NM, MM, W, false, TR>(S, n, m, it.len, st, p.QxN, psi, v);
+        cb = backward<NM, MM, W, false, false, TR>(S, n, m, it.len, st, p.QxN, psi, v);
     }
     cb += block_sum(S, sum_c(p.c ? p.c + (int64_t)it.t0 * p.sc : nullptr, p.sc, it.len));
     if (own) out[SL.lx() + i] = -psi;
@@ -90,7 +91,7 @@ __global__ void __launch_bounds__(64 * W) ks_leaf_down(GroupArgs g) {
         // on the down records first
         const int ic = MA::out_col();
         double psi = (p.lN && ic < n) ? -p.lN[ic] : 0.0, v = 0.0;
-        double cb = backward<NM, MM, W, false, TR>(S, n, m, it.len, st, p.QxN, psi, v);
+        double cb = backward<NM, MM, W, false, false, TR>(S, n, m, it.len, st, p.QxN, psi, v);
         cb += block_sum(S, sum_c(p.c ? p.c + (int64_t)it.t0 * p.sc : nullptr, p.sc, it.len));
         if (p.obj) {
             // optimal value 1/2 x0'P_0 x0 - Psi_0'x0 + cbar_0
@@ -222,15 +223,15 @@ __global__ void __launch_bounds__(64 * W) ks_tree(GroupArgs g) {
         const int count = it.count;
         const int ic = MA::out_col(), ir = MA::out_row();
         const bool ownc = MA::lead_col() && ic < n, ownr = MA::lead_row() && ir < n;
-        // the constants of the item's master stages, one per slot
-        auto c_sum = [&] { return block_sum(S, sum_c(slot(it.first) + SL.c(), SL.size(), count)); };
         if (sv::skip_inst(g, it.inst)) {
             // converged or excluded: nothing to do (its dependents belong to the same instance)
         } else if (it.kind == ITEM_UP) {
             double psi = 0.0, v = 0.0;
-            double cb = backward<NM, NM, W, true, double>(S, n, n, count, SlotStages{slots, it.first, n, true}, nullptr,
-                                                          psi, v);
-            cb += c_sum();
+            // the constants of the item's master stages, one per slot
+            const double cs = sum_c(slot(it.first) + SL.c(), SL.size(), count);
+            double cb = backward<NM, NM, W, true, true, double>(S, n, n, count, SlotStages{slots, it.first, n, true},
+                                                                nullptr, psi, v);
+            cb += block_sum(S, cs);
             double *out = slot(it.out_slot);
             if (ownc) {
                 out[SL.a() + ic] = v;
@@ -245,47 +246,45 @@ __global__ void __launch_bounds__(64 * W) ks_tree(GroupArgs g) {
             double psi = ic < n ? -term[SL.lx() + ic] : 0.0, v = 0.0;
             if (top && ownc) slot(it.first + count - 1)[SL.Psi() + ic] = psi;
             const SlotStages st{slots, it.first, n, !top};
-            const double *P0 = term + SL.Qx();
-            double cb = backward<NM, NM, W, false, double>(S, n, n, count, st, P0, psi, v);
-            cb += c_sum() + term[SL.c()];
+            const double cs = sum_c(slot(it.first) + SL.c(), SL.size(), count), ct = term[SL.c()];
+            const sv::Prob p = sv::load_prob(g.probs, it.inst);
+            double px = 0.0;
+            if (top) {
+                // P_0 x_0, for the optimal value, ahead of the chain
+                for (int e = tid; e < NM; e += 64 * W) S.x[e] = e < n ? p.x0[e] : 0.0;
+                wsync();
+                if (p.obj) {
+                    Mat<double, NM, NM, W> mp;
+                    mp.load_col(term + SL.P(), n, n, n);
+                    px = mp.col(S.x);
+                }
+            }
+            double cb = backward<NM, NM, W, false, true, double>(S, n, n, count, st, term + SL.Qx(), psi, v);
+            cb += block_sum(S, cs) + ct;
             if (!top) {
                 double *out = slot(it.out_slot);
                 if (ownc) out[SL.lx() + ic] = -psi;
                 if (tid == 0) out[SL.c()] = cb;
             } else {
-                const sv::Prob p = sv::load_prob(g.probs, it.inst);
-                for (int e = tid; e < NM; e += 64 * W) S.x[e] = e < n ? p.x0[e] : 0.0;
                 __threadfence_block();      // Psi and k are read back by other lanes
                 __syncthreads();
                 if (p.obj) {
-                    Mat<double, NM, NM, W> mp;
-                    mp.load_col(term + SL.P(), n, n, n);
-                    const double px = mp.col(S.x);
                     const double o = block_sum(S, ownc ? S.x[ic] * (0.5 * px - psi) : 0.0);
                     if (tid == 0) p.obj[0] = o + cb;
                 }
-                auto none = [](int) { return (double *)nullptr; };
-                auto fst = [&](int s) {
-                    Stage<double> q = st(s);
-                    q.P = nullptr;
-                    return q;
-                };
-                forward<NM, NM, W, EX, EX, double>(S, n, n, n, count, fst, false, [&](int s) { return slot(it.first + s) + SL.xh(); },
-                                           none, none);
-                if (ownr) term[SL.xh() + ir] = S.x[ir];
                 // terminal costate of child s, lam_{s+1} = P_{s+1} x_{s+1} -
                 // Psi_{s+1}, from the cost to go sent to it and the initial
-                // state of the next child (of the terminal node for the last)
-                __threadfence_block();
-                __syncthreads();
-                for (int s = 0; s < count; ++s) {
-                    double *sl = slot(it.first + s);
-                    const double *xn = (s + 1 < count ? slot(it.first + s + 1) : term) + SL.xh();
-                    for (int e = tid; e < n; e += 64 * W) S.x[e] = xn[e];
-                    wsync();
-                    const double l = sym_apply<NM, NM, W>(sl + SL.P(), S.x, n);
-                    if (ownr) sl[SL.lamN() + ir] = l - sl[SL.Psi() + ir];
-                    wsync();
+                // state of the next child (of the terminal node for the last):
+                // what the sweep has at stage s + 1 anyway
+                forward<NM, NM, W, EX, EX, double>(
+                    S, n, n, n, count, st, false, [&](int s) { return slot(it.first + s) + SL.xh(); },
+                    [](int) { return (double *)nullptr; },
+                    [&](int s) { return s > 0 ? slot(it.first + s - 1) + SL.lamN() : (double *)nullptr; });
+                double *sl = slot(it.first + count - 1);
+                const double l = sym_apply<NM, NM, W>(sl + SL.P(), S.x, n);
+                if (ownr) {
+                    term[SL.xh() + ir] = S.x[ir];
+                    sl[SL.lamN() + ir] = l - sl[SL.Psi() + ir];
                 }
             }
         } else {
@@ -327,7 +326,14 @@ __global__ void __launch_bounds__(64 * W) ks_tree(GroupArgs g) {
 // Wavefronts per unit: one at n <= 16 (no workgroup barrier to wait at), four
 // at n <= 32, eight at n <= 64, so that an n x n matrix takes 4, 4 and 8
 // registers (doubles) a thread.  Sizes that fill them have an instance
-// without bounds checks.
+// without bounds checks.  Backward sweeps of more leaves of 32 states than four
+// a CU, full sizes: one wavefront each, without barriers and with longer runs of a
+// matrix to a load, since the memory is then the bound and not the chain of a
+// leaf (32 x 16, FP64: 2048 leaves of 64 stages 790 -> 730 us, 4000 1.41 -> 1.32
+// ms; at 256 leaves of 32 stages four wavefronts take 78 us and one 112).  Up to
+// a leaf a CU the reductions take v by L_t'g, which ends sooner (32 x 16, 64
+// leaves of 16 stages 37 us, else 40); more of them do without those bytes (512
+// leaves of 128 stages 425 and 431 us, 16 x 16, 4096 of 64 650 and 705).
 template <int NM, int MM, int W, class TR>
 hipError_t leaf_of(const GroupArgs &g, bool down, hipStream_t st) {
     const dim3 grid(g.nleaves), block(64 * W);
@@ -336,10 +342,16 @@ hipError_t leaf_of(const GroupArgs &g, bool down, hipStream_t st) {
         hipLaunchKernelGGL((ks_leaf_down<NM, MM, W, true, TR>), grid, block, 0, st, g);
     else if (down)
         hipLaunchKernelGGL((ks_leaf_down<NM, MM, W, false, TR>), grid, block, 0, st, g);
+    else if (ex && NM == 32 && g.nleaves > 1024)
+        hipLaunchKernelGGL((ks_leaf_up<NM, MM, NM == 32 ? 1 : W, true, false, TR>), grid, dim3(64), 0, st, g);
+    else if (ex && g.nleaves > 256)
+        hipLaunchKernelGGL((ks_leaf_up<NM, MM, W, true, false, TR>), grid, block, 0, st, g);
     else if (ex)
-        hipLaunchKernelGGL((ks_leaf_up<NM, MM, W, true, TR>), grid, block, 0, st, g);
+        hipLaunchKernelGGL((ks_leaf_up<NM, MM, W, true, true, TR>), grid, block, 0, st, g);
+    else if (g.nleaves > 256)
+        hipLaunchKernelGGL((ks_leaf_up<NM, MM, W, false, false, TR>), grid, block, 0, st, g);
     else
-        hipLaunchKernelGGL((ks_leaf_up<NM, MM, W, false, TR>), grid, block, 0, st, g);
+        hipLaunchKernelGGL((ks_leaf_up<NM, MM, W, false, true, TR>), grid, block, 0, st, g);
     return hipGetLastError();
 }
 template <class TR>
@@ -381,9 +393,13 @@ hipError_t fused_leaf_forward(const GroupArgs &g, hipStream_t st) {
     return vs::fwd_of<32, 32, 4>(g, st);
 }
 
+// Up to 32 states one wavefront per work item, so that four items a CU are at
+// work at once; trees of few items two, for the chain of each (32 states, FP64: 41
+// items 83 us with one, 69 with two, 72 with four; 1152 items 347, 444 and 467 us).
 hipError_t sweep_tree(const GroupArgs &g, int grid, hipStream_t st) {
     if (g.nx <= 16) return vs::tree_of<16, 1>(g, grid, st);
-    if (g.nx <= 32) return vs::tree_of<32, 4>(g, grid, st);
+    if (g.nx <= 32 && g.nitems <= 128) return vs::tree_of<32, 2>(g, grid, st);
+    if (g.nx <= 32) return vs::tree_of<32, 1>(g, grid, st);
     return vs::tree_of<64, 8>(g, grid, st);
 }
 

@@ -6,7 +6,7 @@
 // P_{t+1}, V_{t+1}, L^{-1}, L^{-T}, K and L_t = -G^{-1} B'V_{t+1}:
 //   pt = Psi - P a;  g = B'pt - l_w;  Psi_t = A'pt - l_x + K'g
 //   z = L^{-1} g,  k = L^{-T} z;  cbar += 1/2 a'Pa - Psi'a + c - 1/2 z'z
-//   Alg. 4: v += V'a - L_t'g    (= V'(a + B k), since G k = g)
+//   Alg. 4: v += V'(a + B k), or V'a - L_t'g (the same, since G k = g)
 // Forward:
 //   w = K x + k_0 + L_t lam_N,  lam = P x - Psi_0 + V lam_N,  x+ = A x + a + B w
 // (k_0, Psi_0 of the reduction and lam_N sent by the parent; the last item of
@@ -115,7 +115,7 @@ struct Mat {
 template <int NM, int MM, int W>
 struct Smem {
     alignas(16) double av[2][NM], pt[NM], x[NM], lamN[NM];
-    alignas(16) double gw[MM], z[MM];
+    alignas(16) double gw[MM], z[MM], kk[MM], u[NM];
     double red[W];
 };
 
@@ -143,11 +143,14 @@ __device__ __forceinline__ double block_sum(Smem<NM, MM, W> &S, double v) {
 
 // Backward sweep.  psi: Psi of the end in the lanes of the column form
 // (replicated over the parts); P0: P of the end (nullptr: zero).  RED: Alg. 4
-// (V = I at the end); v_0 is returned in v.  st(s): the stage's operands;
+// (V = I at the end); v_0 is returned in v.  LT: v by L_t'g; else by V'(a + B k),
+// which needs k and so runs two stages behind, but reads B again (from the
+// cache) instead of L_t: a seventh fewer bytes where the memory is the bound, and
+// 2 to 3 us more at the end of a sweep.  st(s): the stage's operands;
 // per stage Psi_t goes to st(s).Psi and k_{t+1} to st(s).k (null: not kept).
 // Returns the sum of the terms of cbar other than the constants c in every
 // lane; psi ends as Psi_0.
-template <int NM, int MM, int W, bool RED, class TR, class St>
+template <int NM, int MM, int W, bool RED, bool LT, class TR, class St>
 __device__ __forceinline__ double backward(Smem<NM, MM, W> &S, int n, int m, int count, St st, const double *P0,
                                            double &psi, double &v) {
     typedef Mat<TR, NM, NM, W> MNN;       // P, V' (records)
@@ -162,6 +165,22 @@ __device__ __forceinline__ double backward(Smem<NM, MM, W> &S, int n, int m, int
     MB mB;
     MMM mL, mLT;
     MNM mK, mLt;
+    typedef Mat<double, NM, MM, W> MBR;   // B by rows
+    constexpr bool VB = RED && !LT;
+    MBR mBr;                              // B and a of the stage whose k comes next
+    double ar = 0.0;
+    const TR *pV = nullptr, *pVn = nullptr;     // V after the stage before that one, and after that one
+    const int ir = MBR::out_row();
+    const bool ownr = MBR::lead_row() && ir < n;
+    auto load_Br = [&](const Stage<TR> &q) {
+        mBr.template load_row<false>(q.B, m, n, m);
+        ar = (ownr && q.a) ? gl(q.a + (uint32_t)ir) : 0.0;
+    };
+    auto add_v = [&](bool ident) { v += ident ? (i < n ? S.u[i] : 0.0) : mV.col(S.u); };
+    auto put_u = [&] {
+        const double u = MBR::sum_row(mBr.part_row(S.kk)) + ar;
+        if (ownr) S.u[ir] = u;
+    };
     // entry i (jj) of a stage's vectors, zero in the padding
     auto at = [&](const double *q) { return (q && i < n) ? gl(q + (uint32_t)i) : 0.0; };
     auto atm = [&](const double *q) { return (q && jj < m) ? gl(q + (uint32_t)jj) : 0.0; };
@@ -172,7 +191,7 @@ __device__ __forceinline__ double backward(Smem<NM, MM, W> &S, int n, int m, int
     auto load2 = [&](const Stage<TR> &q) {
         mLT.load_col(q.LT, m, m, m);
         mK.load_col(q.K, n, n, m);
-        if (RED) mLt.load_col(q.Lt, n, n, m);
+        if (RED && LT) mLt.load_col(q.Lt, n, n, m);
     };
     double acc = 0.0;
     v = 0.0;
@@ -189,7 +208,9 @@ __device__ __forceinline__ double backward(Smem<NM, MM, W> &S, int n, int m, int
     if (count > 2) a2 = at(st(count - 3).a);
     mL.load_col(cur.Li, m, m, m);
     for (int e = threadIdx.x; e < NM; e += 64 * W) S.av[0][e] = S.av[1][e] = S.pt[e] = 0.0;
-    for (int e = threadIdx.x; e < MM; e += 64 * W) S.gw[e] = S.z[e] = 0.0;
+    for (int e = threadIdx.x; e < MM; e += 64 * W) S.gw[e] = S.z[e] = S.kk[e] = 0.0;
+    if (VB)
+        for (int e = threadIdx.x; e < NM; e += 64 * W) S.u[e] = 0.0;
     wsync();
     if (own) {
         S.av[(count - 1) & 1][i] = a0;
@@ -225,14 +246,19 @@ __device__ __forceinline__ double backward(Smem<NM, MM, W> &S, int n, int m, int
         if (kout) {
             const double k = mL.col(S.z);
             if (ownm) gs(kout + jj, k);
+            if (VB && ownm) S.kk[jj] = k;
             mL.load_col(cur.Li, m, m, m);
+        }
+        if (VB && s + 2 < count) {
+            add_v(s + 3 == count);
+            mV.load_col(pV, n, n, n);
         }
         double pa = 0.0;
         if (s > 0) {
             pa = mP.col(S.av[(s - 1) & 1]);
             if (s > 1) mP.load_col(nxt.P, n, n, n);
         }
-        if (RED) {
+        if (RED && LT) {
             v += s + 1 < count ? mV.col(S.av[s & 1]) : a0;
             if (s > 0) mV.load_col(cur.V, n, n, n);
         }
@@ -240,7 +266,15 @@ __device__ __forceinline__ double backward(Smem<NM, MM, W> &S, int n, int m, int
         // ---- z = L^{-1} g, Psi_t = A'pt - l_x + K'g, v -= L_t'g
         const double z = mLT.col(S.gw);
         psi = y + mK.col(S.gw);
-        if (RED) v -= mLt.col(S.gw);
+        if (RED && LT) v -= mLt.col(S.gw);
+        if (VB) {
+            if (s + 1 < count) {
+                put_u();
+                pV = pVn;
+            }
+            pVn = cur.V;
+            load_Br(cur);
+        }
         if (ownm) {
             S.z[jj] = z;
             acc -= 0.5 * z * z;
@@ -264,8 +298,18 @@ __device__ __forceinline__ double backward(Smem<NM, MM, W> &S, int n, int m, int
     if (kout) {
         const double k = mL.col(S.z);
         if (ownm) gs(kout + jj, k);
+        if (VB && ownm) S.kk[jj] = k;
+    }
+    if (VB && count > 1) {
+        add_v(count == 2);
+        mV.load_col(pV, n, n, n);
     }
     wsync();
+    if (VB) {
+        put_u();
+        wsync();
+        add_v(count == 1);
+    }
     return block_sum(S, acc);
 }
 
