@@ -37,7 +37,10 @@
  *        info_dev[2*i]   = rs_status of instance i (RS_OK, RS_ERR_NOT_SPD,
  *                          RS_ERR_SINGULAR_MASTER, RS_ERR_NOT_CONVERGED)
  *        info_dev[2*i+1] = failing stage index (or -1)
- *    and are valid once the stream has reached the end of the call.
+ *    and are valid once the stream has reached the end of the call.  x, w,
+ *    lam and obj of an instance with RS_ERR_NOT_SPD or RS_ERR_SINGULAR_MASTER
+ *    are written but mean nothing (infinities and NaN among them); the other
+ *    instances of the call are not affected.
  *  - No exception crosses the ABI.  A plan must not be used by two calls in
  *    flight at the same time (its workspace holds the tree's state).
  */

@@ -139,9 +139,10 @@ __device__ __forceinline__ void put_sym(const Ln<T> &L, T *M, int ti, int tj, v4
 
 __device__ __forceinline__ double rcp_est(double d) { return __builtin_amdgcn_rcp(d); }
 __device__ __forceinline__ float rcp_est(float d) { return __builtin_amdgcn_rcpf(d); }
-// Positive and finite.
-__device__ __forceinline__ bool usable_pivot(double d) { return __builtin_amdgcn_class(d, 0x180); }
-__device__ __forceinline__ bool usable_pivot(float d) { return __builtin_amdgcn_classf(d, 0x180); }
+// A pivot whose reciprocal is neither subnormal nor infinite (the hardware's
+// estimate flushes those).
+__device__ __forceinline__ bool plain_pivot(double d) { return d >= 0x1p-1021 && d <= 0x1p+1021; }
+__device__ __forceinline__ bool plain_pivot(float d) { return d >= 0x1p-125f && d <= 0x1p+125f; }
 
 // Value of lane 16 H + i in the lanes i of all four rows of 16: two swaps
 // between rows (the pairs of rows, then the halves of the wave).
@@ -182,7 +183,7 @@ __device__ __forceinline__ float fma_t(float a, float b, float c) { return __bui
 // a scalar register.  a / d from the hardware's estimate r of 1 / d:
 // a r (1 + e + e^2) with e = 1 - d r (e^3 is below the rounding).  The pivots
 // stay on the diagonal: they are checked, and their square roots taken, at
-// the end.
+// the end (see chol_block_any for the blocks that fail the check).
 template <int K, class T>
 __device__ __forceinline__ void elim_step(T (&a)[4], int i, int h, int steps) {
     if constexpr (K % 4 == 0 && K > 0) {
@@ -200,6 +201,62 @@ __device__ __forceinline__ void elim_step(T (&a)[4], int i, int h, int steps) {
         a[c] = (c == kc && h == H && i > K) ? nm : t;
     }
     if constexpr (K + 1 < 16) elim_step<K + 1>(a, i, h, steps);
+}
+
+// Reciprocal square root of a pivot, or of the unit pivot that takes the place of
+// one that is not positive or not finite (fail is set).
+template <class T>
+__device__ __forceinline__ T pivot_rsq(T d, int &fail) {
+    if (!(d > T(0)) || !__builtin_isfinite(d)) {
+        fail = 1;
+        d = T(1);
+    }
+    T s = mf::rsq_est(d);
+    s = s * (T(1.5) - T(0.5) * d * s * s);
+    return s * (T(1.5) - T(0.5) * d * s * s);
+}
+
+// chol_block for a block with a pivot that is not plain: one step after another
+// through the pivots' square roots, in LDS (so that it needs few registers), a
+// failed factorization going on with unit pivots, and so with numbers.
+template <int PU, int GS, class T>
+__device__ __forceinline__ int chol_block_any(T *G, int kb, int steps) {
+    int l = lane();
+    asm volatile("" : "+v"(l));
+    const int i = l & 15, j0 = 4 * (l >> 4), o = 16 * kb;
+    int fail = 0;
+    if (GS > 1) {
+#pragma unroll 1
+        for (int c = 0; c < 4; ++c) {
+            T v = G[at<PU>(o + i, o + j0 + c)];
+#pragma unroll 1
+            for (int g = 1; g < GS; ++g) v += G[g * PU * PU + at<PU>(o + i, o + j0 + c)];
+            G[at<PU>(o + i, o + j0 + c)] = v;
+        }
+    }
+#pragma unroll 1
+    for (int K = 0; K < steps && K < 16; ++K) {
+        wave_fence();
+        const T s = pivot_rsq(G[at<PU>(o + K, o + K)], fail);
+        const T nm = i > K ? -(G[at<PU>(o + i, o + K)] * s) * s : T(0);
+        wave_fence();
+#pragma unroll 1
+        for (int j = j0; j < j0 + 4; ++j) {
+            T &e = G[at<PU>(o + i, o + j)];
+            const T t = fma_t(nm, G[at<PU>(o + K, o + j)], e);
+            if (i > K) e = j == K ? nm : t;
+        }
+    }
+    wave_fence();
+    int none = 0;
+    const T is = pivot_rsq(G[at<PU>(o + i, o + i)], none);
+    wave_fence();
+#pragma unroll 1
+    for (int j = j0; j < j0 + 4; ++j) {
+        T &e = G[at<PU>(o + i, o + j)];
+        e = j < i ? e * is : j == i ? is : T(0);
+    }
+    return fail;
 }
 
 // Inverse Cholesky factor of the 16 x 16 diagonal block kb of G, in place
@@ -227,6 +284,7 @@ __device__ __forceinline__ int chol_block(T *G, int kb, int steps) {
     elim_step<0>(a, i, h, steps);
     const T p01 = (i & 1) ? a[1] : a[0], p23 = (i & 1) ? a[3] : a[2];
     const T piv = __shfl((i & 2) ? p23 : p01, 16 * (i >> 2) + i, 64);        // row i's pivot, from row group i / 4
+    if (__any(i < steps && !plain_pivot(piv))) return chol_block_any<PU, GS>(G, kb, steps);
     T is = mf::rsq_est(piv);
     is = is * (T(1.5) - T(0.5) * piv * is * is);
     is = is * (T(1.5) - T(0.5) * piv * is * is);
@@ -235,7 +293,7 @@ __device__ __forceinline__ int chol_block(T *G, int kb, int steps) {
         const int j = 4 * h + c;
         G[at<PU>(16 * kb + i, 16 * kb + j)] = j < i ? a[c] * is : j == i ? is : T(0);
     }
-    return __any(i < steps && !usable_pivot(piv)) ? 1 : 0;
+    return 0;
 }
 
 // Cholesky factorization and inverse of the NB x NB blocks of G (lower part
