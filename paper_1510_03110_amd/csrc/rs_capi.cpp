@@ -89,7 +89,7 @@ struct rs_plan_s {
     // the padded inputs exist in the kernels only: a plan for the fused solve
     // alone reads the caller's arrays as they are (no padded copies)
     bool pad_in_kernel = false;
-    size_t counted = 0;                 // total as rs_batch_solve_noalloc counts it (scratch_counted)
+    size_t counted = 0;                 // total as rs_batch_solve_noalloc counts it (scratch_counted; with padded copies)
     size_t off_padargs = 0;
     std::vector<Group> groups;
     size_t off_probs = 0, off_info = 0, off_queues = 0, off_tables = 0, tables_bytes = 0;
@@ -742,14 +742,16 @@ static rs_status plan_create(int32_t count, const int32_t *dims_in, int stride, 
             off = align_up(off + sizeof(double) * (nx + 2 * N * nx + N * nu + nx + 2 * (N + 1) * nx + N * nu));
         }
     }
+    size_t no_copies = 0;      // padded copies that the kernels do without
     for (int i : P->pad_inst) {
         // B, Q_xw (N nx x PAD_NU), Q_w (N PAD_NU^2), l_w and w (N PAD_NU)
         const size_t nx = dims[3 * i], N = dims[3 * i + 2];
+        const size_t bytes = align_up(sizeof(double) * N * (2 * nx * PAD_NU + PAD_NU * PAD_NU + 2 * PAD_NU));
         P->off_pad[i] = off;
-        off = align_up(off + sizeof(double) * N * (2 * nx * PAD_NU + PAD_NU * PAD_NU + 2 * PAD_NU));
+        (P->pad_in_kernel ? no_copies : off) += bytes;
     }
     P->total = off;
-    P->counted = off - uncounted;
+    P->counted = off + no_copies - uncounted;
     P->tables.assign(P->tables_bytes, 0);
     std::memcpy(P->tables.data() + (P->off_inst - P->off_tables), P->inst.data(), sizeof(InstInfo) * count);
     for (auto &g : P->groups) {
