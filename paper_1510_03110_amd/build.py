@@ -13,11 +13,9 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD_DIR = os.path.join(PKG, "_build")
 LIB_PATH = os.path.join(BUILD_DIR, "librs.so")
-SOURCES = ["rs_kernels.hip", "rs_fused.hip", "rs_solve.hip", "rs_refine.hip", "rs_large.hip", "rs_mid.hip", "rs_mid32.hip", "rs_vsweep.hip",
-           "rs_mhe.hip",
-           "rs_ip.hip", "rs_pad.hip", "rs_static.hip", "rs_capi.cpp"]
-HEADERS = ["rs_types.hpp", "rs_device.hpp", "rs_mfma.hpp", "rs_launch.hpp", "rs_vec.hpp", "rs_col.hpp",
-           "rs_vsweep.hpp"]
+SOURCES = ["rs_kernels.hip", "rs_fused.hip", "rs_solve.hip", "rs_refine.hip", "rs_large.hip", "rs_mid.hip",
+           "rs_mid32.hip", "rs_vsweep.hip", "rs_mhe.hip", "rs_ip.hip",
+           "rs_pad.hip", "rs_static.hip", "rs_capi.cpp"]
 
 # roctx (the ranges the C ABI marks around its calls and kernel launches)
 LINK_LIBS = ["-L/opt/rocm/lib", "-lrocprofiler-sdk-roctx", "-Wl,-rpath,/opt/rocm/lib"]

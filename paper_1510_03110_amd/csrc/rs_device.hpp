@@ -9,18 +9,7 @@
 
 namespace rs {
 
-constexpr int NT = 256;          // threads per workgroup (4 wavefronts)
-
 // ------------------------------------------------------------------ scalars
-__device__ __forceinline__ double bcast_lane(double v, int lane) {
-    int64_t b = __double_as_longlong(v);
-    int lo = __builtin_amdgcn_readlane((int)(uint32_t)(b & 0xffffffffll), lane);
-    int hi = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)b >> 32), lane);
-    return __longlong_as_double((int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
-}
-__device__ __forceinline__ float bcast_lane(float v, int lane) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
-}
 // Wave-uniform copy of an integer that is the same in every lane.  Loop
 // bounds and branch conditions around barriers go through this so that the
 // compiler sees uniform control flow and keeps every barrier in lock-step.

@@ -138,7 +138,8 @@ __device__ __forceinline__ int nwav() { return (int)(blockDim.x >> 6); }
 // Where the result of a large-block product goes: element (i, j) of
 // v = sgn * opA(A) opB(B) + D is stored to C and, when given, to the record R;
 // with `sym` (the lower products of symmetric results, i >= j) also to (j, i).
-// D is problem data (FP64) or a workspace matrix (element type T), or none.
+// D is problem data (FP64; BF16 products only) or a workspace matrix (element
+// type T), or none.
 template <class T>
 struct Ep {
     T *C = nullptr;
@@ -235,9 +236,9 @@ __device__ __attribute__((noinline)) void gemm_panel(LdsPtr<T> sm, int M, int N,
     const int ldc = uni(ep.ldc), ldd = uni(ep.ldd), ldr = uni(ep.ldr);
     const Buf bA = buf(A, TA ? (K - 1) * lda + M : (M - 1) * lda + K);
     const Buf bB = buf(B, TB ? (N - 1) * ldb + K : (K - 1) * ldb + N);
-    const Buf bD64 = buf(ep.D64, (M - 1) * ldd + N), bDT = buf(ep.DT, (M - 1) * ldd + N);
+    const Buf bDT = buf(ep.DT, (M - 1) * ldd + N);
     const Buf bC = buf(ep.C, (M - 1) * ldc + N), bR = buf(ep.R, (M - 1) * ldr + N);
-    const bool d64 = uni_ptr(ep.D64) != nullptr, hasC = uni_ptr(reinterpret_cast<const double *>(ep.C)) != nullptr,
+    const bool hasC = uni_ptr(reinterpret_cast<const double *>(ep.C)) != nullptr,
                dt = uni_ptr(reinterpret_cast<const double *>(ep.DT)) != nullptr,
                hasR = uni_ptr(reinterpret_cast<const double *>(ep.R)) != nullptr;
     const int tid = threadIdx.x, w = wave(), l = lane(), r16 = l & 15, k4 = l >> 4;
@@ -258,10 +259,7 @@ __device__ __attribute__((noinline)) void gemm_panel(LdsPtr<T> sm, int M, int N,
     auto byte = [](uint32_t e, uint32_t size) { return e == ~0u ? BEYOND : e * size; };
     auto start = [&](int ti, int tj) {
         v4_t<T> v = mf::zero4<T>();
-        if (d64) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = (T)buf_get<double>(bD64, byte(at(ti, tj, r, ldd), 8));
-        } else if (dt) {
+        if (dt) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) v[r] = buf_get<T>(bDT, byte(at(ti, tj, r, ldd), SZ));
         }
@@ -477,15 +475,12 @@ __device__ __forceinline__ void gemm_big(int M, int N, int K, const T *A, int ld
     else
         gemm_tile<TA, TB>(M, N, K, A, lda, B, ldb, lower, epi);
 }
-template <bool BF, bool TA, bool TB, class T>
-__device__ __forceinline__ void gemm_big_panel(LdsPtr<T> sm, int M, int N, int K, const T *A, int lda, const T *B, int ldb,
-                                               bool lower, const Ep<T> &ep) {
-    if constexpr (BF)
-        gemm_bf16<TA, TB>(M, N, K, A, lda, B, ldb, lower, [&](int i, int j, float c) {
-            if (!lower || i >= j) put(ep, i, j, c);
-        });
-    else
-        gemm_panel<TA, TB>(sm, M, N, K, A, lda, B, ldb, lower, ep);
+template <bool TA, bool TB>
+__device__ __forceinline__ void gemm_bf16_to(int M, int N, int K, const float *A, int lda, const float *B, int ldb,
+                                             bool lower, const Ep<float> &ep) {
+    gemm_bf16<TA, TB>(M, N, K, A, lda, B, ldb, lower, [&](int i, int j, float c) {
+        if (!lower || i >= j) put(ep, i, j, c);
+    });
 }
 
 // Epilogue descriptors: store to C (leading dimension ldc); plus a
@@ -622,19 +617,6 @@ struct SlotOut {
     bool up;
     bool lt;
     __device__ double *at(int s) const { return slots + (int64_t)(first + s) * SlotLayout{n}.size(); }
-    __device__ void P(int s, int i, int j, double v) const {
-        if (up) at(s)[SlotLayout{n}.uP() + i * n + j] = v;
-    }
-    __device__ void K(int s, int i, int j, double v) const {
-        const SlotLayout L{n};
-        at(s)[(up ? L.uK() : L.K()) + i * n + j] = v;
-    }
-    __device__ void V(int s, int i, int j, double v) const {
-        if (up) at(s)[SlotLayout{n}.uV() + i * n + j] = v;
-    }
-    __device__ void Lt(int s, int i, int j, double v) const {
-        if (lt) at(s)[SlotLayout{n}.dL() + i * n + j] = v;
-    }
     // the records of stage s that the products write (row length n)
     __device__ double *Prec(int s) const { return up ? at(s) + SlotLayout{n}.uP() : nullptr; }
     __device__ double *Krec(int s) const { return at(s) + (up ? SlotLayout{n}.uK() : SlotLayout{n}.K()); }
@@ -753,12 +735,13 @@ __device__ __forceinline__ void mpass_tile(T *sm, WS<T> &S, Get get, int count, 
     }
 }
 
-// The same pass with the products on LDS panels (gemm_panel) and their
-// results through epilogue descriptors: the stages with n_x > 64.
-template <class T, bool RED, bool BF, int PU, class Get, class Pre, class Out>
-__device__ __forceinline__ void mpass_panel(T *sm_, WS<T> &S, Get get, int count, int32_t *info, int inst, int stage_base, int fail_code, Pre pre,
+// The same pass with the FP32 products on LDS panels (gemm_panel), the others on
+// BF16 operands, and their results through epilogue descriptors: the stages with
+// n_x > 64 of BF16 plans.
+template <bool RED, int PU, class Get, class Pre, class Out>
+__device__ __forceinline__ void mpass_panel(float *sm_, WS<float> &S, Get get, int count, int32_t *info, int inst, int stage_base, int fail_code, Pre pre,
                       const Out &out, int *bad) {
-    static_assert(!BF || sizeof(T) == 4, "BF16 products accumulate in FP32");
+    typedef float T;
     const int n = S.n, m = S.m, nw = S.nw, tid = threadIdx.x;
     count = uni(count);
     const LdsPtr<T> sm = (LdsPtr<T>)sm_;
@@ -766,27 +749,15 @@ __device__ __forceinline__ void mpass_panel(T *sm_, WS<T> &S, Get get, int count
         pre(s);
         T *Li = out.Lrec(s), *LiT = out.LTrec(s);
         const StageSrc src = get(s);
-        // FP64: the data where they are; FP32: [A B] converted
-        const T *A, *B;
-        int lda, ldb;
-        if constexpr (sizeof(T) == 8) {
-            A = src.A;
-            B = src.B;
-            lda = n;
-            ldb = m;
-        } else {
-            load_ab(S, src);
-            __syncthreads();
-            A = S.AB;
-            B = S.AB + n;
-            lda = ldb = nw;
-        }
+        load_ab(S, src);
+        __syncthreads();
+        const T *A = S.AB, *B = S.AB + n;
         // W = P [A B]; Alg. 4: B'V, A'V
-        gemm_big_panel<BF, false, false>(sm, n, n, n, S.P, n, A, lda, false, to(S.W, nw));
-        gemm_big_panel<BF, false, false>(sm, n, m, n, S.P, n, B, ldb, false, to(S.W + n, nw));
+        gemm_bf16_to<false, false>(n, n, n, S.P, n, A, nw, false, to(S.W, nw));
+        gemm_bf16_to<false, false>(n, m, n, S.P, n, B, nw, false, to(S.W + n, nw));
         if constexpr (RED) {
-            gemm_panel<true, false>(sm, m, n, n, B, ldb, S.V, n, false, to(S.BV, n));
-            gemm_panel<true, false>(sm, n, n, n, A, lda, S.V, n, false, to(S.AV, n));
+            gemm_panel<true, false>(sm, m, n, n, B, nw, S.V, n, false, to(S.BV, n));
+            gemm_panel<true, false>(sm, n, n, n, A, nw, S.V, n, false, to(S.AV, n));
         }
         __syncthreads();
         // F = Qx + A'W_A (symmetric), H = Qxw + A'W_B, G = Qw + B'W_B (symmetric)
@@ -795,20 +766,20 @@ __device__ __forceinline__ void mpass_panel(T *sm_, WS<T> &S, Get get, int count
             e.D64 = src.Qx;
             e.ldd = n;
             e.sym = true;
-            gemm_big_panel<BF, true, false>(sm, n, n, n, A, lda, S.W, nw, true, e);
+            gemm_bf16_to<true, false>(n, n, n, A, nw, S.W, nw, true, e);
         }
         {
             Ep<T> e = to(S.H, m);
             e.D64 = src.Qxw;
             e.ldd = m;
-            gemm_big_panel<BF, true, false>(sm, n, m, n, A, lda, S.W + n, nw, false, e);
+            gemm_bf16_to<true, false>(n, m, n, A, nw, S.W + n, nw, false, e);
         }
         {
             Ep<T> e = to(S.G, m);
             e.D64 = src.Qw;
             e.ldd = m;
             e.sym = true;
-            gemm_big_panel<BF, true, false>(sm, m, m, n, B, ldb, S.W + n, nw, true, e);
+            gemm_bf16_to<true, false>(m, m, n, B, nw, S.W + n, nw, true, e);
         }
         __syncthreads();
         chol_inv<PU>(sm_, S.G, m, Li, LiT, bad);
@@ -898,7 +869,7 @@ __device__ __forceinline__ void mpass(T *sm, WS<T> &S, Get get, int count, int32
     if constexpr (BIG && !BF)
         mpass_cols<T, RED, PU>(sm, S, get, count, info, inst, stage_base, fail_code, pre, out, bad);
     else if constexpr (BIG)
-        mpass_panel<T, RED, BF, PU>(sm, S, get, count, info, inst, stage_base, fail_code, pre, out, bad);
+        mpass_panel<RED, PU>(sm, S, get, count, info, inst, stage_base, fail_code, pre, out, bad);
     else
         mpass_tile<T, RED, BF, PU>(sm, S, get, count, info, inst, stage_base, fail_code, pre, out, bad);
 }

@@ -1,6 +1,5 @@
 // Matrix-core helpers (gfx950): the 16x16x4 matrix instruction of each element
-// type with its operand and result layouts, tile loops, and the 16 x 16
-// Cholesky factorization of the large-block kernels.
+// type with its operand and result layouts, and tile indices.
 #pragma once
 #include "rs_device.hpp"
 
@@ -44,12 +43,6 @@ template <class T>
 __device__ __forceinline__ int trow(int ti, int r) { return 16 * ti + MT<T>::row(r); }
 __device__ __forceinline__ int tcol(int tj) { return 16 * tj + (lane() & 15); }
 
-template <class T, class F>
-__device__ __forceinline__ void tile_for(int ti, int tj, F f) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) f(r, trow<T>(ti, r), tcol(tj));
-}
-
 // Lower-triangular tile index t (0 .. T(T+1)/2-1) of a T x T tile grid.
 __device__ __forceinline__ void lower_tile(int t, int &ti, int &tj) {
     ti = 0;
@@ -62,18 +55,6 @@ __device__ __forceinline__ void wave_fence() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-}
-
-// Value of lane N of this lane's row of 16 lanes (DPP row_newbcast; one
-// 64-bit move for a double).
-template <int N>
-__device__ __forceinline__ double row_bcast(double v) {
-    return __longlong_as_double(
-        __builtin_amdgcn_update_dpp(0ll, __double_as_longlong(v), 0x150 + N, 0xF, 0xF, false));
-}
-template <int N>
-__device__ __forceinline__ float row_bcast(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + N, 0xF, 0xF, false));
 }
 
 __device__ __forceinline__ double rsq_est(double d) { return __builtin_amdgcn_rsq(d); }
