@@ -618,7 +618,9 @@ static rs_status plan_create(int32_t count, const int32_t *dims_in, int stride, 
     }
     // Launch order of the leaves (kept in their m1): a leaf that holds the
     // terminal has about two thirds of the work per stage of a reduced one.
-    // Up to LEAVES_AT_ONCE (a workgroup per CU) all start together.
+    // Up to LEAVES_AT_ONCE (a workgroup per CU) all start together whatever their
+    // shape, as do the leaves of the small shapes beyond that (three and more
+    // workgroups a CU), for which the order changes nothing.
     constexpr size_t LEAVES_AT_ONCE = 256;
     for (auto &g : P->groups) {
         g.ordered = !P->receding && P->leaf_chunk == 0 && g.leaves.size() > LEAVES_AT_ONCE;

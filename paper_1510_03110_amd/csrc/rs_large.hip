@@ -5,8 +5,8 @@
 // The matrix side serves n_x > 64, shapes with more 16-wide tiles of inputs
 // than of states, and the BF16 products; the others up to n_x = 64 run on the
 // column-owner kernels (rs_mid.hip), which keep a stage in registers and LDS
-// (64 x 32, N = 1024, batch of 64: leaf factorization 26.3 ms here, 5.7 ms
-// there; master levels 4.2 and 0.95 ms).  The vector side serves n_x or
+// (64 x 32, N = 1024, batch of 64: leaf factorization 26.3 ms here, 5.9 ms
+// there; master levels 4.2 and 0.74 ms).  The vector side serves n_x or
 // n_u > 64, and the tree of RS_PLAN_REFACTOR_DOWN at any size; the others run
 // on the prefetching sweeps (rs_vsweep.hip).
 //

@@ -6,7 +6,7 @@
 //
 // Bound: the dependent chain of a stage (G, its Cholesky factorization, Y, P)
 // on one workgroup per CU at n_x = 64 (123 KB of LDS), then the matrix cores.
-// (64, 32), FP64, 1024 leaves of 64 stages: 22 us a stage, 39 TFLOP/s (98 us
+// (64, 32), FP64, 1024 leaves of 64 stages: 23 us a stage, 38 TFLOP/s (98 us
 // with every operand read through the L2); a 64 x 64 master stage takes about
 // 55 us (161 us); 8 x 4 stages (one tile, two wavefronts) 4 us (13.6 us).
 //   kc_leaf   one workgroup per leaf: Alg. 4 or the last-leaf elimination (up),
@@ -149,8 +149,9 @@ __global__ void __launch_bounds__(128 * NXT, 2) kc_tree(GroupArgs g) {
 
 inline int tiles(int d) { return (d + 15) / 16; }
 
-// Sizes that fill the tiles have an instance without bounds checks (the
-// shapes in use: n_x of 16, 32 and 64).
+// Sizes that fill the tiles have an instance without bounds checks: n_x of 16, 32
+// and 64, the shapes that the workloads use; 48 states, and in FP32 64 with more
+// than 32 inputs, run on the checked one (not measured against each other).
 template <class T, int A, int B>
 hipError_t leaf(const GroupArgs &g, hipStream_t st, int down) {
     const dim3 grid(g.nleaves), block(128 * A);

@@ -2,10 +2,10 @@
 // prefetching sweeps (rs_vsweep.hpp), and the leaf solve of the fused path.
 //   ks_leaf_up / ks_tree / ks_leaf_down
 // Measured in FP64 (one product after another, then this form): 64 x 32,
-// windows of 16 sessions with 33 k stages: leaf up 2.09 -> 1.16 ms, tree
-// 1.14 -> 0.85 ms, leaf down 2.46 -> 1.01 ms (4.8 GB, 4.7 TB/s: the memory is
-// the bound); 64 problems of N = 1024: 2.81 -> 1.85 and 3.28 -> 1.75 ms
-// (5.4 TB/s); 8 x 4 windows: 0.47 -> 0.11, 0.46 -> 0.14 and 0.39 -> 0.08 ms
+// windows of 16 sessions with 33 k stages: leaf up 2.09 -> 1.11 ms, tree
+// 1.14 -> 0.89 ms, leaf down 2.46 -> 0.96 ms (4.8 GB, 4.9 TB/s: the memory is
+// the bound); 64 problems of N = 1024: 2.81 -> 1.76 and 3.28 -> 1.71 ms
+// (5.5 TB/s); 8 x 4 windows: 0.47 -> 0.11, 0.46 -> 0.14 and 0.39 -> 0.08 ms
 // (latency: 1.7 us a stage).
 #include <hip/hip_runtime.h>
 
@@ -326,14 +326,18 @@ __global__ void __launch_bounds__(64 * W) ks_tree(GroupArgs g) {
 // Wavefronts per unit: one at n <= 16 (no workgroup barrier to wait at), four
 // at n <= 32, eight at n <= 64, so that an n x n matrix takes 4, 4 and 8
 // registers (doubles) a thread.  Sizes that fill them have an instance
-// without bounds checks.  Backward sweeps of more leaves of 32 states than four
-// a CU, full sizes: one wavefront each, without barriers and with longer runs of a
-// matrix to a load, since the memory is then the bound and not the chain of a
-// leaf (32 x 16, FP64: 2048 leaves of 64 stages 790 -> 730 us, 4000 1.41 -> 1.32
-// ms; at 256 leaves of 32 stages four wavefronts take 78 us and one 112).  Up to
-// a leaf a CU the reductions take v by L_t'g, which ends sooner (32 x 16, 64
-// leaves of 16 stages 37 us, else 40); more of them do without those bytes (512
-// leaves of 128 stages 425 and 431 us, 16 x 16, 4096 of 64 650 and 705).
+// without bounds checks.
+// Backward sweeps of 32 states, full sizes, with more leaves than four a CU: one
+// wavefront each, without barriers and with longer runs of a matrix to a load,
+// since the memory is then the bound and not the chain of a leaf (32 x 16, FP64:
+// 2048 leaves of 64 stages 790 -> 730 us, 4000 1.41 -> 1.32 ms; at 256 leaves of 32
+// stages four wavefronts take 78 us and one 112).
+// The reductions take v by L_t'g, which ends sooner (32 x 16, FP64: 64 leaves of 16
+// stages 37 us and 40 the other way; 8 x 4, 6400 leaves of 16 116 and 126), and by
+// V'(a + B k) where the memory is the bound: full sizes, in FP64 more leaves than
+// one a CU (16 x 16, 4096 leaves of 64 stages 705 and 650 us; 32 x 16, 512 of 128
+// 431 and 425).  An FP32 L_t has half the bytes: there above four a CU (16 x 16,
+// 8000 of 64 stages 247 and 224 us; 32 x 16, 512 of 128 113 and 117).
 template <int NM, int MM, int W, class TR>
 hipError_t leaf_of(const GroupArgs &g, bool down, hipStream_t st) {
     const dim3 grid(g.nleaves), block(64 * W);
@@ -344,12 +348,10 @@ hipError_t leaf_of(const GroupArgs &g, bool down, hipStream_t st) {
         hipLaunchKernelGGL((ks_leaf_down<NM, MM, W, false, TR>), grid, block, 0, st, g);
     else if (ex && NM == 32 && g.nleaves > 1024)
         hipLaunchKernelGGL((ks_leaf_up<NM, MM, NM == 32 ? 1 : W, true, false, TR>), grid, dim3(64), 0, st, g);
-    else if (ex && g.nleaves > 256)
+    else if (ex && g.nleaves > (sizeof(TR) == 8 ? 256 : 1024))
         hipLaunchKernelGGL((ks_leaf_up<NM, MM, W, true, false, TR>), grid, block, 0, st, g);
     else if (ex)
         hipLaunchKernelGGL((ks_leaf_up<NM, MM, W, true, true, TR>), grid, block, 0, st, g);
-    else if (g.nleaves > 256)
-        hipLaunchKernelGGL((ks_leaf_up<NM, MM, W, false, false, TR>), grid, block, 0, st, g);
     else
         hipLaunchKernelGGL((ks_leaf_up<NM, MM, W, false, true, TR>), grid, block, 0, st, g);
     return hipGetLastError();

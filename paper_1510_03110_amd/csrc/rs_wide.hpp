@@ -6,7 +6,7 @@
 // products, 81 us on the matrix cores of one CU.  With every product read from
 // and written to a workspace (one product after another) a stage moved 4.3 MB;
 // the workspaces of 256 units exceed every cache, so that traffic, not the
-// matrix cores, set the time (366 us a stage with 256 units at work; 178 us in
+// matrix cores, set the time (366 us a stage with 256 units at work; 187 us in
 // this form).  Here wave j owns column block j of W, F, H', Y, K, P and of A'V, B'V, X, L_t, V, Q_w_hat, which pass from
 // one product to the next in its registers (the layout in which a product
 // leaves is the one in which it enters the next as right-hand operand), and
