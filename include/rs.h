@@ -195,11 +195,14 @@ typedef struct rs_options {
  * by a forward sweep on the records of its own reduction (Alg. 4 keeps
  * P, K, V, L_t and the preliminary Psi, k of each master stage; with the
  * terminal costate lam_N sent by the parent, w = K x + k + L_t lam_N and
- * lam = P x - Psi + V lam_N), the superposition that the leaf solve also
- * uses: the master levels are factored once.  With this flag the down pass
- * factors every such subproblem again from its parent's message (P, Psi;
- * Alg. 6 as the paper states it), twice the master-level matrix work; kept
- * for comparison.  Both give the same solution up to rounding. */
+ * lam = P x - Psi + V lam_N), the superposition that the leaf solve on a
+ * stored factorization also uses: the master levels are factored once.  With
+ * this flag the down pass factors every such subproblem again from its
+ * parent's message (P, Psi; Alg. 6 as the paper states it), twice the
+ * master-level matrix work; kept for comparison.  Both give the same solution
+ * up to rounding (the second factorization's rounding is the smaller where
+ * small state weights and unstable dynamics magnify that of lam_N; the fused
+ * solve of shapes that are not multiples of 16 after padding always does so). */
 #define RS_PLAN_REFACTOR_DOWN 32
 
 /* Per-instance result report (device memory, 40 bytes each). */
@@ -409,9 +412,10 @@ rs_status rs_batch_solve(rs_plan plan, const rs_problem *probs, void *work,
  * rs_batch_solve for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * the workspace is a device array of RS_NOALLOC_SCRATCH_BYTES (64 MiB; 128 MiB
- * with the room below) that the library holds on every GPU it runs on from its load until the process
- * ends, so the caller passes only the problems (inputs and outputs, as for
- * rs_batch_solve), the stream and the optional status array.  The call
+ * with the room below) that the library holds on every GPU it runs on from its
+ * load until the process ends, so the caller passes only the problems (inputs
+ * and outputs, as for rs_batch_solve), the stream and the optional status
+ * array.  The call
  * allocates nothing (no hipMalloc, hipFree, pinned or library allocation):
  * the plan's pinned staging is taken at plan creation.  Every call on one GPU
  * shares that GPU's array, which keeps the last call's contents; each call
@@ -422,7 +426,9 @@ rs_status rs_batch_solve(rs_plan plan, const rs_problem *probs, void *work,
  * same as rs_batch_solve's.  Errors: RS_ERR_NOMEM if the plan's workspace
  * (rs_plan_workspace_size; for shapes whose n_x or n_u is not a multiple of
  * 16 without the V and L_t of the fused solve's leaf records, for which the
- * library holds room of its own) exceeds RS_NOALLOC_SCRATCH_BYTES, RS_ERR_ARG for
+ * library holds room of its own, and for shapes padded to n_u = 16 with the
+ * padded copies also where the kernels pad on load) exceeds
+ * RS_NOALLOC_SCRATCH_BYTES, RS_ERR_ARG for
  * receding-horizon plans (their stored factors cannot live in a shared
  * array) and as rs_batch_solve, RS_ERR_HIP if the plan was created without
  * a device.

@@ -91,8 +91,8 @@ struct SlotLayout {
     __host__ __device__ int dL() const { return 10 * n * n + 5 * n + 2; }
     __host__ __device__ int dLT() const { return 11 * n * n + 5 * n + 2; }
     // costate at the end of the node's subproblem (its terminal lam_N), sent
-    // down by the fused matrix-core tree and by the superposition sweep of the
-    // large-block tree (whose up pass then keeps L_t = -G^{-1} B' V in dL)
+    // down by the superposition sweeps: kf_tree on full tiles, ks_tree, kw_tree
+    // (kc_tree and kl_tree then keep L_t = -G^{-1} B' V of the up pass in dL)
     __host__ __device__ int lamN() const { return 12 * n * n + 5 * n + 2; }
     __host__ __device__ int size() const { return ((12 * n * n + 6 * n + 2) + 7) & ~7; }
 };

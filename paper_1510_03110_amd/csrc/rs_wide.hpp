@@ -7,12 +7,13 @@
 // and written to a workspace (one product after another) a stage moved 4.3 MB;
 // the workspaces of 256 units exceed every cache, so that traffic, not the
 // matrix cores, set the time (366 us a stage with 256 units at work; 187 us in
-// this form).  Here wave j owns column block j of W, F, H', Y, K, P and of A'V, B'V, X, L_t, V, Q_w_hat, which pass from
-// one product to the next in its registers (the layout in which a product
-// leaves is the one in which it enters the next as right-hand operand), and
-// only left-hand operands come through LDS: panels of 16 rows of P, A, B, L, Y
-// and X, shared by the eight waves, the next one in flight while one is
-// multiplied.  P and V are kept in the records that the solve needs anyway.
+// this form).  Here wave j owns column block j of W, F, H', Y, K, P and of A'V,
+// B'V, X, L_t, V, Q_w_hat, which pass from one product to the next in its
+// registers (the layout in which a product leaves is the one in which it enters
+// the next as right-hand operand), and only left-hand operands come through
+// LDS: panels of 16 rows of P, A, B, L, Y and X, shared by the eight waves, the
+// next one in flight while one is multiplied.  P and V are kept in the records
+// that the solve needs anyway.
 #pragma once
 #include "rs_col.hpp"
 
