@@ -73,8 +73,9 @@ const ShapeEntry *find_shape(int nx, int nu) {
             e.scratch_per_stage = leaf_rec_len(a, b);
             table[n++] = e;
         };
-        // the shapes with a fused solve; every other one runs on the stored
-        // factorization
+        // the shapes with a fused solve, the sizes of the workloads; every other
+        // one runs on the stored factorization (the fused kernels' run-time sizes
+        // would take any n_u <= n_x <= 32; not measured beyond this list)
         const int shapes[][2] = {{1, 1}, {2, 1}, {2, 2}, {3, 2}, {4, 2}, {4, 4}, {6, 3}, {8, 4}, {16, 8}, {20, 10},
                                  {16, 16}, {32, 16}, {32, 32}};
         for (const auto &m : shapes) add(m[0], m[1]);
